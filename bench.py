@@ -29,6 +29,8 @@ KERNEL_FLOPS = {  # per sample, by instrumented kernel name
     "fc_wgrad": 2 * MACS["fc"], "head_wgrad": 2 * MACS["head_pv"],
     "conv2_dgrad": 2 * MACS["conv2"], "conv3_dgrad": 2 * MACS["conv3"], "fc_dgrad": 2 * MACS["fc"],
     "head_dgrad": 2 * MACS["head_pv"],
+    # fc input gradient + fc and head weight gradients, one launch
+    "dense_bwd": 4 * MACS["fc"] + 2 * MACS["head_pv"],
     # conv2 input gradient + conv1 weight gradient + conv2 and conv3 weight gradients, one launch
     "conv_bwd": 2 * MACS["conv2"] + 2 * MACS["conv1"] + 2 * MACS["conv2"] + 2 * MACS["conv3"],
 }
@@ -44,6 +46,7 @@ KERNEL_BYTES = {
     "fc_wgrad": ACT["a3"] + ACT["h"], "head_wgrad": ACT["h"] + ACT["z"],
     "conv2_dgrad": ACT["a2"] + 2 * ACT["a1"], "conv3_dgrad": ACT["a3"] + 2 * ACT["a2"],
     "fc_dgrad": ACT["h"] + 2 * ACT["a3"], "head_dgrad": ACT["z"] + 2 * ACT["h"],
+    "dense_bwd": ACT["h"] + 2 * ACT["a3"] + ACT["a3"] + ACT["h"] + ACT["z"],
     # d(pre1) stays on chip; d(pre2) is read by two of the three parts
     "conv_bwd": ACT["a2"] + ACT["obs"] + ACT["a1"] + ACT["a2"] + ACT["a2"] + ACT["a3"],
 }
@@ -51,7 +54,7 @@ KERNEL_BYTES_PER_LAUNCH = {  # bf16 weights read (forward / input gradient) or f
     "conv1_fwd": 2 * 8192, "conv2_fwd": 2 * 32768, "conv3_fwd": 2 * 36864, "conv23_fwd": 2 * 32768 + 2 * 36864, "conv123_fwd": 2 * 8192 + 2 * 32768 + 2 * 36864, "fc_fwd": 2 * 1605632, "head_fwd": 2 * 9728,
     "conv2_dgrad": 2 * 32768, "conv3_dgrad": 2 * 36864, "fc_dgrad": 2 * 1605632, "head_dgrad": 2 * 9728,
     "conv1_wgrad": 4 * 8192, "conv2_wgrad": 4 * 32768, "conv3_wgrad": 4 * 36864, "fc_wgrad": 4 * 1605632,
-    "head_wgrad": 4 * 9728, "conv_bwd": 2 * 32768 + 4 * 8192 + 4 * 32768 + 4 * 36864,
+    "head_wgrad": 4 * 9728, "dense_bwd": 2 * 1605632 + 4 * 1605632 + 4 * 9728, "conv_bwd": 2 * 32768 + 4 * 8192 + 4 * 32768 + 4 * 36864,
 }
 # whole step, per sample: the forward's bytes, then observations again, saved activations once, and every
 # activation gradient written and read once
@@ -151,7 +154,7 @@ def flop_models(A, head):
     """Algorithmic flops and HBM bytes per sample (and bytes per launch) by instrumented kernel name."""
     hm = head_macs(A, head)
     flops = dict(KERNEL_FLOPS)
-    flops.update({"head_fwd": 2 * hm, "head_wgrad": 2 * hm, "head_dgrad": 2 * hm,
+    flops.update({"head_fwd": 2 * hm, "head_wgrad": 2 * hm, "head_dgrad": 2 * hm, "dense_bwd": 4 * MACS["fc"] + 2 * hm,
                   "conv_infer": 2 * (MACS["conv1"] + MACS["conv2"] + MACS["conv3"])})
     z = 4 * (A * 51 if head == "c51" else A + 1)
     kb = dict(KERNEL_BYTES)
@@ -437,13 +440,10 @@ def workload_report(args, arn, wl, np, torch):
 # ---------------------------------------------------------------------------
 KERNEL_NAME_PATTERNS = [   # first match wins: mangled or demangled rocprofv3 kernel name -> instrumented launch name
     (r"conv123_fwd_kernel", "conv123_fwd"), (r"conv23_fwd_fused", "conv23_fwd"), (r"infer_conv_(pipelined_)?kernel", "conv_infer"),
-    (r"conv_backward_kernel", "conv_bwd"), (r"conv1_fwd_resident", "conv1_fwd"), (r"ResConv2Fwd", "conv2_fwd"),
+    (r"conv_backward_kernel", "conv_bwd"), (r"dense_backward_kernel", "dense_bwd"), (r"reduce_all_kernel", "reduce"), (r"conv1_fwd_resident", "conv1_fwd"), (r"ResConv2Fwd", "conv2_fwd"),
     (r"ResConv3Fwd", "conv3_fwd"), (r"ResConv3Dgrad", "conv3_dgrad"), (r"FcFwd", "fc_fwd"), (r"FcDgrad", "fc_dgrad"),
     (r"pv_head_kernel<true>|pv_head_kernelILb1", "pv_head"), (r"pv_head_kernel<false>|pv_head_kernelILb0", "pv_head_infer"),
-    (r"HeadWgrad", "head_wgrad"), (r"HeadFwdC51", "head_fwd"), (r"HeadDgrad", "head_dgrad"),
-    (r"UnmapHeadBias", "head_bias"), (r"UnmapHead", "head_reduce"),
-    (r"gemm_tn_kernel.*DenseGather", "fc_wgrad"), (r"fc_reduce", "fc_reduce"), (r"fc_finish", "fc_finish"),
-    (r"conv_reduce_kernel", "conv_reduce"), (r"loss_finalize", "loss_finalize"), (r"c51_dist", "c51_dist"),
+    (r"HeadFwdC51", "head_fwd"), (r"HeadDgrad", "head_dgrad"), (r"fc_finish", "fc_finish"), (r"c51_dist", "c51_dist"),
     (r"c51_loss", "loss"), (r"pack_all", "pack_all"), (r"__amd_rocclr_copyBuffer", "copy"),
 ]
 
@@ -529,8 +529,8 @@ def summarise_counters(root, tag, sq):
         md = ["# %s: shader-core counters per kernel" % tag, "",
               "Commands (one MI355X, repository root; one pass of eight SQ counters each; weight gradients kept on the "
               "caller's stream so that dispatches do not overlap):", "",
-              "    ARN_SINGLE_STREAM=1 rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
-              "    ARN_SINGLE_STREAM=1 rocprofv3 --pmc SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_LDS SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INST_LEVEL_LDS -d DIR/sq_b -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
+              "    rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
+              "    rocprofv3 --pmc SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_LDS SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INST_LEVEL_LDS -d DIR/sq_b -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
               "    python3 bench.py --summarise-counters DIR --sq --tag %s" % tag, "",
               "Per-dispatch averages. SQ_BUSY_CYCLES sums the 32 shader engines, SQ_VALU_MFMA_BUSY_CYCLES the 1024 SIMDs, "
               "SQ_LDS_IDX_ACTIVE the 256 CUs; shares of the wavefronts' resident cycles (SQ_WAVE_CYCLES): waiting at an "
@@ -570,7 +570,7 @@ def summarise_counters(root, tag, sq):
     rows.sort(key=lambda r: -r[3])
     md = ["# %s: HBM traffic per kernel launch" % tag, "",
           "Commands (one MI355X, repository root; weight gradients kept on the caller's stream so that dispatches do not overlap):", "",
-          "    ARN_SINGLE_STREAM=1 rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o bench --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
+          "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o bench --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
           "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o copy --output-format csv -- python3 bench.py --calibrate-copy 256",
           "    (the same two with WRITE_SIZE)",
           "    python3 bench.py --summarise-counters DIR --tag %s" % tag, "",

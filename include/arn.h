@@ -30,16 +30,10 @@
  *     and `arn_batch` structs themselves live in HOST memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Calls enqueue work and return; they never synchronise, allocate or free
- *     device memory.  arn_train_step_grads also uses one library-owned stream
- *     per device (created on first use, default priority) for work that can run
- *     next to the caller's stream; it is forked from and joined back to `stream`
- *     with events inside the call, so to the caller the call behaves as if all
- *     of its work were on `stream`.  Set ARN_SINGLE_STREAM=1 to disable it.
- *     That stream and its events are shared by all calls on a device: two
- *     arn_train_step_grads calls issued concurrently from different host threads
- *     on the same device are not supported (issue them from one thread, on one
- *     or several streams; successive calls are ordered by the events).  The
- *     profiling switch (arn_profile_*) is likewise process-global.
+ *     device memory.  Every launch of a call is on `stream`, in order; calls issued
+ *     from several host threads or on several streams are independent as long as
+ *     they do not share output or workspace memory.  The profiling switch
+ *     (arn_profile_*) is process-global.
  *   - Return value: ARN_OK (0) or a negative arn_status.  Argument errors are
  *     detected on the host before anything is launched.
  *   - Arithmetic: bf16 MFMA operands, fp32 accumulation, fp32 epilogues and

@@ -16,6 +16,7 @@
 #include "arn_resident.h"
 #include "arn_resident_conv.h"
 #include "arn_conv_bwd.h"
+#include "arn_dense_bwd.h"
 #include "arn_conv23_fwd.h"
 #include "arn_infer_fwd.h"
 #include "arn_small_kernels.h"
@@ -76,31 +77,6 @@ struct ProfScope {
 
 inline unsigned cdiv(long a, long b) { return (unsigned)((a + b - 1) / b); }
 
-// A second, library-owned stream (default priority) on which the weight-gradient kernels and their
-// reductions run next to the input-gradient chain of the caller's stream; joined back with events
-// before the call returns.  Created once per device on first use.  ARN_SINGLE_STREAM=1 disables it.
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork[5] = {}, join = nullptr;
-    int state = 0;   // 0 unknown, 1 ready, -1 unavailable
-};
-SideStream *side_stream() {
-    static SideStream per_dev[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    SideStream &ss = per_dev[dev];
-    std::lock_guard<std::mutex> lock(g_lazy_mutex);
-    if (ss.state == 0) {
-        const char *off = getenv("ARN_SINGLE_STREAM");
-        bool ok = !(off && off[0] == '1');
-        ok = ok && hipStreamCreateWithFlags(&ss.stream, hipStreamNonBlocking) == hipSuccess;
-        for (int i = 0; ok && i < 5; ++i) ok = hipEventCreateWithFlags(&ss.fork[i], hipEventDisableTiming) == hipSuccess;
-        ok = ok && hipEventCreateWithFlags(&ss.join, hipEventDisableTiming) == hipSuccess;
-        ss.state = ok ? 1 : -1;
-    }
-    return ss.state == 1 ? &ss : nullptr;
-}
-
 // Device address of this GPU's copy of `scratch`, looked up once per device with that device current.
 void *static_scratch_ptr() {
     static void *per_dev[64];
@@ -126,39 +102,31 @@ void launch_nt_split(const char *name, const P &p, long M, int n_tiles, int z, h
     hipLaunchKernelGGL((gemm_nt_kernel<P, true>), dim3(cdiv(M, P::BM), n_tiles, z), dim3(ThreadsOf<P>::value), 0, s, p);
 }
 
-template <class P>
-void launch_tn(const char *name, const P &p, float *part, long M, int N1, int KP, int splits, hipStream_t s) {
-    ProfScope ps(name, s);
-    long rows = (M + splits - 1) / splits;
-    rows = (rows + 63) / 64 * 64;
-    hipLaunchKernelGGL(gemm_tn_kernel<P>, dim3(KP / P::BK2, N1 / P::BN1, splits), dim3(256), 0, s, p, part,
-                       (int)rows);
-}
+// rows of the batch per split of a weight-gradient contraction: whole k-tiles
+inline int rows_per_split(long M, int splits) { return (int)((M + splits - 1) / splits + 63) / 64 * 64; }
 
 // sample-resident convolution: a fixed, contiguous range of samples per workgroup
+struct ResidentGrid {
+    int spw, wgs, parts;   // samples per workgroup, sample ranges, workgroups that share a range
+};
+template <class C>
+ResidentGrid resident_grid(int B) {
+    const int groups = (B + C::G - 1) / C::G;
+    const int target = C::NBUF == 1 && ResWaves<C>::value == 4 ? 512 : 256;   // single-buffered four-wavefront kernels share a CU
+    ResidentGrid g;
+    g.spw = resident_spw(groups, target) * C::G;
+    // with few sample groups, the position tiles of a group are dealt to several workgroups
+    constexpr int tiles = (C::G * C::P + 15) / 16;
+    g.wgs = (int)cdiv(B, g.spw);
+    g.parts = 128 / g.wgs;   // every extra workgroup repeats the weight fetch and the staging: measured to pay only up to about 128 workgroups
+    g.parts = g.parts < 1 ? 1 : g.parts > tiles ? tiles : g.parts;
+    return g;
+}
 template <class C>
 void launch_resident(const char *name, const typename C::Args &a, int B, hipStream_t s) {
     ProfScope ps(name, s);
-    const int groups = (B + C::G - 1) / C::G;
-    constexpr int waves = ResWaves<C>::value;
-    const int target = C::NBUF == 1 && waves == 4 ? 512 : 256;               // single-buffered four-wavefront kernels share a CU
-    const int spw = resident_spw(groups, target) * C::G;
-    // with few sample groups, the position tiles of a group are dealt to several workgroups
-    constexpr int tiles = (C::G * C::P + 15) / 16;
-    const int wgs = (int)cdiv(B, spw);
-    int parts = 128 / wgs;   // every extra workgroup repeats the weight fetch and the staging: measured to pay only up to about 128 workgroups
-    parts = parts < 1 ? 1 : parts > tiles ? tiles : parts;
-    hipLaunchKernelGGL(resident_conv_kernel<C>, dim3(wgs, parts), dim3(64 * waves), 0, s, a, B, spw);
-}
-
-template <class F>
-void launch_reduce(const char *name, const F &f, const float *part, float *dW, long wcount, long bcount, int splits,
-                   float wscale, hipStream_t s) {
-    ProfScope ps(name, s);
-    const long block = wcount + bcount;
-    const int ng = splits >= 64 ? 8 : splits >= 16 ? 4 : splits >= 4 ? 2 : 1;
-    hipLaunchKernelGGL(reduce_partials_kernel<F>, dim3(cdiv(block, 256 / ng)), dim3(256), 0, s, f, part, dW, block,
-                       wcount, splits, wscale, ng);
+    const ResidentGrid g = resident_grid<C>(B);
+    hipLaunchKernelGGL(resident_conv_kernel<C>, dim3(g.wgs, g.parts), dim3(64 * ResWaves<C>::value), 0, s, a, B, g.spw);
 }
 
 struct Packed {   // typed views of the packed blob
@@ -343,48 +311,48 @@ void forward_launches(const Dims &d, const Packed &w, const uint8_t *obs, int B,
     else forward_trunk<Geo84>(d, w, obs, B, ws, o, z_out, zstride, masks, s);
 }
 
-// Events that let work queued on the side stream see everything queued on the caller's stream so far.
-struct Fork {
-    SideStream *ss = nullptr;
-    hipStream_t s = nullptr, s2 = nullptr;
-    int n = 0;
-    void operator()() {
-        if (!ss) return;
-        (void)hipEventRecord(ss->fork[n], s);
-        (void)hipStreamWaitEvent(s2, ss->fork[n], 0);
-        ++n;
-    }
+// Backward pass below d(pre_fc) for geometry G, in four launches: the dense layers' gradients, conv3's input gradient,
+// the convolutions' weight gradients (with conv2's input gradient), the sums of all weight-gradient partials.
+// Within a launch, pieces of work that do not depend on each other are ranges of workgroups.  A launch costs about 4 us
+// on the GPU and 3 us on the host however small it is, a cross-stream event about 6 us on both streams: with the dense
+// weight gradients and five short kernels on a second stream the step took 139 us at 333 samples (host 105 us), this
+// way 126 (host 40); from 2048 samples up the two are level.
+struct HeadGrads {   // the head's part of it
+    HeadWgrad wgrad;
+    float *part;
+    ReducePartials<UnmapHead> reduce;
+    ReducePartials<UnmapHeadBias> bias;
+    LossTotals loss;
 };
-
-// Backward pass below d(pre_fc) for geometry G.  Everything that needs only d(pre_fc) -- the fc weight gradient
-// and its reduction, next to the head's -- runs on the side stream; the chain fc dgrad -> conv3 dgrad ->
-// conv2 dgrad (fused with conv1's weight gradient), the other convolutions' weight gradients and one reduction
-// kernel for all three of them stay on the caller's stream.  (Every cross-stream event costs the waiting and the recording stream about 6 us, and two
-// heavy kernels side by side mostly share the memory system, so more overlap than this measured slower.)
 template <class G>
 void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o, const ParamOffsets &po,
-                    const Splits &sp, float *dW, Fork &fk) {
+                    const Splits &sp, const HeadGrads &hg, float *dW, hipStream_t s) {
     typedef ConvConfigs<G> Cfg;
-    hipStream_t s = fk.s, s2 = fk.s2;
     __bf16 *a1 = (__bf16 *)(ws + o.a1), *a2 = (__bf16 *)(ws + o.a2), *a3 = (__bf16 *)(ws + o.a3);
     __bf16 *dph = (__bf16 *)(ws + o.dph), *dp3 = (__bf16 *)(ws + o.dp3);
     __bf16 *dp2 = (__bf16 *)(ws + o.dp2);
     float *part1 = (float *)(ws + o.pw1), *part2 = (float *)(ws + o.pw2), *part3 = (float *)(ws + o.pw3);
+    float *partfc = (float *)(ws + o.pwfc);
     {
-        typedef Wgrad<DenseGather<G::FEAT>, 128, 64, 2, HID, G::FEAT> FcW;
-        FcW p;
-        p.in = a3; p.M = B; p.dy = dph;
-        float *part = (float *)(ws + o.pwfc);
-        launch_tn("fc_wgrad", p, part, B, HID, G::FEAT, sp.fc, s2);
-        ProfScope ps("fc_reduce", s2);
-        hipLaunchKernelGGL((fc_reduce_kernel<G::FEAT, G::P3>), dim3(HID + 1), dim3(256), 0, s2, part, dW, (long)po.wfc,
-                           (long)po.bfc, sp.fc);
-    }
-    {
-        // 128 x 128 tiles from 1024 samples up (fewer operand bytes from the L2 per flop), 128 x 64 below (more workgroups)
-        auto launch = [&](auto p) {
-            p.in = dph; p.M = B; p.w = w.wfcd; p.maskbits = (const uint8_t *)(ws + o.m3); p.out = dp3;
-            launch_nt("fc_dgrad", p, B, (G::FEAT + p.BN - 1) / p.BN, 1, s);
+        // fc input gradient in 128 x 128 tiles from 1024 samples up (fewer operand bytes from the L2 per flop),
+        // 128 x 64 below (more workgroups)
+        auto launch = [&](auto dg) {
+            typedef decltype(dg) Dg;
+            typedef Wgrad<DenseGather<G::FEAT>, 128, 64, 2, HID, G::FEAT> FcW;
+            dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
+            DenseBackwardArgs<Dg, FcW> p;
+            p.dg = dg;
+            p.dg_x = cdiv(B, Dg::BM); p.dg_blocks = p.dg_x * ((G::FEAT + Dg::BN - 1) / Dg::BN);
+            p.wg.in = a3; p.wg.M = B; p.wg.dy = dph;
+            p.wg_part = partfc; p.wg_rows = rows_per_split(B, sp.fc);
+            p.wg_blocks = (G::FEAT / FcW::BK2) * (HID / FcW::BN1) * sp.fc;
+            p.hw = hg.wgrad;
+            p.hw_part = hg.part; p.hw_rows = rows_per_split(B, sp.hd);
+            p.hw_blocks = (HID / HeadWgrad::BK2) * (hg.wgrad.N1 / HeadWgrad::BN1) * sp.hd;
+            p.loss = hg.loss;
+            ProfScope ps("dense_bwd", s);
+            hipLaunchKernelGGL((dense_backward_kernel<Dg, FcW>), dim3(p.dg_blocks + p.wg_blocks + p.hw_blocks + 1),
+                               dim3(DENSE_THREADS), 0, s, p);
         };
         if (B >= 1024) launch(FcDgradT<G::FEAT, 128>());
         else launch(FcDgradT<G::FEAT, 64>());
@@ -411,21 +379,19 @@ void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const 
                            dim3(ConvBackward<G, typename Cfg::Dgrad2>::THREADS), 0, s, p);
     }
     {
-        // one launch adds the partials of all three convolutions (x = u8/255: conv1's pixel scale comes out of
-        // the contraction and is applied here; bias gradients have no such factor)
-        ProfScope ps("conv_reduce", s);
-        ConvReducePlan pl;
-        pl.seg[0] = make_reduce_seg(part1, (long)C1 * KW1, C1, sp.c1, 1.f / 255.f);
-        pl.seg[1] = make_reduce_seg(part2, (long)C2 * KW2, C2, sp.c2, 1.f);
-        pl.seg[2] = make_reduce_seg(part3, (long)C3 * KW3, C3, sp.c3, 1.f);
-        pl.w1 = (long)po.w1; pl.b1 = (long)po.b1; pl.w2 = (long)po.w2; pl.b2 = (long)po.b2;
-        pl.w3 = (long)po.w3; pl.b3 = (long)po.b3;
-        int blk = 0;
-        for (int k = 0; k < 3; ++k) {
-            pl.seg[k].first_block = blk;
-            blk += (int)cdiv(pl.seg[k].block, 256 / pl.seg[k].ng);
-        }
-        hipLaunchKernelGGL(conv_reduce_kernel, dim3(blk), dim3(256), 0, s, pl, dW);
+        // one launch adds the partials of every layer (x = u8/255: conv1's pixel scale comes out of the contraction and
+        // is applied here; bias gradients have no such factor)
+        ReduceAllPlan pl;
+        pl.conv1 = make_reduce(UnmapConv1{(long)po.w1, (long)po.b1}, part1, (long)C1 * KW1, C1, sp.c1, 1.f / 255.f);
+        pl.conv2 = make_reduce(UnmapConv<C1, K2, C2>{(long)po.w2, (long)po.b2}, part2, (long)C2 * KW2, C2, sp.c2);
+        pl.conv3 = make_reduce(UnmapConv<C2, K3, C3>{(long)po.w3, (long)po.b3}, part3, (long)C3 * KW3, C3, sp.c3);
+        pl.head = hg.reduce; pl.head_bias = hg.bias;
+        pl.n1 = reduce_blocks(pl.conv1); pl.n2 = reduce_blocks(pl.conv2); pl.n3 = reduce_blocks(pl.conv3);
+        pl.nh = reduce_blocks(pl.head);
+        pl.fc_part = partfc; pl.fc_w = (long)po.wfc; pl.fc_b = (long)po.bfc; pl.fc_splits = sp.fc;
+        ProfScope ps("reduce", s);
+        hipLaunchKernelGGL((reduce_all_kernel<G::FEAT, G::P3>),
+                           dim3(HID + 1 + pl.n1 + pl.n2 + pl.n3 + pl.nh + reduce_blocks(pl.head_bias)), dim3(256), 0, s, pl, dW);
     }
 }
 
@@ -728,44 +694,21 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
     }
 
     // ---- backward ----
-    // The input-gradient chain (head -> fc -> conv3 -> conv2, then conv1's weight gradient) runs on the
-    // caller's stream; every other weight gradient and its reduction runs on the side stream as soon as
-    // the gradient it consumes exists.
-    Fork fk;
-    fk.ss = side_stream();
-    fk.s = s;
-    fk.s2 = fk.ss ? fk.ss->stream : s;
-    SideStream *ss = fk.ss;
-    hipStream_t s2 = fk.s2;
-    fk();   // dz (and, for the policy/value head, d(pre_fc))
-    {
-        // the reported loss values are off the critical path: block partial sums are added on the side stream
-        ProfScope ps("loss_finalize", s2);
-        const bool pv = loss_kind == ARN_LOSS_A2C || loss_kind == ARN_LOSS_PPO;
-        hipLaunchKernelGGL(loss_finalize_kernel, dim3(1), dim3(64), 0, s2, lossp, lblocks, B,
-                           pv ? cfg->value_coef : 0.f, pv ? cfg->entropy_coef : 0.f, loss);
-    }
-    {
-        HeadWgrad p;
-        p.in = h; p.M = B; p.N1 = d.NHP; p.dy = dz;
-        float *part = (float *)(ws + o.pwh);
-        launch_tn("head_wgrad", p, part, B, d.NHP, HID, sp.hd, s2);
-        launch_reduce("head_reduce", UnmapHead{head_rows(d, po), d.NHP}, part, dW, (long)d.NHP * HID, d.NHP, sp.hd, 1.f, s2);
-        // the head's bias gradient: the loss kernel's fp32 block partials, added in block order
-        launch_reduce("head_bias", UnmapHeadBias{head_rows(d, po)}, hbp, dW, 0, d.small ? 32 : d.NHP, lblocks, 1.f, s2);
-    }
     if (d.head == ARN_HEAD_C51) {
         HeadDgrad p;
         p.in = dz; p.M = B; p.K = d.NHP; p.w = w.whd; p.h = h; p.out = dph;
         launch_nt("head_dgrad", p, B, HID / HeadDgrad::BN, 1, s);
     }
-    if (d.head == ARN_HEAD_C51) fk();   // d(pre_fc) comes from the head's input-gradient GEMM above
-    if (d.geom == ARN_GEOM_PAPER) backward_trunk<GeoPaper>(w, batch->obs, B, ws, o, po, sp, dW, fk);
-    else backward_trunk<Geo84>(w, batch->obs, B, ws, o, po, sp, dW, fk);
-    if (ss) {   // join: the caller's stream continues only after the side stream's work
-        (void)hipEventRecord(ss->join, s2);
-        (void)hipStreamWaitEvent(s, ss->join, 0);
-    }
+    HeadGrads hg;
+    hg.wgrad.in = h; hg.wgrad.M = B; hg.wgrad.N1 = d.NHP; hg.wgrad.dy = dz;
+    hg.part = (float *)(ws + o.pwh);
+    hg.reduce = make_reduce(UnmapHead{head_rows(d, po), d.NHP}, hg.part, (long)d.NHP * HID, d.NHP, sp.hd);
+    // the head's bias gradient: the loss kernel's fp32 block partials, added in block order
+    hg.bias = make_reduce(UnmapHeadBias{head_rows(d, po)}, hbp, 0, d.small ? 32 : d.NHP, lblocks);
+    const bool pv = loss_kind == ARN_LOSS_A2C || loss_kind == ARN_LOSS_PPO;
+    hg.loss = LossTotals{lossp, lblocks, B, pv ? cfg->value_coef : 0.f, pv ? cfg->entropy_coef : 0.f, loss};
+    if (d.geom == ARN_GEOM_PAPER) backward_trunk<GeoPaper>(w, batch->obs, B, ws, o, po, sp, hg, dW, s);
+    else backward_trunk<Geo84>(w, batch->obs, B, ws, o, po, sp, hg, dW, s);
     if (d.a3c) {
         ProfScope ps("a3c_gather", s);
         const A3cMap m = make_a3c_map(d);

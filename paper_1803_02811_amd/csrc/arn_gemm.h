@@ -1,10 +1,10 @@
 // MFMA building blocks for gfx950: two workgroup-level contraction kernels that
 // the dense layers (fc, categorical head) are instances of.
 //
-//   gemm_nt_kernel : out[m][n] = sum_k act(m,k) * W[n][k]
+//   gemm_nt_body : out[m][n] = sum_k act(m,k) * W[n][k]
 //       forward layers and input gradients.  `act` is gathered on the fly by the
 //       problem struct; W is a packed bf16 matrix with k contiguous.
-//   gemm_tn_kernel : out[n][k] = sum_m dY[m][n] * act(m,k)
+//   gemm_tn_body : out[n][k] = sum_m dY[m][n] * act(m,k)
 //       weight gradients: the contraction runs over the batch/position index,
 //       which is the slow index of both operands in memory, so fragments are
 //       taken from LDS with the transposing read ds_read_b64_tr_b16.
@@ -231,15 +231,21 @@ struct WeightRows<P, decltype((void)P::N_ROWS)> {
     static constexpr int value = P::N_ROWS;
 };
 
+// LDS bytes of gemm_nt_body<P, SPLIT>
 template <class P, bool SPLIT = false>
-__global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p) {
+constexpr int gemm_nt_lds_bytes() {
+    return StagesOf<P>::value * LDS_ROW * 16 * (P::BM * (ActLo<P, SPLIT>::value ? 2 : 1) + P::BN * (SPLIT ? 2 : 1));
+}
+
+// The work of workgroup (bx, by, bz) of a grid of gx x gy x gz workgroups, in the caller's LDS buffer.
+template <class P, bool SPLIT = false>
+__device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int by, int bz, int gx, int gy, int gz) {
     constexpr int NT = ThreadsOf<P>::value, NW = NT / 64, RS = NT / 8;   // threads, wavefronts, rows staged per pass
     constexpr int BM = P::BM, BN = P::BN, WN = P::WAVES_N, WM = NW / WN;
     constexpr int TN = BN / (32 * WN), TM = BM / (32 * WM);
     constexpr int A_CH = BM / RS, W_CH = BN / RS;     // 16-byte chunks staged per thread and k-tile
     static_assert(BM % RS == 0 && BN % RS == 0, "staging passes");
     constexpr bool ALO = ActLo<P, SPLIT>::value;
-    int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
     int kt_begin = 0, KT = p.K / 64;
     if constexpr (HasKSplit<P>::value) {
         // Split-k launches: workgroups go to the eight XCDs round robin in linear order (x fastest), and each XCD has
@@ -248,7 +254,6 @@ __global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p)
         // memory is halved (measured: 77.2 -> 38.6 MB per launch of the fc layer at 2048 samples; the launch itself
         // 26.9 -> 26.5 us, 17.0 -> 15.2 us at 1024 samples).  Only for grids that split evenly; otherwise the plain
         // mapping.
-        const int gx = gridDim.x, gy = gridDim.y, gz = gridDim.z;
         const bool pow2 = (gz & (gz - 1)) == 0;
         if (pow2 && gz >= 8) {
             const int L = bx + gx * (by + gy * bz), c = L & 7, zpc = gz >> 3;
@@ -272,10 +277,8 @@ __global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p)
     // with two LDS stages tile kt is consumed from stage kt&1 while tile kt+1 is written to the other
     constexpr int NST = StagesOf<P>::value;
     constexpr int SA = BM * LDS_ROW, SW = BN * LDS_ROW;
-    __shared__ u32x4 sA[NST * SA];
-    __shared__ u32x4 sW[NST * SW];
-    __shared__ u32x4 sA2[ALO ? NST * SA : 1];
-    __shared__ u32x4 sW2[SPLIT ? NST * SW : 1];
+    u32x4 *const sA = lds, *const sW = sA + NST * SA;
+    u32x4 *const sA2 = sW + NST * SW, *const sW2 = sA2 + (ALO ? NST * SA : 0);   // used where the operand has a low part
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wn = wave % WN, wm = wave / WN;
@@ -405,6 +408,12 @@ __global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p)
         }
 }
 
+template <class P, bool SPLIT = false>
+__global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p) {
+    __shared__ u32x4 lds[gemm_nt_lds_bytes<P, SPLIT>() / 16];
+    gemm_nt_body<P, SPLIT>(lds, p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.y, gridDim.z);
+}
+
 // ---------------------------------------------------------------------------
 // Transposing LDS fragment read.
 //
@@ -442,15 +451,20 @@ __device__ __forceinline__ bf16x8 tr_fragment(const u32x4 *tile, int row_u4, int
 // `rows_per_split` (a multiple of 64) consecutive m; partials are summed by
 // reduce_partials_kernel in split order, which fixes the rounding order.
 // ---------------------------------------------------------------------------
+// This is the work of workgroup (bx, by, split) of 256 threads, in the caller's LDS buffer of gemm_tn_lds_bytes<P>().
+constexpr int TN_PAD = 4;   // padding of a staged row in u32x4, see below
 template <class P>
-__global__ __launch_bounds__(256) void gemm_tn_kernel(const P p, float *__restrict__ part, int rows_per_split) {
+constexpr int gemm_tn_lds_bytes() { return 64 * (P::BN1 / 8 + TN_PAD + P::BK2 / 8 + TN_PAD) * 16; }
+
+template <class P>
+__device__ __forceinline__ void gemm_tn_body(u32x4 *lds, const P &p, float *__restrict__ part, int rows_per_split, int bx, int by,
+                                             int split) {
     constexpr int BN1 = P::BN1, BK2 = P::BK2, WX = P::WAVES_X, WY = 4 / WX;
     constexpr int TY = BN1 / (32 * WY), TX = BK2 / (32 * WX);
     constexpr int YC = BN1 / 8, XC = BK2 / 8;          // 16-byte chunks per staged row
     // Padding of a staged row: 64 bytes, which puts consecutive rows 64 bytes apart modulo 256 (rows are multiples of
     // 128 bytes).  A transposing read takes 64 contiguous bytes of each of four consecutive rows: with 16 bytes of
     // padding 54 % of the LDS-active cycles were bank conflicts, with 32 bytes 33 %, with 64 none (measured).
-    constexpr int TN_PAD = 4;
     constexpr int YROW = YC + TN_PAD, XROW = XC + TN_PAD;        // padded LDS row, in u32x4
     static_assert(YC % 8 == 0 && XC % 8 == 0, "rows of whole 128 bytes");
     constexpr int Y_CH = 64 * YC / 256, X_CH = 64 * XC / 256;
@@ -459,12 +473,11 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const P p, float *__restri
     constexpr bool SCRATCH_IN_Y = BIAS_SCRATCH <= 64 * YROW * 16;
     static_assert(256 % YC == 0 && (SCRATCH_IN_Y || BIAS_SCRATCH <= 64 * XROW * 16), "bias-gradient scratch");
 
-    __shared__ u32x4 sY[64 * YROW];
-    __shared__ u32x4 sX[64 * XROW];
+    u32x4 *const sY = lds, *const sX = lds + 64 * YROW;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wx = wave % WX, wy = wave / WX;
-    const int x0 = blockIdx.x * BK2, y0 = blockIdx.y * BN1, split = blockIdx.z;
+    const int x0 = bx * BK2, y0 = by * BN1;
     const long m_begin = (long)split * rows_per_split;
     long m_end = m_begin + rows_per_split;
     if (m_end > p.M) m_end = p.M;
@@ -495,7 +508,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const P p, float *__restri
     // bias gradient (column sums of dY), kept by the workgroups of the first tile column: a thread always
     // stages the same eight dY columns (256 is a multiple of YC), so it adds what it stages, in fp32
     float bs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const bool keeps_bias = blockIdx.x == 0;
+    const bool keeps_bias = bx == 0;
 
     if (m_begin < m_end) gload(m_begin);
     for (long mt = m_begin; mt < m_end; mt += 64) {

@@ -108,66 +108,58 @@ struct MapConv2Dgrad { // packed [z][ci][(ty*2+tx)*64+co]  <-  W2[co][ci][py+2(1
 // each add a contiguous share of the splits in split order, then the group sums
 // are added in group order -- a fixed association, so the result is bit-reproducible.
 template <class F>
-__global__ __launch_bounds__(256) void reduce_partials_kernel(F f, const float *__restrict__ part,
-                                                              float *__restrict__ dW, long block, long wcount,
-                                                              int splits, float wscale, int ng) {
-    __shared__ float red[256];
-    const int opb = 256 / ng;
+struct ReducePartials {
+    F f;
+    const float *part;
+    long block, wcount;     // entries per partial; how many of them are weights
+    int splits, ng;
+    float wscale;
+};
+inline int reduce_groups(int splits) { return splits >= 64 ? 8 : splits >= 16 ? 4 : splits >= 4 ? 2 : 1; }
+template <class F>
+inline ReducePartials<F> make_reduce(const F &f, const float *part, long wcount, long bcount, int splits, float wscale = 1.f) {
+    return ReducePartials<F>{f, part, wcount + bcount, wcount, splits, reduce_groups(splits), wscale};
+}
+template <class F>
+inline int reduce_blocks(const ReducePartials<F> &r) { return (int)((r.block + 256 / r.ng - 1) / (256 / r.ng)); }
+
+template <class F>
+__device__ __forceinline__ void reduce_partials(float *red, int b, const ReducePartials<F> &r, float *__restrict__ dW) {
+    const int opb = 256 / r.ng;
     const int o = threadIdx.x % opb, q = threadIdx.x / opb;
-    const long i = (long)blockIdx.x * opb + o;
-    const int per = (splits + ng - 1) / ng;
-    const int k0 = q * per, k1 = k0 + per < splits ? k0 + per : splits;
+    const long i = (long)b * opb + o;
+    const int per = (r.splits + r.ng - 1) / r.ng;
+    const int k0 = q * per, k1 = k0 + per < r.splits ? k0 + per : r.splits;
     float s = 0.f;
-    if (i < block) {
+    if (i < r.block) {
         int k = k0;
         for (; k + 8 <= k1; k += 8) {     // eight independent loads in flight, added in split order
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = part[(size_t)(k + j) * block + i];
+            for (int j = 0; j < 8; ++j) v[j] = r.part[(size_t)(k + j) * r.block + i];
 #pragma unroll
             for (int j = 0; j < 8; ++j) s += v[j];
         }
-        for (; k < k1; ++k) s += part[(size_t)k * block + i];
+        for (; k < k1; ++k) s += r.part[(size_t)k * r.block + i];
     }
     red[threadIdx.x] = s;
     __syncthreads();
-    if (q == 0 && i < block) {
-        const long dst = f(i);
+    if (q == 0 && i < r.block) {
+        const long dst = r.f(i);
         if (dst < 0) return;
         float t = red[o];
-        for (int g = 1; g < ng; ++g) t += red[g * opb + o];
-        dW[dst] = i < wcount ? t * wscale : t;
+        for (int g = 1; g < r.ng; ++g) t += red[g * opb + o];
+        dW[dst] = i < r.wcount ? t * r.wscale : t;
     }
 }
-// The same reduction for the three convolutions in one launch: a block finds the layer its index falls in
-// (uniform per block) and applies that layer's index map.
-struct ReduceSeg {
-    const float *part;
-    long block, wcount;     // entries per partial ([N*K' + N]); how many of them are weights
-    int splits, ng, first_block;
-    float wscale;
-};
-inline ReduceSeg make_reduce_seg(const float *part, long wcount, long bcount, int splits, float wscale) {
-    ReduceSeg g;
-    g.part = part; g.block = wcount + bcount; g.wcount = wcount; g.splits = splits; g.wscale = wscale;
-    g.ng = splits >= 64 ? 8 : splits >= 16 ? 4 : splits >= 4 ? 2 : 1;
-    g.first_block = 0;
-    return g;
-}
-struct ConvReducePlan {
-    ReduceSeg seg[3];       // conv1, conv2, conv3
-    long w1, b1, w2, b2, w3, b3;
-};
-
 // The fc layer's partials are [n][pos*64 + c] while the canonical weight is [n][c*P3 + pos]: one workgroup
 // per output row n adds the splits with contiguous reads, permutes the row in LDS (stride 49 words at
 // 84x84: no bank conflicts) and writes it out contiguously.  Workgroup HID handles the bias gradient.
 template <int FEAT, int P3>
-__global__ __launch_bounds__(256) void fc_reduce_kernel(const float *__restrict__ part, float *__restrict__ dW,
-                                                        long woff, long boff, int splits) {
-    __shared__ float row[FEAT];
+__device__ __forceinline__ void fc_reduce(float *row, int n, const float *__restrict__ part, float *__restrict__ dW, long woff,
+                                          long boff, int splits) {
     constexpr long block = (long)HID * FEAT + HID;
-    const int n = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     if (n == HID) {
         for (int j = tid; j < HID; j += 256) {
             float s = 0.f;
@@ -221,39 +213,6 @@ struct UnmapConv1 {
     long woff, boff;
     __device__ long operator()(long i) const { return i >= C1 * KW1 ? boff + (i - C1 * KW1) : woff + i; }
 };
-__global__ __launch_bounds__(256) void conv_reduce_kernel(ConvReducePlan pl, float *__restrict__ dW) {
-    __shared__ float red[256];
-    const int k = (int)blockIdx.x >= pl.seg[2].first_block ? 2 : ((int)blockIdx.x >= pl.seg[1].first_block ? 1 : 0);
-    // segment fields selected without dynamic indexing of the argument block
-    const ReduceSeg g = k == 2 ? pl.seg[2] : (k == 1 ? pl.seg[1] : pl.seg[0]);
-    const int opb = 256 / g.ng;
-    const int o = threadIdx.x % opb, q = threadIdx.x / opb;
-    const long i = (long)((int)blockIdx.x - g.first_block) * opb + o;
-    const int per = (g.splits + g.ng - 1) / g.ng;
-    const int k0 = q * per, k1 = k0 + per < g.splits ? k0 + per : g.splits;
-    float s = 0.f;
-    if (i < g.block) {
-        int z = k0;
-        for (; z + 8 <= k1; z += 8) {     // eight independent loads in flight, added in split order
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = g.part[(size_t)(z + j) * g.block + i];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += v[j];
-        }
-        for (; z < k1; ++z) s += g.part[(size_t)z * g.block + i];
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (q == 0 && i < g.block) {
-        const long dst = k == 2 ? UnmapConv<C2, K3, C3>{pl.w3, pl.b3}(i)
-                                : (k == 1 ? UnmapConv<C1, K2, C2>{pl.w2, pl.b2}(i) : UnmapConv1{pl.w1, pl.b1}(i));
-        float t = red[o];
-        for (int j = 1; j < g.ng; ++j) t += red[j * opb + o];
-        dW[dst] = i < g.wcount ? t * g.wscale : t;
-    }
-}
-
 struct UnmapHeadBias {   // index = head row -> its bias entry in the flat gradient (or -1)
     MapHeadRow h;
     __device__ long operator()(long i) const { return h.brow((int)i); }
@@ -267,6 +226,34 @@ struct UnmapHead {       // the weight-gradient GEMM's partial block; its bias s
         return b < 0 ? -1 : b + i % HID;
     }
 };
+
+// Every weight-gradient partial of the gradient step, in one launch: ranges of workgroups, one per layer.
+struct ReduceAllPlan {
+    ReducePartials<UnmapConv1> conv1;
+    ReducePartials<UnmapConv<C1, K2, C2>> conv2;
+    ReducePartials<UnmapConv<C2, K3, C3>> conv3;
+    ReducePartials<UnmapHead> head;
+    ReducePartials<UnmapHeadBias> head_bias;
+    int n1, n2, n3, nh;       // workgroups of conv1, conv2, conv3, head; the fc layer has HID + 1, the head's bias the rest
+    const float *fc_part;
+    long fc_w, fc_b;
+    int fc_splits;
+};
+template <int FEAT, int P3>
+__global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceAllPlan pl, float *__restrict__ dW) {
+    __shared__ float scratch[FEAT > 256 ? FEAT : 256];
+    int b = blockIdx.x;
+    if (b < HID + 1) { fc_reduce<FEAT, P3>(scratch, b, pl.fc_part, dW, pl.fc_w, pl.fc_b, pl.fc_splits); return; }
+    b -= HID + 1;
+    if (b < pl.n3) { reduce_partials(scratch, b, pl.conv3, dW); return; }
+    b -= pl.n3;
+    if (b < pl.n2) { reduce_partials(scratch, b, pl.conv2, dW); return; }
+    b -= pl.n2;
+    if (b < pl.n1) { reduce_partials(scratch, b, pl.conv1, dW); return; }
+    b -= pl.n1;
+    if (b < pl.nh) { reduce_partials(scratch, b, pl.head, dW); return; }
+    reduce_partials(scratch, b - pl.nh, pl.head_bias, dW);
+}
 
 // h = relu(sum_z partial[z] + bias), written as bf16 hi (and lo = residual) -- the
 // second half of the split-k fc layer.  One thread per four outputs.
@@ -295,10 +282,9 @@ __global__ void fc_finish_kernel(const float *__restrict__ partial, int ksplit, 
 // loss[0..3] = {total, policy|cross-entropy, value mse, entropy}: one wavefront;
 // lane l adds the partials of blocks l, l+64, ... in that order, then the lanes
 // are added in a fixed tree -- the same association on every run.
-__global__ __launch_bounds__(64) void loss_finalize_kernel(const float *__restrict__ lossp, int blocks, int B,
-                                                           float value_coef, float entropy_coef,
-                                                           float *__restrict__ loss) {
-    if (blockIdx.x != 0) return;
+__device__ __forceinline__ void loss_finalize(const float *__restrict__ lossp, int blocks, int B, float value_coef,
+                                              float entropy_coef, float *__restrict__ loss) {
+    if (threadIdx.x >= 64) return;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f;
     for (int b = threadIdx.x; b < blocks; b += 64) {
         s0 += lossp[b * 4 + 0];
