@@ -19,6 +19,7 @@
 #include "arn_dense_bwd.h"
 #include "arn_conv23_fwd.h"
 #include "arn_infer_fwd.h"
+#include "arn_infer_small.h"
 #include "arn_small_kernels.h"
 #include "arn_update.h"
 
@@ -165,18 +166,58 @@ Packed view_packed(const void *blob, const Dims &d) {
     return p;
 }
 
-// fc layer and, for the categorical head, the head GEMM; shared by both geometries.  F16: act3 and the fc
-// weights are fp16 and the layer is one product (no-gradient forward); otherwise three bf16 products.
-template <int FEAT_, bool F16 = false>
+// Arguments of the head kernels that the entry points share.  ks: k ranges of the fc partial sums.
+PvHeadArgs pv_head_args(const Dims &d, const Packed &w, int B, char *ws, const Workspace &o, int ks) {
+    PvHeadArgs p = {};
+    p.partial = (const float *)(ws + o.fcp); p.ks = ks; p.bfc = w.bfc;
+    p.wh = w.wh; p.whl = w.whl; p.bh = w.bh; p.B = B; p.A = d.A;
+    p.qmode = d.head == ARN_HEAD_Q ? 1 : d.head == ARN_HEAD_DUEL ? 2 : 0;
+    return p;
+}
+// Samples per workgroup of the head kernel in the inference calls: small batches are spread over more CUs
+inline int infer_rows_per_block(int B) { return B <= 512 ? 4 : B <= 4096 ? 8 : PVH_ROWS; }
+
+template <class G, bool F16, int MODE>
+void launch_fc_small(const char *name, const FcSmallArgs &p, int B, hipStream_t s) {
+    ProfScope ps(name, s);
+    auto launch = [&](auto nt, auto mt) {
+        constexpr int NT = decltype(nt)::value, MT = decltype(mt)::value;
+        hipLaunchKernelGGL((fc_small_kernel<G::FEAT, G::NHID, NT, MT, F16, MODE>), dim3(G::NHID / (16 * NT), cdiv(B, 16 * MT)),
+                           dim3(fc_small_threads<G::FEAT>()), 0, s, p);
+    };
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    // about 128 workgroups where the batch allows, then the tile with the fewest operand bytes per output
+    if (fc_small_rows(B) == 16) launch(One(), One());
+    else if (B <= 128) launch(One(), Two());
+    else launch(Two(), Two());
+}
+
+// fc layer and, for the categorical head, the head GEMM.  F16: act3 and the fc weights are fp16 and the layer is one
+// product (no-gradient forward); otherwise three bf16 products.  `head`: no-gradient forward with one of the small
+// heads: its outputs are written too.  Without it (gradient step) the caller launches pv_head_kernel on the fc sums.
+template <class G, bool F16>
 void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const Workspace &o, float *z_out,
-                          int zstride, hipStream_t s) {
+                          int zstride, PvHeadArgs *head, hipStream_t s) {
     __bf16 *a3 = (__bf16 *)(ws + o.a3), *a3l = (__bf16 *)(ws + o.a3l);
     __bf16 *h = (__bf16 *)(ws + o.h), *hl = (__bf16 *)(ws + o.hl);
-    {
-        typedef typename std::conditional<F16, FcFwdF16T<FEAT_>, FcFwdT<FEAT_>>::type Fc;
+    if (fc_small(G::FEAT, B, F16)) {
+        FcSmallArgs p = {};
+        p.act = a3; p.act_lo = a3l; p.w = F16 ? (const void *)w.wfch : (const void *)w.wfc; p.w_lo = w.wfcl; p.B = B;
+        p.partial = (float *)(ws + o.fcp); p.bias = w.bfc; p.h = h; p.h_lo = hl;
+        if (!d.small) {
+            launch_fc_small<G, F16, FC_HIDDEN>("fc_fwd", p, B, s);
+        } else if constexpr (F16) {
+            p.head = *head; p.zp = (float *)(ws + o.zp); p.counters = (unsigned *)(ws + o.cnt);
+            launch_fc_small<G, F16, FC_HEAD>("fc_head", p, B, s);
+        } else {
+            launch_fc_small<G, F16, FC_PARTIAL>("fc_fwd", p, B, s);
+        }
+    } else {
+        typedef typename std::conditional<F16, FcFwdF16T<G::FEAT>, FcFwdT<G::FEAT>>::type Fc;
         Fc p;
         p.in = a3; p.lo_off = a3l - a3; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
-        p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(B, F16); p.partial = (float *)(ws + o.fcp);
+        p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(G::FEAT, B, F16); p.partial = (float *)(ws + o.fcp);
         p.to_partial = p.ksplit > 1 || d.small;
         if constexpr (F16) launch_nt("fc_fwd", p, B, HID / Fc::BN, p.ksplit, s);
         else launch_nt_split("fc_fwd", p, B, HID / Fc::BN, p.ksplit, s);
@@ -186,13 +227,18 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
             hipLaunchKernelGGL(fc_finish_kernel, dim3(cdiv(total / 4, 256)), dim3(256), 0, s, p.partial, p.ksplit,
                                w.bfc, h, hl, total);
         }
+        if (d.small && head) {
+            ProfScope ps("pv_head", s);
+            head->ks = p.ksplit;
+            head->rpb = infer_rows_per_block(B);
+            hipLaunchKernelGGL(pv_head_kernel<false>, dim3(cdiv(B, head->rpb)), dim3(PVH_THREADS), 0, s, *head);
+        }
     }
     if (d.head == ARN_HEAD_C51) {
         HeadFwdC51 p;
         p.in = h; p.lo_off = hl - h; p.M = B; p.w = w.wh; p.w_lo = w.whl; p.bias = w.bh; p.z = z_out; p.ZW = d.NH; p.ZS = zstride;
         launch_nt_split("head_fwd", p, B, d.NHP / 64, 1, s);
     }
-    // policy/value and action-value heads: the caller launches pv_head_kernel on the fc partial sums
 }
 
 // Which configurations of the sample-resident kernels a geometry uses: the 84x84 network has hand-laid LDS
@@ -253,6 +299,7 @@ void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, ch
         p.a1 = a1; p.a1_lo = a1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.w3 = w.w3; p.w3_lo = w.w3l; p.b2 = w.b2; p.b3 = w.b3;
         p.a2 = masks ? a2 : nullptr; p.a3 = a3; p.a3_lo = a3l;
         p.m2 = masks ? (uint8_t *)(ws + o.m2) : nullptr; p.m3 = masks ? (uint8_t *)(ws + o.m3) : nullptr;
+        p.frag = fc_small(G::FEAT, B, false);
         const int spw = resident_spw(B, 256);
         if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, masks ? (uint8_t *)(ws + o.m1) : nullptr, p, B, spw, s);
         else Cfg::launch_conv23(p, B, spw, s);
@@ -266,39 +313,53 @@ void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, ch
         {
             typename Cfg::Fwd3::Args p;
             p.in = a2; p.in_lo = a2l; p.w = w.w3; p.w_lo = w.w3l; p.mask = nullptr; p.bias = w.b3; p.out = a3; p.out_lo = a3l;
-            p.mask_out = masks ? (uint8_t *)(ws + o.m3) : nullptr;
+            p.mask_out = masks ? (uint8_t *)(ws + o.m3) : nullptr; p.frag = fc_small(G::FEAT, B, false);
             launch_resident<typename Cfg::Fwd3>("conv3_fwd", p, B, s);
         }
     }
-    fc_and_head_launches<G::FEAT>(d, w, B, ws, o, z_out, zstride, s);
+    fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);
 }
 
-// Forward pass that carries no gradient (action selection): the three convolutions in one kernel and one fp16
-// product per layer, act3 in fp16, then the fc layer in fp16.  The heads run as in the training forward.
+// one workgroup per range of samples; the software-pipelined variant where its 17 KB of weights and biases fit beside the
+// LDS images (84x84)
+template <class G, bool FRAG>
+void launch_infer_conv(const InferConvArgs &p, int B, hipStream_t s) {
+    typedef typename ConvConfigs<G>::Fwd2 F2;
+    typedef typename ConvConfigs<G>::Fwd3 F3;
+    const int spw = resident_spw(B, 256);
+    if constexpr (infer_pipelined_fits<G, F2, F3>())
+        hipLaunchKernelGGL((infer_conv_pipelined_kernel<G, F2, F3, FRAG>), dim3(cdiv(B, spw)), dim3(INF_THREADS), 0, s, p, B, spw);
+    else
+        hipLaunchKernelGGL((infer_conv_kernel<G, F2, F3, FRAG>), dim3(cdiv(B, spw)), dim3(INF_THREADS), 0, s, p, B, spw);
+}
+
+// Forward pass that carries no gradient (action selection): the convolutions in one kernel and one fp16 product per
+// layer, act3 in fp16, then the fc layer in fp16.  C51: z_out = atom logits, rows of zstride floats; the other heads
+// write what `head` asks for.
 template <class G>
 void infer_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o,
-                 float *z_out, int zstride, hipStream_t s) {
+                 float *z_out, int zstride, PvHeadArgs *head, hipStream_t s) {
     typedef ConvConfigs<G> Cfg;
     {
         ProfScope ps("conv_infer", s);
         InferConvArgs p;
         p.obs = obs; p.w1 = w.w1h; p.w2 = w.w2h; p.w3 = w.w3h; p.b1 = w.b1; p.b2 = w.b2; p.b3 = w.b3;
         p.a3 = (_Float16 *)(ws + o.a3);
-        const int spw = resident_spw(B, 256);
-        // the software-pipelined variant where its 17 KB of weights and biases fit beside the LDS images (84x84)
-        if constexpr (infer_pipelined_fits<G, typename Cfg::Fwd2, typename Cfg::Fwd3>())
-            hipLaunchKernelGGL((infer_conv_pipelined_kernel<G, typename Cfg::Fwd2, typename Cfg::Fwd3>), dim3(cdiv(B, spw)),
-                               dim3(INF_THREADS), 0, s, p, B, spw);
-        else
-            hipLaunchKernelGGL((infer_conv_kernel<G, typename Cfg::Fwd2, typename Cfg::Fwd3>), dim3(cdiv(B, spw)),
-                               dim3(INF_THREADS), 0, s, p, B, spw);
+        p.counters = (unsigned *)(ws + o.cnt);
+        p.n_counters = fc_small(G::FEAT, B, true) && d.small ? (int)cdiv(B, fc_small_rows(B)) : 0;
+        const BandPlan bp = band_plan<G>(B);
+        if (bp.bands > 1)   // at most 128 samples
+            hipLaunchKernelGGL((infer_conv_band_kernel<G, typename Cfg::Fwd2, typename Cfg::Fwd3>), dim3(B * bp.bands),
+                               dim3(INF_THREADS), 0, s, p, bp.rows, bp.bands);
+        else if (fc_small(G::FEAT, B, true)) launch_infer_conv<G, true>(p, B, s);
+        else launch_infer_conv<G, false>(p, B, s);
     }
-    fc_and_head_launches<G::FEAT, true>(d, w, B, ws, o, z_out, zstride, s);
+    fc_and_head_launches<G, true>(d, w, B, ws, o, z_out, zstride, head, s);
 }
 void infer_launches(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o,
-                    float *z_out, int zstride, hipStream_t s) {
-    if (d.geom == ARN_GEOM_PAPER) infer_trunk<GeoPaper>(d, w, obs, B, ws, o, z_out, zstride, s);
-    else infer_trunk<Geo84>(d, w, obs, B, ws, o, z_out, zstride, s);
+                    float *z_out, int zstride, PvHeadArgs *head, hipStream_t s) {
+    if (d.geom == ARN_GEOM_PAPER) infer_trunk<GeoPaper>(d, w, obs, B, ws, o, z_out, zstride, head, s);
+    else infer_trunk<Geo84>(d, w, obs, B, ws, o, z_out, zstride, head, s);
 }
 
 // trunk + heads forward.  C51: z_out = atom logits, rows of zstride floats (NH = dense, or NHP for the
@@ -338,12 +399,12 @@ void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const 
         // 128 x 64 below (more workgroups)
         auto launch = [&](auto dg) {
             typedef decltype(dg) Dg;
-            typedef Wgrad<DenseGather<G::FEAT>, 128, 64, 2, HID, G::FEAT> FcW;
+            typedef Wgrad<LastActsGather<G::FEAT>, 128, 64, 2, HID, G::FEAT> FcW;
             dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
             DenseBackwardArgs<Dg, FcW> p;
             p.dg = dg;
             p.dg_x = cdiv(B, Dg::BM); p.dg_blocks = p.dg_x * ((G::FEAT + Dg::BN - 1) / Dg::BN);
-            p.wg.in = a3; p.wg.M = B; p.wg.dy = dph;
+            p.wg.in = a3; p.wg.M = B; p.wg.frag = fc_small(G::FEAT, B, false); p.wg.dy = dph;
             p.wg_part = partfc; p.wg_rows = rows_per_split(B, sp.fc);
             p.wg_blocks = (G::FEAT / FcW::BK2) * (HID / FcW::BN1) * sp.fc;
             p.hw = hg.wgrad;
@@ -393,19 +454,6 @@ void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const 
         hipLaunchKernelGGL((reduce_all_kernel<G::FEAT, G::P3>),
                            dim3(HID + 1 + pl.n1 + pl.n2 + pl.n3 + pl.nh + reduce_blocks(pl.head_bias)), dim3(256), 0, s, pl, dW);
     }
-}
-
-// Samples per workgroup of the head kernel in the inference calls: small batches are spread over more CUs
-inline int infer_rows_per_block(int B) { return B <= 512 ? 4 : B <= 4096 ? 8 : PVH_ROWS; }
-
-// Arguments of the fused policy/value head kernel that both entry points share.
-// f16: the fc partial sums come from the no-gradient forward (its own number of k ranges)
-PvHeadArgs pv_head_args(const Dims &d, const Packed &w, int B, char *ws, const Workspace &o, bool f16) {
-    PvHeadArgs p = {};
-    p.partial = (const float *)(ws + o.fcp); p.ks = fc_ksplit(B, f16); p.bfc = w.bfc;
-    p.wh = w.wh; p.whl = w.whl; p.bh = w.bh; p.B = B; p.A = d.A;
-    p.qmode = d.head == ARN_HEAD_Q ? 1 : d.head == ARN_HEAD_DUEL ? 2 : 0;
-    return p;
 }
 
 // Lays the flat fp32 parameters out in every packed form, one launch.
@@ -511,14 +559,10 @@ int policy_forward_launches(const arn_config *cfg, const Dims &d, const Workspac
                             const uint8_t *obs, int B, float *logits, float *value, float *probs, int32_t *greedy,
                             char *ws, hipStream_t s) {
     const Packed w = view_packed(w_packed, d);
-    infer_launches(d, w, obs, B, ws, o, logits, d.NH, s);
-    if (d.small) {
-        ProfScope ps("pv_head", s);
-        PvHeadArgs p = pv_head_args(d, w, B, ws, o, true);
-        p.logits = logits; p.value = value; p.probs = probs; p.greedy = greedy;
-        p.rpb = infer_rows_per_block(B);
-        hipLaunchKernelGGL(pv_head_kernel<false>, dim3(cdiv(B, p.rpb)), dim3(PVH_THREADS), 0, s, p);
-    } else if (value || probs || greedy) {
+    PvHeadArgs p = pv_head_args(d, w, B, ws, o, 1);
+    p.logits = logits; p.value = value; p.probs = probs; p.greedy = greedy;
+    infer_launches(d, w, obs, B, ws, o, logits, d.NH, &p, s);
+    if (!d.small && (value || probs || greedy)) {
         ProfScope ps("c51_dist", s);
         hipLaunchKernelGGL(c51_dist_kernel, dim3(cdiv(B, C51_WAVES)), dim3(64 * C51_WAVES), 0, s, logits, d.NH, B, d.A,
                            d.atoms, cfg->v_min, cfg->v_max, cfg->gamma, (const float *)nullptr,
@@ -574,14 +618,10 @@ int arn_policy_act(const arn_config *cfg, const void *w_packed, const uint8_t *o
     char *ws = (char *)workspace;
     const Packed w = view_packed(w_packed, d);
     float *z = (float *)(ws + o.z);   // categorical head only
-    infer_launches(d, w, obs, B, ws, o, z, d.NHP, s);
-    if (d.small) {
-        ProfScope ps("pv_head", s);
-        PvHeadArgs p = pv_head_args(d, w, B, ws, o, true);
-        p.u = u; p.u2 = u2; p.epsilon = epsilon; p.act_out = action; p.logp_out = logp;
-        p.rpb = infer_rows_per_block(B);
-        hipLaunchKernelGGL(pv_head_kernel<false>, dim3(cdiv(B, p.rpb)), dim3(PVH_THREADS), 0, s, p);
-    } else {
+    PvHeadArgs p = pv_head_args(d, w, B, ws, o, 1);
+    p.u = u; p.u2 = u2; p.epsilon = epsilon; p.act_out = action; p.logp_out = logp;
+    infer_launches(d, w, obs, B, ws, o, z, d.NHP, &p, s);
+    if (!d.small) {
         ProfScope ps("c51_dist", s);
         hipLaunchKernelGGL(c51_dist_kernel, dim3(cdiv(B, C51_WAVES)), dim3(64 * C51_WAVES), 0, s, z, d.NHP, B, d.A, d.atoms,
                            cfg->v_min, cfg->v_max, cfg->gamma, (const float *)nullptr, (const uint8_t *)nullptr,
@@ -639,7 +679,7 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
         // target network on next states -> projected target m; its activations are then overwritten
         const Packed wt = view_packed(batch->w_target_packed, d);
         float *ztgt = (float *)(ws + o.ztgt), *m = (float *)(ws + o.m);
-        infer_launches(d, wt, batch->next_obs, B, ws, o, ztgt, d.NHP, s);
+        infer_launches(d, wt, batch->next_obs, B, ws, o, ztgt, d.NHP, nullptr, s);
         {
             ProfScope ps("c51_target", s);
             hipLaunchKernelGGL(c51_dist_kernel, dim3(cdiv(B, C51_WAVES)), dim3(64 * C51_WAVES), 0, s, ztgt, d.NHP, B, d.A,
@@ -658,28 +698,20 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
             // states -> its greedy action.  The activations of these passes are then overwritten.
             wt_view = view_packed(batch->w_target_packed, d);
             wt = &wt_view;
-            infer_launches(d, *wt, batch->next_obs, B, ws, o, nullptr, 0, s);
-            {
-                ProfScope ps("q_target", s);
-                PvHeadArgs p = pv_head_args(d, *wt, B, ws, o, true);
-                p.logits = (float *)(ws + o.qt);
-                if (!cfg->double_q) p.greedy = batch->next_action;
-                p.rpb = loss_block(B);
-                hipLaunchKernelGGL(pv_head_kernel<false>, dim3(lblocks), dim3(PVH_THREADS), 0, s, p);
-            }
+            PvHeadArgs p = pv_head_args(d, *wt, B, ws, o, 1);
+            p.logits = (float *)(ws + o.qt);
+            if (!cfg->double_q) p.greedy = batch->next_action;
+            infer_launches(d, *wt, batch->next_obs, B, ws, o, nullptr, 0, &p, s);
             if (cfg->double_q) {
-                infer_launches(d, w, batch->next_obs, B, ws, o, nullptr, 0, s);
-                ProfScope ps("q_select", s);
-                PvHeadArgs p = pv_head_args(d, w, B, ws, o, true);
-                p.greedy = astar;
-                p.rpb = loss_block(B);
-                hipLaunchKernelGGL(pv_head_kernel<false>, dim3(lblocks), dim3(PVH_THREADS), 0, s, p);
+                PvHeadArgs q = pv_head_args(d, w, B, ws, o, 1);
+                q.greedy = astar;
+                infer_launches(d, w, batch->next_obs, B, ws, o, nullptr, 0, &q, s);
             }
         }
         forward_launches(d, w, batch->obs, B, ws, o, nullptr, 0, true, s);
         // fc finish, head, objective, dz and the head's input gradient d(pre_fc) in one kernel
         ProfScope ps("pv_head", s);
-        PvHeadArgs p = pv_head_args(d, w, B, ws, o, false);
+        PvHeadArgs p = pv_head_args(d, w, B, ws, o, fc_ksplit(d.feat, B, false));
         p.action = batch->action; p.adv = batch->adv; p.ret = batch->ret; p.old_logp = batch->old_logp;
         p.objective = loss_kind == ARN_LOSS_PPO ? 1 : loss_kind == ARN_LOSS_DQN ? 2 : 0;
         p.clip_eps = cfg->clip_eps; p.value_coef = cfg->value_coef; p.entropy_coef = cfg->entropy_coef;

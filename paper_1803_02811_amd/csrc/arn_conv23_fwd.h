@@ -23,6 +23,7 @@ struct Conv23Args {
     __bf16 *a2;                      // act2 hi [B][P2][64] for the backward pass, or null
     __bf16 *a3, *a3_lo;              // act3 [B][P3][64], hi and lo
     uint8_t *m2, *m3;                // sign bits of act2 / act3 for the backward pass, or null
+    bool frag;                       // act3 in fragment order (LastActs)
 };
 
 // LDS bytes of conv23_fwd_fused_body<P2, P3>: conv2's input image and two of conv3's, hi and lo parts each
@@ -252,7 +253,7 @@ __device__ __forceinline__ void conv23_fwd_fused_body(u32x4 *lds, int block, con
                 const int pos = t * 16 + li;
                 const bool valid = pos < R3;
                 const size_t at = ((size_t)s * R3 + pos) * P3::CO + n0;
-                if (valid) store_bf16x4_split(a.a3, a.a3_lo, at, r0, r1, r2, r3, std::integral_constant<bool, FULL>());
+                if (valid) store_bf16x4_split(a.a3, a.a3_lo, LastActs<P3::CO, R3>::at(a.frag, s, pos, n0), r0, r1, r2, r3, std::integral_constant<bool, FULL>());
                 if (FULL || a.m3) {
                     const uint32_t bits = sign_bits16(r0, r1, r2, r3, lg);     // all lanes take part
                     if (lg == 0 && valid) *reinterpret_cast<uint16_t *>(a.m3 + (at >> 3)) = (uint16_t)bits;
@@ -281,13 +282,14 @@ __global__ __launch_bounds__(C23_THREADS) void conv123_fwd_kernel(const uint8_t 
     static_assert(RES_THREADS == C23_THREADS, "one block size for both bodies");
     constexpr int L1 = conv1_fwd_lds_bytes<Geo>(), L23 = conv23_fwd_lds_bytes<P2, P3>();
     __shared__ u32x4 lds[(L1 > L23 ? L1 : L23) / 16];
-    conv1_fwd_resident_body<Geo, true>(lds, blockIdx.x, 0, 1, obs, w1, w1_lo, b1, const_cast<__bf16 *>(a.a1), const_cast<__bf16 *>(a.a1_lo),
+    const int block = sample_block(blockIdx.x, gridDim.x, spw, a.frag);
+    conv1_fwd_resident_body<Geo, true>(lds, block, 0, 1, obs, w1, w1_lo, b1, const_cast<__bf16 *>(a.a1), const_cast<__bf16 *>(a.a1_lo),
                                  m1, B, spw);
     // The barrier orders this workgroup's act1 stores before its own reads (a workgroup's wavefronts share the CU's
     // vector cache).  A device-wide fence here is ruinous: it writes back and invalidates the whole L2 of the XCD,
     // once per workgroup (measured: 186 instead of 97 us).
     __syncthreads();
-    conv23_fwd_fused_body<P2, P3, true>(lds, blockIdx.x, a, B, spw);
+    conv23_fwd_fused_body<P2, P3, true>(lds, block, a, B, spw);
 }
 
 }  // namespace arn

@@ -105,6 +105,41 @@ __host__ __device__ constexpr long frag_index(long row, long k, long K) {
     return ((row >> 4) * (K >> 5) + (k >> 5)) * 512 + ((((k & 31) >> 3) << 4) + (row & 15)) * 8 + (k & 7);
 }
 
+// Workgroups go to the eight XCDs round robin.  This renumbers blocks 0 .. n-1 so that an XCD gets runs of `run` (a power of
+// two) consecutive ones: data that neighbouring blocks write side by side in a cache line then meets in one L2.
+__device__ __forceinline__ int xcd_runs(int b, int n, int run) {
+    int base = 0;
+    for (; run > 1; run >>= 1) {
+        const int chunk = 8 * run, full = (n - base) / chunk * chunk;
+        if (b - base < full) {
+            const int r = (b - base) % chunk;
+            return b - r + (r & 7) * run + (r >> 3);
+        }
+        base += full;
+    }
+    return b;
+}
+// sample range of `spw` samples that workgroup b of n works on: with the activations in fragment order the 16-byte words of
+// eight consecutive samples share a cache line (256 samples, a workgroup each: 10.2 -> 9.4 us for the three convolutions)
+__device__ __forceinline__ int sample_block(int b, int n, int spw, bool frag) {
+    return frag ? xcd_runs(b, n, spw == 1 ? 8 : spw == 2 ? 4 : 1) : b;
+}
+
+// Addresses (in elements) of the last convolution's activations [sample][position][NC channels], the fc layer's input:
+// rows, or -- for the batches that fc_small_kernel serves -- fragment order over (sample, position * NC + channel).
+template <int NC, int P>
+struct LastActs {
+    static_assert(NC % 32 == 0, "whole k-steps per position");
+    template <bool FRAG>
+    static __device__ __forceinline__ size_t at(int s, int pos, int n) {   // n: multiple of 4
+        if constexpr (FRAG)
+            return (size_t)(s >> 4) * (NC * P * 16) + (s & 15) * 8 + (size_t)(pos * (NC * 16) + (n >> 5) * FRAG_STEP + ((n & 31) >> 3) * 128 + (n & 7));
+        else
+            return ((size_t)s * P + pos) * NC + n;
+    }
+    static __device__ __forceinline__ size_t at(bool frag, int s, int pos, int n) { return frag ? at<true>(s, pos, n) : at<false>(s, pos, n); }
+};
+
 __device__ __forceinline__ u32x4 zero_u4() { return u32x4{0u, 0u, 0u, 0u}; }
 
 // Waits until every global load of this wavefront has returned (s_waitcnt vmcnt(0), other counters unchanged).
@@ -220,6 +255,17 @@ struct HasPrefetch<P, decltype((void)&P::prefetch)> {
     static constexpr bool value = true;
 };
 
+// Problems with a static member FRAG_W = true hold their weights in fragment order (frag_index): a k-tile of BN rows is
+// contiguous kilobytes, staged as they are; fragment reads from them are conflict-free without padding.
+template <class P, class = void>
+struct FragW {
+    static constexpr bool value = false;
+};
+template <class P>
+struct FragW<P, decltype((void)P::FRAG_W)> {
+    static constexpr bool value = P::FRAG_W;
+};
+
 // Problems whose number of weight rows N_ROWS is not a multiple of BN: the last tile's rows past the end are read from
 // the last row (and the problem's epilogue drops their columns).
 template <class P, class = void>
@@ -245,7 +291,8 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
     constexpr int TN = BN / (32 * WN), TM = BM / (32 * WM);
     constexpr int A_CH = BM / RS, W_CH = BN / RS;     // 16-byte chunks staged per thread and k-tile
     static_assert(BM % RS == 0 && BN % RS == 0, "staging passes");
-    constexpr bool ALO = ActLo<P, SPLIT>::value;
+    constexpr bool ALO = ActLo<P, SPLIT>::value, FRAGW = FragW<P>::value;
+    constexpr int WSTEP = FRAGW ? FRAG_STEP * 2 / 8 : 8;   // 16-byte words from one k-tile of a weight row (or tile) to the next
     int kt_begin = 0, KT = p.K / 64;
     if constexpr (HasKSplit<P>::value) {
         // Split-k launches: workgroups go to the eight XCDs round robin in linear order (x fastest), and each XCD has
@@ -293,10 +340,16 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
     const u32x4 *wsrc2[W_CH];
 #pragma unroll
     for (int i = 0; i < W_CH; ++i) {
-        const int nrow = n0 + r0 + RS * i;
-        const size_t at = (size_t)(nrow < WeightRows<P>::value ? nrow : WeightRows<P>::value - 1) * p.K;
-        wsrc[i] = reinterpret_cast<const u32x4 *>(p.weights(z) + at) + kc;
-        if constexpr (SPLIT) wsrc2[i] = reinterpret_cast<const u32x4 *>(p.weights_lo(z) + at) + kc;
+        size_t at;
+        if constexpr (FRAGW) {
+            const int c = tid + NT * i;   // 128 16-byte words per 16 rows and k-tile
+            at = ((size_t)(n0 / 16 + (c >> 7)) * (p.K / 32)) * FRAG_STEP + (c & 127) * 8;
+        } else {
+            const int nrow = n0 + r0 + RS * i;
+            at = (size_t)(nrow < WeightRows<P>::value ? nrow : WeightRows<P>::value - 1) * p.K + kc * 8;
+        }
+        wsrc[i] = reinterpret_cast<const u32x4 *>(p.weights(z) + at);
+        if constexpr (SPLIT) wsrc2[i] = reinterpret_cast<const u32x4 *>(p.weights_lo(z) + at);
     }
 
     u32x4 ra[A_CH], rw[W_CH], ra2[ALO ? A_CH : 1], rw2[SPLIT ? W_CH : 1];
@@ -308,8 +361,8 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
         }
 #pragma unroll
         for (int i = 0; i < W_CH; ++i) {
-            rw[i] = wsrc[i][kt * 8];
-            if constexpr (SPLIT) rw2[i] = wsrc2[i][kt * 8];
+            rw[i] = wsrc[i][kt * WSTEP];
+            if constexpr (SPLIT) rw2[i] = wsrc2[i][kt * WSTEP];
         }
     };
 
@@ -329,8 +382,9 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
         }
 #pragma unroll
         for (int i = 0; i < W_CH; ++i) {
-            sW[st * SW + (r0 + RS * i) * LDS_ROW + kc] = rw[i];
-            if constexpr (SPLIT) sW2[st * SW + (r0 + RS * i) * LDS_ROW + kc] = rw2[i];
+            const int at = st * SW + (FRAGW ? tid + NT * i : (r0 + RS * i) * LDS_ROW + kc);
+            sW[at] = rw[i];
+            if constexpr (SPLIT) sW2[at] = rw2[i];
         }
     };
 
@@ -362,7 +416,9 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
             bf16x8 fw[TN], fa[TM], fw2[SPLIT ? TN : 1], fa2[ALO ? TM : 1];
 #pragma unroll
             for (int a = 0; a < TN; ++a) {
-                const int at = st * SW + ((wn * TN + a) * 32 + fr) * LDS_ROW + kk * 2 + fg;
+                const int row = (wn * TN + a) * 32 + fr;
+                const int at = st * SW + (FRAGW ? (row >> 4) * 128 + (kk >> 1) * 64 + ((kk & 1) * 2 + fg) * 16 + (row & 15)
+                                                : row * LDS_ROW + kk * 2 + fg);
                 fw[a] = as_bf16x8(sW[at]);
                 if constexpr (SPLIT) fw2[a] = as_bf16x8(sW2[at]);
             }

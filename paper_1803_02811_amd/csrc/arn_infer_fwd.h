@@ -37,6 +37,15 @@ __device__ __forceinline__ u32x4 u8x8_to_f16x8(uint32_t lo, uint32_t hi) {
     return r;
 }
 
+__device__ __forceinline__ f32x4 mfma_f16(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// Batches that fc_small_kernel serves (FRAG) accumulate conv2 and conv3 in two halves of the contraction, as
+// infer_conv_band_kernel does, so that a sample's bits do not depend on the size of its batch.
+template <bool FRAG>
+constexpr int half_of(int step, int steps) { return FRAG && 2 * step >= steps ? 1 : 0; }
+__device__ __forceinline__ f32x4 sum_halves(const f32x4 (&a)[2]) { return a[0] + a[1]; }
+__device__ __forceinline__ f32x4 sum_halves(const f32x4 (&a)[1]) { return a[0]; }
+
 // relu(v) as four fp16 (finite: clamped to the largest half)
 __device__ __forceinline__ u32x2 relu_f16x4(float a, float b, float c, float d) {
     const f16x4 h = {(_Float16)fminf(fmaxf(a, 0.f), F16_MAX), (_Float16)fminf(fmaxf(b, 0.f), F16_MAX),
@@ -49,14 +58,20 @@ struct InferConvArgs {
     const _Float16 *w1, *w2, *w3;       // forward weights [co][k'] in fragment order (frag_index)
     const float *b1, *b2, *b3;
     _Float16 *a3;                       // [B][P3][64]
+    unsigned *counters;                 // cleared for the fc kernel's count of finished workgroups
+    int n_counters;
 };
+__device__ __forceinline__ void clear_counters(const InferConvArgs &a) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < a.n_counters; i += INF_THREADS) a.counters[i] = 0;
+}
 
 // P2 / P3: LDS image descriptions of conv2's and conv3's input (ResConv2Fwd / ResConv3Fwd or their bordered
 // variants); only the addressing members are used, for one sample and a single part.
 template <class Geo, class P2, class P3>
 constexpr int infer_conv_lds_bytes() { return 2 * Geo::OBS_BYTES + P2::IMG + P3::IMG; }
 
-template <class Geo, class P2, class P3>
+template <class Geo, class P2, class P3, bool FRAG>   // FRAG: a3 in fragment order (LastActs)
 __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConvArgs a, int B, int spw) {
     constexpr int IN_H = Geo::IN_H, IN_W = Geo::IN_W, W1 = Geo::W1, NP1 = Geo::P1, NP2 = Geo::P2, NP3 = Geo::P3;
     constexpr int OBS_BYTES = Geo::OBS_BYTES, IMG_U4 = OBS_BYTES / 16, NL = (IMG_U4 + INF_THREADS - 1) / INF_THREADS;
@@ -76,7 +91,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, lg = lane >> 4;
-    const int s_begin = blockIdx.x * spw;
+    const int s_begin = sample_block(blockIdx.x, gridDim.x, spw, FRAG) * spw;
     const int s_end = s_begin + spw < B ? s_begin + spw : B;
     if (s_begin >= s_end) return;
 
@@ -101,6 +116,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
         }
     };
     gload(s_begin);
+    clear_counters(a);
 
     // conv1: wavefront w owns channel tile w & 1 and position tiles (w >> 1) + 4 j
     const int ct1 = wave & 1, t1_first = wave >> 1;
@@ -172,7 +188,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
             const bool valid = row < NP2;
             row = valid ? row : NP2 - 1;
             const int base = P2::base_off(row) + 16 * lg;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            f32x4 acc[FRAG ? 2 : 1] = {};
             f16x8 fa[Q2], fb[Q2];
             auto load_q = [&](int q, f16x8 (&f)[Q2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -187,14 +203,15 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
             for (int q = 0; q < KS2 / Q2; q += 2) {
                 load_q(q + 1, fb);
 #pragma unroll
-                for (int j = 0; j < Q2; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[q * Q2 + j], fa[j], acc, 0, 0, 0);
+                for (int j = 0; j < Q2; ++j) acc[half_of<FRAG>(q * Q2 + j, KS2)] = mfma_f16(w2[q * Q2 + j], fa[j], acc[half_of<FRAG>(q * Q2 + j, KS2)]);
                 if (q + 2 < KS2 / Q2) load_q(q + 2, fa);
 #pragma unroll
-                for (int j = 0; j < Q2; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[(q + 1) * Q2 + j], fb[j], acc, 0, 0, 0);
+                for (int j = 0; j < Q2; ++j) acc[half_of<FRAG>((q + 1) * Q2 + j, KS2)] = mfma_f16(w2[(q + 1) * Q2 + j], fb[j], acc[half_of<FRAG>((q + 1) * Q2 + j, KS2)]);
             }
+            const f32x4 v = sum_halves(acc);
             if (valid)
                 *reinterpret_cast<u32x2 *>(a2l + P3::dst_off(row) + (ct * 16 + 4 * lg) * 2) =
-                    relu_f16x4(acc[0] + bias2.x, acc[1] + bias2.y, acc[2] + bias2.z, acc[3] + bias2.w);
+                    relu_f16x4(v[0] + bias2.x, v[1] + bias2.y, v[2] + bias2.z, v[3] + bias2.w);
         }
         __syncthreads();          // act2 complete; every read of the act1 image done; the next frame image staged
         if (s + 1 < s_end) load_w1();   // conv1's weights for the next sample arrive while conv3 runs
@@ -207,7 +224,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
             const bool valid = row < NP3;
             row = valid ? row : NP3 - 1;
             const int base = P3::base_off(row) + 16 * lg;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            f32x4 acc[FRAG ? 2 : 1] = {};
             f16x8 fa[Q3], fb[Q3];
             auto load_q = [&](int q, f16x8 (&f)[Q3]) __attribute__((always_inline)) {
 #pragma unroll
@@ -220,15 +237,16 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
             load_q(0, fa);
             load_q(1, fb);
 #pragma unroll
-            for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[j], fa[j], acc, 0, 0, 0);
+            for (int j = 0; j < Q3; ++j) acc[0] = mfma_f16(w3[j], fa[j], acc[0]);
             load_q(2, fa);
 #pragma unroll
-            for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[Q3 + j], fb[j], acc, 0, 0, 0);
+            for (int j = 0; j < Q3; ++j) acc[half_of<FRAG>(Q3 + j, KS3)] = mfma_f16(w3[Q3 + j], fb[j], acc[half_of<FRAG>(Q3 + j, KS3)]);
 #pragma unroll
-            for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[2 * Q3 + j], fa[j], acc, 0, 0, 0);
+            for (int j = 0; j < Q3; ++j) acc[half_of<FRAG>(2 * Q3 + j, KS3)] = mfma_f16(w3[2 * Q3 + j], fa[j], acc[half_of<FRAG>(2 * Q3 + j, KS3)]);
+            const f32x4 v = sum_halves(acc);
             if (valid)
-                *reinterpret_cast<u32x2 *>(a.a3 + ((size_t)s * NP3 + row) * C3 + ct * 16 + 4 * lg) =
-                    relu_f16x4(acc[0] + bias3.x, acc[1] + bias3.y, acc[2] + bias3.z, acc[3] + bias3.w);
+                *reinterpret_cast<u32x2 *>(a.a3 + LastActs<C3, NP3>::template at<FRAG>(s, row, ct * 16 + 4 * lg)) =
+                    relu_f16x4(v[0] + bias3.x, v[1] + bias3.y, v[2] + bias3.z, v[3] + bias3.w);
         }
         // no barrier here: conv1 of the next sample writes the act1 image (its readers passed the barrier above)
         // and reads the frame image staged before that barrier; conv2 of the next sample, which overwrites the
@@ -259,7 +277,7 @@ constexpr int infer_pipelined_lds_bytes() { return 2 * Geo::OBS_BYTES + P2::IMG 
 template <class Geo, class P2, class P3>
 constexpr bool infer_pipelined_fits() { return infer_pipelined_lds_bytes<Geo, P2, P3>() <= 160 * 1024; }
 
-template <class Geo, class P2, class P3>
+template <class Geo, class P2, class P3, bool FRAG>   // FRAG: a3 in fragment order (LastActs)
 __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const InferConvArgs a, int B, int spw) {
     constexpr int IN_H = Geo::IN_H, IN_W = Geo::IN_W, W1 = Geo::W1, NP1 = Geo::P1, NP2 = Geo::P2, NP3 = Geo::P3;
     constexpr int OBS_BYTES = Geo::OBS_BYTES, IMG_U4 = OBS_BYTES / 16, NL = (IMG_U4 + INF_THREADS - 1) / INF_THREADS;
@@ -284,11 +302,10 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
-    const int s_begin = blockIdx.x * spw;
+    const int s_begin = sample_block(blockIdx.x, gridDim.x, spw, FRAG) * spw;
     const int s_end = s_begin + spw < B ? s_begin + spw : B;
     if (s_begin >= s_end) return;
 
-    // frame of a later sample, in registers until the image buffer is free
     // frame of a later sample, in registers until the image buffer is free
     u32x4 rimg[NL];
     auto gload = [&](int s) __attribute__((always_inline)) {
@@ -310,6 +327,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
         }
     };
     gload(s_begin);
+    clear_counters(a);
     // conv1: wavefront w owns channel tile w & 1 and position tiles (w >> 1) + 4 j
     const int ct1 = wave & 1, t1_first = wave >> 1;
     // conv1's weights go to LDS once
@@ -428,7 +446,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
                 const int tn = t + 2;
                 const bool more = tn < NT2;
                 const int base_n = tile_at(more ? tn : t, row_n, valid_n);
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                f32x4 acc[FRAG ? 2 : 1] = {};
                 float4 bias2;
 #pragma unroll
                 for (int q = 0; q < NB2; q += 2) {
@@ -436,7 +454,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
                     load_q(base, q + 1, fb);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int j = 0; j < Q2; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[q * Q2 + j], fa[j], acc, 0, 0, 0);
+                    for (int j = 0; j < Q2; ++j) acc[half_of<FRAG>(q, NB2)] = mfma_f16(w2[q * Q2 + j], fa[j], acc[half_of<FRAG>(q, NB2)]);
                     __builtin_amdgcn_sched_barrier(0);
                     if (q + 2 < NB2) {
                         load_q(base, q + 2, fa);
@@ -446,12 +464,13 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
                     }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int j = 0; j < Q2; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[(q + 1) * Q2 + j], fb[j], acc, 0, 0, 0);
+                    for (int j = 0; j < Q2; ++j) acc[half_of<FRAG>(q + 1, NB2)] = mfma_f16(w2[(q + 1) * Q2 + j], fb[j], acc[half_of<FRAG>(q + 1, NB2)]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
+                const f32x4 v = sum_halves(acc);
                 if (valid)
                     *reinterpret_cast<u32x2 *>(a2l + P3::dst_off(row) + (ct * 16 + 4 * lg) * 2) =
-                        relu_f16x4(acc[0] + bias2.x, acc[1] + bias2.y, acc[2] + bias2.z, acc[3] + bias2.w);
+                        relu_f16x4(v[0] + bias2.x, v[1] + bias2.y, v[2] + bias2.z, v[3] + bias2.w);
                 if (!more) break;
                 t = tn; base = base_n; row = row_n; valid = valid_n;
             }
@@ -487,27 +506,28 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const
                 const int tn = t + 2;
                 more = tn < NT3;
                 base_n = tile_at(more ? tn : t, row_n, valid_n);
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                f32x4 acc[FRAG ? 2 : 1] = {};
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[j], x[j], acc, 0, 0, 0);
+                for (int j = 0; j < Q3; ++j) acc[0] = mfma_f16(w3[j], x[j], acc[0]);
                 __builtin_amdgcn_sched_barrier(0);
                 load_q(base, 2, x);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[Q3 + j], y[j], acc, 0, 0, 0);
+                for (int j = 0; j < Q3; ++j) acc[half_of<FRAG>(Q3 + j, KS3)] = mfma_f16(w3[Q3 + j], y[j], acc[half_of<FRAG>(Q3 + j, KS3)]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (more) load_q(base_n, 0, y);
                 const float4 bias3 = *bias3p;
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < Q3; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[2 * Q3 + j], x[j], acc, 0, 0, 0);
+                for (int j = 0; j < Q3; ++j) acc[half_of<FRAG>(2 * Q3 + j, KS3)] = mfma_f16(w3[2 * Q3 + j], x[j], acc[half_of<FRAG>(2 * Q3 + j, KS3)]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (more) load_q(base_n, 1, x);
                 __builtin_amdgcn_sched_barrier(0);
+                const f32x4 v = sum_halves(acc);
                 if (valid)
-                    *reinterpret_cast<u32x2 *>(a.a3 + ((size_t)s * NP3 + row) * C3 + ct * 16 + 4 * lg) =
-                        relu_f16x4(acc[0] + bias3.x, acc[1] + bias3.y, acc[2] + bias3.z, acc[3] + bias3.w);
+                    *reinterpret_cast<u32x2 *>(a.a3 + LastActs<C3, NP3>::template at<FRAG>(s, row, ct * 16 + 4 * lg)) =
+                        relu_f16x4(v[0] + bias3.x, v[1] + bias3.y, v[2] + bias3.z, v[3] + bias3.w);
                 t = tn; base = base_n; row = row_n; valid = valid_n;
             };
             load_q(base, 0, fa);

@@ -24,17 +24,20 @@ constexpr int HID = 512;
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Frame size and padding of the convolution stack as compile-time constants (the filter shapes above are
-// common to both).  Geo84 restates the constants above; GeoPaper is the appendix's own setting: 104x80
-// frames, no padding on conv1, padding 1 on conv2 and conv3.
-template <int IN_H_, int IN_W_, int PAD2_, int PAD3_>
+// Frame size, padding and channel counts of the network as compile-time constants (the filter sizes and strides
+// above are common to all).  Geo84 restates the constants above; GeoPaper is the appendix's own setting: 104x80
+// frames, no padding on conv1, padding 1 on conv2 and conv3.  HL x WL: the last feature map, NCL its channels.
+template <int IN_H_, int IN_W_, int PAD2_, int PAD3_, int NC1_ = arn::C1, int NC2_ = arn::C2, bool HAS3_ = true, int NHID_ = HID>
 struct Geometry {
     static constexpr int IN_H = IN_H_, IN_W = IN_W_, PAD2 = PAD2_, PAD3 = PAD3_;
+    static constexpr int NC1 = NC1_, NC2 = NC2_, NHID = NHID_, KW2 = NC1_ * K2 * K2;
+    static constexpr bool HAS3 = HAS3_;
     static constexpr int H1 = (IN_H - K1) / S1 + 1, W1 = (IN_W - K1) / S1 + 1;
     static constexpr int H2 = (H1 + 2 * PAD2 - K2) / S2 + 1, W2 = (W1 + 2 * PAD2 - K2) / S2 + 1;
     static constexpr int H3 = (H2 + 2 * PAD3 - K3) / S3 + 1, W3 = (W2 + 2 * PAD3 - K3) / S3 + 1;
     static constexpr int P1 = H1 * W1, P2 = H2 * W2, P3 = H3 * W3;
-    static constexpr int OBS_BYTES = IN_C * IN_H * IN_W, FEAT = C3 * P3;
+    static constexpr int HL = HAS3 ? H3 : H2, WL = HAS3 ? W3 : W2, PL = HL * WL, NCL = HAS3 ? C3 : NC2;
+    static constexpr int OBS_BYTES = IN_C * IN_H * IN_W, FEAT = NCL * PL;
 };
 typedef Geometry<84, 84, 0, 0> Geo84;
 typedef Geometry<104, 80, 1, 1> GeoPaper;
@@ -269,7 +272,15 @@ inline Splits make_splits(const Dims &d, int B) {
 // f16: the one-product fc layer of the no-gradient forward, whose GEMM is a third of the work: from 128 samples up
 // eight ranges are the better trade (inference at 256 samples 25.4 -> 23.8 us per call, at 512 33.7 -> 31.6; at 64 and
 // below sixteen stay ahead by half a microsecond, and the three-product layer of the gradient step at every size).
-inline int fc_ksplit(int B, bool f16 = false) {
+// Small batches run in fc_small_kernel (one workgroup per 16 or 32 units and 16 or 32 samples, no k ranges in memory).  Its
+// workgroups of one XCD share a band of weights and each XCD reads all activations, so it pays as long as those are few:
+// up to about 2.5 M of them, counting hi and lo parts (one product, 3136 inputs, 256 samples: 10.8 us with the head
+// against 8.4 + 5.7; three products, 6912 inputs, 512 samples: 29.6 against 18.8).
+constexpr int FC_SMALL_MAX = 512;
+inline bool fc_small(int feat, int B, bool f16) { return B <= FC_SMALL_MAX && (long)B * feat * (f16 ? 1 : 2) <= 2500000; }
+inline int fc_small_rows(int B) { return B <= 64 ? 16 : 32; }   // samples per workgroup
+inline int fc_ksplit(int feat, int B, bool f16) {
+    if (fc_small(feat, B, f16)) return 1;
     const int tiles = ((B + 127) / 128) * 4;
     int ks = 256 / tiles;
     if (ks < 1) ks = 1;
@@ -292,6 +303,7 @@ struct Workspace {
     size_t a1, a2, a3, h;               // bf16 NHWC activations
     size_t a1l, a2l, a3l, hl;           // their low parts (written and read by the forward pass only)
     size_t fcp;                         // fp32 [ksplit][B][512] partial sums of the fc forward GEMM
+    size_t zp, cnt;                     // fc_small_kernel: contributions to the head outputs [HID/16][padded B][32], counters
     size_t z, zv;                       // categorical head: fp32 atom logits, rows padded to NHP floats
     size_t ztgt, m;                     // C51: target-net atom logits, projected target
     size_t qt, astar;                   // DQN: target-net Q(s',.) fp32 [B][A]; Double-DQN: online greedy action on s' int32 [B]
@@ -315,14 +327,20 @@ inline Workspace make_workspace(const Dims &d, int B, int mode) {
     const size_t p1 = (size_t)d.p1, p2 = (size_t)d.p2, feat = (size_t)d.feat;
     w.a1 = take(b * p1 * C1 * 2);
     w.a2 = take(b * p2 * C2 * 2);
-    w.a3 = take(b * feat * 2);
+    const size_t b3 = B <= FC_SMALL_MAX ? align_up(b, 32) : b;   // fragment order: whole sample tiles
+    w.a3 = take(b3 * feat * 2);
     w.h = take(b * HID * 2);
     w.a1l = take(b * p1 * C1 * 2);
     w.a2l = take(b * p2 * C2 * 2);
-    w.a3l = take(b * feat * 2);
+    w.a3l = take(b3 * feat * 2);
     w.hl = take(b * HID * 2);
     // the fused policy/value head kernel always reads fp32 partials; the categorical path only when k is split
-    w.fcp = take((size_t)(fc_ksplit(B) > 1 || d.small ? fc_ksplit(B) : 0) * b * HID * 4);
+    const int ks = fc_ksplit(d.feat, B, false), ks16 = fc_ksplit(d.feat, B, true), ksm = ks > ks16 ? ks : ks16;
+    w.fcp = take((size_t)(ksm > 1 || d.small ? ksm : 0) * b * HID * 4);
+    if (fc_small(d.feat, B, true) && d.small) {
+        w.zp = take((size_t)(HID / 16) * align_up(b, 32) * 32 * 4);
+        w.cnt = take((size_t)FC_SMALL_MAX / 16 * 4);
+    }
     // categorical head: atom logits of arn_policy_act (arn_policy_forward writes them to its `logits` argument)
     if (mode == ARN_MODE_FORWARD) w.z = take(d.small ? 0 : b * (size_t)d.NHP * 4);
     if (mode == ARN_MODE_TRAIN) {

@@ -67,7 +67,7 @@ template <int FEAT_>
 struct FcFwdT : DenseGather<FEAT_> {
     typedef typename DenseGather<FEAT_>::Row Row;
     static constexpr int BM = 128, BN = 128, WAVES_N = 2, K = FEAT_, STAGES = 2, THREADS = 512;
-    static constexpr bool ACT_LO = true;
+    static constexpr bool ACT_LO = true, FRAG_W = true;
     int ksplit;
     bool to_partial;     // write fp32 partial sums even with ksplit == 1 (the consumer finishes the layer)
     const __bf16 *w, *w_lo = nullptr;
@@ -189,7 +189,18 @@ struct Wgrad : Gather {
         return *reinterpret_cast<const u32x4 *>(dy + (size_t)m * N1 + n);
     }
 };
-typedef Wgrad<DenseGather<FEAT>, 128, 64, 2, HID, FEAT> FcWgrad;
+// the fc layer's input, in rows or in fragment order (LastActs)
+template <int K_>
+struct LastActsGather {
+    const __bf16 *in;
+    int M;
+    bool frag;
+    typedef const __bf16 *Row;
+    __device__ __forceinline__ Row row_at(long m) const { return in + (frag ? (size_t)(m >> 4) * (K_ * 16) + (m & 15) * 8 : (size_t)m * K_); }
+    __device__ __forceinline__ u32x4 load_at(Row r, int k) const {   // m < M, k: multiple of 8
+        return *reinterpret_cast<const u32x4 *>(r + (frag ? (k >> 5) * FRAG_STEP + ((k & 31) >> 3) * 128 : k));
+    }
+};
 // heads: N1 (padded head rows) is a run-time value
 struct HeadWgrad : DenseGather<HID> {
     static constexpr int BN1 = 64, BK2 = 128, WAVES_X = 4, KP = HID;

@@ -86,6 +86,81 @@ __device__ __forceinline__ float group16_scan(float v, int c) {   // inclusive p
 __device__ __forceinline__ int group16_min(int v) { return row16_min(v); }
 __device__ __forceinline__ float group16_max(float v) { return row16_max(v); }
 
+// What the sample's head outputs mean, in the 16 lanes of its group; lane c holds rows c and c + 16.
+struct HeadRows {
+    float z0, z1, x0, x1;   // the lane's two rows: outputs (action values for a dueling head); -inf outside the actions
+    float v, mx;            // the value row; the maximum over the actions
+    int arg;                // lowest index that attains it
+    bool on0, on1;
+};
+__device__ __forceinline__ HeadRows head_rows_of(float z0, float z1, int c, int A, int qmode) {
+    HeadRows h;
+    h.on0 = c < A; h.on1 = c + 16 < A;
+    // value = head row A (policy/value and dueling heads)
+    const float vsel = A < 16 ? z0 : z1;
+    h.v = __shfl(vsel, A & 15, 16);
+    if (qmode == 2) {   // Q = V + A - mean(A)
+        const float mean = group16_sum((h.on0 ? z0 : 0.f) + (h.on1 ? z1 : 0.f)) / (float)A;
+        z0 = h.v + z0 - mean;
+        z1 = h.v + z1 - mean;
+    }
+    h.z0 = z0; h.z1 = z1;
+    h.x0 = h.on0 ? z0 : -INFINITY; h.x1 = h.on1 ? z1 : -INFINITY;
+    h.mx = group16_max(fmaxf(h.x0, h.x1));
+    // lowest index among the maxima: the maximum is known, take the smallest index that attains it
+    h.arg = group16_min(h.x0 == h.mx ? c : (h.x1 == h.mx ? c + 16 : 64));
+    return h;
+}
+
+// Inference outputs of sample n (live: it exists), by the 16 lanes c of its group: action values or logits, value,
+// softmax, greedy action, and the drawn action.
+__device__ __forceinline__ void infer_outputs(const PvHeadArgs &p, int n, bool live, int c, float z0, float z1) {
+    const int A = p.A;
+    const HeadRows h = head_rows_of(z0, z1, c, A, p.qmode);
+    const bool policy = p.qmode == 0;
+    float e0 = 0.f, e1 = 0.f, s = 1.f;
+    if (policy) {
+        e0 = h.on0 ? expf(h.x0 - h.mx) : 0.f;
+        e1 = h.on1 ? expf(h.x1 - h.mx) : 0.f;
+        s = group16_sum(e0 + e1);
+    }
+    if (live) {
+        if (p.logits) {
+            if (h.on0) p.logits[(size_t)n * A + c] = h.z0;
+            if (h.on1) p.logits[(size_t)n * A + c + 16] = h.z1;
+        }
+        if (p.value && c == 0) p.value[n] = policy ? h.v : h.mx;
+        if (p.probs && policy) {
+            const float inv = 1.f / s;
+            if (h.on0) p.probs[(size_t)n * A + c] = e0 * inv;
+            if (h.on1) p.probs[(size_t)n * A + c + 16] = e1 * inv;
+        }
+        if (p.greedy && c == 0) p.greedy[n] = h.arg;
+    }
+    if (p.act_out) {
+        const float uu = live ? p.u[n] : 0.f;
+        int act;
+        if (policy) {
+            // inverse CDF on the unnormalised weights: first k with sum_{j<=k} e_j > u * s
+            const float c0 = group16_scan(e0, c);
+            const float tot0 = __shfl(c0, 15, 16);
+            const float c1 = tot0 + group16_scan(e1, c);
+            const float thr = uu * s;
+            act = group16_min(h.on0 && c0 > thr ? c : (h.on1 && c1 > thr ? c + 16 : 64));
+            act = act < A ? act : A - 1;
+            if (p.logp_out) {
+                const float lse = h.mx + logf(s);
+                const float lp = group16_sum((c == act ? h.x0 - lse : 0.f) + (c + 16 == act ? h.x1 - lse : 0.f));
+                if (live && c == 0) p.logp_out[n] = lp;
+            }
+        } else {
+            const int rnd = min((int)((double)(live ? p.u2[n] : 0.f) * (double)A), A - 1);   // exact product
+            act = uu < p.epsilon ? rnd : h.arg;
+        }
+        if (live && c == 0) p.act_out[n] = act;
+    }
+}
+
 template <bool TRAIN>
 __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p) {
     __shared__ __attribute__((aligned(16))) __bf16 sH[PVH_ROWS * PVH_HS];
@@ -214,66 +289,14 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
         for (int w = 1; w < 4; ++w) { a0 += sZ[w][c][srow]; a1 += sZ[w][c + 16][srow]; }
         z0 += a0; z1 += a1;
     }
-    const int A = p.A;
-    const bool on0 = c < A, on1 = c + 16 < A;
-    // value = head row A (policy/value and dueling heads)
-    const float vsel = A < 16 ? z0 : z1;
-    const float v = __shfl(vsel, A & 15, 16);
-    if (p.qmode == 2) {   // Q = V + A - mean(A)
-        const float mean = group16_sum((on0 ? z0 : 0.f) + (on1 ? z1 : 0.f)) / (float)A;
-        z0 = v + z0 - mean;
-        z1 = v + z1 - mean;
-    }
-    const float x0 = on0 ? z0 : -INFINITY, x1 = on1 ? z1 : -INFINITY;
-    const float mx = group16_max(fmaxf(x0, x1));
-    // lowest index among the maxima: the maximum is known, take the smallest index that attains it
-    const int arg = group16_min(x0 == mx ? c : (x1 == mx ? c + 16 : 64));
-
     if constexpr (!TRAIN) {
-        const bool policy = p.qmode == 0;
-        float e0 = 0.f, e1 = 0.f, s = 1.f;
-        if (policy) {
-            e0 = on0 ? expf(x0 - mx) : 0.f;
-            e1 = on1 ? expf(x1 - mx) : 0.f;
-            s = group16_sum(e0 + e1);
-        }
-        if (live) {
-            if (p.logits) {
-                if (on0) p.logits[(size_t)n * A + c] = z0;
-                if (on1) p.logits[(size_t)n * A + c + 16] = z1;
-            }
-            if (p.value && c == 0) p.value[n] = policy ? v : mx;
-            if (p.probs && policy) {
-                const float inv = 1.f / s;
-                if (on0) p.probs[(size_t)n * A + c] = e0 * inv;
-                if (on1) p.probs[(size_t)n * A + c + 16] = e1 * inv;
-            }
-            if (p.greedy && c == 0) p.greedy[n] = arg;
-        }
-        if (p.act_out) {
-            const float uu = live ? p.u[n] : 0.f;
-            int act;
-            if (policy) {
-                // inverse CDF on the unnormalised weights: first k with sum_{j<=k} e_j > u * s
-                const float c0 = group16_scan(e0, c);
-                const float tot0 = __shfl(c0, 15, 16);
-                const float c1 = tot0 + group16_scan(e1, c);
-                const float thr = uu * s;
-                act = group16_min(on0 && c0 > thr ? c : (on1 && c1 > thr ? c + 16 : 64));
-                act = act < A ? act : A - 1;
-                if (p.logp_out) {
-                    const float lse = mx + logf(s);
-                    const float lp = group16_sum((c == act ? x0 - lse : 0.f) + (c + 16 == act ? x1 - lse : 0.f));
-                    if (live && c == 0) p.logp_out[n] = lp;
-                }
-            } else {
-                const int rnd = min((int)((double)(live ? p.u2[n] : 0.f) * (double)A), A - 1);   // exact product
-                act = uu < p.epsilon ? rnd : arg;
-            }
-            if (live && c == 0) p.act_out[n] = act;
-        }
-        return;
+        infer_outputs(p, n, live, c, z0, z1);
     } else {
+        const int A = p.A;
+        const HeadRows hr = head_rows_of(z0, z1, c, A, p.qmode);
+        z0 = hr.z0, z1 = hr.z1;
+        const bool on0 = hr.on0, on1 = hr.on1;
+        const float x0 = hr.x0, x1 = hr.x1, v = hr.v, mx = hr.mx;
         // ---- 3. objective terms and the gradient at the head outputs ----
         const float invB = 1.f / (float)p.B;
         float g0, g1, t0 = 0.f, t1 = 0.f, t2 = 0.f;   // dz of the lane's two rows; the sample's three loss terms

@@ -148,6 +148,8 @@ constexpr int PACK_FC_ROWS = 8, PACK_FC_CH = 8;
 // fp16 copy of a weight: values beyond the largest half are clamped to it instead of becoming infinite
 __device__ __forceinline__ _Float16 to_f16_finite(float v) { return (_Float16)fminf(fmaxf(v, -65504.f), 65504.f); }
 constexpr int PACK_FC_MAX_P3 = 108;   // 12 x 9 positions after conv3 on 104 x 80 frames
+// LDS row: 8 modulo 64 words, so that eight rows x eight neighbouring positions are 64 different banks
+constexpr int PACK_FC_LDS_ROW = PACK_FC_CH * PACK_FC_MAX_P3 + 8;
 static_assert(P3 <= PACK_FC_MAX_P3 && GeoPaper::P3 <= PACK_FC_MAX_P3, "fc tile buffer");
 static_assert(HID % PACK_FC_ROWS == 0 && C3 % PACK_FC_CH == 0 && PACK_FC_CH == 8 && PACK_FC_ROWS % 8 == 0, "fc tile shape");
 struct PackPlan {
@@ -212,7 +214,7 @@ inline PackPlan make_pack_plan(const Dims &d, void *w_packed) {
 // Flat order Wfc[n][c * P3 + pos]; forward layout [n][pos * 64 + c]; input-gradient layout [pos * 64 + c][n].
 template <int P3_>
 __device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__restrict__ w, int tile,
-                                             float (&s_t)[PACK_FC_ROWS][PACK_FC_CH * PACK_FC_MAX_P3]) {
+                                             float (&s_t)[PACK_FC_ROWS][PACK_FC_LDS_ROW]) {
     constexpr int p3 = P3_, feat = C3 * P3_, run = PACK_FC_CH * p3;
     constexpr int NL = (PACK_FC_ROWS * run + 255) / 256;
     const int n0 = (tile / (C3 / PACK_FC_CH)) * PACK_FC_ROWS, c0 = (tile % (C3 / PACK_FC_CH)) * PACK_FC_CH;
@@ -232,8 +234,9 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__
     }
     __syncthreads();
     // forward layout: one 16-byte word = channels c0 .. c0+7 of (row r, position pos)
+    // (fragment order, frag_index: the eight rows' words are neighbours)
     for (int i = tid; i < PACK_FC_ROWS * p3; i += 256) {
-        const int r = i / p3, pos = i - r * p3;
+        const int r = i % PACK_FC_ROWS, pos = i / PACK_FC_ROWS;
         float v[PACK_FC_CH];
 #pragma unroll
         for (int c = 0; c < PACK_FC_CH; ++c) v[c] = s_t[r][c * p3 + pos];
@@ -245,7 +248,7 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__
             lo[c] = (__bf16)(v[c] - (float)hi[c]);
             hf[c] = to_f16_finite(v[c]);
         }
-        const size_t at = (size_t)(n0 + r) * feat + (size_t)pos * C3 + c0;
+        const size_t at = (size_t)frag_index(n0 + r, (long)pos * C3 + c0, feat);
         *reinterpret_cast<bf16x8 *>(pl.fc_hi + at) = hi;
         *reinterpret_cast<bf16x8 *>(pl.fc_lo + at) = lo;
         *reinterpret_cast<f16x8 *>(pl.fc_f16 + at) = hf;
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(256) void a3c_gather_kernel(A3cMap m, const float *
 
 __global__ __launch_bounds__(256) void pack_all_kernel(PackPlan pl, const float *__restrict__ w) {
     if ((int)blockIdx.x >= pl.fc_first_block) {
-        __shared__ float s_t[PACK_FC_ROWS][PACK_FC_CH * PACK_FC_MAX_P3];
+        __shared__ float s_t[PACK_FC_ROWS][PACK_FC_LDS_ROW];
         const int tile = (int)blockIdx.x - pl.fc_first_block;
         if (pl.p3 == P3) pack_fc_tile<P3>(pl, w, tile, s_t);
         else pack_fc_tile<GeoPaper::P3>(pl, w, tile, s_t);

@@ -1,0 +1,51 @@
+"""GPU parity where the small-batch kernels hand over: sizes on both sides of every tile and dispatch edge of the banded
+convolutions and of fc_small_kernel, against the CPU oracle (the bars of tests/gpu_util.py)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import nature_cnn as orc
+
+pytestmark = pytest.mark.gpu
+NETS = {"84": (wl.FRAME, {}), "paper": (wl.PAPER_FRAME, {"geometry": orc.PAPER_104x80})}
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("geometry,head,sizes", [
+    ("84", "pv", (17, 32, 36, 37, 63, 65, 127, 128, 129, 255, 257, 511, 512, 513)),
+    ("84", "c51", (33, 129, 513)),
+    ("paper", "duel", (21, 22, 65, 86, 128, 129, 257, 361, 362))])
+def test_forward_at_dispatch_edges(gu, geometry, head, sizes):
+    A = 7
+    frame, kw = NETS[geometry]
+    flat = wl.he_normal_params(A, head, 2602, bias_std=0.1, fc_inputs=wl.FC_INPUTS[frame])
+    spec = orc.NetSpec(A, head, **kw)
+    obs = wl.rect_frames(max(sizes), 1602, frame=frame)
+    ref = orc.forward(orc.unflatten(flat, spec), obs, spec)
+    want = ref[{"pv": "logits", "duel": "q", "c51": "atom_logits"}[head]]
+    net = gu.GpuNet(A, head, flat, geometry=geometry)
+    for B in sizes:
+        out = net.forward(obs[:B])
+        got = out["q" if head == "duel" else "logits"]
+        gu.tol_check(got, want[:B].reshape(got.shape), "B=%d" % B)
+
+
+@pytest.mark.parametrize("geometry,B", [("84", 129), ("84", 398), ("84", 399), ("paper", 65), ("paper", 180), ("paper", 181)])
+def test_gradients_at_dispatch_edges(gu, geometry, B):
+    A = 7
+    frame, kw = NETS[geometry]
+    fc_in = wl.FC_INPUTS[frame]
+    flat = wl.he_normal_params(A, "pv", 2603, bias_std=0.1, fc_inputs=fc_in)
+    batch = wl.actor_critic_batch(3, B=B, frame=frame)
+    batch["action"] %= A
+    ref = orc.train_step_grads(flat, batch, "a2c", orc.NetSpec(A, "pv", **kw))
+    dW, _ = gu.GpuNet(A, "pv", flat, geometry=geometry).train(batch, "a2c")
+    gu.check_grads(gu.per_tensor(dW, A, "pv", fc_inputs=fc_in), gu.per_tensor(ref["flat"], A, "pv", fc_inputs=fc_in),
+                   "%s B=%d" % (geometry, B))
