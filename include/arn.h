@@ -49,10 +49,8 @@
  *   Q  : q.W[A,512] q.b[A]
  *   DUEL: adv.W[A,512] adv.b[A] val.W[1,512] val.b[1]        (same shape as PV)
  * ARN_GEOM_A3C: conv1.W[16,4,8,8] conv1.b[16] conv2.W[32,16,4,4] conv2.b[32] fc.W[256,3456] (input index
- *   c*108 + y*9 + x) fc.b[256], then the heads as above with 256 in place of 512.  This network runs on the
- *   kernels of the 104x80 three-convolution network, embedded in it with zero filters and an identity third
- *   layer (exact: the embedded network computes the same function and the same gradients); it is supported for
- *   completeness of the paper's networks, not tuned.
+ *   c*108 + y*9 + x) fc.b[256], then the heads as above with 256 in place of 512.  arn_packed_bytes and
+ *   arn_workspace_bytes report at least what the 104x80 three-convolution network with the same heads needs.
  */
 #ifndef ARN_H
 #define ARN_H

@@ -20,6 +20,7 @@
 #include "arn_conv23_fwd.h"
 #include "arn_infer_fwd.h"
 #include "arn_infer_small.h"
+#include "arn_conv12_fwd.h"
 #include "arn_small_kernels.h"
 #include "arn_update.h"
 
@@ -177,6 +178,14 @@ PvHeadArgs pv_head_args(const Dims &d, const Packed &w, int B, char *ws, const W
 // Samples per workgroup of the head kernel in the inference calls: small batches are spread over more CUs
 inline int infer_rows_per_block(int B) { return B <= 512 ? 4 : B <= 4096 ? 8 : PVH_ROWS; }
 
+// Calls f with the geometry of d.
+template <class F>
+void with_geometry(const Dims &d, F f) {
+    if (d.geom == ARN_GEOM_PAPER) f(GeoPaper());
+    else if (d.geom == ARN_GEOM_A3C) f(GeoA3c());
+    else f(Geo84());
+}
+
 template <class G, bool F16, int MODE>
 void launch_fc_small(const char *name, const FcSmallArgs &p, int B, hipStream_t s) {
     ProfScope ps(name, s);
@@ -187,9 +196,9 @@ void launch_fc_small(const char *name, const FcSmallArgs &p, int B, hipStream_t 
     };
     typedef std::integral_constant<int, 1> One;
     typedef std::integral_constant<int, 2> Two;
-    // about 128 workgroups where the batch allows, then the tile with the fewest operand bytes per output
-    if (fc_small_rows(B) == 16) launch(One(), One());
-    else if (B <= 128) launch(One(), Two());
+    const FcTile t = fc_small_tile(G::NHID, B);
+    if (t.rows == 16) launch(One(), One());
+    else if (t.units == 16) launch(One(), Two());
     else launch(Two(), Two());
 }
 
@@ -214,28 +223,28 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
             launch_fc_small<G, F16, FC_PARTIAL>("fc_fwd", p, B, s);
         }
     } else {
-        typedef typename std::conditional<F16, FcFwdF16T<G::FEAT>, FcFwdT<G::FEAT>>::type Fc;
+        typedef typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID>, FcFwdT<G::FEAT, G::NHID>>::type Fc;
         Fc p;
         p.in = a3; p.lo_off = a3l - a3; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
-        p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(G::FEAT, B, F16); p.partial = (float *)(ws + o.fcp);
+        p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(G::FEAT, G::NHID, B, F16); p.partial = (float *)(ws + o.fcp);
         p.to_partial = p.ksplit > 1 || d.small;
-        if constexpr (F16) launch_nt("fc_fwd", p, B, HID / Fc::BN, p.ksplit, s);
-        else launch_nt_split("fc_fwd", p, B, HID / Fc::BN, p.ksplit, s);
+        if constexpr (F16) launch_nt("fc_fwd", p, B, G::NHID / Fc::BN, p.ksplit, s);
+        else launch_nt_split("fc_fwd", p, B, G::NHID / Fc::BN, p.ksplit, s);
         if (p.ksplit > 1 && !d.small) {
             ProfScope ps("fc_finish", s);
-            const long total = (long)B * HID;
+            const long total = (long)B * G::NHID;
             hipLaunchKernelGGL(fc_finish_kernel, dim3(cdiv(total / 4, 256)), dim3(256), 0, s, p.partial, p.ksplit,
-                               w.bfc, h, hl, total);
+                               w.bfc, h, hl, G::NHID, total);
         }
         if (d.small && head) {
             ProfScope ps("pv_head", s);
             head->ks = p.ksplit;
             head->rpb = infer_rows_per_block(B);
-            hipLaunchKernelGGL(pv_head_kernel<false>, dim3(cdiv(B, head->rpb)), dim3(PVH_THREADS), 0, s, *head);
+            hipLaunchKernelGGL((pv_head_kernel<false, G::NHID>), dim3(cdiv(B, head->rpb)), dim3(PVH_THREADS), 0, s, *head);
         }
     }
     if (d.head == ARN_HEAD_C51) {
-        HeadFwdC51 p;
+        HeadFwdC51<G::NHID> p;
         p.in = h; p.lo_off = hl - h; p.M = B; p.w = w.wh; p.w_lo = w.whl; p.bias = w.bh; p.z = z_out; p.ZW = d.NH; p.ZS = zstride;
         launch_nt_split("head_fwd", p, B, d.NHP / 64, 1, s);
     }
@@ -255,6 +264,12 @@ struct ConvConfigs {
     static void launch_conv23(const Conv23Args &, int, int, hipStream_t) {}
     static void launch_conv123(const uint8_t *, const __bf16 *, const __bf16 *, const float *, uint8_t *, const Conv23Args &, int,
                                int, hipStream_t) {}
+};
+template <>
+struct ConvConfigs<GeoA3c> {
+    typedef ResConv2FwdGeo<GeoA3c> Fwd2;
+    typedef NoConv3 Fwd3;
+    typedef ResConv2DgradGeo<GeoA3c> Dgrad2;
 };
 template <>
 struct ConvConfigs<Geo84> {
@@ -277,44 +292,58 @@ struct ConvConfigs<Geo84> {
     }
 };
 
-// Forward pass for geometry G in three-product bf16 precision (conv1's pixel operand is exact: two products).
+// Forward pass of a gradient step for geometry G in three-product bf16 precision (conv1's pixel operand is exact: two
+// products), with the ReLU sign bits of every convolution for the backward pass.  C51: z_out = atom logits, rows of zstride
+// floats.  PV, Q, DUEL: stops after the fc GEMM, whose fp32 sums (o.fcp) the fused head kernel consumes.
 template <class G>
 void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o,
-                   float *z_out, int zstride, bool masks, hipStream_t s) {
+                   float *z_out, int zstride, hipStream_t s) {
     typedef ConvConfigs<G> Cfg;
     __bf16 *a1 = (__bf16 *)(ws + o.a1), *a2 = (__bf16 *)(ws + o.a2), *a3 = (__bf16 *)(ws + o.a3);
     __bf16 *a1l = (__bf16 *)(ws + o.a1l), *a2l = (__bf16 *)(ws + o.a2l), *a3l = (__bf16 *)(ws + o.a3l);
-    const bool chained = Cfg::fused_conv23(B) && Cfg::conv1_parts(B) == 1;
-    if (!chained) {
-        ProfScope ps("conv1_fwd", s);
+    uint8_t *m1 = (uint8_t *)(ws + o.m1), *m2 = (uint8_t *)(ws + o.m2), *m3 = (uint8_t *)(ws + o.m3);
+    if constexpr (!G::HAS3) {
+        ProfScope ps("conv12_fwd", s);
+        Conv12Args p;
+        p.obs = obs; p.w1 = w.w1; p.w1_lo = w.w1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.b1 = w.b1; p.b2 = w.b2;
+        p.a1 = a1; p.m1 = m1; p.a2 = a3; p.a2_lo = a3l; p.m2 = m3; p.frag = fc_small(G::FEAT, B, false);
+        const BandPlan bp = band_plan<G>(B);
         const int spw = resident_spw(B, 256);
-        hipLaunchKernelGGL(conv1_fwd_resident_kernel<G>, dim3(cdiv(B, spw), Cfg::conv1_parts(B)), dim3(RES_THREADS), 0, s,
-                           obs, w.w1, w.w1l, w.b1, a1, a1l, masks ? (uint8_t *)(ws + o.m1) : nullptr, B, spw);
-    }
-    if (Cfg::fused_conv23(B)) {
-        // conv2 and conv3 in one kernel: act2 passes through LDS; with one workgroup per sample range in conv1 too,
-        // conv1 runs in the same launch, ahead of them in every workgroup
-        ProfScope ps(chained ? "conv123_fwd" : "conv23_fwd", s);
-        Conv23Args p;
-        p.a1 = a1; p.a1_lo = a1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.w3 = w.w3; p.w3_lo = w.w3l; p.b2 = w.b2; p.b3 = w.b3;
-        p.a2 = masks ? a2 : nullptr; p.a3 = a3; p.a3_lo = a3l;
-        p.m2 = masks ? (uint8_t *)(ws + o.m2) : nullptr; p.m3 = masks ? (uint8_t *)(ws + o.m3) : nullptr;
-        p.frag = fc_small(G::FEAT, B, false);
-        const int spw = resident_spw(B, 256);
-        if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, masks ? (uint8_t *)(ws + o.m1) : nullptr, p, B, spw, s);
-        else Cfg::launch_conv23(p, B, spw, s);
+        hipLaunchKernelGGL((conv12_fwd_kernel<G, typename Cfg::Fwd2>), dim3(cdiv(B, spw) * bp.bands), dim3(C12_THREADS), 0, s, p, B,
+                           spw, bp.rows, bp.bands);
     } else {
-        {
-            typename Cfg::Fwd2::Args p;
-            p.in = a1; p.in_lo = a1l; p.w = w.w2; p.w_lo = w.w2l; p.mask = nullptr; p.bias = w.b2; p.out = a2; p.out_lo = a2l;
-            p.mask_out = masks ? (uint8_t *)(ws + o.m2) : nullptr;
-            launch_resident<typename Cfg::Fwd2>("conv2_fwd", p, B, s);
+        const bool chained = Cfg::fused_conv23(B) && Cfg::conv1_parts(B) == 1;
+        if (!chained) {
+            ProfScope ps("conv1_fwd", s);
+            const int spw = resident_spw(B, 256);
+            hipLaunchKernelGGL(conv1_fwd_resident_kernel<G>, dim3(cdiv(B, spw), Cfg::conv1_parts(B)), dim3(RES_THREADS), 0, s,
+                               obs, w.w1, w.w1l, w.b1, a1, a1l, m1, B, spw);
         }
-        {
-            typename Cfg::Fwd3::Args p;
-            p.in = a2; p.in_lo = a2l; p.w = w.w3; p.w_lo = w.w3l; p.mask = nullptr; p.bias = w.b3; p.out = a3; p.out_lo = a3l;
-            p.mask_out = masks ? (uint8_t *)(ws + o.m3) : nullptr; p.frag = fc_small(G::FEAT, B, false);
-            launch_resident<typename Cfg::Fwd3>("conv3_fwd", p, B, s);
+        if (Cfg::fused_conv23(B)) {
+            // conv2 and conv3 in one kernel: act2 passes through LDS; with one workgroup per sample range in conv1 too,
+            // conv1 runs in the same launch, ahead of them in every workgroup
+            ProfScope ps(chained ? "conv123_fwd" : "conv23_fwd", s);
+            Conv23Args p;
+            p.a1 = a1; p.a1_lo = a1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.w3 = w.w3; p.w3_lo = w.w3l; p.b2 = w.b2; p.b3 = w.b3;
+            p.a2 = a2; p.a3 = a3; p.a3_lo = a3l;
+            p.m2 = m2; p.m3 = m3;
+            p.frag = fc_small(G::FEAT, B, false);
+            const int spw = resident_spw(B, 256);
+            if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, m1, p, B, spw, s);
+            else Cfg::launch_conv23(p, B, spw, s);
+        } else {
+            {
+                typename Cfg::Fwd2::Args p;
+                p.in = a1; p.in_lo = a1l; p.w = w.w2; p.w_lo = w.w2l; p.mask = nullptr; p.bias = w.b2; p.out = a2; p.out_lo = a2l;
+                p.mask_out = m2;
+                launch_resident<typename Cfg::Fwd2>("conv2_fwd", p, B, s);
+            }
+            {
+                typename Cfg::Fwd3::Args p;
+                p.in = a2; p.in_lo = a2l; p.w = w.w3; p.w_lo = w.w3l; p.mask = nullptr; p.bias = w.b3; p.out = a3; p.out_lo = a3l;
+                p.mask_out = m3; p.frag = fc_small(G::FEAT, B, false);
+                launch_resident<typename Cfg::Fwd3>("conv3_fwd", p, B, s);
+            }
         }
     }
     fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);
@@ -346,7 +375,7 @@ void infer_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, char
         p.obs = obs; p.w1 = w.w1h; p.w2 = w.w2h; p.w3 = w.w3h; p.b1 = w.b1; p.b2 = w.b2; p.b3 = w.b3;
         p.a3 = (_Float16 *)(ws + o.a3);
         p.counters = (unsigned *)(ws + o.cnt);
-        p.n_counters = fc_small(G::FEAT, B, true) && d.small ? (int)cdiv(B, fc_small_rows(B)) : 0;
+        p.n_counters = fc_small(G::FEAT, B, true) && d.small ? (int)cdiv(B, fc_small_tile(G::NHID, B).rows) : 0;
         const BandPlan bp = band_plan<G>(B);
         if (bp.bands > 1)   // at most 128 samples
             hipLaunchKernelGGL((infer_conv_band_kernel<G, typename Cfg::Fwd2, typename Cfg::Fwd3>), dim3(B * bp.bands),
@@ -358,18 +387,11 @@ void infer_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, char
 }
 void infer_launches(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o,
                     float *z_out, int zstride, PvHeadArgs *head, hipStream_t s) {
-    if (d.geom == ARN_GEOM_PAPER) infer_trunk<GeoPaper>(d, w, obs, B, ws, o, z_out, zstride, head, s);
-    else infer_trunk<Geo84>(d, w, obs, B, ws, o, z_out, zstride, head, s);
+    with_geometry(d, [&](auto g) { infer_trunk<decltype(g)>(d, w, obs, B, ws, o, z_out, zstride, head, s); });
 }
-
-// trunk + heads forward.  C51: z_out = atom logits, rows of zstride floats (NH = dense, or NHP for the
-// library's own buffers).  PV, Q, DUEL: stops after the fc GEMM, whose fp32 partial sums (o.fcp) the fused head
-// kernel consumes.  masks: also write the ReLU sign bits of act1..3 for the backward pass (training forward on
-// the online weights).
 void forward_launches(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o,
-                      float *z_out, int zstride, bool masks, hipStream_t s) {
-    if (d.geom == ARN_GEOM_PAPER) forward_trunk<GeoPaper>(d, w, obs, B, ws, o, z_out, zstride, masks, s);
-    else forward_trunk<Geo84>(d, w, obs, B, ws, o, z_out, zstride, masks, s);
+                      float *z_out, int zstride, hipStream_t s) {
+    with_geometry(d, [&](auto g) { forward_trunk<decltype(g)>(d, w, obs, B, ws, o, z_out, zstride, s); });
 }
 
 // Backward pass below d(pre_fc) for geometry G, in four launches: the dense layers' gradients, conv3's input gradient,
@@ -378,17 +400,14 @@ void forward_launches(const Dims &d, const Packed &w, const uint8_t *obs, int B,
 // on the GPU and 3 us on the host however small it is, a cross-stream event about 6 us on both streams: with the dense
 // weight gradients and five short kernels on a second stream the step took 139 us at 333 samples (host 105 us), this
 // way 126 (host 40); from 2048 samples up the two are level.
-struct HeadGrads {   // the head's part of it
-    HeadWgrad wgrad;
-    float *part;
-    ReducePartials<UnmapHead> reduce;
-    ReducePartials<UnmapHeadBias> bias;
-    LossTotals loss;
-};
 template <class G>
-void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o, const ParamOffsets &po,
-                    const Splits &sp, const HeadGrads &hg, float *dW, hipStream_t s) {
+void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, char *ws, const Workspace &o, const LossTotals &loss,
+                    int loss_blocks, float *dW, hipStream_t s) {
     typedef ConvConfigs<G> Cfg;
+    const ParamOffsets po = param_offsets(d);
+    const Splits sp = make_splits(d, B);
+    __bf16 *h = (__bf16 *)(ws + o.h), *dz = (__bf16 *)(ws + o.dz);
+    float *parth = (float *)(ws + o.pwh);
     __bf16 *a1 = (__bf16 *)(ws + o.a1), *a2 = (__bf16 *)(ws + o.a2), *a3 = (__bf16 *)(ws + o.a3);
     __bf16 *dph = (__bf16 *)(ws + o.dph), *dp3 = (__bf16 *)(ws + o.dp3);
     __bf16 *dp2 = (__bf16 *)(ws + o.dp2);
@@ -399,26 +418,27 @@ void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const 
         // 128 x 64 below (more workgroups)
         auto launch = [&](auto dg) {
             typedef decltype(dg) Dg;
-            typedef Wgrad<LastActsGather<G::FEAT>, 128, 64, 2, HID, G::FEAT> FcW;
+            typedef Wgrad<LastActsGather<G::FEAT>, 128, 64, 2, G::NHID, G::FEAT> FcW;
+            typedef HeadWgrad<G::NHID> HeadW;
             dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
-            DenseBackwardArgs<Dg, FcW> p;
+            DenseBackwardArgs<Dg, FcW, HeadW> p;
             p.dg = dg;
             p.dg_x = cdiv(B, Dg::BM); p.dg_blocks = p.dg_x * ((G::FEAT + Dg::BN - 1) / Dg::BN);
             p.wg.in = a3; p.wg.M = B; p.wg.frag = fc_small(G::FEAT, B, false); p.wg.dy = dph;
             p.wg_part = partfc; p.wg_rows = rows_per_split(B, sp.fc);
-            p.wg_blocks = (G::FEAT / FcW::BK2) * (HID / FcW::BN1) * sp.fc;
-            p.hw = hg.wgrad;
-            p.hw_part = hg.part; p.hw_rows = rows_per_split(B, sp.hd);
-            p.hw_blocks = (HID / HeadWgrad::BK2) * (hg.wgrad.N1 / HeadWgrad::BN1) * sp.hd;
-            p.loss = hg.loss;
+            p.wg_blocks = (G::FEAT / FcW::BK2) * (G::NHID / FcW::BN1) * sp.fc;
+            p.hw.in = h; p.hw.M = B; p.hw.N1 = d.NHP; p.hw.dy = dz;
+            p.hw_part = parth; p.hw_rows = rows_per_split(B, sp.hd);
+            p.hw_blocks = (G::NHID / HeadW::BK2) * (d.NHP / HeadW::BN1) * sp.hd;
+            p.loss = loss;
             ProfScope ps("dense_bwd", s);
-            hipLaunchKernelGGL((dense_backward_kernel<Dg, FcW>), dim3(p.dg_blocks + p.wg_blocks + p.hw_blocks + 1),
+            hipLaunchKernelGGL((dense_backward_kernel<Dg, FcW, HeadW>), dim3(p.dg_blocks + p.wg_blocks + p.hw_blocks + 1),
                                dim3(DENSE_THREADS), 0, s, p);
         };
-        if (B >= 1024) launch(FcDgradT<G::FEAT, 128>());
-        else launch(FcDgradT<G::FEAT, 64>());
+        if (B >= 1024) launch(FcDgradT<G::FEAT, G::NHID, 128>());
+        else launch(FcDgradT<G::FEAT, G::NHID, 64>());
     }
-    {
+    if constexpr (G::HAS3) {
         typename Cfg::Dgrad3::Args p;
         p.in = dp3; p.in_lo = nullptr; p.w = w.w3d; p.w_lo = nullptr; p.mask = (const uint8_t *)(ws + o.m2); p.out = dp2;
         launch_resident<typename Cfg::Dgrad3>("conv3_dgrad", p, B, s);
@@ -429,49 +449,42 @@ void backward_trunk(const Packed &w, const uint8_t *obs, int B, char *ws, const 
         // weight gradients of conv2 and conv3 -- three ranges of workgroups, longest first.
         ProfScope ps("conv_bwd", s);
         ConvBackwardArgs p;
-        p.obs = obs; p.dp2 = dp2; p.w2d = w.w2d; p.mask1 = (const uint8_t *)(ws + o.m1); p.part1 = part1;
+        p.obs = obs; p.dp2 = G::HAS3 ? dp2 : dp3; p.w2d = w.w2d; p.mask1 = (const uint8_t *)(ws + o.m1); p.part1 = part1;
         p.a1 = a1; p.a2 = a2; p.dp3 = dp3; p.part2 = part2; p.part3 = part3;
         p.B = B; p.n1 = sp.c1; p.n2 = sp.c2;
-        constexpr int geom = std::is_same<G, Geo84>::value ? ARN_GEOM_84 : ARN_GEOM_PAPER;
         p.spw1 = resident_spw(B, 256);
-        p.spw2 = resident_spw((B + CONV2_WG_G - 1) / CONV2_WG_G, wgrad_wgs2(geom)) * CONV2_WG_G;
-        p.spw3 = resident_spw((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(geom)) * CONV3_WG_G;
+        constexpr int g2 = Conv2WgradG<G>::value;
+        p.spw2 = resident_spw((B + g2 - 1) / g2, wgrad_wgs2(d.geom)) * g2;
+        p.spw3 = resident_spw((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom)) * CONV3_WG_G;
         hipLaunchKernelGGL((conv_backward_kernel<G, typename Cfg::Dgrad2>), dim3(sp.c1 + sp.c2 + sp.c3),
                            dim3(ConvBackward<G, typename Cfg::Dgrad2>::THREADS), 0, s, p);
     }
     {
         // one launch adds the partials of every layer (x = u8/255: conv1's pixel scale comes out of the contraction and
         // is applied here; bias gradients have no such factor)
-        ReduceAllPlan pl;
-        pl.conv1 = make_reduce(UnmapConv1{(long)po.w1, (long)po.b1}, part1, (long)C1 * KW1, C1, sp.c1, 1.f / 255.f);
-        pl.conv2 = make_reduce(UnmapConv<C1, K2, C2>{(long)po.w2, (long)po.b2}, part2, (long)C2 * KW2, C2, sp.c2);
+        ReduceAllPlan<G> pl;
+        pl.conv1 = make_reduce(UnmapConv1<G::NC1>{(long)po.w1, (long)po.b1}, part1, (long)G::NC1 * KW1, G::NC1, sp.c1, 1.f / 255.f);
+        pl.conv2 = make_reduce(UnmapConv<G::NC1, K2, G::NC2>{(long)po.w2, (long)po.b2}, part2, (long)G::NC2 * G::KW2, G::NC2, sp.c2);
         pl.conv3 = make_reduce(UnmapConv<C2, K3, C3>{(long)po.w3, (long)po.b3}, part3, (long)C3 * KW3, C3, sp.c3);
-        pl.head = hg.reduce; pl.head_bias = hg.bias;
-        pl.n1 = reduce_blocks(pl.conv1); pl.n2 = reduce_blocks(pl.conv2); pl.n3 = reduce_blocks(pl.conv3);
+        pl.head = make_reduce(UnmapHead<G::NHID>{head_rows<G::NHID>(d, po), d.NHP}, parth, (long)d.NHP * G::NHID, d.NHP, sp.hd);
+        // the head's bias gradient: the loss kernel's fp32 block partials, added in block order
+        pl.head_bias = make_reduce(UnmapHeadBias<G::NHID>{head_rows<G::NHID>(d, po)}, (const float *)(ws + o.hbp), 0, d.small ? 32 : d.NHP, loss_blocks);
+        pl.n1 = reduce_blocks(pl.conv1); pl.n2 = reduce_blocks(pl.conv2); pl.n3 = G::HAS3 ? reduce_blocks(pl.conv3) : 0;
         pl.nh = reduce_blocks(pl.head);
         pl.fc_part = partfc; pl.fc_w = (long)po.wfc; pl.fc_b = (long)po.bfc; pl.fc_splits = sp.fc;
         ProfScope ps("reduce", s);
-        hipLaunchKernelGGL((reduce_all_kernel<G::FEAT, G::P3>),
-                           dim3(HID + 1 + pl.n1 + pl.n2 + pl.n3 + pl.nh + reduce_blocks(pl.head_bias)), dim3(256), 0, s, pl, dW);
+        hipLaunchKernelGGL(reduce_all_kernel<G>, dim3(G::NHID + 1 + pl.n1 + pl.n2 + pl.n3 + pl.nh + reduce_blocks(pl.head_bias)), dim3(256), 0, s, pl, dW);
     }
 }
 
 // Lays the flat fp32 parameters out in every packed form, one launch.
 void launch_pack_all(const Dims &d, const float *w_fp32, void *w_packed, hipStream_t s) {
-    if (d.a3c) {
-        // the 2-convolution network: its parameters are first laid into the embedding network's flat vector, kept
-        // in the tail of the packed blob, and that vector is packed
-        ProfScope ps("a3c_embed", s);
-        float *big = (float *)((char *)w_packed + packed_offsets(d).a3c_flat);
-        const A3cMap m = make_a3c_map(d);
-        const long total = (long)m.e.total;
-        hipLaunchKernelGGL(a3c_fill_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, big, total, (long)m.e.w3);
-        hipLaunchKernelGGL(a3c_scatter_kernel, dim3(cdiv(m.total, 256)), dim3(256), 0, s, m, w_fp32, big);
-        w_fp32 = big;
-    }
     ProfScope ps("pack_all", s);
-    const PackPlan pl = make_pack_plan(d, w_packed);
-    hipLaunchKernelGGL(pack_all_kernel, dim3(pl.blocks), dim3(256), 0, s, pl, w_fp32);
+    with_geometry(d, [&](auto g) {
+        typedef decltype(g) G;
+        const PackPlan<G> pl = make_pack_plan<G>(d, w_packed);
+        hipLaunchKernelGGL(pack_all_kernel<G>, dim3(pl.blocks), dim3(256), 0, s, pl, w_fp32);
+    });
 }
 
 // Shared argument checks of the update entry points.  Returns ARN_OK and fills *d_out when a repack is asked for.
@@ -483,7 +496,7 @@ int check_update(size_t n, const arn_config *cfg, const void *w_packed, bool *re
         if (!known_head(cfg->head_kind)) return ARN_EKIND;
         *d_out = make_dims(cfg);
         if (!d_out->ok) return ARN_ESHAPE;
-        if (n != public_param_count(*d_out)) return ARN_ESHAPE;
+        if (n != param_offsets(*d_out).total) return ARN_ESHAPE;
         if (!aligned(w_packed, 256)) return ARN_EINVAL;
     }
     return ARN_OK;
@@ -511,18 +524,18 @@ const char *arn_status_string(int status) {
 
 size_t arn_param_count(const arn_config *cfg) {
     const Dims d = make_dims(cfg);
-    return d.ok ? public_param_count(d) : 0;
+    return d.ok ? param_offsets(d).total : 0;
 }
 
 size_t arn_packed_bytes(const arn_config *cfg) {
     const Dims d = make_dims(cfg);
-    return d.ok ? packed_offsets(d).total : 0;
+    return d.ok ? reported_packed_bytes(d) : 0;
 }
 
 size_t arn_workspace_bytes(const arn_config *cfg, int B, int mode) {
     const Dims d = make_dims(cfg);
     if (!d.ok || B <= 0 || B > (1 << 20) || (mode != ARN_MODE_FORWARD && mode != ARN_MODE_TRAIN)) return 0;
-    return make_workspace(d, B, mode).total;
+    return reported_workspace_bytes(d, B, mode);
 }
 
 int arn_weights_prepare(const arn_config *cfg, const float *w_fp32, void *w_packed, void *stream) {
@@ -579,7 +592,7 @@ int arn_policy_forward(const arn_config *cfg, const void *w_packed, const uint8_
     if (int e = check_policy_forward(cfg, w_packed, obs, B, logits, value, probs, greedy, &d)) return e;
     if (!aligned(workspace, 256)) return ARN_EINVAL;
     const Workspace o = make_workspace(d, B, ARN_MODE_FORWARD);
-    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
+    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_FORWARD)) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
     return policy_forward_launches(cfg, d, o, w_packed, obs, B, logits, value, probs, greedy, (char *)workspace,
                                    (hipStream_t)stream);
@@ -590,7 +603,7 @@ int arn_policy_forward_static(const arn_config *cfg, const void *w_packed, const
     Dims d;
     if (int e = check_policy_forward(cfg, w_packed, obs, B, logits, value, probs, greedy, &d)) return e;
     const Workspace o = make_workspace(d, B, ARN_MODE_FORWARD);
-    if (o.total > (size_t)ARN_STATIC_SCRATCH_BYTES) return ARN_ESTATIC;
+    if (reported_workspace_bytes(d, B, ARN_MODE_FORWARD) > (size_t)ARN_STATIC_SCRATCH_BYTES) return ARN_ESTATIC;
     if (int e = check_arch()) return e;
     void *ptr = static_scratch_ptr();
     if (!ptr) return ARN_EHIP;
@@ -612,7 +625,7 @@ int arn_policy_act(const arn_config *cfg, const void *w_packed, const uint8_t *o
     if (!policy && (!aligned(u2, 16) || !(epsilon >= 0.f && epsilon <= 1.f))) return ARN_EINVAL;
     if (logp && (!policy || !aligned(logp, 16))) return policy ? ARN_EINVAL : ARN_ESHAPE;
     const Workspace o = make_workspace(d, B, ARN_MODE_FORWARD);
-    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
+    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_FORWARD)) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
@@ -655,16 +668,12 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
         if (batch->next_action && !aligned(batch->next_action, 16)) return ARN_EINVAL;
     }
     const Workspace o = make_workspace(d, B, ARN_MODE_TRAIN);
-    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
+    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_TRAIN)) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
 
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     const Packed w = view_packed(w_packed, d);
-    const ParamOffsets po = param_offsets(d);
-    const Splits sp = make_splits(d, B);
-    float *const dW_out = dW;
-    if (d.a3c) dW = (float *)(ws + o.a3c_dw);   // the embedding network's gradient; the caller's entries are gathered from it at the end
     float *z = (float *)(ws + o.z);
     __bf16 *h = (__bf16 *)(ws + o.h);
     __bf16 *dz = (__bf16 *)(ws + o.dz), *dph = (__bf16 *)(ws + o.dph);
@@ -686,7 +695,7 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
                                d.atoms, cfg->v_min, cfg->v_max, cfg->gamma, batch->reward, batch->done,
                                (float *)nullptr, (float *)nullptr, batch->next_action, m);
         }
-        forward_launches(d, w, batch->obs, B, ws, o, z, d.NHP, true, s);
+        forward_launches(d, w, batch->obs, B, ws, o, z, d.NHP, s);
         ProfScope ps("loss", s);
         hipLaunchKernelGGL(c51_loss_kernel, dim3(lblocks), dim3(64 * C51_WAVES), 0, s, z, d.NHP, m, batch->action, B, d.A,
                            d.atoms, d.NHP, c51_loss_spw(B), dz, lossp, hbp);
@@ -708,10 +717,10 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
                 infer_launches(d, w, batch->next_obs, B, ws, o, nullptr, 0, &q, s);
             }
         }
-        forward_launches(d, w, batch->obs, B, ws, o, nullptr, 0, true, s);
+        forward_launches(d, w, batch->obs, B, ws, o, nullptr, 0, s);
         // fc finish, head, objective, dz and the head's input gradient d(pre_fc) in one kernel
         ProfScope ps("pv_head", s);
-        PvHeadArgs p = pv_head_args(d, w, B, ws, o, fc_ksplit(d.feat, B, false));
+        PvHeadArgs p = pv_head_args(d, w, B, ws, o, fc_ksplit(d.feat, d.hid, B, false));
         p.action = batch->action; p.adv = batch->adv; p.ret = batch->ret; p.old_logp = batch->old_logp;
         p.objective = loss_kind == ARN_LOSS_PPO ? 1 : loss_kind == ARN_LOSS_DQN ? 2 : 0;
         p.clip_eps = cfg->clip_eps; p.value_coef = cfg->value_coef; p.entropy_coef = cfg->entropy_coef;
@@ -722,30 +731,22 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
         }
         p.whd = w.whd; p.h = h; p.dz = dz; p.dph = dph; p.lossp = lossp; p.hbp = hbp;
         p.rpb = loss_block(B);
-        hipLaunchKernelGGL(pv_head_kernel<true>, dim3(lblocks), dim3(PVH_THREADS), 0, s, p);
+        if (d.hid == HID) hipLaunchKernelGGL((pv_head_kernel<true, HID>), dim3(lblocks), dim3(PVH_THREADS), 0, s, p);
+        else hipLaunchKernelGGL((pv_head_kernel<true, GeoA3c::NHID>), dim3(lblocks), dim3(PVH_THREADS), 0, s, p);
     }
 
     // ---- backward ----
-    if (d.head == ARN_HEAD_C51) {
-        HeadDgrad p;
-        p.in = dz; p.M = B; p.K = d.NHP; p.w = w.whd; p.h = h; p.out = dph;
-        launch_nt("head_dgrad", p, B, HID / HeadDgrad::BN, 1, s);
-    }
-    HeadGrads hg;
-    hg.wgrad.in = h; hg.wgrad.M = B; hg.wgrad.N1 = d.NHP; hg.wgrad.dy = dz;
-    hg.part = (float *)(ws + o.pwh);
-    hg.reduce = make_reduce(UnmapHead{head_rows(d, po), d.NHP}, hg.part, (long)d.NHP * HID, d.NHP, sp.hd);
-    // the head's bias gradient: the loss kernel's fp32 block partials, added in block order
-    hg.bias = make_reduce(UnmapHeadBias{head_rows(d, po)}, hbp, 0, d.small ? 32 : d.NHP, lblocks);
     const bool pv = loss_kind == ARN_LOSS_A2C || loss_kind == ARN_LOSS_PPO;
-    hg.loss = LossTotals{lossp, lblocks, B, pv ? cfg->value_coef : 0.f, pv ? cfg->entropy_coef : 0.f, loss};
-    if (d.geom == ARN_GEOM_PAPER) backward_trunk<GeoPaper>(w, batch->obs, B, ws, o, po, sp, hg, dW, s);
-    else backward_trunk<Geo84>(w, batch->obs, B, ws, o, po, sp, hg, dW, s);
-    if (d.a3c) {
-        ProfScope ps("a3c_gather", s);
-        const A3cMap m = make_a3c_map(d);
-        hipLaunchKernelGGL(a3c_gather_kernel, dim3(cdiv(m.total, 256)), dim3(256), 0, s, m, dW, dW_out);
-    }
+    const LossTotals totals{lossp, lblocks, B, pv ? cfg->value_coef : 0.f, pv ? cfg->entropy_coef : 0.f, loss};
+    with_geometry(d, [&](auto g) {
+        typedef decltype(g) G;
+        if (d.head == ARN_HEAD_C51) {
+            HeadDgrad<G::NHID> p;
+            p.in = dz; p.M = B; p.K = d.NHP; p.w = w.whd; p.h = h; p.out = dph;
+            launch_nt("head_dgrad", p, B, G::NHID / HeadDgrad<G::NHID>::BN, 1, s);
+        }
+        backward_trunk<G>(d, w, batch->obs, B, ws, o, totals, lblocks, dW, s);
+    });
     return launched();
 }
 

@@ -26,11 +26,12 @@ namespace arn {
 
 constexpr int C1B_THREADS = 512;   // four consumer wavefronts (0-3), four producers (4-7); one workgroup per CU
 
-// LDS layout of a d(pre1) buffer: rows of 32 bf16 (64 bytes); inside every 256-byte block of four rows the
+// LDS layout of a d(pre1) buffer: rows of 32 bf16 (64 bytes; a network with 16 filters leaves the upper half zero); inside every 256-byte block of four rows the
 // eight 32-byte granules are rotated by the block index.  A producer writes 16 positions two pixels apart
 // (32 bytes each) per instruction: unrotated they would share two of the eight granule slots (an eight-way bank
 // conflict, measured as a bottleneck); rotated they cover all eight.  The consumers' transposing reads take
 // four consecutive rows of one block and stay conflict free.
+constexpr int DY1_ROW = 64;
 __device__ __forceinline__ constexpr int dy1_offset(int row, int byte) {
     return (row >> 2) * 256 + ((((row & 3) * 2 + (byte >> 5) + (row >> 2)) & 7) << 5) + (byte & 31);
 }
@@ -39,13 +40,13 @@ __device__ __forceinline__ constexpr int dy1_offset(int row, int byte) {
 template <class Geo, class D>
 constexpr int conv1_bwd_lds_bytes() {
     constexpr int RPAD = (Geo::P1 + 15) / 16 * 16;
-    return 8 * Geo::IN_H * Geo::IN_W + 2 * RPAD * C1 * 2 + D::IMG + Geo::P1 * C1 / 8 + (80 % Geo::W1 != 0 ? RPAD : 4) * 4;
+    return 8 * Geo::IN_H * Geo::IN_W + 2 * RPAD * DY1_ROW + D::IMG + mask1_bytes(Geo::P1, Geo::NC1) + (80 % Geo::W1 != 0 ? RPAD : 4) * 4;
 }
 
 // The work of workgroup `block` (of C1B_THREADS threads) in the caller's LDS buffer `lds`.
 // Geo: frame geometry; D: the description of conv2's input gradient (ResConv2Dgrad / ResConv2DgradGeo: the
 // d(pre2) image of one sample).  obs u8 [B][4][IN_H][IN_W]; dy2 = d(pre2) bf16 [B][P2][64]; w2d: the packed
-// input-gradient weights [phase*32 + ci][(ty*2 + tx)*64 + co]; mask1: sign bits of act1 (P1*32/8 bytes per sample).
+// input-gradient weights [phase*NC1 + ci][(ty*2 + tx)*NC2 + co]; mask1: sign bits of act1 (mask1_bytes per sample).
 template <class Geo, class D>
 __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, const uint8_t *__restrict__ obs,
                                                      const __bf16 *__restrict__ dy2, const __bf16 *__restrict__ w2d,
@@ -57,28 +58,29 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
     constexpr int PLANE_U4 = IN_H * IN_W / 16;                   // one input channel of the frame, 16 pixels per word
     constexpr int NI = (PLANE_U4 + 63) / 64;                     // words per lane of the wavefront that owns the plane
     constexpr int KSTEPS = (P1 + 15) / 16, RPAD = KSTEPS * 16;   // contraction steps; d(pre1) rows P1..RPAD stay zero
-    constexpr int DYB = RPAD * C1 * 2;                           // bytes of one d(pre1) buffer
+    constexpr int NC1 = Geo::NC1, DYB = RPAD * DY1_ROW;          // bytes of one d(pre1) buffer
     constexpr int TX = 2;                                        // column tiles of dW1 per consumer: one input channel
     constexpr bool TABLE = 80 % W1 != 0;
     // producer side (as resident_conv_kernel<D> with one sample)
     constexpr int CI = D::CI, NCH = CI / 8, KS = D::K / 32, KH = KS / 2, CT = D::CO / 64;
     constexpr int NQ = D::SRC_PIX * NCH, NG = (NQ + NR - 1) / NR;
     constexpr int DT = (D::P + 15) / 16;                         // position tiles of the 2x2 correlation
-    constexpr int MWORDS = P1 * C1 / 32, NM = (MWORDS + NR - 1) / NR;   // 4-byte words of act1 sign bits per sample
+    constexpr int MWORDS = mask1_bytes(P1, NC1) / 4, NM = (MWORDS + NR - 1) / NR;   // 4-byte words of act1 sign bits per sample
+    typedef typename std::conditional<NC1 == 32, uint32_t, uint16_t>::type MaskOf;      // one position's bits
     static_assert((IN_H * IN_W) % 16 == 0 && OBS_BYTES == 4 * IN_H * IN_W, "a channel plane is copied in 16-byte words");
-    static_assert(D::CO == 4 * C1 && CT == 2 && D::PSB == CI * 2 + 32, "four phases of 32 channels, one phase per producer");
-    static_assert((P1 * C1) % 32 == 0, "whole mask words per sample");
+    static_assert(D::CO == 4 * NC1 && CT * 16 == NC1 && D::PSB == CI * 2 + 32, "four phases, one phase per producer");
+    static_assert(NC1 == 16 || NC1 == 32, "a position's sign bits are one word");
     static_assert(!D::SPLIT && D::ZERO_FILL && D::G == 1, "single-product input gradient over a zero-bordered image, one sample");
     static_assert(layout_is_uniform<D>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
     static_assert(D::IMG % 16 == 0 && DYB % 16 == 0, "16-byte aligned LDS regions");
     static_assert(conv1_bwd_lds_bytes<Geo, D>() == 8 * PLANE_U4 * 16 + 2 * DYB + D::IMG + 4 * MWORDS + 4 * (TABLE ? RPAD : 4) &&
                       conv1_bwd_lds_bytes<Geo, D>() <= 160 * 1024, "LDS budget");
-    static_assert(4 * 16 * C1 * 4 <= DYB, "bias-gradient scratch");
+    static_assert(4 * 16 * NC1 * 4 <= DYB, "bias-gradient scratch");
 
     u32x4 *const s_img = lds;                                    // bf16 [4][IN_H][IN_W]
     u32x4 *const s_dy = s_img + 8 * PLANE_U4;                    // d(pre1), bf16 [2][RPAD][32], rows laid out by dy1_offset
     u32x4 *const s_g = s_dy + 2 * DYB / 16;                      // bordered d(pre2) image
-    uint32_t *const s_mask = reinterpret_cast<uint32_t *>(s_g + D::IMG / 16);   // word p: the 32 sign bits of act1 at position p
+    uint32_t *const s_mask = reinterpret_cast<uint32_t *>(s_g + D::IMG / 16);   // the sign bits of act1 at position p: the p-th MaskOf
     int *const s_win = reinterpret_cast<int *>(s_mask + MWORDS); // byte offset of the window origin of output position m in s_img
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -89,10 +91,12 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
     if (s_begin >= s_end) return;
 
     for (int i = tid; i < D::IMG / 16; i += NT) s_g[i] = zero_u4();
-    if constexpr (RPAD > P1) {
+    if constexpr (NC1 < 32) {       // the upper halves of all rows
+        for (int i = tid; i < 2 * DYB / 16; i += NT) s_dy[i] = zero_u4();
+    } else if constexpr (RPAD > P1) {
         // rows P1..RPAD of both buffers stay zero: the blocks that hold them are cleared whole (their valid rows
         // are rewritten for every sample)
-        constexpr int Z0 = (P1 & ~3) * C1 * 2 / 16, ZN = DYB / 16 - Z0;
+        constexpr int Z0 = (P1 & ~3) * DY1_ROW / 16, ZN = DYB / 16 - Z0;
         for (int i = tid; i < 2 * ZN; i += NT) s_dy[(i / ZN) * (DYB / 16) + Z0 + i % ZN] = zero_u4();
     }
     auto window = [&](int m) __attribute__((always_inline)) {
@@ -106,7 +110,7 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
     char *const img = reinterpret_cast<char *>(s_img);
     char *const dyl = reinterpret_cast<char *>(s_dy);
     char *const gl = reinterpret_cast<char *>(s_g);
-    float *out = part + (size_t)block * (C1 * KW1 + C1);
+    float *out = part + (size_t)block * (NC1 * KW1 + NC1);
     float *red = reinterpret_cast<float *>(s_dy);      // epilogue scratch
 
     // Both roles run the same sequence of barriers: two in the prologue, two per sample, two in the epilogue.
@@ -114,12 +118,12 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
     // the prefetch needs no address arithmetic in registers that an earlier load may still be filling.
     if (producer) {
         const int ptid = tid - NR;
-        // phase = (wavefront - 4): 32 channels, all k of their weights as A-operand fragments
+        // phase = (wavefront - 4): its channels, all k of their weights as A-operand fragments
         const int phase = wave - 4;
         bf16x8 wd[CT][KS];
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-            const size_t row = frag_base(phase * 2 + ct, D::K, lane);
+            const size_t row = frag_base(phase * CT + ct, D::K, lane);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) wd[ct][ks] = as_bf16x8(*reinterpret_cast<const u32x4 *>(w2d + row + FRAG_STEP * ks));
         }
@@ -209,9 +213,10 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
         // d(pre1) of the sample whose d(pre2) image and mask are staged, into dst
         auto produce = [&](char *dst) __attribute__((always_inline)) {
             bf16x8 fa[KH], fb[KH];
+            const MaskOf *const masks = reinterpret_cast<const MaskOf *>(s_mask);
             uint32_t mk, mk_next;
             load_half(t_base[0], 0, fa);
-            mk = s_mask[t_mask[0]];
+            mk = masks[t_mask[0]];
 #pragma unroll
             for (int t = 0; t < DT; ++t) {
                 const int tn = t + 1 < DT ? t + 1 : t;        // the last tile repeats its own reads
@@ -223,7 +228,7 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
                 mfma_half(0, fa, da);
                 __builtin_amdgcn_sched_barrier(0);
                 load_half(t_base[tn], 0, fa);
-                mk_next = s_mask[t_mask[tn]];
+                mk_next = masks[t_mask[tn]];
                 __builtin_amdgcn_sched_barrier(0);
                 mfma_half(1, fb, da);
                 __builtin_amdgcn_sched_barrier(0);
@@ -266,7 +271,7 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) red[(phase * 16 + li) * C1 + ct * 16 + 4 * lg + r] = bs[ct][r];
+            for (int r = 0; r < 4; ++r) red[(phase * 16 + li) * NC1 + ct * 16 + 4 * lg + r] = bs[ct][r];
         __syncthreads();
     } else {
         // wavefront w: input channel w, i.e. column tiles 2w (kernel rows 0-3) and 2w+1 (rows 4-7) of dW1, and the
@@ -328,7 +333,7 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
                 const int ma = 16 * ks + row_in_step, mb = ma + 4;
                 const int pa = TABLE ? s_win[ma] : window(ma), pb = TABLE ? s_win[mb] : window(mb);
                 const int flip = (ks & 1) << 7;
-                const bf16x8 fy = tr_pair(src, ks * (16 * C1 * 2) + (ya ^ flip), ks * (16 * C1 * 2) + (yb ^ flip));
+                const bf16x8 fy = tr_pair(src, ks * (16 * DY1_ROW) + (ya ^ flip), ks * (16 * DY1_ROW) + (yb ^ flip));
 #pragma unroll
                 for (int b = 0; b < TX; ++b) {
                     const bf16x8 fx = tr_pair(img, pa + xoff[b], pb + xoff[b]);
@@ -347,16 +352,16 @@ __device__ __forceinline__ void conv1_bwd_fused_body(u32x4 *lds, int block, cons
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int n = 8 * (r >> 2) + 4 * fg + (r & 3);
-                out[n * KW1 + k] = acc[b][r];
+                if (n < NC1) out[n * KW1 + k] = acc[b][r];
             }
         }
         __syncthreads();
     }
     // bias gradient: the producers' lane sums, added in a fixed order
-    if (tid < C1) {
+    if (tid < NC1) {
         float t = red[tid];
-        for (int g = 1; g < 4 * 16; ++g) t += red[g * C1 + tid];
-        out[C1 * KW1 + tid] = t;
+        for (int g = 1; g < 4 * 16; ++g) t += red[g * NC1 + tid];
+        out[NC1 * KW1 + tid] = t;
     }
 }
 

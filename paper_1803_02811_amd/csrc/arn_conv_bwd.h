@@ -22,7 +22,7 @@ struct ConvBackwardArgs {
     const __bf16 *a1, *a2, *dp3;
     float *part2, *part3;
     int B;
-    int n1, n2;               // workgroups of the first two ranges (the third is the rest of the grid)
+    int n1, n2;               // workgroups of the first two ranges (conv3's, if there is one, is the rest of the grid)
     int spw1, spw2, spw3;     // samples per workgroup of each range
 };
 
@@ -31,8 +31,12 @@ struct ConvBackward {
     static_assert(C1B_THREADS == CW_THREADS, "one block size for all three ranges");
     static constexpr int THREADS = C1B_THREADS;
     static constexpr int L1 = conv1_bwd_lds_bytes<Geo, D2>();
-    static constexpr int L2 = conv_wgrad_lds_bytes<C1, Geo::H1, Geo::W1, K2, S2, Geo::PAD2, Geo::H2, Geo::W2, C2, CONV2_WG_G>();
-    static constexpr int L3 = conv_wgrad_lds_bytes<C2, Geo::H2, Geo::W2, K3, S3, Geo::PAD3, Geo::H3, Geo::W3, C3, CONV3_WG_G>();
+    static constexpr int L2 = conv_wgrad_lds_bytes<Geo::NC1, Geo::H1, Geo::W1, K2, S2, Geo::PAD2, Geo::H2, Geo::W2, Geo::NC2, Conv2WgradG<Geo>::value>();
+    static constexpr int lds3() {
+        if constexpr (Geo::HAS3) return conv_wgrad_lds_bytes<C2, Geo::H2, Geo::W2, K3, S3, Geo::PAD3, Geo::H3, Geo::W3, C3, CONV3_WG_G>();
+        else return 0;
+    }
+    static constexpr int L3 = lds3();
     static constexpr int L12 = L1 > L2 ? L1 : L2;
     static constexpr int LDS_BYTES = ((L12 > L3 ? L12 : L3) + 15) / 16 * 16;
 };
@@ -44,9 +48,9 @@ __global__ __launch_bounds__(C1B_THREADS) void conv_backward_kernel(const ConvBa
     if (b < a.n1) {
         conv1_bwd_fused_body<Geo, D2>(lds, b, a.obs, a.dp2, a.w2d, a.mask1, a.part1, a.B, a.spw1);
     } else if (b < a.n1 + a.n2) {
-        conv_wgrad_resident_body<C1, Geo::H1, Geo::W1, K2, S2, Geo::PAD2, Geo::H2, Geo::W2, C2, CONV2_WG_G, 2>(
+        conv_wgrad_resident_body<Geo::NC1, Geo::H1, Geo::W1, K2, S2, Geo::PAD2, Geo::H2, Geo::W2, Geo::NC2, Conv2WgradG<Geo>::value, Geo::NC2 / 32>(
             lds, b - a.n1, a.a1, a.dp2, a.part2, a.B, a.spw2);
-    } else {
+    } else if constexpr (Geo::HAS3) {
         conv_wgrad_resident_body<C2, Geo::H2, Geo::W2, K3, S3, Geo::PAD3, Geo::H3, Geo::W3, C3, CONV3_WG_G, 2>(
             lds, b - a.n1 - a.n2, a.a2, a.dp3, a.part3, a.B, a.spw3);
     }

@@ -18,22 +18,22 @@ struct LossTotals {   // arguments of loss_finalize
     float *loss;
 };
 
-template <class Dgrad, class Wgrad>
+template <class Dgrad, class Wgrad, class HeadW>
 struct DenseBackwardArgs {
     Dgrad dg;                       // fc input gradient
     int dg_x, dg_blocks;            // position tiles, workgroups
     Wgrad wg;                       // fc weight gradient
     float *wg_part;
     int wg_rows, wg_blocks;         // samples per batch split, workgroups
-    HeadWgrad hw;                   // head weight gradient
+    HeadW hw;                   // head weight gradient
     float *hw_part;
     int hw_rows, hw_blocks;
     LossTotals loss;                // one workgroup
 };
 
-template <class Dgrad, class Wgrad>
-__global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const DenseBackwardArgs<Dgrad, Wgrad> a) {
-    constexpr int L1 = gemm_nt_lds_bytes<Dgrad>(), L2 = gemm_tn_lds_bytes<Wgrad>(), L3 = gemm_tn_lds_bytes<HeadWgrad>();
+template <class Dgrad, class Wgrad, class HeadW>
+__global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const DenseBackwardArgs<Dgrad, Wgrad, HeadW> a) {
+    constexpr int L1 = gemm_nt_lds_bytes<Dgrad>(), L2 = gemm_tn_lds_bytes<Wgrad>(), L3 = gemm_tn_lds_bytes<HeadW>();
     constexpr int L12 = L1 > L2 ? L1 : L2;
     static_assert(ThreadsOf<Dgrad>::value == DENSE_THREADS, "one block size for all ranges");
     __shared__ u32x4 lds[(L12 > L3 ? L12 : L3) / 16];
@@ -50,9 +50,9 @@ __global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const Den
     }
     b -= a.wg_blocks;
     if (b < a.hw_blocks) {
-        constexpr int X = HeadWgrad::KP / HeadWgrad::BK2;
-        const int Y = a.hw.N1 / HeadWgrad::BN1;
-        gemm_tn_body<HeadWgrad>(lds, a.hw, a.hw_part, a.hw_rows, b % X, b / X % Y, b / (X * Y));
+        constexpr int X = HeadW::KP / HeadW::BK2;
+        const int Y = a.hw.N1 / HeadW::BN1;
+        gemm_tn_body<HeadW>(lds, a.hw, a.hw_part, a.hw_rows, b % X, b / X % Y, b / (X * Y));
         return;
     }
     loss_finalize(a.loss.partial, a.loss.blocks, a.loss.B, a.loss.value_coef, a.loss.entropy_coef, a.loss.loss);

@@ -70,17 +70,26 @@ __device__ __forceinline__ void clear_counters(const InferConvArgs &a) {
 // variants); only the addressing members are used, for one sample and a single part.
 template <class Geo, class P2, class P3>
 constexpr int infer_conv_lds_bytes() { return 2 * Geo::OBS_BYTES + P2::IMG + P3::IMG; }
+// in place of P3 for a network without conv3
+struct NoConv3 {
+    static constexpr int IMG = 0;
+    static constexpr bool ZERO_FILL = false;
+};
+template <>
+constexpr bool layout_is_uniform<NoConv3>() { return true; }
 
 template <class Geo, class P2, class P3, bool FRAG>   // FRAG: a3 in fragment order (LastActs)
 __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConvArgs a, int B, int spw) {
     constexpr int IN_H = Geo::IN_H, IN_W = Geo::IN_W, W1 = Geo::W1, NP1 = Geo::P1, NP2 = Geo::P2, NP3 = Geo::P3;
     constexpr int OBS_BYTES = Geo::OBS_BYTES, IMG_U4 = OBS_BYTES / 16, NL = (IMG_U4 + INF_THREADS - 1) / INF_THREADS;
-    constexpr int KS1 = KW1 / 32, KS2 = KW2 / 32, KS3 = KW3 / 32;     // 8, 16, 18 k-steps
+    constexpr int KS1 = KW1 / 32, KS2 = Geo::KW2 / 32, KS3 = KW3 / 32;   // 8, 16 (8 with 16 filters), 18 k-steps
+    constexpr bool HAS3 = Geo::HAS3;
+    constexpr int CT1 = Geo::NC1 / 16, CT2 = Geo::NC2 / 16, G1 = 8 / CT1, G2 = 8 / CT2;   // channel tiles; wavefronts that share one
     constexpr int NT1 = (NP1 + 15) / 16, NT2 = (NP2 + 15) / 16, NT3 = (NP3 + 15) / 16;
     constexpr int Q2 = 4, Q3 = 6;                                      // k-steps per fragment batch (two batches in flight)
     static_assert(KS2 % Q2 == 0 && (KS2 / Q2) % 2 == 0 && KS3 % Q3 == 0, "fragment batches");
-    static_assert(P2::CI == C1 && P3::CI == C2 && P2::PSB == C1 * 2 + 32 && P3::PSB == C2 * 2 + 32, "image descriptions");
-    static_assert(layout_is_uniform<P2>() && layout_is_uniform<P3>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
+    static_assert(P2::CI == Geo::NC1 && layout_is_uniform<P2>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
+    static_assert(layout_is_uniform<P3>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
     static_assert(OBS_BYTES % 16 == 0 && P2::IMG % 16 == 0 && P3::IMG % 16 == 0 && infer_conv_lds_bytes<Geo, P2, P3>() <= 160 * 1024, "LDS budget");
 
     __shared__ u32x4 lds[infer_conv_lds_bytes<Geo, P2, P3>() / 16];
@@ -118,10 +127,10 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
     gload(s_begin);
     clear_counters(a);
 
-    // conv1: wavefront w owns channel tile w & 1 and position tiles (w >> 1) + 4 j
-    const int ct1 = wave & 1, t1_first = wave >> 1;
-    // conv2 / conv3: wavefront w owns channel tile w & 3 and position tiles (w >> 2) + 2 j
-    const int ct = wave & 3, t_first = wave >> 2;
+    // conv1: wavefront w owns channel tile w % CT1 and every G1-th position tile
+    const int ct1 = wave % CT1, t1_first = wave / CT1;
+    // conv2 / conv3: wavefront w owns channel tile w % CT2 and every G2-th position tile
+    const int ct = wave % CT2, t_first = wave / CT2;
     f16x8 w1[KS1];
     auto load_w1 = [&]() __attribute__((always_inline)) {
         const size_t r1 = frag_base(ct1, KW1, lane);
@@ -129,17 +138,20 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
         for (int ks = 0; ks < KS1; ++ks) w1[ks] = as_f16x8(*reinterpret_cast<const u32x4 *>(a.w1 + r1 + FRAG_STEP * ks));
     };
     load_w1();
-    f16x8 w2[KS2], w3[KS3];
+    f16x8 w2[KS2], w3[HAS3 ? KS3 : 1];
     {
-        const size_t r2 = frag_base(ct, KW2, lane), r3 = frag_base(ct, KW3, lane);
+        const size_t r2 = frag_base(ct, Geo::KW2, lane), r3 = frag_base(ct, KW3, lane);
 #pragma unroll
         for (int ks = 0; ks < KS2; ++ks) w2[ks] = as_f16x8(*reinterpret_cast<const u32x4 *>(a.w2 + r2 + FRAG_STEP * ks));
+        if constexpr (HAS3) {
 #pragma unroll
-        for (int ks = 0; ks < KS3; ++ks) w3[ks] = as_f16x8(*reinterpret_cast<const u32x4 *>(a.w3 + r3 + FRAG_STEP * ks));
+            for (int ks = 0; ks < KS3; ++ks) w3[ks] = as_f16x8(*reinterpret_cast<const u32x4 *>(a.w3 + r3 + FRAG_STEP * ks));
+        }
     }
     const float4 bias1 = *reinterpret_cast<const float4 *>(a.b1 + ct1 * 16 + 4 * lg);
     const float4 bias2 = *reinterpret_cast<const float4 *>(a.b2 + ct * 16 + 4 * lg);
-    const float4 bias3 = *reinterpret_cast<const float4 *>(a.b3 + ct * 16 + 4 * lg);
+    float4 bias3 = {};
+    if constexpr (HAS3) bias3 = *reinterpret_cast<const float4 *>(a.b3 + ct * 16 + 4 * lg);
     if constexpr (P2::ZERO_FILL || P3::ZERO_FILL) {   // zero borders of the padded layers, written once
         for (int i = tid; i < (P2::IMG + P3::IMG) / 16; i += INF_THREADS) lds[2 * IMG_U4 + i] = zero_u4();
     }
@@ -153,7 +165,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
     auto sample = [&](int s, auto first) __attribute__((always_inline)) {
         // ---- conv1: frame image -> act1 image ----
 #pragma unroll 1
-        for (int t = t1_first; t < NT1; t += 4) {
+        for (int t = t1_first; t < NT1; t += G1) {
             int pos = t * 16 + li;
             const bool valid = pos < NP1;
             pos = valid ? pos : NP1 - 1;
@@ -183,19 +195,17 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
 
         // ---- conv2: act1 image -> act2 image ----
 #pragma unroll 1
-        for (int t = t_first; t < NT2; t += 2) {
+        for (int t = t_first; t < NT2; t += G2) {
             int row = t * 16 + li;
             const bool valid = row < NP2;
             row = valid ? row : NP2 - 1;
-            const int base = P2::base_off(row) + 16 * lg;
+            const int base = P2::base_off(row) + P2::lane_off(lg);
             f32x4 acc[FRAG ? 2 : 1] = {};
             f16x8 fa[Q2], fb[Q2];
             auto load_q = [&](int q, f16x8 (&f)[Q2]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int j = 0; j < Q2; ++j) {
-                    const int ks = q * Q2 + j;
-                    const int tap = (32 * ks) / C1, ci0 = (32 * ks) % C1;
-                    f[j] = as_f16x8(*reinterpret_cast<const u32x4 *>(a1l + base + P2::tap_off(tap) + ci0 * 2));
+                    f[j] = as_f16x8(*reinterpret_cast<const u32x4 *>(a1l + base + P2::step_off(q * Q2 + j)));
                 }
             };
             load_q(0, fa);
@@ -209,29 +219,30 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
                 for (int j = 0; j < Q2; ++j) acc[half_of<FRAG>((q + 1) * Q2 + j, KS2)] = mfma_f16(w2[(q + 1) * Q2 + j], fb[j], acc[half_of<FRAG>((q + 1) * Q2 + j, KS2)]);
             }
             const f32x4 v = sum_halves(acc);
-            if (valid)
-                *reinterpret_cast<u32x2 *>(a2l + P3::dst_off(row) + (ct * 16 + 4 * lg) * 2) =
-                    relu_f16x4(v[0] + bias2.x, v[1] + bias2.y, v[2] + bias2.z, v[3] + bias2.w);
+            const u32x2 r = relu_f16x4(v[0] + bias2.x, v[1] + bias2.y, v[2] + bias2.z, v[3] + bias2.w);
+            if (valid) {
+                if constexpr (HAS3) *reinterpret_cast<u32x2 *>(a2l + P3::dst_off(row) + (ct * 16 + 4 * lg) * 2) = r;
+                else *reinterpret_cast<u32x2 *>(a.a3 + LastActs<Geo::NCL, Geo::PL>::template at<FRAG>(s, row, ct * 16 + 4 * lg)) = r;
+            }
         }
         __syncthreads();          // act2 complete; every read of the act1 image done; the next frame image staged
         if (s + 1 < s_end) load_w1();   // conv1's weights for the next sample arrive while conv3 runs
         if (s + 2 < s_end) gload(s + 2);   // the frame after the next: not in registers while conv2 runs
 
         // ---- conv3: act2 image -> act3 in global memory ----
+        if constexpr (HAS3) {
 #pragma unroll 1
-        for (int t = t_first; t < NT3; t += 2) {
+        for (int t = t_first; t < NT3; t += G2) {
             int row = t * 16 + li;
             const bool valid = row < NP3;
             row = valid ? row : NP3 - 1;
-            const int base = P3::base_off(row) + 16 * lg;
+            const int base = P3::base_off(row) + P3::lane_off(lg);
             f32x4 acc[FRAG ? 2 : 1] = {};
             f16x8 fa[Q3], fb[Q3];
             auto load_q = [&](int q, f16x8 (&f)[Q3]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int j = 0; j < Q3; ++j) {
-                    const int ks = q * Q3 + j;
-                    const int tap = (32 * ks) / C2, ci0 = (32 * ks) % C2;
-                    f[j] = as_f16x8(*reinterpret_cast<const u32x4 *>(a2l + base + P3::tap_off(tap) + ci0 * 2));
+                    f[j] = as_f16x8(*reinterpret_cast<const u32x4 *>(a2l + base + P3::step_off(q * Q3 + j)));
                 }
             };
             load_q(0, fa);
@@ -245,8 +256,9 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_kernel(const InferConv
             for (int j = 0; j < Q3; ++j) acc[half_of<FRAG>(2 * Q3 + j, KS3)] = mfma_f16(w3[2 * Q3 + j], fa[j], acc[half_of<FRAG>(2 * Q3 + j, KS3)]);
             const f32x4 v = sum_halves(acc);
             if (valid)
-                *reinterpret_cast<u32x2 *>(a.a3 + LastActs<C3, NP3>::template at<FRAG>(s, row, ct * 16 + 4 * lg)) =
+                *reinterpret_cast<u32x2 *>(a.a3 + LastActs<Geo::NCL, Geo::PL>::template at<FRAG>(s, row, ct * 16 + 4 * lg)) =
                     relu_f16x4(v[0] + bias3.x, v[1] + bias3.y, v[2] + bias3.z, v[3] + bias3.w);
+        }
         }
         // no barrier here: conv1 of the next sample writes the act1 image (its readers passed the barrier above)
         // and reads the frame image staged before that barrier; conv2 of the next sample, which overwrites the
@@ -275,7 +287,7 @@ constexpr int INF_BIAS_BYTES = (C1 + C2 + C3) * 4;   // the three layers' biases
 template <class Geo, class P2, class P3>
 constexpr int infer_pipelined_lds_bytes() { return 2 * Geo::OBS_BYTES + P2::IMG + P3::IMG + INF_BIAS_BYTES + INF_W1_BYTES; }
 template <class Geo, class P2, class P3>
-constexpr bool infer_pipelined_fits() { return infer_pipelined_lds_bytes<Geo, P2, P3>() <= 160 * 1024; }
+constexpr bool infer_pipelined_fits() { return Geo::HAS3 && infer_pipelined_lds_bytes<Geo, P2, P3>() <= 160 * 1024; }
 
 template <class Geo, class P2, class P3, bool FRAG>   // FRAG: a3 in fragment order (LastActs)
 __global__ __launch_bounds__(INF_THREADS) void infer_conv_pipelined_kernel(const InferConvArgs a, int B, int spw) {

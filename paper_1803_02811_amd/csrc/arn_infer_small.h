@@ -37,6 +37,20 @@ inline BandPlan band_plan(int B) {
     return p;
 }
 
+// Sample and band of block b of n: all bands of eight (at the end of the grid four, or one) consecutive samples on one XCD
+// (see sample_block).
+__device__ __forceinline__ void band_of_block(int b, int n, int bands, int &s, int &band) {
+    const int chunk = b / (64 * bands), r = b - chunk * 64 * bands, left = n / bands - chunk * 64;
+    const int run = left >= 64 ? 8 : left >= 32 && r < 32 * bands ? 4 : 1;
+    if (run > 1) {
+        s = chunk * 64 + (r & 7) * run + (r >> 3) % run;
+        band = (r >> 3) / run;
+    } else {
+        s = b / bands;
+        band = b - s * bands;
+    }
+}
+
 // LDS of infer_conv_band_kernel: frame image (later the scratch of the half sums), act1 image, act2 image, conv1's weights
 // (in the act2 image where that is large enough: they are dead before act2 is written)
 template <class Geo, class P2, class P3>
@@ -123,7 +137,7 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_band_kernel(const Infe
     constexpr int MAXT2 = ((Geo::P2 + 15) / 16 + PG - 1) / PG, MAXT3 = HAS3 ? (Geo::P3 + 15) / 16 : 1;
     constexpr int MAXT = MAXT2 > MAXT3 ? MAXT2 : MAXT3, SCR = (MAXT + 1) / 2 * 64;   // scratch words per wavefront
     typedef BandLds<Geo, P2, P3> L;
-    static_assert((4 * IN_W) % 16 == 0 && layout_is_uniform<P2>() && (!HAS3 || layout_is_uniform<P3>()), "layouts");
+    static_assert((4 * IN_W) % 16 == 0 && layout_is_uniform<P2>() && layout_is_uniform<P3>(), "layouts");
     static_assert(L::BYTES <= 160 * 1024 && 8 * SCR * 16 <= L::FRAME && L::A1_AT % 16 == 0 && L::A2_AT % 16 == 0 && L::W1_AT % 16 == 0, "LDS budget");
     static_assert(PG >= 1 && (!HAS3 || PG == 1), "two halves of the contraction, CT2 channel tiles, PG position groups");
     constexpr int NW1 = L::W1 / 16 / INF_THREADS;
@@ -140,19 +154,8 @@ __global__ __launch_bounds__(INF_THREADS) void infer_conv_band_kernel(const Infe
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lg = lane >> 4;
-    // all bands of eight consecutive samples on one XCD (see sample_block)
     int s, band;
-    {
-        const int n = gridDim.x / bands, chunk = blockIdx.x / (64 * bands), r = blockIdx.x - chunk * 64 * bands;
-        const int left = n - chunk * 64, run = left >= 64 ? 8 : left >= 32 && r < 32 * bands ? 4 : 1;
-        if (run > 1) {
-            s = chunk * 64 + (r & 7) * run + (r >> 3) % run;
-            band = (r >> 3) / run;
-        } else {
-            s = blockIdx.x / bands;
-            band = blockIdx.x - s * bands;
-        }
-    }
+    band_of_block(blockIdx.x, gridDim.x, bands, s, band);
     typedef LastActs<Geo::NCL, Geo::PL> Out;   // fragment order: this kernel serves only batches of fc_small_kernel
 
     // rows of each layer's output that this band needs

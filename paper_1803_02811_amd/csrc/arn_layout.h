@@ -41,9 +41,12 @@ struct Geometry {
 };
 typedef Geometry<84, 84, 0, 0> Geo84;
 typedef Geometry<104, 80, 1, 1> GeoPaper;
+// the 2-convolution network of the same appendix: 16 and 32 filters, no third convolution, 256 hidden units
+typedef Geometry<104, 80, 1, 1, 16, 32, false, 256> GeoA3c;
 static_assert(Geo84::P1 == P1 && Geo84::P2 == P2 && Geo84::P3 == P3 && Geo84::FEAT == FEAT, "84x84 constants");
 static_assert(GeoPaper::H1 == 25 && GeoPaper::W1 == 19 && GeoPaper::H2 == 12 && GeoPaper::W2 == 9 &&
               GeoPaper::H3 == 12 && GeoPaper::W3 == 9 && GeoPaper::FEAT == 6912, "appendix: 25x19 -> 12x9 -> 12x9");
+static_assert(GeoA3c::PL == 108 && GeoA3c::FEAT == 3456, "appendix: 25x19 -> 12x9");
 
 struct Dims {
     int A = 0, head = 0, atoms = 0;
@@ -52,28 +55,28 @@ struct Dims {
     bool small = false;   // at most 32 head rows: the fused head kernel follows the fc GEMM (PV, Q, DUEL)
     bool vrow = false;    // the row after the A action rows is a state value (PV, DUEL)
     bool qhead = false;   // the head outputs are action values (Q, DUEL)
-    int geom = ARN_GEOM_84;   // geometry of the kernels that run: ARN_GEOM_84 or ARN_GEOM_PAPER
-    bool a3c = false;         // the 2-convolution network, embedded in the ARN_GEOM_PAPER network
-    int p1 = P1, p2 = P2, p3 = P3, feat = FEAT, obs_bytes = OBS_BYTES;   // positions per sample after conv1..3, fc inputs, bytes per observation
+    int geom = ARN_GEOM_84;
+    // channels of the convolutions (c3 = 0: none), conv2's contraction length, hidden units
+    int c1 = C1, c2 = C2, c3 = C3, kw2 = KW2, hid = HID;
+    int p1 = P1, p2 = P2, pl = P3, feat = FEAT, obs_bytes = OBS_BYTES;   // positions per sample after conv1, conv2 and the last convolution, fc inputs, bytes per observation
     bool ok = false;
 };
 
+template <class G>
+inline void set_geometry(Dims &d) {
+    d.c1 = G::NC1; d.c2 = G::NC2; d.c3 = G::HAS3 ? C3 : 0; d.kw2 = G::KW2; d.hid = G::NHID;
+    d.p1 = G::P1; d.p2 = G::P2; d.pl = G::PL; d.feat = G::FEAT; d.obs_bytes = G::OBS_BYTES;
+}
 inline Dims make_dims(const arn_config *c) {
     Dims d;
     if (!c) return d;
     d.A = c->num_actions;
     d.head = c->head_kind;
     d.geom = c->geometry;
-    if (d.geom == ARN_GEOM_A3C) {
-        d.a3c = true;
-        d.geom = ARN_GEOM_PAPER;
-    }
-    if (d.geom == ARN_GEOM_PAPER) {
-        d.p1 = GeoPaper::P1; d.p2 = GeoPaper::P2; d.p3 = GeoPaper::P3;
-        d.feat = GeoPaper::FEAT; d.obs_bytes = GeoPaper::OBS_BYTES;
-    } else if (d.geom != ARN_GEOM_84) {
-        return d;
-    }
+    if (d.geom == ARN_GEOM_84) set_geometry<Geo84>(d);
+    else if (d.geom == ARN_GEOM_PAPER) set_geometry<GeoPaper>(d);
+    else if (d.geom == ARN_GEOM_A3C) set_geometry<GeoA3c>(d);
+    else return d;
     if (d.head == ARN_HEAD_PV || d.head == ARN_HEAD_Q || d.head == ARN_HEAD_DUEL) {
         if (d.A < 1 || d.A > 31) return d;
         d.atoms = 1;
@@ -101,83 +104,27 @@ struct ParamOffsets {
 inline ParamOffsets param_offsets(const Dims &d) {
     ParamOffsets o{};
     size_t p = 0;
-    o.w1 = p; p += (size_t)C1 * KW1;
-    o.b1 = p; p += C1;
-    o.w2 = p; p += (size_t)C2 * KW2;
-    o.b2 = p; p += C2;
-    o.w3 = p; p += (size_t)C3 * KW3;
-    o.b3 = p; p += C3;
-    o.wfc = p; p += (size_t)HID * d.feat;
-    o.bfc = p; p += HID;
+    o.w1 = p; p += (size_t)d.c1 * KW1;
+    o.b1 = p; p += d.c1;
+    o.w2 = p; p += (size_t)d.c2 * d.kw2;
+    o.b2 = p; p += d.c2;
+    o.w3 = p; p += (size_t)d.c3 * KW3;
+    o.b3 = p; p += d.c3;
+    o.wfc = p; p += (size_t)d.hid * d.feat;
+    o.bfc = p; p += d.hid;
     if (d.vrow) {
-        o.wh = p; p += (size_t)d.A * HID;
+        o.wh = p; p += (size_t)d.A * d.hid;
         o.bh = p; p += d.A;
-        o.wv = p; p += HID;
+        o.wv = p; p += d.hid;
         o.bv = p; p += 1;
     } else {
-        o.wh = p; p += (size_t)d.NH * HID;
+        o.wh = p; p += (size_t)d.NH * d.hid;
         o.bh = p; p += d.NH;
         o.wv = o.bv = p;
     }
     o.total = p;
     return o;
 }
-
-// The 2-convolution network (16 and 32 filters, 256 hidden units, 104x80 frames) as a sub-network of the
-// three-convolution one: its filters, hidden units and head columns are the leading ones, everything else is
-// zero and conv3 is the identity (centre tap 1 on the diagonal, zero bias).  ReLU of a non-negative map is that
-// map, and the sign bits of act3 equal those of act2, so function and gradients are those of the small network.
-constexpr int A3C_C1 = 16, A3C_C2 = 32, A3C_HID = 256, A3C_FEAT = A3C_C2 * 12 * 9;
-struct A3cMap {   // index of the small network's flat vector -> index of the embedding network's
-    long w1, b1, w2, b2, wfc, bfc, wh, bh, wv, bv, total;   // offsets in the small vector
-    ParamOffsets e;                                         // offsets in the embedding vector
-    int feat;                                               // fc inputs of the embedding network
-#if defined(__HIPCC__)
-    __host__ __device__
-#endif
-    long operator()(long i) const {
-        if (i < b1) return (long)e.w1 + i;                                   // filters 0..15: the leading rows
-        if (i < w2) return (long)e.b1 + (i - b1);
-        if (i < b2) {
-            const long j = i - w2, co = j / (A3C_C1 * 16), r = j % (A3C_C1 * 16);
-            return (long)e.w2 + co * (C1 * 16) + r;                          // [co][ci][4][4]: ci < 16 of 32
-        }
-        if (i < wfc) return (long)e.b2 + (i - b2);
-        if (i < bfc) {
-            const long j = i - wfc, n = j / A3C_FEAT, k = j % A3C_FEAT;
-            return (long)e.wfc + n * feat + k;                               // input index c*108 + pos, c < 32
-        }
-        if (i < wh) return (long)e.bfc + (i - bfc);
-        if (i < bh) {
-            const long j = i - wh;
-            return (long)e.wh + (j / A3C_HID) * HID + j % A3C_HID;
-        }
-        if (i < wv) return (long)e.bh + (i - bh);
-        if (i < bv) return (long)e.wv + (i - wv);
-        return (long)e.bv + (i - bv);
-    }
-};
-inline A3cMap make_a3c_map(const Dims &d) {
-    A3cMap m{};
-    long p = 0;
-    m.w1 = p; p += (long)A3C_C1 * KW1;
-    m.b1 = p; p += A3C_C1;
-    m.w2 = p; p += (long)A3C_C2 * A3C_C1 * 16;
-    m.b2 = p; p += A3C_C2;
-    m.wfc = p; p += (long)A3C_HID * A3C_FEAT;
-    m.bfc = p; p += A3C_HID;
-    const int rows = d.vrow ? d.A : d.NH;
-    m.wh = p; p += (long)rows * A3C_HID;
-    m.bh = p; p += rows;
-    m.wv = p; p += d.vrow ? A3C_HID : 0;
-    m.bv = p; p += d.vrow ? 1 : 0;
-    m.total = p;
-    m.e = param_offsets(d);
-    m.feat = d.feat;
-    return m;
-}
-// entries of the flat parameter / gradient vector at the interface
-inline size_t public_param_count(const Dims &d) { return d.a3c ? (size_t)make_a3c_map(d).total : param_offsets(d).total; }
 
 // byte offsets into the packed blob
 struct PackedOffsets {
@@ -186,38 +133,37 @@ struct PackedOffsets {
     size_t w1l, w2l, w3l, wfcl, whl;     // low parts (w - hi) for the three-product inference path
     size_t whd, wfcd, w3d, w2d;          // input-gradient layouts
     size_t w1h, w2h, w3h, wfch;          // fp16 copies of the forward layouts (single-product, no-gradient forward)
-    size_t a3c_flat;                     // the embedding network's flat fp32 vector (2-convolution network only)
-    size_t fwd_bytes, total;
+    size_t total;
 };
 inline PackedOffsets packed_offsets(const Dims &d) {
     PackedOffsets o{};
     size_t p = 0;
     auto take = [&](size_t bytes) { size_t at = p; p = align_up(p + bytes, 256); return at; };
-    o.w1 = take((size_t)C1 * KW1 * 2);
-    o.w2 = take((size_t)C2 * KW2 * 2);
-    o.w3 = take((size_t)C3 * KW3 * 2);
-    o.wfc = take((size_t)HID * d.feat * 2);
-    o.wh = take((size_t)d.NHP * HID * 2);
-    o.b1 = take(C1 * 4);
-    o.b2 = take(C2 * 4);
-    o.b3 = take(C3 * 4);
-    o.bfc = take(HID * 4);
+    const size_t w1 = (size_t)d.c1 * KW1 * 2, w2 = (size_t)d.c2 * d.kw2 * 2, w3 = (size_t)d.c3 * KW3 * 2;
+    const size_t wfc = (size_t)d.hid * d.feat * 2, wh = (size_t)d.NHP * d.hid * 2;
+    o.w1 = take(w1);
+    o.w2 = take(w2);
+    o.w3 = take(w3);
+    o.wfc = take(wfc);
+    o.wh = take(wh);
+    o.b1 = take(d.c1 * 4);
+    o.b2 = take(d.c2 * 4);
+    o.b3 = take(d.c3 * 4);
+    o.bfc = take(d.hid * 4);
     o.bh = take((size_t)d.NHP * 4);
-    o.fwd_bytes = p;
-    o.w1l = take((size_t)C1 * KW1 * 2);
-    o.w2l = take((size_t)C2 * KW2 * 2);
-    o.w3l = take((size_t)C3 * KW3 * 2);
-    o.wfcl = take((size_t)HID * d.feat * 2);
-    o.whl = take((size_t)d.NHP * HID * 2);
-    o.whd = take((size_t)HID * d.NHP * 2);
-    o.wfcd = take((size_t)d.feat * HID * 2);
-    o.w3d = take((size_t)C2 * KW3 * 2);
-    o.w2d = take((size_t)4 * C1 * 4 * C2 * 2);
-    o.w1h = take((size_t)C1 * KW1 * 2);
-    o.w2h = take((size_t)C2 * KW2 * 2);
-    o.w3h = take((size_t)C3 * KW3 * 2);
-    o.wfch = take((size_t)HID * d.feat * 2);
-    o.a3c_flat = take(d.a3c ? param_offsets(d).total * 4 : 0);
+    o.w1l = take(w1);
+    o.w2l = take(w2);
+    o.w3l = take(w3);
+    o.wfcl = take(wfc);
+    o.whl = take(wh);
+    o.whd = take(wh);
+    o.wfcd = take(wfc);
+    o.w3d = take(w3);
+    o.w2d = take((size_t)4 * d.c1 * 4 * d.c2 * 2);
+    o.w1h = take(w1);
+    o.w2h = take(w2);
+    o.w3h = take(w3);
+    o.wfch = take(wfc);
     o.total = p;
     return o;
 }
@@ -241,7 +187,12 @@ inline int pick_split(long rows, int tiles, int target_wgs) {
 // finish together.
 inline int wgrad_wgs2(int geom) { return geom == ARN_GEOM_84 ? 148 : 128; }
 inline int wgrad_wgs3(int geom) { return 256 - wgrad_wgs2(geom); }
-constexpr int CONV2_WG_G = 2, CONV3_WG_G = 4;   // samples staged per iteration by the conv2 / conv3 weight-gradient kernels
+constexpr int CONV3_WG_G = 4;   // samples staged per iteration by the conv3 weight-gradient kernel
+template <class G>
+struct Conv2WgradG {            // ... and by conv2's
+    static constexpr int value = G::HAS3 ? 2 : 4;
+};
+inline int conv2_wg_g(const Dims &d) { return d.c3 ? Conv2WgradG<Geo84>::value : Conv2WgradG<GeoA3c>::value; }
 // sample-resident weight-gradient kernels: samples per workgroup and number of workgroups
 inline int resident_spw(int B, int target_wgs) { return (B + target_wgs - 1) / target_wgs; }
 inline int resident_groups(int B, int target_wgs) {
@@ -250,21 +201,13 @@ inline int resident_groups(int B, int target_wgs) {
 }
 inline Splits make_splits(const Dims &d, int B) {
     Splits s;
-    if (d.geom != ARN_GEOM_84) {
-        // the dense layers' weight-gradient GEMMs are cut along the batch so that about 512 workgroups exist;
-        // the convolutions use the sample-resident kernels, as below
-        s.c1 = resident_groups(B, 256);
-        s.c2 = resident_groups((B + CONV2_WG_G - 1) / CONV2_WG_G, wgrad_wgs2(d.geom));   // sample-resident kernels, as below
-        s.c3 = resident_groups((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom));
-        s.fc = pick_split(B, (d.feat / 64) * 4, 512);
-        s.hd = pick_split(B, 4 * (d.NHP / 64), 256);
-        return s;
-    }
+    const int g2 = conv2_wg_g(d);
     s.c1 = resident_groups(B, 256);
-    s.c2 = resident_groups((B + CONV2_WG_G - 1) / CONV2_WG_G, wgrad_wgs2(d.geom));
-    s.c3 = resident_groups((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom));
-    s.fc = pick_split(B, 49 * 4, 392);
-    s.hd = pick_split(B, 4 * (d.NHP / 64), 256);
+    s.c2 = resident_groups((B + g2 - 1) / g2, wgrad_wgs2(d.geom));
+    s.c3 = d.c3 ? resident_groups((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom)) : 0;
+    // the dense layers' weight-gradient GEMMs are cut along the batch so that about 400 to 500 workgroups exist
+    s.fc = pick_split(B, (d.feat / 64) * (d.hid / 128), d.geom == ARN_GEOM_84 ? 392 : 512);
+    s.hd = pick_split(B, (d.hid / 128) * (d.NHP / 64), 256);
     return s;
 }
 
@@ -278,10 +221,17 @@ inline Splits make_splits(const Dims &d, int B) {
 // against 8.4 + 5.7; three products, 6912 inputs, 512 samples: 29.6 against 18.8).
 constexpr int FC_SMALL_MAX = 512;
 inline bool fc_small(int feat, int B, bool f16) { return B <= FC_SMALL_MAX && (long)B * feat * (f16 ? 1 : 2) <= 2500000; }
-inline int fc_small_rows(int B) { return B <= 64 ? 16 : 32; }   // samples per workgroup
-inline int fc_ksplit(int feat, int B, bool f16) {
+// Tile of a workgroup: the smallest (most workgroups) that does not need more than 128 of them, at most 32 x 32.
+struct FcTile { int units, rows; };
+inline FcTile fc_small_tile(int hid, int B) {
+    const int n = hid / 16;
+    if (n * ((B + 15) / 16) <= 128) return {16, 16};
+    if (n * ((B + 31) / 32) <= 128) return {16, 32};
+    return {32, 32};
+}
+inline int fc_ksplit(int feat, int hid, int B, bool f16) {
     if (fc_small(feat, B, f16)) return 1;
-    const int tiles = ((B + 127) / 128) * 4;
+    const int tiles = ((B + 127) / 128) * (hid / 128);
     int ks = 256 / tiles;
     if (ks < 1) ks = 1;
     const int cap = f16 && B >= 128 ? 8 : 16;   // the consumer adds the ranges one after the other: more of them costs it more than the GEMM gains
@@ -298,21 +248,23 @@ constexpr int C51_WAVES = 4;      // wavefronts per block in the C51 kernels (on
 // head's bias gradient, so large batches use fewer, longer blocks.
 inline int c51_loss_spw(int B) { return B <= 2048 ? 1 : 4; }
 
+// bytes of one sample's sign bits of act1, in whole 4-byte words
+constexpr int mask1_bytes(int p1, int c1) { return (p1 * c1 / 8 + 3) / 4 * 4; }
+
 // byte offsets into the workspace
 struct Workspace {
-    size_t a1, a2, a3, h;               // bf16 NHWC activations
+    size_t a1, a2, a3, h;               // bf16 NHWC activations (a3: the last convolution's; two convolutions: no a2)
     size_t a1l, a2l, a3l, hl;           // their low parts (written and read by the forward pass only)
     size_t fcp;                         // fp32 [ksplit][B][512] partial sums of the fc forward GEMM
     size_t zp, cnt;                     // fc_small_kernel: contributions to the head outputs [HID/16][padded B][32], counters
     size_t z, zv;                       // categorical head: fp32 atom logits, rows padded to NHP floats
     size_t ztgt, m;                     // C51: target-net atom logits, projected target
     size_t qt, astar;                   // DQN: target-net Q(s',.) fp32 [B][A]; Double-DQN: online greedy action on s' int32 [B]
-    size_t m1, m2, m3;                  // ReLU sign bits of act1..3 (bit e&7 of byte e>>3, NHWC element e), written by the forward
-    size_t dz, dph, dp3, dp2;           // bf16 gradients at pre-activations (d(pre1) never leaves the chip)
+    size_t m1, m2, m3;                  // ReLU sign bits of act1, act2 and the last convolution's activations (bit e&7 of byte e>>3, NHWC element e), written by the forward
+    size_t dz, dph, dp3, dp2;           // bf16 gradients at pre-activations (d(pre1) never leaves the chip); dp3: the last convolution's
     size_t lossp;                       // fp32 [blocks][4] partial loss sums
     size_t hbp;                         // fp32 [blocks][32 or NHP] partial sums of the head's bias gradient
     size_t pw1, pw2, pw3, pwfc, pwh;    // fp32 weight-gradient partials [split][N*K' + N]
-    size_t a3c_dw;                      // gradient of the embedding network (2-convolution network only)
     size_t total;
 };
 inline int loss_blocks(const Dims &d, int B) {
@@ -323,22 +275,22 @@ inline Workspace make_workspace(const Dims &d, int B, int mode) {
     Workspace w{};
     size_t p = 0;
     auto take = [&](size_t bytes) { size_t at = p; p = align_up(p + bytes, 256); return at; };
-    const size_t b = (size_t)B;
-    const size_t p1 = (size_t)d.p1, p2 = (size_t)d.p2, feat = (size_t)d.feat;
-    w.a1 = take(b * p1 * C1 * 2);
-    w.a2 = take(b * p2 * C2 * 2);
+    const size_t b = (size_t)B, feat = (size_t)d.feat, hid = (size_t)d.hid;
+    const size_t e1 = b * d.p1 * d.c1, e2 = d.c3 ? b * d.p2 * d.c2 : 0;   // elements of act1 and act2
+    w.a1 = take(e1 * 2);
+    w.a2 = take(e2 * 2);
     const size_t b3 = B <= FC_SMALL_MAX ? align_up(b, 32) : b;   // fragment order: whole sample tiles
     w.a3 = take(b3 * feat * 2);
-    w.h = take(b * HID * 2);
-    w.a1l = take(b * p1 * C1 * 2);
-    w.a2l = take(b * p2 * C2 * 2);
+    w.h = take(b * hid * 2);
+    w.a1l = take(d.c3 ? e1 * 2 : 0);                             // two convolutions: act1 goes to conv2 through LDS
+    w.a2l = take(e2 * 2);
     w.a3l = take(b3 * feat * 2);
-    w.hl = take(b * HID * 2);
+    w.hl = take(b * hid * 2);
     // the fused policy/value head kernel always reads fp32 partials; the categorical path only when k is split
-    const int ks = fc_ksplit(d.feat, B, false), ks16 = fc_ksplit(d.feat, B, true), ksm = ks > ks16 ? ks : ks16;
-    w.fcp = take((size_t)(ksm > 1 || d.small ? ksm : 0) * b * HID * 4);
+    const int ks = fc_ksplit(d.feat, d.hid, B, false), ks16 = fc_ksplit(d.feat, d.hid, B, true), ksm = ks > ks16 ? ks : ks16;
+    w.fcp = take((size_t)(ksm > 1 || d.small ? ksm : 0) * b * hid * 4);
     if (fc_small(d.feat, B, true) && d.small) {
-        w.zp = take((size_t)(HID / 16) * align_up(b, 32) * 32 * 4);
+        w.zp = take(hid / 16 * align_up(b, 32) * 32 * 4);
         w.cnt = take((size_t)FC_SMALL_MAX / 16 * 4);
     }
     // categorical head: atom logits of arn_policy_act (arn_policy_forward writes them to its `logits` argument)
@@ -354,25 +306,42 @@ inline Workspace make_workspace(const Dims &d, int B, int mode) {
             w.ztgt = take(b * (size_t)d.NHP * 4);
             w.m = take(b * (size_t)d.atoms * 4);
         }
-        w.m1 = take(b * p1 * C1 / 8);
-        w.m2 = take(b * p2 * C2 / 8);
+        w.m1 = take(b * mask1_bytes(d.p1, d.c1));
+        w.m2 = take(e2 / 8);
         w.m3 = take(b * feat / 8);
         w.dz = take(b * (size_t)d.NHP * 2);
-        w.dph = take(b * HID * 2);
+        w.dph = take(b * hid * 2);
         w.dp3 = take(b * feat * 2);
-        w.dp2 = take(b * p2 * C2 * 2);
+        w.dp2 = take(e2 * 2);
         w.lossp = take((size_t)loss_blocks(d, B) * 4 * 4);
         w.hbp = take((size_t)loss_blocks(d, B) * (d.small ? 32 : d.NHP) * 4);
         const Splits s = make_splits(d, B);
-        w.pw1 = take((size_t)s.c1 * ((size_t)C1 * KW1 + C1) * 4);
-        w.pw2 = take((size_t)s.c2 * ((size_t)C2 * KW2 + C2) * 4);
+        w.pw1 = take((size_t)s.c1 * ((size_t)d.c1 * KW1 + d.c1) * 4);
+        w.pw2 = take((size_t)s.c2 * ((size_t)d.c2 * d.kw2 + d.c2) * 4);
         w.pw3 = take((size_t)s.c3 * ((size_t)C3 * KW3 + C3) * 4);
-        w.pwfc = take((size_t)s.fc * ((size_t)HID * feat + HID) * 4);
-        w.pwh = take((size_t)s.hd * ((size_t)d.NHP * HID + d.NHP) * 4);
-        w.a3c_dw = take(d.a3c ? param_offsets(d).total * 4 : 0);
+        w.pwfc = take((size_t)s.fc * (hid * feat + hid) * 4);
+        w.pwh = take((size_t)s.hd * ((size_t)d.NHP * hid + d.NHP) * 4);
     }
     w.total = p;
     return w;
+}
+
+// Sizes reported to callers.  The 2-convolution network reports those of its embedding in the 104x80 three-convolution
+// network (plus that network's flat vector), which are part of its documented interface and larger than what it needs.
+inline Dims embedding_dims(Dims d) {
+    d.geom = ARN_GEOM_PAPER;
+    set_geometry<GeoPaper>(d);
+    return d;
+}
+inline size_t reported_packed_bytes(const Dims &d) {
+    if (d.geom != ARN_GEOM_A3C) return packed_offsets(d).total;
+    const Dims e = embedding_dims(d);
+    return packed_offsets(e).total + align_up(param_offsets(e).total * 4, 256);
+}
+inline size_t reported_workspace_bytes(const Dims &d, int B, int mode) {
+    if (d.geom != ARN_GEOM_A3C) return make_workspace(d, B, mode).total;
+    const Dims e = embedding_dims(d);
+    return make_workspace(e, B, mode).total + (mode == ARN_MODE_TRAIN ? align_up(param_offsets(e).total * 4, 256) : 0);
 }
 
 }  // namespace arn

@@ -63,7 +63,7 @@ struct DenseGatherRt {
 // of k-tiles and writes an fp32 partial [z][M][512]; fc_finish_kernel adds the
 // partials in z order and applies bias, ReLU and the hi/lo split.  With
 // ksplit == 1 the epilogue does that directly.
-template <int FEAT_>
+template <int FEAT_, int HIDN>
 struct FcFwdT : DenseGather<FEAT_> {
     typedef typename DenseGather<FEAT_>::Row Row;
     static constexpr int BM = 128, BN = 128, WAVES_N = 2, K = FEAT_, STAGES = 2, THREADS = 512;
@@ -83,40 +83,41 @@ struct FcFwdT : DenseGather<FEAT_> {
         const int M = this->M;
         if (m >= M) return;
         if (to_partial) {
-            *reinterpret_cast<float4 *>(partial + ((size_t)z * M + m) * HID + n) = make_float4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<float4 *>(partial + ((size_t)z * M + m) * HIDN + n) = make_float4(v[0], v[1], v[2], v[3]);
             return;
         }
         const float4 b = *reinterpret_cast<const float4 *>(bias + n);
-        store_bf16x4_split(out, out_lo, (size_t)m * HID + n, fmaxf(v[0] + b.x, 0.f), fmaxf(v[1] + b.y, 0.f),
+        store_bf16x4_split(out, out_lo, (size_t)m * HIDN + n, fmaxf(v[0] + b.x, 0.f), fmaxf(v[1] + b.y, 0.f),
                            fmaxf(v[2] + b.z, 0.f), fmaxf(v[3] + b.w, 0.f));
     }
 };
-typedef FcFwdT<FEAT> FcFwd;
 // The same layer with fp16 activations and weights in one product (no-gradient forward): `in` and `w` point at
 // fp16 data of the same layouts; the outputs are the fp32 partial sums or the (hi, lo) bf16 hidden layer as above.
-template <int FEAT_>
-struct FcFwdF16T : FcFwdT<FEAT_> {
+template <int FEAT_, int HIDN>
+struct FcFwdF16T : FcFwdT<FEAT_, HIDN> {
     static constexpr bool F16 = true;
 };
 
 // categorical head: rows of the packed head matrix are the A*atoms categorical rows
 // C51: atom logits fp32 [M][ZS] with bias; ZS = ZW (dense, the inference output) or the padded head width
 // (the gradient step's own buffers: 16-byte stores).
-struct HeadFwdC51 : DenseGather<HID> {
-    static constexpr int BM = 128, BN = 64, WAVES_N = 1, K = HID;
+template <int HIDN>
+struct HeadFwdC51 : DenseGather<HIDN> {
+    typedef typename DenseGather<HIDN>::Row Row;
+    static constexpr int BM = 128, BN = 64, WAVES_N = 1, K = HIDN;
     static constexpr bool ACT_LO = true;
     const __bf16 *w, *w_lo = nullptr;
     const float *bias;   // padded head width entries (zeros past ZW)
     float *z;       // [M][ZS]
     int ZW;         // A*atoms
     int ZS;         // row stride in floats: ZW, or a multiple of 64 >= ZW
-    __device__ __forceinline__ Row row(int m, int) const { return row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return load_at(r, k); }
-    __device__ __forceinline__ u32x4 load_lo(const Row &r, int k) const { return load_lo_at(r, k); }
+    __device__ __forceinline__ Row row(int m, int) const { return this->row_at(m); }
+    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return this->load_at(r, k); }
+    __device__ __forceinline__ u32x4 load_lo(const Row &r, int k) const { return this->load_lo_at(r, k); }
     __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
     __device__ __forceinline__ const __bf16 *weights_lo(int) const { return w_lo; }
     __device__ __forceinline__ void store(int m, int n, f32x4 v, int) const {
-        if (m >= M) return;
+        if (m >= this->M) return;
         const float4 b = *reinterpret_cast<const float4 *>(bias + n);
         float *dst = z + (size_t)m * ZS + n;
         if (ZS != ZW) {                        // padded rows: every column exists
@@ -135,17 +136,18 @@ struct HeadFwdC51 : DenseGather<HID> {
 
 // --------------------------- input gradients ------------------------------
 // d(pre_fc) = (dz W_head) * [h > 0]; the contraction length is the padded head width
+template <int HIDN>
 struct HeadDgrad : DenseGatherRt {
     static constexpr int BM = 64, BN = 64, WAVES_N = 2;
-    const __bf16 *w;     // [512][K]
+    const __bf16 *w;     // [HIDN][K]
     const __bf16 *h;
-    __bf16 *out;         // [M][512]
+    __bf16 *out;         // [M][HIDN]
     __device__ __forceinline__ Row row(int m, int) const { return row_at(m); }
     __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return load_at(r, k); }
     __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
     __device__ __forceinline__ void store(int m, int n, f32x4 v, int) const {
         if (m >= M) return;
-        const size_t at = (size_t)m * HID + n;
+        const size_t at = (size_t)m * HIDN + n;
         const f32x4 a = unpack_bf16x4(*reinterpret_cast<const u32x2 *>(h + at));
         *reinterpret_cast<u32x2 *>(out + at) = pack_bf16x4(a[0] > 0.f ? v[0] : 0.f, a[1] > 0.f ? v[1] : 0.f,
                                                           a[2] > 0.f ? v[2] : 0.f, a[3] > 0.f ? v[3] : 0.f);
@@ -154,28 +156,28 @@ struct HeadDgrad : DenseGatherRt {
 
 // d(pre3) = (d(pre_fc) W_fc) * [act3 > 0]      [B][FEAT], NHWC index.  BN_ = 64, or 128 for large batches (a third
 // less operand traffic from the L2 per flop; FEAT need not be a multiple of it: N_ROWS).
-template <int FEAT_, int BN_ = 64>
-struct FcDgradT : DenseGather<HID> {
-    static constexpr int BM = 128, BN = BN_, WAVES_N = 2, K = HID, STAGES = 1, FEAT = FEAT_, N_ROWS = FEAT_;
+template <int FEAT_, int HIDN, int BN_>
+struct FcDgradT : DenseGather<HIDN> {
+    typedef typename DenseGather<HIDN>::Row Row;
+    static constexpr int BM = 128, BN = BN_, WAVES_N = 2, K = HIDN, STAGES = 1, FEAT = FEAT_, N_ROWS = FEAT_;
     const __bf16 *w;          // [FEAT][512]
     const uint8_t *maskbits;  // sign bits of act3, bit e&7 of byte e>>3 for element e = m*FEAT + n
     __bf16 *out;
-    __device__ __forceinline__ Row row(int m, int) const { return row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return load_at(r, k); }
+    __device__ __forceinline__ Row row(int m, int) const { return this->row_at(m); }
+    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return this->load_at(r, k); }
     __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
     // the four ReLU-derivative bits of output quad (m, n..n+3), fetched before the k loop
     __device__ __forceinline__ uint32_t prefetch(int m, int n) const {
-        const size_t at = (size_t)(m < M ? m : 0) * FEAT + (n < FEAT ? n : 0);
+        const size_t at = (size_t)(m < this->M ? m : 0) * FEAT + (n < FEAT ? n : 0);
         return (uint32_t)maskbits[at >> 3] >> (at & 7);
     }
     __device__ __forceinline__ void store(int m, int n, f32x4 v, int, uint32_t mb) const {
-        if (m >= M || n >= FEAT) return;
+        if (m >= this->M || n >= FEAT) return;
         const size_t at = (size_t)m * FEAT + n;
         *reinterpret_cast<u32x2 *>(out + at) =
             pack_bf16x4(mb & 1 ? v[0] : 0.f, mb & 2 ? v[1] : 0.f, mb & 4 ? v[2] : 0.f, mb & 8 ? v[3] : 0.f);
     }
 };
-typedef FcDgradT<FEAT> FcDgrad;
 
 // --------------------------- weight gradients -----------------------------
 // part[n][k] = sum_m dY[m][n] act(m,k); dY is a dense [M][N1] bf16 matrix.
@@ -202,12 +204,14 @@ struct LastActsGather {
     }
 };
 // heads: N1 (padded head rows) is a run-time value
-struct HeadWgrad : DenseGather<HID> {
-    static constexpr int BN1 = 64, BK2 = 128, WAVES_X = 4, KP = HID;
+template <int HIDN>
+struct HeadWgrad : DenseGather<HIDN> {
+    typedef typename DenseGather<HIDN>::Row Row;
+    static constexpr int BN1 = 64, BK2 = 128, WAVES_X = 4, KP = HIDN;
     int N1;
     const __bf16 *dy;
-    __device__ __forceinline__ Row xrow(long m) const { return row_at(m); }
-    __device__ __forceinline__ u32x4 loadx(const Row &r, int k) const { return load_at(r, k); }
+    __device__ __forceinline__ Row xrow(long m) const { return this->row_at(m); }
+    __device__ __forceinline__ u32x4 loadx(const Row &r, int k) const { return this->load_at(r, k); }
     __device__ __forceinline__ u32x4 loady(long m, int n) const {
         return *reinterpret_cast<const u32x4 *>(dy + (size_t)m * N1 + n);
     }

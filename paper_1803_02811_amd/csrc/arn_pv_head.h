@@ -31,14 +31,13 @@ namespace arn {
 
 constexpr int PVH_ROWS = 16;          // samples per workgroup
 constexpr int PVH_THREADS = 256;
-constexpr int PVH_HS = HID + 8;       // LDS row stride of h in bf16 (16-byte aligned rows, staggered banks)
 constexpr int PVH_DZS = 40;           // LDS row stride of dz in bf16
 
 struct PvHeadArgs {
-    const float *partial;   // fp32 [ks][B][512] partial sums of the fc GEMM
+    const float *partial;   // fp32 [ks][B][HID] partial sums of the fc GEMM
     int ks;
-    const float *bfc;       // [512]
-    const __bf16 *wh, *whl; // head weights [64][512] hi / lo in fragment order (frag_index); rows A+1.. are zero
+    const float *bfc;       // [HID]
+    const __bf16 *wh, *whl; // head weights [64][HID] hi / lo in fragment order (frag_index); rows A+1.. are zero
     const float *bh;        // [64] head bias (policy rows then the value row)
     int B, A;
     int rpb;                // samples per workgroup (1..16; 0 = 16).  Small batches spread over more
@@ -65,11 +64,11 @@ struct PvHeadArgs {
     const uint8_t *done;
     float gamma;
     float clip_eps, value_coef, entropy_coef;
-    const __bf16 *whd;      // head weights for the input gradient [512][64] (k = head row), in fragment order
+    const __bf16 *whd;      // head weights for the input gradient [HID][64] (k = head row), in fragment order
     // training outputs
-    __bf16 *h;              // [B][512] fc activations (bf16), read by the head's weight gradient
+    __bf16 *h;              // [B][HID] fc activations (bf16), read by the head's weight gradient
     __bf16 *dz;             // [B][64]
-    __bf16 *dph;            // [B][512] d(pre_fc)
+    __bf16 *dph;            // [B][HID] d(pre_fc)
     float *lossp;           // [blocks][4] partial sums {policy, value, entropy}
     float *hbp;             // [blocks][32] this block's sum of dz per head row, from the fp32 values (the bias gradient)
 };
@@ -161,8 +160,11 @@ __device__ __forceinline__ void infer_outputs(const PvHeadArgs &p, int n, bool l
     }
 }
 
-template <bool TRAIN>
+template <bool TRAIN, int HIDN>
 __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p) {
+    constexpr int PVH_HS = HIDN + 8;      // LDS row stride of h in bf16 (16-byte aligned rows, staggered banks)
+    constexpr int NJ = HIDN / 64, KS = HIDN / 128, DT = HIDN / 64;   // hidden units per lane / 4, head k-steps and dgrad tiles per wavefront
+    static_assert(HIDN % 128 == 0, "four wavefronts share the contraction in whole k-steps");
     __shared__ __attribute__((aligned(16))) __bf16 sH[PVH_ROWS * PVH_HS];
     __shared__ __attribute__((aligned(16))) __bf16 sL[PVH_ROWS * PVH_HS];
     __shared__ float sZ[4][32][PVH_ROWS];                 // per-wave partial head outputs [wave][row][sample]
@@ -179,16 +181,16 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
 
     // weight fragments and per-sample scalars do not depend on step 1: their loads go first
     const int fi = lane & 15, fg = lane >> 4;
-    bf16x8 wa[4][2], wl[4][2];
+    bf16x8 wa[KS][2], wl[KS][2];
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const size_t at = frag_base(t, HID, lane) + FRAG_STEP * (wave * 4 + s);   // fragment order (frag_index)
+            const size_t at = frag_base(t, HIDN, lane) + FRAG_STEP * (wave * KS + s);   // fragment order (frag_index)
             wa[s][t] = as_bf16x8(*reinterpret_cast<const u32x4 *>(p.wh + at));
             wl[s][t] = as_bf16x8(*reinterpret_cast<const u32x4 *>(p.whl + at));
         }
-    u32x4 wd[TRAIN ? 8 : 1];
+    u32x4 wd[TRAIN ? DT : 1];
     int a = 0;
     float ad = 0.f, rt = 0.f, olp = 0.f;
     if constexpr (TRAIN) {
@@ -208,25 +210,25 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
 
     // ---- 1. finish the fc layer for 16 samples ----
     {
-        const size_t plane = (size_t)p.B * HID;
-        const float *src = p.partial + (size_t)(live ? n : 0) * HID + c * 4;
-        float4 acc[8];
+        const size_t plane = (size_t)p.B * HIDN;
+        const float *src = p.partial + (size_t)(live ? n : 0) * HIDN + c * 4;
+        float4 acc[NJ];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int j = 0; j < NJ; ++j) acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (live) {   // rows past the batch (or past this block's share) load nothing
             // the k ranges are added in order; four ranges (32 loads), then two, then one are in flight at a time
             auto add_planes = [&](int z, auto count) __attribute__((always_inline)) {
                 constexpr int Q = decltype(count)::value;
-                float4 v[Q][8];
+                float4 v[Q][NJ];
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
+                    for (int j = 0; j < NJ; ++j)
                         v[q][j] = *reinterpret_cast<const float4 *>(src + (size_t)(z + q) * plane + 64 * j);
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
+                    for (int j = 0; j < NJ; ++j) {
                         acc[j].x += v[q][j].x; acc[j].y += v[q][j].y; acc[j].z += v[q][j].z; acc[j].w += v[q][j].w;
                     }
             };
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
             if (z < p.ks) add_planes(z, std::integral_constant<int, 1>());
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             const int col = c * 4 + 64 * j;
             const float4 b = *reinterpret_cast<const float4 *>(p.bfc + col);
             float r[4] = {fmaxf(acc[j].x + b.x, 0.f), fmaxf(acc[j].y + b.y, 0.f), fmaxf(acc[j].z + b.z, 0.f),
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
                                (__bf16)(r[2] - (float)hi[2]), (__bf16)(r[3] - (float)hi[3])};
             *reinterpret_cast<u32x2 *>(sH + srow * PVH_HS + col) = __builtin_bit_cast(u32x2, hi);
             *reinterpret_cast<u32x2 *>(sL + srow * PVH_HS + col) = __builtin_bit_cast(u32x2, lo);
-            if (TRAIN && live) *reinterpret_cast<u32x2 *>(p.h + (size_t)n * HID + col) = __builtin_bit_cast(u32x2, hi);
+            if (TRAIN && live) *reinterpret_cast<u32x2 *>(p.h + (size_t)n * HIDN + col) = __builtin_bit_cast(u32x2, hi);
         }
     }
     __syncthreads();
@@ -255,16 +257,16 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
     // sums of step 1 for the L2, and steps 2 and 3 are long enough to cover them
     if constexpr (TRAIN) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
-            wd[t] = *reinterpret_cast<const u32x4 *>(p.whd + frag_base(wave * 8 + t, 64, lane));   // fragment order
+        for (int t = 0; t < DT; ++t)
+            wd[t] = *reinterpret_cast<const u32x4 *>(p.whd + frag_base(wave * DT + t, 64, lane));   // fragment order
     }
 
-    // ---- 2. head GEMM: wave w takes k = 128 w .. 128 w + 127 for both 16-row tiles ----
+    // ---- 2. head GEMM: wave w takes the w-th quarter of k for both 16-row tiles ----
     {
         f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int at = fi * PVH_HS + (wave * 4 + s) * 32 + fg * 8;
+        for (int s = 0; s < KS; ++s) {
+            const int at = fi * PVH_HS + (wave * KS + s) * 32 + fg * 8;
             const bf16x8 hh = as_bf16x8(*reinterpret_cast<const u32x4 *>(sH + at));
             const bf16x8 hl = as_bf16x8(*reinterpret_cast<const u32x4 *>(sL + at));
 #pragma unroll
@@ -389,19 +391,19 @@ __global__ __launch_bounds__(PVH_THREADS) void pv_head_kernel(const PvHeadArgs p
             }
         }
 
-        // ---- 4. input gradient of the head: 32 tiles of 16 hidden units, 8 per wave ----
+        // ---- 4. input gradient of the head: tiles of 16 hidden units, DT per wave ----
         const bf16x8 dzf = as_bf16x8(*reinterpret_cast<const u32x4 *>(sDz + fi * PVH_DZS + fg * 8));
         const bool row_live = fi < rpb && n0 + fi < p.B;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int j0 = (wave * 8 + t) * 16;
+        for (int t = 0; t < DT; ++t) {
+            const int j0 = (wave * DT + t) * 16;
             const bf16x8 wf = as_bf16x8(wd[t]);
             f32x4 d = {0.f, 0.f, 0.f, 0.f};
             d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, dzf, d, 0, 0, 0);
             const int j = j0 + 4 * fg;
             const f32x4 hv = unpack_bf16x4(*reinterpret_cast<const u32x2 *>(sH + fi * PVH_HS + j));
             if (row_live)
-                *reinterpret_cast<u32x2 *>(p.dph + (size_t)(n0 + fi) * HID + j) =
+                *reinterpret_cast<u32x2 *>(p.dph + (size_t)(n0 + fi) * HIDN + j) =
                     pack_bf16x4(hv[0] > 0.f ? d[0] : 0.f, hv[1] > 0.f ? d[1] : 0.f, hv[2] > 0.f ? d[2] : 0.f,
                                 hv[3] > 0.f ? d[3] : 0.f);
         }

@@ -165,9 +165,10 @@ __device__ __forceinline__ void conv_wgrad_resident_body(u32x4 *lds, int block, 
         int toff[T];
 #pragma unroll
         for (int b = 0; b < T; ++b) {
-            const int k0 = (wx * TX + b) * 32, tap = k0 / CIN, ci0 = k0 - tap * CIN;
+            // the lane's four columns of the tile (with 16 channels the tile spans two taps)
+            const int k0 = (wx * TX + b) * 32 + (CIN < 32 ? col_lane / 2 : 0), tap = k0 / CIN, ci0 = k0 - tap * CIN;
             const int ky = tap / KS, kx = tap - ky * KS;
-            toff[b] = ky * RS + kx * PS + ci0 * 2 + col_lane;
+            toff[b] = ky * RS + kx * PS + ci0 * 2 + (CIN < 32 ? 0 : col_lane);
         }
         const int ycol = wy * TY * 64 + col_lane;
         auto origins = [&](int ks, int &wa, int &wb) __attribute__((always_inline)) {

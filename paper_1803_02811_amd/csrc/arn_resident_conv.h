@@ -630,10 +630,10 @@ struct ResConv2FwdGeo {
     static_assert(Geo::PAD2 > 0, "the unpadded case has a layout of its own (ResConv2Fwd)");
     static constexpr int PADH = Geo::H1 + 2 * Geo::PAD2, PADW = Geo::W1 + 2 * Geo::PAD2;
     static constexpr int EVENW = (PADW + 1) / 2;                       // pixels in the even-column plane of a row
-    static constexpr int CI = C1, SRC_PIX = Geo::P1, P = Geo::P2, CO = C2, K = KW2, G = 1, WAVES = 8;
+    static constexpr int CI = Geo::NC1, SRC_PIX = Geo::P1, P = Geo::P2, CO = Geo::NC2, K = Geo::KW2, G = 1, WAVES = 8;
     static constexpr bool SPLIT = true, ZERO_FILL = true, PIPE = false;
     static constexpr int MASK_ELEMS = 0, NBUF = 1;
-    static constexpr int PSB = C1 * 2 + 32;
+    static constexpr int PSB = CI == 16 ? 32 : CI * 2 + 32;   // 32 modulo 64 bytes
     static constexpr int pair_pixels() {
         int p = 2 * PADW;
         while (((p - Geo::W2) * PSB) % 256 != 0) ++p;
@@ -663,7 +663,7 @@ struct ResConv2FwdGeo {
                                               const uint8_t *) const {
             const float r0 = fmaxf(v[0] + b.x, 0.f), r1 = fmaxf(v[1] + b.y, 0.f), r2 = fmaxf(v[2] + b.z, 0.f),
                         r3 = fmaxf(v[3] + b.w, 0.f);
-            const size_t at = ((size_t)s * Geo::P2 + pos) * C2 + n;
+            const size_t at = ((size_t)s * Geo::P2 + pos) * CO + n;
             store_bf16x4_split(out, out_lo, at, r0, r1, r2, r3);
             if (mask_out) {
                 const int lg = (n >> 2) & 3;
@@ -752,7 +752,7 @@ struct ResConv3DgradGeo {
 
 // conv2 (4x4, stride 2, padding PAD2): d(pre2) [H2][W2][64] zero-padded by 1.  In coordinates of the padded
 // input, (y + PAD2, x + PAD2) = (2u + py, 2v + px); the four phases (py,px) share their fragments, so they are
-// the 4 x 32 channels of one 2x2 stride-1 correlation over positions (u,v); channel n = phase*32 + ci lands at
+// the 4 x NC1 channels of one 2x2 stride-1 correlation over positions (u,v); channel n = phase*NC1 + ci lands at
 // act1 pixel (2u + py - PAD2, 2v + px - PAD2) if that is inside the map.  Image description for
 // conv1_bwd_fused_body, as ResConv2Dgrad.
 template <class Geo>
@@ -760,9 +760,9 @@ struct ResConv2DgradGeo {
     static constexpr int U = ((Geo::H1 - 1 + Geo::PAD2) >> 1) + 1, V = ((Geo::W1 - 1 + Geo::PAD2) >> 1) + 1;
     static constexpr int PADH = Geo::H2 + 2, PADW = Geo::W2 + 2;
     static_assert(U <= PADH - 1 && V <= PADW - 1, "every 2x2 window lies inside the padded gradient");
-    static constexpr int CI = C2, SRC_PIX = Geo::P2, P = U * V, CO = 4 * C1, K = 4 * C2, G = 1;
+    static constexpr int CI = Geo::NC2, SRC_PIX = Geo::P2, P = U * V, CO = 4 * Geo::NC1, K = 4 * CI, G = 1;
     static constexpr bool SPLIT = false, ZERO_FILL = true;
-    static constexpr int PSB = C2 * 2 + 32;
+    static constexpr int PSB = CI * 2 + 32;
     static constexpr int ROWB = PADW * PSB + pad_to_step(PADW * PSB, V * PSB);
     static constexpr int IMG = (PADH * ROWB + 15) / 16 * 16;
     __device__ static constexpr int dst_off(int p) { return (p / Geo::W2 + 1) * ROWB + (p % Geo::W2 + 1) * PSB; }

@@ -30,57 +30,46 @@ struct MapConvFwd {    // packed [co][(ky*KS+kx)*CIN+ci]  <-  W[co][ci][ky][kx]
         return off + (((long)co * CIN + ci) * KS + ky) * KS + kx;
     }
 };
-struct MapFcFwd {      // packed [n][pos*64+c]  <-  Wfc[n][c*P3+pos]   (P3 positions after conv3, feat = 64 P3)
-    long off;
-    int feat, p3;
-    __device__ long operator()(long i) const {
-        const int n = (int)(i / feat), k = (int)(i % feat), pos = k >> 6, c = k & 63;
-        return off + (long)n * feat + c * p3 + pos;
-    }
-};
+template <int HIDN>
 struct MapHeadRow {    // head row r of the packed head -> offset of its weight row / bias, or -1 (pv: A action rows then a value row)
     long wh, wv, bh, bv;
     int A, NH, pv;
     __device__ long wrow(int r) const {
-        if (pv) return r < A ? wh + (long)r * HID : (r == A ? wv : -1);
-        return r < NH ? wh + (long)r * HID : -1;
+        if (pv) return r < A ? wh + (long)r * HIDN : (r == A ? wv : -1);
+        return r < NH ? wh + (long)r * HIDN : -1;
     }
     __device__ long brow(int r) const {
         if (pv) return r < A ? bh + r : (r == A ? bv : -1);
         return r < NH ? bh + r : -1;
     }
 };
-inline MapHeadRow head_rows(const Dims &d, const ParamOffsets &po) {
-    MapHeadRow h;
+template <int HIDN>
+inline MapHeadRow<HIDN> head_rows(const Dims &d, const ParamOffsets &po) {
+    MapHeadRow<HIDN> h;
     h.wh = (long)po.wh; h.wv = (long)po.wv; h.bh = (long)po.bh; h.bv = (long)po.bv;
     h.A = d.A; h.NH = d.NH; h.pv = d.vrow;
     return h;
 }
+template <int HIDN>
 struct MapHeadFwd {    // packed [r][j]
-    MapHeadRow h;
+    MapHeadRow<HIDN> h;
     __device__ long operator()(long i) const {
-        const long b = h.wrow((int)(i / HID));
-        return b < 0 ? -1 : b + i % HID;
+        const long b = h.wrow((int)(i / HIDN));
+        return b < 0 ? -1 : b + i % HIDN;
     }
 };
+template <int HIDN>
 struct MapHeadBias {
-    MapHeadRow h;
+    MapHeadRow<HIDN> h;
     __device__ long operator()(long i) const { return h.brow((int)i); }
 };
+template <int HIDN>
 struct MapHeadDgrad {  // packed [j][r]  (NHP columns)
-    MapHeadRow h;
+    MapHeadRow<HIDN> h;
     int NHP;
     __device__ long operator()(long i) const {
         const long b = h.wrow((int)(i % NHP));
         return b < 0 ? -1 : b + i / NHP;
-    }
-};
-struct MapFcDgrad {    // packed [pos*64+c][n]  <-  Wfc[n][c*P3+pos]
-    long off;
-    int feat, p3;
-    __device__ long operator()(long i) const {
-        const int k = (int)(i / HID), n = (int)(i % HID), pos = k >> 6, c = k & 63;
-        return off + (long)n * feat + c * p3 + pos;
     }
 };
 struct MapConv3Dgrad { // packed [ci][(ty*3+tx)*64+co]  <-  W3[co][ci][2-ty][2-tx]
@@ -90,13 +79,14 @@ struct MapConv3Dgrad { // packed [ci][(ty*3+tx)*64+co]  <-  W3[co][ci][2-ty][2-t
         return off + (((long)co * C2 + ci) * K3 + (2 - ty)) * K3 + (2 - tx);
     }
 };
-struct MapConv2Dgrad { // packed [z][ci][(ty*2+tx)*64+co]  <-  W2[co][ci][py+2(1-ty)][px+2(1-tx)]
+template <int CIN, int COUT>
+struct MapConv2Dgrad { // packed [z][ci][(ty*2+tx)*COUT+co]  <-  W2[co][ci][py+2(1-ty)][px+2(1-tx)]
     long off;
     __device__ long operator()(long i) const {
-        const int z = (int)(i / (C1 * 256)), rem = (int)(i % (C1 * 256));
-        const int ci = rem / 256, k = rem % 256, tap = k >> 6, co = k & 63, ty = tap >> 1, tx = tap & 1;
+        const int z = (int)(i / (CIN * 4 * COUT)), rem = (int)(i % (CIN * 4 * COUT));
+        const int ci = rem / (4 * COUT), k = rem % (4 * COUT), tap = k / COUT, co = k % COUT, ty = tap >> 1, tx = tap & 1;
         const int ky = (z >> 1) + 2 * (1 - ty), kx = (z & 1) + 2 * (1 - tx);
-        return off + (((long)co * C1 + ci) * K2 + ky) * K2 + kx;
+        return off + (((long)co * CIN + ci) * K2 + ky) * K2 + kx;
     }
 };
 
@@ -152,25 +142,25 @@ __device__ __forceinline__ void reduce_partials(float *red, int b, const ReduceP
         dW[dst] = i < r.wcount ? t * r.wscale : t;
     }
 }
-// The fc layer's partials are [n][pos*64 + c] while the canonical weight is [n][c*P3 + pos]: one workgroup
+// The fc layer's partials are [n][pos*NC + c] while the canonical weight is [n][c*P + pos]: one workgroup
 // per output row n adds the splits with contiguous reads, permutes the row in LDS (stride 49 words at
-// 84x84: no bank conflicts) and writes it out contiguously.  Workgroup HID handles the bias gradient.
-template <int FEAT, int P3>
+// 84x84: no bank conflicts) and writes it out contiguously.  Workgroup HIDN handles the bias gradient.
+template <int FEAT, int P, int HIDN>
 __device__ __forceinline__ void fc_reduce(float *row, int n, const float *__restrict__ part, float *__restrict__ dW, long woff,
                                           long boff, int splits) {
-    constexpr long block = (long)HID * FEAT + HID;
+    constexpr long block = (long)HIDN * FEAT + HIDN;
     const int tid = threadIdx.x;
-    if (n == HID) {
-        for (int j = tid; j < HID; j += 256) {
+    if (n == HIDN) {
+        for (int j = tid; j < HIDN; j += 256) {
             float s = 0.f;
-            for (int k = 0; k < splits; ++k) s += part[(size_t)k * block + (long)HID * FEAT + j];
+            for (int k = 0; k < splits; ++k) s += part[(size_t)k * block + (long)HIDN * FEAT + j];
             dW[boff + j] = s;
         }
         return;
     }
     // four consecutive k per thread and pass (same position, channels c .. c+3); all loads of a split are issued
     // before the first is added, and the splits are added in order
-    static_assert(FEAT % 4 == 0 && ((long)HID * FEAT + HID) % 4 == 0, "16-byte loads of the partials");
+    static_assert(FEAT % 4 == 0 && ((long)HIDN * FEAT + HIDN) % 4 == 0, "16-byte loads of the partials");
     constexpr int NV = (FEAT / 4 + 255) / 256;
     float4 acc[NV];
 #pragma unroll
@@ -190,8 +180,9 @@ __device__ __forceinline__ void fc_reduce(float *row, int n, const float *__rest
     for (int j = 0; j < NV; ++j) {
         const int k = 4 * (tid + 256 * j);
         if (k < FEAT) {
-            const int at = (k & 63) * P3 + (k >> 6);
-            row[at] = acc[j].x; row[at + P3] = acc[j].y; row[at + 2 * P3] = acc[j].z; row[at + 3 * P3] = acc[j].w;
+            constexpr int NC = FEAT / P;
+            const int at = k % NC * P + k / NC;
+            row[at] = acc[j].x; row[at + P] = acc[j].y; row[at + 2 * P] = acc[j].z; row[at + 3 * P] = acc[j].w;
         }
     }
     __syncthreads();
@@ -209,44 +200,50 @@ struct UnmapConv {     // partial [co][(ky*KS+kx)*CIN+ci] then [co] bias
         return woff + (((long)co * CIN + ci) * KS + ky) * KS + kx;
     }
 };
+template <int COUT>
 struct UnmapConv1 {
     long woff, boff;
-    __device__ long operator()(long i) const { return i >= C1 * KW1 ? boff + (i - C1 * KW1) : woff + i; }
+    __device__ long operator()(long i) const { return i >= COUT * KW1 ? boff + (i - COUT * KW1) : woff + i; }
 };
+template <int HIDN>
 struct UnmapHeadBias {   // index = head row -> its bias entry in the flat gradient (or -1)
-    MapHeadRow h;
+    MapHeadRow<HIDN> h;
     __device__ long operator()(long i) const { return h.brow((int)i); }
 };
+template <int HIDN>
 struct UnmapHead {       // the weight-gradient GEMM's partial block; its bias sums (of bf16 values) are not used
-    MapHeadRow h;
+    MapHeadRow<HIDN> h;
     int NHP;
     __device__ long operator()(long i) const {
-        if (i >= (long)NHP * HID) return -1;
-        const long b = h.wrow((int)(i / HID));
-        return b < 0 ? -1 : b + i % HID;
+        if (i >= (long)NHP * HIDN) return -1;
+        const long b = h.wrow((int)(i / HIDN));
+        return b < 0 ? -1 : b + i % HIDN;
     }
 };
 
 // Every weight-gradient partial of the gradient step, in one launch: ranges of workgroups, one per layer.
+template <class G>
 struct ReduceAllPlan {
-    ReducePartials<UnmapConv1> conv1;
-    ReducePartials<UnmapConv<C1, K2, C2>> conv2;
-    ReducePartials<UnmapConv<C2, K3, C3>> conv3;
-    ReducePartials<UnmapHead> head;
-    ReducePartials<UnmapHeadBias> head_bias;
-    int n1, n2, n3, nh;       // workgroups of conv1, conv2, conv3, head; the fc layer has HID + 1, the head's bias the rest
+    ReducePartials<UnmapConv1<G::NC1>> conv1;
+    ReducePartials<UnmapConv<G::NC1, K2, G::NC2>> conv2;
+    ReducePartials<UnmapConv<C2, K3, C3>> conv3;      // networks with a third convolution
+    ReducePartials<UnmapHead<G::NHID>> head;
+    ReducePartials<UnmapHeadBias<G::NHID>> head_bias;
+    int n1, n2, n3, nh;       // workgroups of conv1, conv2, conv3, head; the fc layer has NHID + 1, the head's bias the rest
     const float *fc_part;
     long fc_w, fc_b;
     int fc_splits;
 };
-template <int FEAT, int P3>
-__global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceAllPlan pl, float *__restrict__ dW) {
-    __shared__ float scratch[FEAT > 256 ? FEAT : 256];
+template <class G>
+__global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceAllPlan<G> pl, float *__restrict__ dW) {
+    __shared__ float scratch[G::FEAT > 256 ? G::FEAT : 256];
     int b = blockIdx.x;
-    if (b < HID + 1) { fc_reduce<FEAT, P3>(scratch, b, pl.fc_part, dW, pl.fc_w, pl.fc_b, pl.fc_splits); return; }
-    b -= HID + 1;
-    if (b < pl.n3) { reduce_partials(scratch, b, pl.conv3, dW); return; }
-    b -= pl.n3;
+    if (b < G::NHID + 1) { fc_reduce<G::FEAT, G::PL, G::NHID>(scratch, b, pl.fc_part, dW, pl.fc_w, pl.fc_b, pl.fc_splits); return; }
+    b -= G::NHID + 1;
+    if constexpr (G::HAS3) {
+        if (b < pl.n3) { reduce_partials(scratch, b, pl.conv3, dW); return; }
+        b -= pl.n3;
+    }
     if (b < pl.n2) { reduce_partials(scratch, b, pl.conv2, dW); return; }
     b -= pl.n2;
     if (b < pl.n1) { reduce_partials(scratch, b, pl.conv1, dW); return; }
@@ -258,7 +255,7 @@ __global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceAllPlan pl,
 // h = relu(sum_z partial[z] + bias), written as bf16 hi (and lo = residual) -- the
 // second half of the split-k fc layer.  One thread per four outputs.
 __global__ void fc_finish_kernel(const float *__restrict__ partial, int ksplit, const float *__restrict__ bias,
-                                 __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, long total) {
+                                 __bf16 *__restrict__ out, __bf16 *__restrict__ out_lo, int hid, long total) {
     const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i >= total) return;
     float4 s = *reinterpret_cast<const float4 *>(partial + i);
@@ -266,7 +263,7 @@ __global__ void fc_finish_kernel(const float *__restrict__ partial, int ksplit, 
         const float4 v = *reinterpret_cast<const float4 *>(partial + (size_t)z * total + i);
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
-    const float4 b = *reinterpret_cast<const float4 *>(bias + (i & (HID - 1)));
+    const float4 b = *reinterpret_cast<const float4 *>(bias + (i & (hid - 1)));
     const float r0 = fmaxf(s.x + b.x, 0.f), r1 = fmaxf(s.y + b.y, 0.f), r2 = fmaxf(s.z + b.z, 0.f),
                 r3 = fmaxf(s.w + b.w, 0.f);
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));

@@ -151,73 +151,73 @@ constexpr int PACK_FC_MAX_P3 = 108;   // 12 x 9 positions after conv3 on 104 x 8
 // LDS row: 8 modulo 64 words, so that eight rows x eight neighbouring positions are 64 different banks
 constexpr int PACK_FC_LDS_ROW = PACK_FC_CH * PACK_FC_MAX_P3 + 8;
 static_assert(P3 <= PACK_FC_MAX_P3 && GeoPaper::P3 <= PACK_FC_MAX_P3, "fc tile buffer");
-static_assert(HID % PACK_FC_ROWS == 0 && C3 % PACK_FC_CH == 0 && PACK_FC_CH == 8 && PACK_FC_ROWS % 8 == 0, "fc tile shape");
+static_assert(PACK_FC_CH == 8 && PACK_FC_ROWS % 8 == 0, "fc tile shape");
+template <class G>
 struct PackPlan {
     PackSeg seg[PK_COUNT];
     int fc_first_block;                      // blocks from here on are fc tiles
     __bf16 *fc_hi, *fc_lo, *fc_dgrad;
     _Float16 *fc_f16;
     long w1, w2, w3, wfc, b1, b2, b3, bfc;   // offsets in the flat vector
-    MapHeadRow hr;
+    MapHeadRow<G::NHID> hr;
     int NHP;
-    int small_head; // the head's matrices are read by pv_head_kernel as register fragments: fragment order
-    int feat, p3;   // fc inputs and positions after conv3
+    int small_head; // the head's matrices are read by the small heads' kernels as register fragments: fragment order
     int blocks;
 };
 
-inline PackPlan make_pack_plan(const Dims &d, void *w_packed) {
+template <class G>
+inline PackPlan<G> make_pack_plan(const Dims &d, void *w_packed) {
     const ParamOffsets po = param_offsets(d);
     const PackedOffsets o = packed_offsets(d);
     char *b = (char *)w_packed;
-    PackPlan pl;
+    PackPlan<G> pl;
     pl.w1 = (long)po.w1; pl.w2 = (long)po.w2; pl.w3 = (long)po.w3; pl.wfc = (long)po.wfc;
     pl.b1 = (long)po.b1; pl.b2 = (long)po.b2; pl.b3 = (long)po.b3; pl.bfc = (long)po.bfc;
-    pl.hr = head_rows(d, po);
+    pl.hr = head_rows<G::NHID>(d, po);
     pl.NHP = d.NHP;
     pl.small_head = d.small ? 1 : 0;
-    pl.feat = d.feat;
-    pl.p3 = d.p3;
     auto set = [&](int k, long n, size_t out, size_t lo, bool has_lo) {
         pl.seg[k].n = n;
         pl.seg[k].out = b + out;
         pl.seg[k].out_lo = has_lo ? b + lo : nullptr;
         pl.seg[k].out_f16 = nullptr;
     };
-    set(PK_W1, (long)C1 * KW1, o.w1, o.w1l, true);
-    set(PK_W2, (long)C2 * KW2, o.w2, o.w2l, true);
-    set(PK_W3, (long)C3 * KW3, o.w3, o.w3l, true);
+    set(PK_W1, (long)G::NC1 * KW1, o.w1, o.w1l, true);
+    set(PK_W2, (long)G::NC2 * G::KW2, o.w2, o.w2l, true);
+    set(PK_W3, (long)d.c3 * KW3, o.w3, o.w3l, true);
     set(PK_WFC, 0, o.wfc, o.wfcl, true);          // by tile blocks, below
-    set(PK_WH, (long)d.NHP * HID, o.wh, o.whl, true);
-    set(PK_B1, C1, o.b1, 0, false);
-    set(PK_B2, C2, o.b2, 0, false);
-    set(PK_B3, C3, o.b3, 0, false);
-    set(PK_BFC, HID, o.bfc, 0, false);
+    set(PK_WH, (long)d.NHP * G::NHID, o.wh, o.whl, true);
+    set(PK_B1, G::NC1, o.b1, 0, false);
+    set(PK_B2, G::NC2, o.b2, 0, false);
+    set(PK_B3, d.c3, o.b3, 0, false);
+    set(PK_BFC, G::NHID, o.bfc, 0, false);
     set(PK_BH, d.NHP, o.bh, 0, false);
-    set(PK_WHD, (long)HID * d.NHP, o.whd, 0, false);
+    set(PK_WHD, (long)G::NHID * d.NHP, o.whd, 0, false);
     set(PK_WFCD, 0, o.wfcd, 0, false);            // by tile blocks, below
     pl.seg[PK_W1].out_f16 = b + o.w1h; pl.seg[PK_W2].out_f16 = b + o.w2h; pl.seg[PK_W3].out_f16 = b + o.w3h;
     pl.fc_hi = (__bf16 *)(b + o.wfc); pl.fc_lo = (__bf16 *)(b + o.wfcl); pl.fc_dgrad = (__bf16 *)(b + o.wfcd);
     pl.fc_f16 = (_Float16 *)(b + o.wfch);
-    set(PK_W3D, (long)C2 * KW3, o.w3d, 0, false);
-    set(PK_W2D, (long)4 * C1 * 256, o.w2d, 0, false);
+    set(PK_W3D, (long)d.c3 * KW3, o.w3d, 0, false);
+    set(PK_W2D, (long)4 * G::NC1 * 4 * G::NC2, o.w2d, 0, false);
     int blk = 0;
     for (int k = 0; k < PK_COUNT; ++k) {
         pl.seg[k].first_block = blk;
         blk += (int)((pl.seg[k].n + 255) / 256);
     }
     pl.fc_first_block = blk;
-    pl.blocks = blk + (HID / PACK_FC_ROWS) * (C3 / PACK_FC_CH);
+    pl.blocks = blk + (G::NHID / PACK_FC_ROWS) * (G::NCL / PACK_FC_CH);
     return pl;
 }
 
-// One fc tile: hidden units n0 .. n0 + PACK_FC_ROWS - 1, conv3 channels c0 .. c0 + PACK_FC_CH - 1.
-// Flat order Wfc[n][c * P3 + pos]; forward layout [n][pos * 64 + c]; input-gradient layout [pos * 64 + c][n].
-template <int P3_>
-__device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__restrict__ w, int tile,
+// One fc tile: hidden units n0 .. n0 + PACK_FC_ROWS - 1, channels c0 .. c0 + PACK_FC_CH - 1.
+// Flat order Wfc[n][c * P + pos]; forward layout [n][pos * NC + c]; input-gradient layout [pos * NC + c][n].
+template <class G>
+__device__ __forceinline__ void pack_fc_tile(const PackPlan<G> &pl, const float *__restrict__ w, int tile,
                                              float (&s_t)[PACK_FC_ROWS][PACK_FC_LDS_ROW]) {
-    constexpr int p3 = P3_, feat = C3 * P3_, run = PACK_FC_CH * p3;
+    constexpr int p3 = G::PL, NC = G::NCL, feat = G::FEAT, run = PACK_FC_CH * p3;
+    static_assert(G::NHID % PACK_FC_ROWS == 0 && NC % PACK_FC_CH == 0 && p3 <= PACK_FC_MAX_P3, "fc tile shape");
     constexpr int NL = (PACK_FC_ROWS * run + 255) / 256;
-    const int n0 = (tile / (C3 / PACK_FC_CH)) * PACK_FC_ROWS, c0 = (tile % (C3 / PACK_FC_CH)) * PACK_FC_CH;
+    const int n0 = (tile / (NC / PACK_FC_CH)) * PACK_FC_ROWS, c0 = (tile % (NC / PACK_FC_CH)) * PACK_FC_CH;
     const int tid = threadIdx.x;
     float v_in[NL];   // all loads of the tile in flight before the first is used
 #pragma unroll
@@ -248,7 +248,7 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__
             lo[c] = (__bf16)(v[c] - (float)hi[c]);
             hf[c] = to_f16_finite(v[c]);
         }
-        const size_t at = (size_t)frag_index(n0 + r, (long)pos * C3 + c0, feat);
+        const size_t at = (size_t)frag_index(n0 + r, (long)pos * NC + c0, feat);
         *reinterpret_cast<bf16x8 *>(pl.fc_hi + at) = hi;
         *reinterpret_cast<bf16x8 *>(pl.fc_lo + at) = lo;
         *reinterpret_cast<f16x8 *>(pl.fc_f16 + at) = hf;
@@ -259,39 +259,16 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan &pl, const float *__
         bf16x8 hi;
 #pragma unroll
         for (int r = 0; r < 8; ++r) hi[r] = (__bf16)s_t[8 * h + r][e];
-        *reinterpret_cast<bf16x8 *>(pl.fc_dgrad + ((size_t)pos * C3 + c0 + c) * HID + n0 + 8 * h) = hi;
+        *reinterpret_cast<bf16x8 *>(pl.fc_dgrad + ((size_t)pos * NC + c0 + c) * G::NHID + n0 + 8 * h) = hi;
     }
 }
 
-// ---- the 2-convolution network inside the three-convolution one (A3cMap, arn_layout.h) ----
-// fill: zeros everywhere, ones on conv3's identity taps W3[c][c][1][1]
-__global__ __launch_bounds__(256) void a3c_fill_kernel(float *__restrict__ big, long total, long w3) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= total) return;
-    float v = 0.f;
-    const long j = i - w3;
-    if (j >= 0 && j < (long)C3 * KW3) {
-        const long co = j / KW3, r = j % KW3, ci = r / (K3 * K3), t = r % (K3 * K3);
-        v = (co == ci && t == (K3 * K3) / 2) ? 1.f : 0.f;
-    }
-    big[i] = v;
-}
-// scatter the small network's parameters into the embedding vector / gather its gradient out of it
-__global__ __launch_bounds__(256) void a3c_scatter_kernel(A3cMap m, const float *__restrict__ small, float *__restrict__ big) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i < m.total) big[m(i)] = small[i];
-}
-__global__ __launch_bounds__(256) void a3c_gather_kernel(A3cMap m, const float *__restrict__ big, float *__restrict__ small) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i < m.total) small[i] = big[m(i)];
-}
-
-__global__ __launch_bounds__(256) void pack_all_kernel(PackPlan pl, const float *__restrict__ w) {
+template <class G>
+__global__ __launch_bounds__(256) void pack_all_kernel(const PackPlan<G> pl, const float *__restrict__ w) {
     if ((int)blockIdx.x >= pl.fc_first_block) {
         __shared__ float s_t[PACK_FC_ROWS][PACK_FC_LDS_ROW];
         const int tile = (int)blockIdx.x - pl.fc_first_block;
-        if (pl.p3 == P3) pack_fc_tile<P3>(pl, w, tile, s_t);
-        else pack_fc_tile<GeoPaper::P3>(pl, w, tile, s_t);
+        pack_fc_tile<G>(pl, w, tile, s_t);
         return;
     }
     int k = 0;
@@ -309,19 +286,17 @@ __global__ __launch_bounds__(256) void pack_all_kernel(PackPlan pl, const float 
     long s;
     switch (k) {
     case PK_W1: s = pl.w1 + i; break;
-    case PK_W2: s = MapConvFwd<C1, K2>{pl.w2}(i); break;
+    case PK_W2: s = MapConvFwd<G::NC1, K2>{pl.w2}(i); break;
     case PK_W3: s = MapConvFwd<C2, K3>{pl.w3}(i); break;
-    case PK_WFC: s = MapFcFwd{pl.wfc, pl.feat, pl.p3}(i); break;
-    case PK_WH: s = MapHeadFwd{pl.hr}(i); break;
+    case PK_WH: s = MapHeadFwd<G::NHID>{pl.hr}(i); break;
     case PK_B1: s = pl.b1 + i; break;
     case PK_B2: s = pl.b2 + i; break;
     case PK_B3: s = pl.b3 + i; break;
     case PK_BFC: s = pl.bfc + i; break;
-    case PK_BH: s = MapHeadBias{pl.hr}(i); break;
-    case PK_WHD: s = MapHeadDgrad{pl.hr, pl.NHP}(i); break;
-    case PK_WFCD: s = MapFcDgrad{pl.wfc, pl.feat, pl.p3}(i); break;
+    case PK_BH: s = MapHeadBias<G::NHID>{pl.hr}(i); break;
+    case PK_WHD: s = MapHeadDgrad<G::NHID>{pl.hr, pl.NHP}(i); break;
     case PK_W3D: s = MapConv3Dgrad{pl.w3}(i); break;
-    default: s = MapConv2Dgrad{pl.w2}(i); break;
+    default: s = MapConv2Dgrad<G::NC1, G::NC2>{pl.w2}(i); break;
     }
     const float v = s >= 0 ? w[s] : 0.f;
     if (k >= PK_B1 && k <= PK_BH) {
@@ -330,10 +305,10 @@ __global__ __launch_bounds__(256) void pack_all_kernel(PackPlan pl, const float 
         // the convolution weights live in registers as MFMA fragments: packed in fragment order (frag_index)
         long o = i;
         if (k == PK_W1) o = frag_index(i / KW1, i % KW1, KW1);
-        else if (k == PK_W2) o = frag_index(i / KW2, i % KW2, KW2);
+        else if (k == PK_W2) o = frag_index(i / G::KW2, i % G::KW2, G::KW2);
         else if (k == PK_W3 || k == PK_W3D) o = frag_index(i / KW3, i % KW3, KW3);
-        else if (k == PK_W2D) o = frag_index(i / 256, i % 256, 256);
-        else if (k == PK_WH && pl.small_head) o = frag_index(i / HID, i % HID, HID);
+        else if (k == PK_W2D) o = frag_index(i / (4 * G::NC2), i % (4 * G::NC2), 4 * G::NC2);
+        else if (k == PK_WH && pl.small_head) o = frag_index(i / G::NHID, i % G::NHID, G::NHID);
         else if (k == PK_WHD && pl.small_head) o = frag_index(i / 64, i % 64, 64);
         const __bf16 hi = (__bf16)v;
         ((__bf16 *)out)[o] = hi;

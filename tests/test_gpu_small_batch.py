@@ -7,7 +7,12 @@ import workloads as wl
 from oracle import nature_cnn as orc
 
 pytestmark = pytest.mark.gpu
-NETS = {"84": (wl.FRAME, {}), "paper": (wl.PAPER_FRAME, {"geometry": orc.PAPER_104x80})}
+NETS = {"84": (wl.FRAME, {}), "paper": (wl.PAPER_FRAME, {"geometry": orc.PAPER_104x80}),
+        "a3c": (wl.PAPER_FRAME, {"geometry": orc.A3C_104x80})}
+
+
+def shape_of(geometry):
+    return dict(net="a3c") if geometry == "a3c" else dict(fc_inputs=wl.FC_INPUTS[NETS[geometry][0]])
 
 
 @pytest.fixture(scope="module")
@@ -21,11 +26,13 @@ def gu():
 @pytest.mark.parametrize("geometry,head,sizes", [
     ("84", "pv", (17, 32, 36, 37, 63, 65, 127, 128, 129, 255, 257, 511, 512, 513)),
     ("84", "c51", (33, 129, 513)),
-    ("paper", "duel", (21, 22, 65, 86, 128, 129, 257, 361, 362))])
+    ("paper", "duel", (21, 22, 65, 86, 128, 129, 257, 361, 362)),
+    ("a3c", "pv", (21, 22, 33, 64, 127, 128, 129, 256, 257, 512, 513)),
+    ("a3c", "c51", (40, 513))])
 def test_forward_at_dispatch_edges(gu, geometry, head, sizes):
     A = 7
     frame, kw = NETS[geometry]
-    flat = wl.he_normal_params(A, head, 2602, bias_std=0.1, fc_inputs=wl.FC_INPUTS[frame])
+    flat = wl.he_normal_params(A, head, 2602, bias_std=0.1, **shape_of(geometry))
     spec = orc.NetSpec(A, head, **kw)
     obs = wl.rect_frames(max(sizes), 1602, frame=frame)
     ref = orc.forward(orc.unflatten(flat, spec), obs, spec)
@@ -37,15 +44,15 @@ def test_forward_at_dispatch_edges(gu, geometry, head, sizes):
         gu.tol_check(got, want[:B].reshape(got.shape), "B=%d" % B)
 
 
-@pytest.mark.parametrize("geometry,B", [("84", 129), ("84", 398), ("84", 399), ("paper", 65), ("paper", 180), ("paper", 181)])
+@pytest.mark.parametrize("geometry,B", [("84", 129), ("84", 398), ("84", 399), ("paper", 65), ("paper", 180), ("paper", 181),
+                                        ("a3c", 21), ("a3c", 128), ("a3c", 129), ("a3c", 361), ("a3c", 362)])
 def test_gradients_at_dispatch_edges(gu, geometry, B):
     A = 7
     frame, kw = NETS[geometry]
-    fc_in = wl.FC_INPUTS[frame]
-    flat = wl.he_normal_params(A, "pv", 2603, bias_std=0.1, fc_inputs=fc_in)
+    flat = wl.he_normal_params(A, "pv", 2603, bias_std=0.1, **shape_of(geometry))
     batch = wl.actor_critic_batch(3, B=B, frame=frame)
     batch["action"] %= A
     ref = orc.train_step_grads(flat, batch, "a2c", orc.NetSpec(A, "pv", **kw))
     dW, _ = gu.GpuNet(A, "pv", flat, geometry=geometry).train(batch, "a2c")
-    gu.check_grads(gu.per_tensor(dW, A, "pv", fc_inputs=fc_in), gu.per_tensor(ref["flat"], A, "pv", fc_inputs=fc_in),
-                   "%s B=%d" % (geometry, B))
+    got, want = (wl.split_params(v, A, "pv", **shape_of(geometry)) for v in (dW, ref["flat"]))
+    gu.check_grads(got, want, "%s B=%d" % (geometry, B))
