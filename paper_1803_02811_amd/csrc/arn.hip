@@ -452,10 +452,8 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
         p.obs = obs; p.dp2 = G::HAS3 ? dp2 : dp3; p.w2d = w.w2d; p.mask1 = (const uint8_t *)(ws + o.m1); p.part1 = part1;
         p.a1 = a1; p.a2 = a2; p.dp3 = dp3; p.part2 = part2; p.part3 = part3;
         p.B = B; p.n1 = sp.c1; p.n2 = sp.c2;
-        p.spw1 = resident_spw(B, 256);
-        constexpr int g2 = Conv2WgradG<G>::value;
-        p.spw2 = resident_spw((B + g2 - 1) / g2, wgrad_wgs2(d.geom)) * g2;
-        p.spw3 = resident_spw((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom)) * CONV3_WG_G;
+        const ConvBwdSplit cs = conv_bwd_split(d, B);
+        p.spw1 = cs.spw1; p.spw2 = cs.spw2; p.spw3 = cs.spw3;
         hipLaunchKernelGGL((conv_backward_kernel<G, typename Cfg::Dgrad2>), dim3(sp.c1 + sp.c2 + sp.c3),
                            dim3(ConvBackward<G, typename Cfg::Dgrad2>::THREADS), 0, s, p);
     }

@@ -3,9 +3,8 @@
 // Once conv3's input gradient has produced d(pre2), three pieces of work are independent of each other: conv2's
 // input gradient with conv1's weight gradient (conv1_bwd_fused_body), conv2's weight gradient and conv3's weight
 // gradient (conv_wgrad_resident_body).  Each wants one 512-thread workgroup per CU at a time, so as separate
-// kernels they ran one after the other, each with its own ramp-up and drain; here they are three ranges of
-// workgroups of one grid, longest first, and a CU picks up a workgroup of the next range as soon as its
-// workgroup of the previous one is done.  The LDS buffer is shared (sized for the largest of the three).
+// kernels they ran one after the other, each with its own ramp-up and drain; here they are ranges of workgroups of
+// one grid that runs in one round (conv_bwd_split).  The LDS buffer is shared (sized for the largest of the three).
 #pragma once
 #include "arn_conv1_bwd.h"
 #include "arn_resident.h"

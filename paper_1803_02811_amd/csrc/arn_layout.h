@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/arn.h"
 
 namespace arn {
@@ -180,13 +182,6 @@ inline int pick_split(long rows, int tiles, int target_wgs) {
     if (s > iters) s = iters;
     return (int)s;
 }
-// workgroups of the conv2 / conv3 weight gradients: each writes a full fp32 partial of dW, so fewer workgroups
-// mean less partial traffic (and a cheaper reduction).  The two are ranges of one grid (conv_backward_kernel) and
-// run side by side, one per CU, so together they fill the 256 CUs; the split follows the measured time per sample
-// of the two (84x84 network: conv2's 81 positions x 512 columns against conv3's 49 x 576), so that both ranges
-// finish together.
-inline int wgrad_wgs2(int geom) { return geom == ARN_GEOM_84 ? 148 : 128; }
-inline int wgrad_wgs3(int geom) { return 256 - wgrad_wgs2(geom); }
 constexpr int CONV3_WG_G = 4;   // samples staged per iteration by the conv3 weight-gradient kernel
 template <class G>
 struct Conv2WgradG {            // ... and by conv2's
@@ -199,12 +194,36 @@ inline int resident_groups(int B, int target_wgs) {
     const int spw = resident_spw(B, target_wgs);
     return (B + spw - 1) / spw;
 }
+// The convolutions' backward (conv_backward_kernel): ranges of workgroups, one workgroup per CU, that share the 256 CUs in
+// one round.  A range's workgroup count follows its measured time per sample (relative to the others), so that all finish
+// together; every workgroup has a prologue of about 3 us and writes a full fp32 partial, so one round of longer workgroups
+// also means less of both.  (256 workgroups for the first range and 256 for the others, in two rounds, took 61 + 14.5 us
+// with the sums at 2048 samples and 84x84 frames, this 56.5 + 11; 104x80 frames: 122 against 75 us.)
+struct ConvBwdCost { float c1, c2, c3; };   // conv2 input gradient with conv1 weight gradient, conv2's, conv3's weight gradient
+inline ConvBwdCost conv_bwd_cost(int geom) {
+    if (geom == ARN_GEOM_84) return {3.2f, 1.5f, 1.25f};
+    if (geom == ARN_GEOM_PAPER) return {3.f, 1.5f, 1.5f};
+    return {3.5f, 1.f, 0.f};
+}
+struct ConvBwdSplit { int spw1, spw2, spw3; };   // samples per workgroup
+inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
+    const ConvBwdCost c = conv_bwd_cost(d.geom);
+    const int g2 = conv2_wg_g(d), g3 = CONV3_WG_G;
+    ConvBwdSplit s;
+    for (double t = (double)B * (c.c1 + c.c2 + c.c3) / 256;; t *= 1.01) {
+        auto per = [&](double cost, int g) { const int n = (int)(t / (cost * g)); return (n < 1 ? 1 : n) * g; };
+        s.spw1 = per(c.c1, 1);
+        s.spw2 = per(c.c2, g2);
+        s.spw3 = d.c3 ? per(c.c3, g3) : 1 << 30;
+        if ((B + s.spw1 - 1) / s.spw1 + (B + s.spw2 - 1) / s.spw2 + (d.c3 ? (B + s.spw3 - 1) / s.spw3 : 0) <= 256) return s;
+    }
+}
 inline Splits make_splits(const Dims &d, int B) {
     Splits s;
-    const int g2 = conv2_wg_g(d);
-    s.c1 = resident_groups(B, 256);
-    s.c2 = resident_groups((B + g2 - 1) / g2, wgrad_wgs2(d.geom));
-    s.c3 = d.c3 ? resident_groups((B + CONV3_WG_G - 1) / CONV3_WG_G, wgrad_wgs3(d.geom)) : 0;
+    const ConvBwdSplit cs = conv_bwd_split(d, B);
+    s.c1 = (B + cs.spw1 - 1) / cs.spw1;
+    s.c2 = (B + cs.spw2 - 1) / cs.spw2;
+    s.c3 = d.c3 ? (B + cs.spw3 - 1) / cs.spw3 : 0;
     // the dense layers' weight-gradient GEMMs are cut along the batch so that about 400 to 500 workgroups exist
     s.fc = pick_split(B, (d.feat / 64) * (d.hid / 128), d.geom == ARN_GEOM_84 ? 392 : 512);
     s.hd = pick_split(B, (d.hid / 128) * (d.NHP / 64), 256);
@@ -336,12 +355,13 @@ inline Dims embedding_dims(Dims d) {
 inline size_t reported_packed_bytes(const Dims &d) {
     if (d.geom != ARN_GEOM_A3C) return packed_offsets(d).total;
     const Dims e = embedding_dims(d);
-    return packed_offsets(e).total + align_up(param_offsets(e).total * 4, 256);
+    return std::max(packed_offsets(d).total, packed_offsets(e).total + align_up(param_offsets(e).total * 4, 256));
 }
 inline size_t reported_workspace_bytes(const Dims &d, int B, int mode) {
     if (d.geom != ARN_GEOM_A3C) return make_workspace(d, B, mode).total;
     const Dims e = embedding_dims(d);
-    return make_workspace(e, B, mode).total + (mode == ARN_MODE_TRAIN ? align_up(param_offsets(e).total * 4, 256) : 0);
+    return std::max(make_workspace(d, B, mode).total,
+                    make_workspace(e, B, mode).total + (mode == ARN_MODE_TRAIN ? align_up(param_offsets(e).total * 4, 256) : 0));
 }
 
 }  // namespace arn
