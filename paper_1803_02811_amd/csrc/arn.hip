@@ -93,15 +93,10 @@ void *static_scratch_ptr() {
     return per_dev[dev];
 }
 
-template <class P>
-void launch_nt(const char *name, const P &p, long M, int n_tiles, int z, hipStream_t s) {
+template <bool SPLIT, class P>
+void launch_nt(const char *name, const P &p, int N, int z, hipStream_t s) {
     ProfScope ps(name, s);
-    hipLaunchKernelGGL((gemm_nt_kernel<P, false>), dim3(cdiv(M, P::BM), n_tiles, z), dim3(ThreadsOf<P>::value), 0, s, p);
-}
-template <class P>
-void launch_nt_split(const char *name, const P &p, long M, int n_tiles, int z, hipStream_t s) {
-    ProfScope ps(name, s);
-    hipLaunchKernelGGL((gemm_nt_kernel<P, true>), dim3(cdiv(M, P::BM), n_tiles, z), dim3(ThreadsOf<P>::value), 0, s, p);
+    hipLaunchKernelGGL((gemm_nt_kernel<P, SPLIT>), dim3(cdiv(p.M, P::BM), cdiv(N, NT_BN), z), dim3(NT_THREADS), 0, s, p);
 }
 
 // rows of the batch per split of a weight-gradient contraction: whole k-tiles
@@ -186,6 +181,16 @@ void with_geometry(const Dims &d, F f) {
     else f(Geo84());
 }
 
+// Calls f with the positions per workgroup tile of a dense contraction over M rows and N columns: 128 where that makes at
+// least 256 workgroups, fewer (more workgroups) below.
+template <class F>
+void with_tile(long M, int N, F f) {
+    const long nt = cdiv(N, NT_BN);
+    if (cdiv(M, 128) * nt >= 256) f(std::integral_constant<int, 128>());
+    else if (cdiv(M, 64) * nt >= 256) f(std::integral_constant<int, 64>());
+    else f(std::integral_constant<int, 32>());
+}
+
 template <class G, bool F16, int MODE>
 void launch_fc_small(const char *name, const FcSmallArgs &p, int B, hipStream_t s) {
     ProfScope ps(name, s);
@@ -225,11 +230,10 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
     } else {
         typedef typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID>, FcFwdT<G::FEAT, G::NHID>>::type Fc;
         Fc p;
-        p.in = a3; p.lo_off = a3l - a3; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
+        p.in = a3; p.in_lo = a3l; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
         p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(G::FEAT, G::NHID, B, F16); p.partial = (float *)(ws + o.fcp);
         p.to_partial = p.ksplit > 1 || d.small;
-        if constexpr (F16) launch_nt("fc_fwd", p, B, G::NHID / Fc::BN, p.ksplit, s);
-        else launch_nt_split("fc_fwd", p, B, G::NHID / Fc::BN, p.ksplit, s);
+        launch_nt<!F16>("fc_fwd", p, G::NHID, p.ksplit, s);
         if (p.ksplit > 1 && !d.small) {
             ProfScope ps("fc_finish", s);
             const long total = (long)B * G::NHID;
@@ -244,9 +248,13 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
         }
     }
     if (d.head == ARN_HEAD_C51) {
-        HeadFwdC51<G::NHID> p;
-        p.in = h; p.lo_off = hl - h; p.M = B; p.w = w.wh; p.w_lo = w.whl; p.bias = w.bh; p.z = z_out; p.ZW = d.NH; p.ZS = zstride;
-        launch_nt_split("head_fwd", p, B, d.NHP / 64, 1, s);
+        auto launch = [&](auto bm) {
+            HeadFwdC51<G::NHID, decltype(bm)::value> p;
+            p.in = h; p.in_lo = hl; p.M = B; p.w = w.wh; p.w_lo = w.whl; p.bias = w.bh; p.z = z_out; p.NHP = d.NHP; p.ZW = d.NH;
+            p.ZS = zstride;
+            launch_nt<true>("head_fwd", p, d.NHP, 1, s);
+        };
+        with_tile(B, d.NHP, launch);
     }
 }
 
@@ -414,16 +422,15 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
     float *part1 = (float *)(ws + o.pw1), *part2 = (float *)(ws + o.pw2), *part3 = (float *)(ws + o.pw3);
     float *partfc = (float *)(ws + o.pwfc);
     {
-        // fc input gradient in 128 x 128 tiles from 1024 samples up (fewer operand bytes from the L2 per flop),
-        // 128 x 64 below (more workgroups)
-        auto launch = [&](auto dg) {
-            typedef decltype(dg) Dg;
+        auto launch = [&](auto bm) {
+            typedef FcDgradT<G::FEAT, G::NHID, decltype(bm)::value> Dg;
+            Dg dg;
             typedef Wgrad<LastActsGather<G::FEAT>, 128, 64, 2, G::NHID, G::FEAT> FcW;
             typedef HeadWgrad<G::NHID> HeadW;
             dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
             DenseBackwardArgs<Dg, FcW, HeadW> p;
             p.dg = dg;
-            p.dg_x = cdiv(B, Dg::BM); p.dg_blocks = p.dg_x * ((G::FEAT + Dg::BN - 1) / Dg::BN);
+            p.dg_x = cdiv(B, Dg::BM); p.dg_blocks = p.dg_x * cdiv(G::FEAT, NT_BN);
             p.wg.in = a3; p.wg.M = B; p.wg.frag = fc_small(G::FEAT, B, false); p.wg.dy = dph;
             p.wg_part = partfc; p.wg_rows = rows_per_split(B, sp.fc);
             p.wg_blocks = (G::FEAT / FcW::BK2) * (G::NHID / FcW::BN1) * sp.fc;
@@ -435,8 +442,7 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
             hipLaunchKernelGGL((dense_backward_kernel<Dg, FcW, HeadW>), dim3(p.dg_blocks + p.wg_blocks + p.hw_blocks + 1),
                                dim3(DENSE_THREADS), 0, s, p);
         };
-        if (B >= 1024) launch(FcDgradT<G::FEAT, G::NHID, 128>());
-        else launch(FcDgradT<G::FEAT, G::NHID, 64>());
+        with_tile(B, G::FEAT, launch);
     }
     if constexpr (G::HAS3) {
         typename Cfg::Dgrad3::Args p;
@@ -739,9 +745,11 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
     with_geometry(d, [&](auto g) {
         typedef decltype(g) G;
         if (d.head == ARN_HEAD_C51) {
-            HeadDgrad<G::NHID> p;
-            p.in = dz; p.M = B; p.K = d.NHP; p.w = w.whd; p.h = h; p.out = dph;
-            launch_nt("head_dgrad", p, B, G::NHID / HeadDgrad<G::NHID>::BN, 1, s);
+            with_tile(B, G::NHID, [&](auto bm) {
+                HeadDgrad<G::NHID, decltype(bm)::value> p;
+                p.in = dz; p.M = B; p.K = d.NHP; p.w = w.whd; p.h = h; p.out = dph;
+                launch_nt<false>("head_dgrad", p, G::NHID, 1, s);
+            });
         }
         backward_trunk<G>(d, w, batch->obs, B, ws, o, totals, lblocks, dW, s);
     });

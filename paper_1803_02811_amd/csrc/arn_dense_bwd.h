@@ -35,7 +35,7 @@ template <class Dgrad, class Wgrad, class HeadW>
 __global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const DenseBackwardArgs<Dgrad, Wgrad, HeadW> a) {
     constexpr int L1 = gemm_nt_lds_bytes<Dgrad>(), L2 = gemm_tn_lds_bytes<Wgrad>(), L3 = gemm_tn_lds_bytes<HeadW>();
     constexpr int L12 = L1 > L2 ? L1 : L2;
-    static_assert(ThreadsOf<Dgrad>::value == DENSE_THREADS, "one block size for all ranges");
+    static_assert(NT_THREADS == DENSE_THREADS, "one block size for all ranges");
     __shared__ u32x4 lds[(L12 > L3 ? L12 : L3) / 16];
     int b = blockIdx.x;
     if (b < a.dg_blocks) {

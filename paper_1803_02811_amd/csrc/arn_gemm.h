@@ -2,26 +2,24 @@
 // the dense layers (fc, categorical head) are instances of.
 //
 //   gemm_nt_body : out[m][n] = sum_k act(m,k) * W[n][k]
-//       forward layers and input gradients.  `act` is gathered on the fly by the
-//       problem struct; W is a packed bf16 matrix with k contiguous.
+//       forward layers and input gradients; W is packed in fragment order.
 //   gemm_tn_body : out[n][k] = sum_m dY[m][n] * act(m,k)
 //       weight gradients: the contraction runs over the batch/position index,
 //       which is the slow index of both operands in memory, so fragments are
 //       taken from LDS with the transposing read ds_read_b64_tr_b16.
 //
-// Both use v_mfma_f32_32x32x16_bf16 (fp32 accumulate), 4 (or, for the NT kernel, 8)
-// wavefronts of 64 lanes, and 64-element k-tiles staged through LDS (optionally two
-// stages in the NT kernel) with a register prefetch of the tile after next.
-//
-// MFMA operand layout used throughout (checked on hardware):
-//   A (32 x 16): lane l holds row l%32,  k = 8*(l/32) .. +7
-//   B (16 x 32): lane l holds col l%32,  k = 8*(l/32) .. +7
-//   D (32 x 32): lane l holds col l%32,  rows 8*(r/4) + 4*(l/32) + r%4, r = 0..15
+// MFMA operand layouts (checked on hardware):
+//   16x16x32  A (16 x 32): lane l holds row l%16, k = 8*(l/16) .. +7;  B (32 x 16): lane l holds col l%16, same k;
+//             D (16 x 16): lane l holds col l%16, rows 4*(l/16) + r, r = 0..3
+//   32x32x16  A (32 x 16): lane l holds row l%32, k = 8*(l/32) .. +7;  B (16 x 32): lane l holds col l%32, same k;
+//             D (32 x 32): lane l holds col l%32, rows 8*(r/4) + 4*(l/32) + r%4, r = 0..15
 // The weights (or dY) go in as A and the activations as B, so a lane ends up
 // with 4 consecutive channels of one position: one 8-byte NHWC store.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 namespace arn {
 
@@ -37,8 +35,6 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-constexpr int LDS_ROW = 9;   // u32x4 per staged row: 8 of data (64 bf16) + 1 of padding
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
@@ -161,37 +157,58 @@ __device__ __forceinline__ u32x4 keep_or_zero(u32x4 v, bool keep) {
     return u32x4{v.x & mask, v.y & mask, v.z & mask, v.w & mask};
 }
 
+// Copies 16 bytes per lane from base + voff (base wavefront-uniform) to LDS byte offset lds_off + 16 * lane (lds_off
+// wavefront-uniform), without passing through registers.  It counts as a vector memory operation (wait_global_loads, vmcnt);
+// the compiler does not know of it, so the caller waits before the data is read and before the kernel ends.
+__device__ __forceinline__ void copy_to_lds(const void *base, uint32_t voff, uint32_t lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(base) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+// waits until at most N vector memory operations of this wavefront are outstanding
+template <int N>
+__device__ __forceinline__ void wait_vmem() {
+    static_assert(N >= 0 && N < 64, "six-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // ---------------------------------------------------------------------------
 // out[m][n] = sum_k act(m,k) W[n][k]
 //
 // Problem P supplies
-//   BM, BN           workgroup tile (positions x channels), multiples of 32
-//   WAVES_N          wavefronts along channels (1, 2 or 4)
+//   BM               positions per workgroup tile: 32, 64 or 128 (128 channels)
+//   RING             pairs of 32-wide stages in LDS: 2 or 4
+//   SHORT_K          whether a contraction range may be shorter than RING pairs
 //   K                contraction length, multiple of 64 (static or a data member)
-//   Row row(m, z)    per-row gather state for position m (z = blockIdx.z)
-//   u32x4 load(row, k)   eight bf16 of act(m, k..k+7); zeros where out of range
-//   const __bf16* weights(z)   W, at least gridDim.y*BN rows of K
-//   store(m, n, v, z)    epilogue for channels n..n+3 of position m
-// Grid: x = position tiles, y = channel tiles, z = problem-defined.
+//   M                rows of act (rows past the end are read from the last one and dropped by store)
+//   act(), act_lo()  act, row-major 16-bit values [M][K]
+//   weights(), weights_lo()   W in fragment order (frag_index)
+//   tiles()          16-row tiles of W (even); tiles past the end are read from the last one and dropped by store
+//   WIDE             whether store takes eight channels instead of four
+//   prefetch(m, n)                   what the epilogue of an output reads (bias, sign of an activation), loaded before the
+//                                    k loop: a load in the epilogue would be waited for once per output
+//   store(m, n, v, z, prefetched)    epilogue for channels n..n+3 of position m
+//   store(m, n, v, v4, prefetched)   WIDE: for channels n..n+7
+// Grid: x = position tiles, y = channel tiles, z = range of the contraction (problems with a member ksplit).
 //
-// SPLIT = true is the three-product bf16 scheme used for action-selection
-// inference: each operand is a pair (hi, lo) of bf16 with hi + lo carrying ~16
-// mantissa bits, and the product is accumulated as hi*hi + lo_w*hi_a + hi_w*lo_a
-// in fp32.  P then also supplies weights_lo(z), load_lo(row, k) and the flag
-// ACT_LO (false when the activation operand is exact in one bf16, as for uint8
-// pixels, which drops the third product).
+// SPLIT = true is the three-product bf16 scheme of the gradient step's forward: each operand is a pair (hi, lo) of bf16 with
+// hi + lo carrying ~16 mantissa bits, and the product is accumulated as lo_w*hi_a + hi_w*lo_a + hi*hi in fp32.
+//
+// Four wavefronts, each 64 channels x BM/2 positions.  A stage is 32 of the contraction.  Operands are copied from memory
+// straight to LDS (no registers, no conversion, no write instructions), up to 2 * RING stages ahead of their use, and a
+// wavefront's fragments of stage s+1 are read from LDS between its MFMAs on stage s.  The order of the words in LDS makes
+// the fragment reads conflict-free under the bank rule of arn_resident_conv.h; the copies apply it to their source address.
+//
+// What bounds it: with three products the matrix cores (82% of their cycles in the loop; the chip's power limit then sets
+// the clock, 1.65 - 2.0 GHz, which is also why the MFMAs are 16x16x32: 32x32x16 ran the same loop in fewer cycles at a lower
+// clock, 58 against 55 us); with one product LDS bandwidth (a 64 x 64 wavefront tile reads 8 KB per 256 MFMA cycles and
+// four wavefronts share 128 B per cycle).  Measured before (operands through registers, one stage ahead) and after, us:
+// fc forward of 8192 samples, three products 87 -> 65; of 2048 samples 26.7 -> 22.6; one product, 8192 samples 41 -> 35;
+// categorical head of 8192 samples and 960 rows 35 -> 32, its input gradient 19.4 -> 15.5.
 // ---------------------------------------------------------------------------
-template <class P, bool SPLIT>
-struct ActLo {
-    static constexpr bool value = false;
-};
-template <class P>
-struct ActLo<P, true> {
-    static constexpr bool value = P::ACT_LO;
-};
-
 // Problems with a data member `ksplit` cut the contraction into that many
-// ranges of k-tiles, one per blockIdx.z; their store() receives z and writes a
+// ranges, one per blockIdx.z; their store() receives z and writes a
 // partial sum that a later kernel adds up in z order.
 template <class P, class = void>
 struct HasKSplit {
@@ -200,30 +217,6 @@ struct HasKSplit {
 template <class P>
 struct HasKSplit<P, decltype((void)P::ksplit)> {
     static constexpr bool value = true;
-};
-
-// Problems with a static member STAGES = 2 double-buffer their LDS tiles (one
-// barrier per k-tile, staging of the next tile overlaps the MFMAs); the default
-// of one stage halves the LDS footprint, which matters more when several
-// workgroups can share a CU.
-template <class P, class = void>
-struct StagesOf {
-    static constexpr int value = 1;
-};
-template <class P>
-struct StagesOf<P, decltype((void)P::STAGES)> {
-    static constexpr int value = P::STAGES;
-};
-
-// Problems with a static member THREADS = 512 run eight wavefronts per workgroup (two per SIMD, so that one
-// wavefront's LDS waits overlap the other's MFMAs); the default is 256.
-template <class P, class = void>
-struct ThreadsOf {
-    static constexpr int value = 256;
-};
-template <class P>
-struct ThreadsOf<P, decltype((void)P::THREADS)> {
-    static constexpr int value = P::THREADS;
 };
 // Problems with a static member F16 = true hold fp16 operands (same 16-byte fragments, the fp16 MFMA): the single
 // product of the forward passes that carry no gradient.
@@ -235,72 +228,33 @@ template <class P>
 struct IsF16<P, decltype((void)P::F16)> {
     static constexpr bool value = P::F16;
 };
-// one 32x32x16 MFMA on fragments held as eight 16-bit lanes: bf16, or fp16 when F16
 template <bool F16>
-__device__ __forceinline__ f32x16 mfma_32x32x16(bf16x8 a, bf16x8 b, f32x16 c) {
-    if constexpr (F16)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+__device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c) {
+    if constexpr (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
-// Problems with a member function prefetch(m, n) have it called for every output quad before the k loop;
-// its result (for example the ReLU-derivative bits of the quad) is handed to store(), which then needs no
-// dependent load in the epilogue.
-template <class P, class = void>
-struct HasPrefetch {
-    static constexpr bool value = false;
-};
-template <class P>
-struct HasPrefetch<P, decltype((void)&P::prefetch)> {
-    static constexpr bool value = true;
-};
-
-// Problems with a static member FRAG_W = true hold their weights in fragment order (frag_index): a k-tile of BN rows is
-// contiguous kilobytes, staged as they are; fragment reads from them are conflict-free without padding.
-template <class P, class = void>
-struct FragW {
-    static constexpr bool value = false;
-};
-template <class P>
-struct FragW<P, decltype((void)P::FRAG_W)> {
-    static constexpr bool value = P::FRAG_W;
-};
-
-// Problems whose number of weight rows N_ROWS is not a multiple of BN: the last tile's rows past the end are read from
-// the last row (and the problem's epilogue drops their columns).
-template <class P, class = void>
-struct WeightRows {
-    static constexpr int value = 1 << 30;
-};
-template <class P>
-struct WeightRows<P, decltype((void)P::N_ROWS)> {
-    static constexpr int value = P::N_ROWS;
-};
-
+constexpr int NT_THREADS = 256, NT_BN = 128;
+template <int N>
+using Count = std::integral_constant<int, N>;
 // LDS bytes of gemm_nt_body<P, SPLIT>
 template <class P, bool SPLIT = false>
-constexpr int gemm_nt_lds_bytes() {
-    return StagesOf<P>::value * LDS_ROW * 16 * (P::BM * (ActLo<P, SPLIT>::value ? 2 : 1) + P::BN * (SPLIT ? 2 : 1));
-}
+constexpr int gemm_nt_lds_bytes() { return P::RING * 2 * (P::BM + NT_BN) * 64 * (SPLIT ? 2 : 1); }
 
 // The work of workgroup (bx, by, bz) of a grid of gx x gy x gz workgroups, in the caller's LDS buffer.
 template <class P, bool SPLIT = false>
 __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int by, int bz, int gx, int gy, int gz) {
-    constexpr int NT = ThreadsOf<P>::value, NW = NT / 64, RS = NT / 8;   // threads, wavefronts, rows staged per pass
-    constexpr int BM = P::BM, BN = P::BN, WN = P::WAVES_N, WM = NW / WN;
-    constexpr int TN = BN / (32 * WN), TM = BM / (32 * WM);
-    constexpr int A_CH = BM / RS, W_CH = BN / RS;     // 16-byte chunks staged per thread and k-tile
-    static_assert(BM % RS == 0 && BN % RS == 0, "staging passes");
-    constexpr bool ALO = ActLo<P, SPLIT>::value, FRAGW = FragW<P>::value;
-    constexpr int WSTEP = FRAGW ? FRAG_STEP * 2 / 8 : 8;   // 16-byte words from one k-tile of a weight row (or tile) to the next
-    int kt_begin = 0, KT = p.K / 64;
+    constexpr int BM = P::BM, PARTS = SPLIT ? 2 : 1, RING = P::RING;
+    constexpr int MB = BM / 32;                                  // position tiles of 16 per wavefront; four channel tiles
+    constexpr int GA = BM / 32;                                  // 8-row groups of act a wavefront copies per pair of stages and part
+    static_assert(BM == 32 || BM == 64 || BM == 128, "tile shape");
+    static_assert(RING == 2 || RING == 4, "slots");
+    int st_begin = 0, st_end = p.K / 32;
     if constexpr (HasKSplit<P>::value) {
         // Split-k launches: workgroups go to the eight XCDs round robin in linear order (x fastest), and each XCD has
         // an L2 of its own.  With the plain mapping an XCD sees every k range of its position tiles and all of W;
         // remapped, an XCD works on one k range (or a few) of a band of position tiles, so what its L2 fetches from
-        // memory is halved (measured: 77.2 -> 38.6 MB per launch of the fc layer at 2048 samples; the launch itself
-        // 26.9 -> 26.5 us, 17.0 -> 15.2 us at 1024 samples).  Only for grids that split evenly; otherwise the plain
-        // mapping.
+        // memory is halved (measured: 77.2 -> 38.6 MB per launch of the fc layer at 2048 samples).  Only for grids that
+        // split evenly; otherwise the plain mapping.
         const bool pow2 = (gz & (gz - 1)) == 0;
         if (pow2 && gz >= 8) {
             const int L = bx + gx * (by + gy * bz), c = L & 7, zpc = gz >> 3;
@@ -315,157 +269,172 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
             bx = (c % g) * xs + r % xs;
             by = r / xs;
         }
-        const int total = KT;
-        kt_begin = bz * total / p.ksplit;
-        KT = (bz + 1) * total / p.ksplit;
+        const int pairs = st_end / 2;                            // an even number of stages each, at least two
+        st_begin = bz * pairs / p.ksplit * 2;
+        st_end = (bz + 1) * pairs / p.ksplit * 2;
     }
-    static_assert(TN >= 1 && TM >= 1, "tile shape");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    const int wn = wave & 1, wm = wave >> 1;
+    const int m0 = bx * BM, n0 = by * NT_BN, z = bz;
+    const int NS = st_end - st_begin;
 
-    // with two LDS stages tile kt is consumed from stage kt&1 while tile kt+1 is written to the other
-    constexpr int NST = StagesOf<P>::value;
-    constexpr int SA = BM * LDS_ROW, SW = BN * LDS_ROW;
-    u32x4 *const sA = lds, *const sW = sA + NST * SA;
-    u32x4 *const sA2 = sW + NST * SW, *const sW2 = sA2 + (ALO ? NST * SA : 0);   // used where the operand has a low part
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wn = wave % WN, wm = wave / WN;
-    const int m0 = bx * BM, n0 = by * BN, z = bz;
-    const int kc = tid & 7;      // which 16-byte chunk of the 128-byte k-tile row
-    const int r0 = tid >> 3;     // first staged row; this thread also stages r0+RS, r0+2RS, ...
-
-    typename P::Row rows[A_CH];
+    // Sources of this wavefront's copies: GA groups of 8 rows x 64 k of act, two 16-row x 32-k tiles of W.  An activation
+    // group is copied for two stages at once (whole 128-byte lines): word c of row r is stored at c ^ ((r >> 1) & 7).
+    uint32_t a_off[GA], a_dst[GA];
 #pragma unroll
-    for (int i = 0; i < A_CH; ++i) rows[i] = p.row(m0 + r0 + RS * i, z);
-    const u32x4 *wsrc[W_CH];
-    const u32x4 *wsrc2[W_CH];
-#pragma unroll
-    for (int i = 0; i < W_CH; ++i) {
-        size_t at;
-        if constexpr (FRAGW) {
-            const int c = tid + NT * i;   // 128 16-byte words per 16 rows and k-tile
-            at = ((size_t)(n0 / 16 + (c >> 7)) * (p.K / 32)) * FRAG_STEP + (c & 127) * 8;
-        } else {
-            const int nrow = n0 + r0 + RS * i;
-            at = (size_t)(nrow < WeightRows<P>::value ? nrow : WeightRows<P>::value - 1) * p.K + kc * 8;
-        }
-        wsrc[i] = reinterpret_cast<const u32x4 *>(p.weights(z) + at);
-        if constexpr (SPLIT) wsrc2[i] = reinterpret_cast<const u32x4 *>(p.weights_lo(z) + at);
+    for (int i = 0; i < GA; ++i) {
+        const int g = wave * GA + i, row = g * 8 + (lane >> 3);
+        a_off[i] = (uint32_t)(min(row, p.M - 1 - m0) * p.K * 2 + ((lane & 7) ^ ((row >> 1) & 7)) * 16);
+        a_dst[i] = g * 1024;
     }
-
-    u32x4 ra[A_CH], rw[W_CH], ra2[ALO ? A_CH : 1], rw2[SPLIT ? W_CH : 1];
-    auto gload = [&](int kt) __attribute__((always_inline)) {
+    // W: a wavefront copies the two tiles of a group of 32 channels.  WIDE problems give row i of tile t of the group channel
+    // 8 * (i / 4) + 4 * t + i % 4, so that a lane's two quads are eight consecutive channels: one 16-byte store of bf16.
+    const int w_tile = min(n0 / 16 + wave * 2, p.tiles() - 2);
+    uint32_t w_off[2];
 #pragma unroll
-        for (int i = 0; i < A_CH; ++i) {
-            ra[i] = p.load(rows[i], kt * 64 + kc * 8);
-            if constexpr (ALO) ra2[i] = p.load_lo(rows[i], kt * 64 + kc * 8);
-        }
-#pragma unroll
-        for (int i = 0; i < W_CH; ++i) {
-            rw[i] = wsrc[i][kt * WSTEP];
-            if constexpr (SPLIT) rw2[i] = wsrc2[i][kt * WSTEP];
-        }
+    for (int i = 0; i < 2; ++i) {
+        const int ch = P::WIDE ? 8 * (li >> 2) + 4 * i + (li & 3) : 16 * i + li;
+        w_off[i] = (uint32_t)((ch >> 4) * (p.K / 32) * (FRAG_STEP * 2) + lg * 256 + (ch & 15) * 16);
+    }
+    const char *a_src[PARTS], *w_src[PARTS];
+    a_src[0] = reinterpret_cast<const char *>(p.act()) + (size_t)m0 * p.K * 2 + (size_t)st_begin * 64;
+    if constexpr (SPLIT) a_src[1] = reinterpret_cast<const char *>(p.act_lo()) + (size_t)m0 * p.K * 2 + (size_t)st_begin * 64;
+    const size_t w_at0 = ((size_t)w_tile * (p.K / 32) + st_begin) * (FRAG_STEP * 2);
+    w_src[0] = reinterpret_cast<const char *>(p.weights()) + w_at0;
+    if constexpr (SPLIT) w_src[1] = reinterpret_cast<const char *>(p.weights_lo()) + w_at0;
+    const uint32_t lds0 = lds_offset(lds);
+    constexpr int A_PAIR = BM * 128, W_STAGE = NT_BN * 64, W_BASE = RING * PARTS * A_PAIR;   // LDS: RING pairs of act, then of W
+    constexpr int A_COPIES = GA * PARTS, W_COPIES = 2 * PARTS, PAIR_COPIES = A_COPIES + 2 * W_COPIES;
+    auto copy_a = [&](int s, int c) __attribute__((always_inline)) {                         // stages s and s+1, s even
+        const int part = c / GA, i = c % GA;
+        copy_to_lds(a_src[part] + (size_t)s * 64, a_off[i], lds0 + ((s >> 1) & (RING - 1)) * (PARTS * A_PAIR) + part * A_PAIR + a_dst[i]);
+    };
+    auto copy_w = [&](int s, int c) __attribute__((always_inline)) {
+        const int part = c >> 1, i = c & 1;
+        copy_to_lds(w_src[part] + (size_t)s * (FRAG_STEP * 2), w_off[i],
+                    lds0 + W_BASE + ((s & (2 * RING - 1)) * PARTS + part) * W_STAGE + (wave * 2 + i) * 1024);
     };
 
-    f32x16 acc[TN][TM];
+    // the lane's outputs: QUADS quads (1, or 2 neighbouring ones) at channel n_of(a) of position m_of(b)
+    constexpr int QUADS = P::WIDE ? 2 : 1;
+    const auto m_of = [&](int b) { return m0 + (wm * MB + b) * 16 + li; };
+    const auto n_of = [&](int a) { return n0 + (wn * 4 + a) * 16 + 4 * QUADS * lg; };
+    decltype(p.prefetch(0, 0)) pre[4 / QUADS][MB];
 #pragma unroll
-    for (int a = 0; a < TN; ++a)
+    for (int a = 0; a < 4; a += QUADS)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
+        for (int b = 0; b < MB; ++b) pre[a / QUADS][b] = p.prefetch(m_of(b), n_of(a));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    for (int s = 0; s < 2 * RING; s += 2)
+        if (s < NS) {
+#pragma unroll
+            for (int c = 0; c < W_COPIES; ++c) copy_w(s, c);
+#pragma unroll
+            for (int c = 0; c < A_COPIES; ++c) copy_a(s, c);
+#pragma unroll
+            for (int c = 0; c < W_COPIES; ++c) copy_w(s + 1, c);
+        }
 
-    auto stage = [&](int st) __attribute__((always_inline)) {   // registers -> LDS stage st
+    f32x4 acc[4][MB];
 #pragma unroll
-        for (int i = 0; i < A_CH; ++i) {       // rows past M were read from row 0: zeroed here
-            sA[st * SA + (r0 + RS * i) * LDS_ROW + kc] = keep_or_zero(ra[i], rows[i].ok);
-            if constexpr (ALO) sA2[st * SA + (r0 + RS * i) * LDS_ROW + kc] = keep_or_zero(ra2[i], rows[i].ok);
-        }
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int i = 0; i < W_CH; ++i) {
-            const int at = st * SW + (FRAGW ? tid + NT * i : (r0 + RS * i) * LDS_ROW + kc);
-            sW[at] = rw[i];
-            if constexpr (SPLIT) sW2[at] = rw2[i];
-        }
+        for (int b = 0; b < MB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // fragments of a stage in the order they are read: per part, MB of act and four of W
+    constexpr int READS = (MB + 4) * PARTS, MFMAS = 4 * MB * (SPLIT ? 3 : 1);
+    struct Frags { u32x4 f[READS]; };
+    const int row = wm * (MB * 16) + li, w_at = wn * 4096 + lane * 16;
+    const int a_at = row * 128 + ((lg ^ ((row >> 1) & 7)) * 16);     // of the even stage; the odd one's words are 4 further: ^ 64
+    auto read_one = [&](int s, int r, Frags &f) __attribute__((always_inline)) {
+        const int part = r / (MB + 4), e = r % (MB + 4);
+        const char *at = reinterpret_cast<const char *>(lds);
+        if (e < MB) at += ((s >> 1) & (RING - 1)) * (PARTS * A_PAIR) + part * A_PAIR + (a_at ^ ((s & 1) * 64)) + e * 2048;
+        else at += W_BASE + ((s & (2 * RING - 1)) * PARTS + part) * W_STAGE + w_at + (e - MB) * 1024;
+        f.f[r] = *reinterpret_cast<const u32x4 *>(at);
     };
-
-    const int fr = lane & 31, fg = lane >> 5;
-    uint32_t pre[HasPrefetch<P>::value ? TN : 1][HasPrefetch<P>::value ? TM : 1][4];
-    if constexpr (HasPrefetch<P>::value) {
-#pragma unroll
-        for (int a = 0; a < TN; ++a)
-#pragma unroll
-            for (int b = 0; b < TM; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    pre[a][b][q] = p.prefetch(m0 + (wm * TM + b) * 32 + fr, n0 + (wn * TN + a) * 32 + 8 * q + 4 * fg);
-    }
-    gload(kt_begin);
-    stage(0);
-    if (kt_begin + 1 < KT) gload(kt_begin + 1);
-    __syncthreads();
-    for (int kt = kt_begin; kt < KT; ++kt) {
-        const int st = NST == 2 ? (kt - kt_begin) & 1 : 0;
-        if constexpr (NST == 2) {
-            // tile kt+1 (in registers since the previous iteration) goes to the free stage,
-            // then the loads of tile kt+2 are issued; both overlap the MFMAs on tile kt
-            if (kt + 1 < KT) stage(st ^ 1);
-            if (kt + 2 < KT) gload(kt + 2);
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            bf16x8 fw[TN], fa[TM], fw2[SPLIT ? TN : 1], fa2[ALO ? TM : 1];
-#pragma unroll
-            for (int a = 0; a < TN; ++a) {
-                const int row = (wn * TN + a) * 32 + fr;
-                const int at = st * SW + (FRAGW ? (row >> 4) * 128 + (kk >> 1) * 64 + ((kk & 1) * 2 + fg) * 16 + (row & 15)
-                                                : row * LDS_ROW + kk * 2 + fg);
-                fw[a] = as_bf16x8(sW[at]);
-                if constexpr (SPLIT) fw2[a] = as_bf16x8(sW2[at]);
-            }
-#pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                const int at = st * SA + ((wm * TM + b) * 32 + fr) * LDS_ROW + kk * 2 + fg;
-                fa[b] = as_bf16x8(sA[at]);
-                if constexpr (ALO) fa2[b] = as_bf16x8(sA2[at]);
-            }
-#pragma unroll
-            for (int a = 0; a < TN; ++a)
-#pragma unroll
-                for (int b = 0; b < TM; ++b) {
-                    if constexpr (SPLIT)
-                        acc[a][b] = mfma_32x32x16<IsF16<P>::value>(fw2[a], fa[b], acc[a][b]);
-                    if constexpr (ALO)
-                        acc[a][b] = mfma_32x32x16<IsF16<P>::value>(fw[a], fa2[b], acc[a][b]);
-                    acc[a][b] = mfma_32x32x16<IsF16<P>::value>(fw[a], fa[b], acc[a][b]);
-                }
-        }
+    auto multiply_one = [&](int q, const Frags &f) __attribute__((always_inline)) {      // no MFMA waits for the previous one
+        const int t = SPLIT ? q / (4 * MB) : 2, a = q % (4 * MB) / MB, b = q % MB;
+        acc[a][b] = mfma_16x16x32<IsF16<P>::value>(f.f[(t == 0 ? (PARTS - 1) * (MB + 4) : 0) + MB + a],
+                                                   f.f[(t == 1 ? (PARTS - 1) * (MB + 4) : 0) + b], acc[a][b]);
+    };
+    // Stage s, whose fragments are in `cur`: wait until at most AHEAD copies are outstanding, so that stage s+1 has
+    // arrived; then its fragments are read between the MFMAs of s.  In the steady state every stage also issues the copies
+    // that take its slot (everyone has read it by then): W of stage s + 2*RING, and after odd stages the pair of act.
+    auto stage = [&](auto ahead, auto w_copies, auto a_copies, int s, const Frags &cur, Frags &next) __attribute__((always_inline)) {
+        constexpr int WC = decltype(w_copies)::value, COPIES = WC + decltype(a_copies)::value;
+        wait_vmem<decltype(ahead)::value>();
         __syncthreads();
-        if constexpr (NST == 1) {
-            if (kt + 1 < KT) {
-                stage(0);
-                if (kt + 2 < KT) gload(kt + 2);
-                __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        int q = 0, c = 0;
+#pragma unroll
+        for (int r = 0; r < READS; ++r) {
+            read_one(s + 1, r, next);
+            for (; c < (r + 1) * COPIES / READS; ++c) {
+                if (c < COPIES - WC) copy_a(s + 2 * RING - 1, c);
+                else copy_w(s + 2 * RING, c - (COPIES - WC));
             }
+            for (; q < (r + 1) * MFMAS / READS; ++q) multiply_one(q, cur);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto store_all = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < 4; a += QUADS)
+#pragma unroll
+            for (int b = 0; b < MB; ++b) {
+                if constexpr (P::WIDE) p.store(m_of(b), n_of(a), acc[a][b], acc[a + 1][b], pre[a / 2][b]);
+                else p.store(m_of(b), n_of(a), acc[a][b], z, pre[a][b]);
+            }
+    };
+    Frags fa, fb;
+    if constexpr (P::SHORT_K) {
+        if (NS < 2 * RING) {                                     // fewer stages than slots: everything is in LDS at once
+            wait_vmem<0>();
+            __syncthreads();
+            for (int s = 0; s < NS; ++s) {
+#pragma unroll
+                for (int r = 0; r < READS; ++r) read_one(s, r, fa);
+#pragma unroll
+                for (int q = 0; q < MFMAS; ++q) multiply_one(q, fa);
+            }
+            store_all();
+            return;
         }
     }
-
+    wait_vmem<(RING - 1) * PAIR_COPIES + W_COPIES>();
+    __syncthreads();
 #pragma unroll
-    for (int a = 0; a < TN; ++a)
+    for (int r = 0; r < READS; ++r) read_one(0, r, fa);
+    int s = 0;
+    for (; s + 2 * RING < NS; s += 2) {
+        stage(Count<(RING - 1) * PAIR_COPIES>(), Count<W_COPIES>(), Count<0>(), s, fa, fb);
+        stage(Count<(RING - 2) * PAIR_COPIES + 2 * W_COPIES>(), Count<W_COPIES>(), Count<A_COPIES>(), s + 1, fb, fa);
+    }
+    auto last_pair = [&](auto left) __attribute__((always_inline)) {    // `left` pairs follow this one
+        constexpr int N = decltype(left)::value;
+        stage(Count<N * PAIR_COPIES>(), Count<0>(), Count<0>(), s, fa, fb);
+        stage(Count<(N - 1) * PAIR_COPIES + W_COPIES>(), Count<0>(), Count<0>(), s + 1, fb, fa);
+        s += 2;
+    };
+    if constexpr (RING > 2) {
+        last_pair(Count<3>());
+        last_pair(Count<2>());
+    }
+    last_pair(Count<1>());
+    stage(Count<0>(), Count<0>(), Count<0>(), s, fa, fb);
 #pragma unroll
-        for (int b = 0; b < TM; ++b) {
-            const int m = m0 + (wm * TM + b) * 32 + fr;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = n0 + (wn * TN + a) * 32 + 8 * q + 4 * fg;
-                f32x4 v = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
-                if constexpr (HasPrefetch<P>::value) p.store(m, n, v, z, pre[a][b][q]);
-                else p.store(m, n, v, z);
-            }
-        }
+    for (int q = 0; q < MFMAS; ++q) multiply_one(q, fb);
+    store_all();
 }
 
 template <class P, bool SPLIT = false>
-__global__ __launch_bounds__(ThreadsOf<P>::value) void gemm_nt_kernel(const P p) {
+constexpr int gemm_nt_wgs() { return 160 * 1024 / gemm_nt_lds_bytes<P, SPLIT>(); }
+// The number of workgroups per CU is stated to the compiler, so that it does not save registers it has.
+template <class P, bool SPLIT = false>
+__global__ __launch_bounds__(NT_THREADS) __attribute__((amdgpu_waves_per_eu(gemm_nt_wgs<P, SPLIT>(), gemm_nt_wgs<P, SPLIT>())))
+void gemm_nt_kernel(const P p) {
     __shared__ u32x4 lds[gemm_nt_lds_bytes<P, SPLIT>() / 16];
     gemm_nt_body<P, SPLIT>(lds, p, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.y, gridDim.z);
 }

@@ -326,12 +326,6 @@ template <> struct FcSmallSplit<3456> { static constexpr int WAVES = 9, STEPS = 
 template <int FEAT>
 constexpr int fc_small_threads() { return 64 * (FcSmallSplit<FEAT>::WAVES > 8 ? FcSmallSplit<FEAT>::WAVES : 8); }
 
-template <bool F16>
-__device__ __forceinline__ f32x4 mfma_16x16x32(u32x4 a, u32x4 b, f32x4 c) {
-    if constexpr (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
-}
-
 // Values that workgroups of one launch hand to each other: agent-scope relaxed accesses bypass the caches that are not
 // coherent between the XCDs, so no cache has to be written back or invalidated as a whole (a release / acquire pair
 // around plain accesses took 14.9 instead of 12.1 us in a 256-sample trial).

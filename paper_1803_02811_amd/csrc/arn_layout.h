@@ -253,7 +253,7 @@ inline int fc_ksplit(int feat, int hid, int B, bool f16) {
     const int tiles = ((B + 127) / 128) * (hid / 128);
     int ks = 256 / tiles;
     if (ks < 1) ks = 1;
-    const int cap = f16 && B >= 128 ? 8 : 16;   // the consumer adds the ranges one after the other: more of them costs it more than the GEMM gains
+    const int cap = f16 ? 8 : 16;   // the consumer adds the ranges one after the other: more of them costs it more than the GEMM gains
     if (ks > cap) ks = cap;
     return ks;
 }

@@ -14,79 +14,34 @@
 
 namespace arn {
 
-// ------------------------------ gathers ----------------------------------
-// dense rows: act [M][K]
-template <int K_>
-struct DenseGather {
-    const __bf16 *in;
-    long lo_off = 0;
-    int M;
-    struct Row {
-        const __bf16 *base;
-        bool ok;
-    };
-    __device__ __forceinline__ Row row_at(long m) const {
-        Row r;
-        r.ok = m < M;
-        r.base = in + (size_t)(r.ok ? m : 0) * K_;
-        return r;
-    }
-    // rows past M read row 0 (in bounds); the kernels zero them when they stage the registers into LDS
-    __device__ __forceinline__ u32x4 load_at(const Row &r, int k) const {
-        return *reinterpret_cast<const u32x4 *>(r.base + k);
-    }
-    __device__ __forceinline__ u32x4 load_lo_at(const Row &r, int k) const {
-        return *reinterpret_cast<const u32x4 *>(r.base + lo_off + k);
-    }
-};
-// dense rows with a run-time row length (head gradients: K = padded head width)
-struct DenseGatherRt {
-    const __bf16 *in;
-    int M, K;
-    struct Row {
-        const __bf16 *base;
-        bool ok;
-    };
-    __device__ __forceinline__ Row row_at(long m) const {
-        Row r;
-        r.ok = m < M;
-        r.base = in + (size_t)(r.ok ? m : 0) * K;
-        return r;
-    }
-    __device__ __forceinline__ u32x4 load_at(const Row &r, int k) const {
-        return *reinterpret_cast<const u32x4 *>(r.base + k);
-    }
-};
-
-
 // fc: h = relu(act3 Wfc^T + b).  With ksplit > 1 each blockIdx.z covers a range
-// of k-tiles and writes an fp32 partial [z][M][512]; fc_finish_kernel adds the
+// of the contraction and writes an fp32 partial [z][M][HIDN]; fc_finish_kernel or pv_head_kernel adds the
 // partials in z order and applies bias, ReLU and the hi/lo split.  With
 // ksplit == 1 the epilogue does that directly.
 template <int FEAT_, int HIDN>
-struct FcFwdT : DenseGather<FEAT_> {
-    typedef typename DenseGather<FEAT_>::Row Row;
-    static constexpr int BM = 128, BN = 128, WAVES_N = 2, K = FEAT_, STAGES = 2, THREADS = 512;
-    static constexpr bool ACT_LO = true, FRAG_W = true;
+struct FcFwdT {
+    static constexpr int BM = 128, RING = 2, K = FEAT_;
+    static constexpr bool SHORT_K = false, WIDE = false;
+    const __bf16 *in, *in_lo;
+    int M;
     int ksplit;
     bool to_partial;     // write fp32 partial sums even with ksplit == 1 (the consumer finishes the layer)
-    const __bf16 *w, *w_lo = nullptr;
+    const __bf16 *w, *w_lo;
     const float *bias;
-    __bf16 *out, *out_lo = nullptr;
+    __bf16 *out, *out_lo;
     float *partial;
-    __device__ __forceinline__ Row row(int m, int) const { return this->row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return this->load_at(r, k); }
-    __device__ __forceinline__ u32x4 load_lo(const Row &r, int k) const { return this->load_lo_at(r, k); }
-    __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
-    __device__ __forceinline__ const __bf16 *weights_lo(int) const { return w_lo; }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, int z) const {
-        const int M = this->M;
+    __device__ __forceinline__ const __bf16 *act() const { return in; }
+    __device__ __forceinline__ const __bf16 *act_lo() const { return in_lo; }
+    __device__ __forceinline__ const __bf16 *weights() const { return w; }
+    __device__ __forceinline__ const __bf16 *weights_lo() const { return w_lo; }
+    __device__ __forceinline__ int tiles() const { return HIDN / 16; }
+    __device__ __forceinline__ float4 prefetch(int, int n) const { return *reinterpret_cast<const float4 *>(bias + n); }
+    __device__ __forceinline__ void store(int m, int n, f32x4 v, int z, float4 b) const {
         if (m >= M) return;
         if (to_partial) {
             *reinterpret_cast<float4 *>(partial + ((size_t)z * M + m) * HIDN + n) = make_float4(v[0], v[1], v[2], v[3]);
             return;
         }
-        const float4 b = *reinterpret_cast<const float4 *>(bias + n);
         store_bf16x4_split(out, out_lo, (size_t)m * HIDN + n, fmaxf(v[0] + b.x, 0.f), fmaxf(v[1] + b.y, 0.f),
                            fmaxf(v[2] + b.z, 0.f), fmaxf(v[3] + b.w, 0.f));
     }
@@ -96,29 +51,34 @@ struct FcFwdT : DenseGather<FEAT_> {
 template <int FEAT_, int HIDN>
 struct FcFwdF16T : FcFwdT<FEAT_, HIDN> {
     static constexpr bool F16 = true;
+    static constexpr int RING = 4;      // one workgroup per CU: bytes on their way hide the latency of memory
 };
 
 // categorical head: rows of the packed head matrix are the A*atoms categorical rows
 // C51: atom logits fp32 [M][ZS] with bias; ZS = ZW (dense, the inference output) or the padded head width
 // (the gradient step's own buffers: 16-byte stores).
-template <int HIDN>
-struct HeadFwdC51 : DenseGather<HIDN> {
-    typedef typename DenseGather<HIDN>::Row Row;
-    static constexpr int BM = 128, BN = 64, WAVES_N = 1, K = HIDN;
-    static constexpr bool ACT_LO = true;
-    const __bf16 *w, *w_lo = nullptr;
+template <int HIDN, int BM_>
+struct HeadFwdC51 {
+    static constexpr int BM = BM_, RING = 2, K = HIDN;
+    static constexpr bool SHORT_K = false, WIDE = false;
+    const __bf16 *in, *in_lo;
+    int M;
+    const __bf16 *w, *w_lo;
     const float *bias;   // padded head width entries (zeros past ZW)
     float *z;       // [M][ZS]
+    int NHP;        // rows of the packed head matrix (multiple of 64)
     int ZW;         // A*atoms
     int ZS;         // row stride in floats: ZW, or a multiple of 64 >= ZW
-    __device__ __forceinline__ Row row(int m, int) const { return this->row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return this->load_at(r, k); }
-    __device__ __forceinline__ u32x4 load_lo(const Row &r, int k) const { return this->load_lo_at(r, k); }
-    __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
-    __device__ __forceinline__ const __bf16 *weights_lo(int) const { return w_lo; }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, int) const {
-        if (m >= this->M) return;
-        const float4 b = *reinterpret_cast<const float4 *>(bias + n);
+    __device__ __forceinline__ const __bf16 *act() const { return in; }
+    __device__ __forceinline__ const __bf16 *act_lo() const { return in_lo; }
+    __device__ __forceinline__ const __bf16 *weights() const { return w; }
+    __device__ __forceinline__ const __bf16 *weights_lo() const { return w_lo; }
+    __device__ __forceinline__ int tiles() const { return NHP / 16; }
+    __device__ __forceinline__ float4 prefetch(int, int n) const {
+        return *reinterpret_cast<const float4 *>(bias + (n < NHP ? n : 0));
+    }
+    __device__ __forceinline__ void store(int m, int n, f32x4 v, int, float4 b) const {
+        if (m >= M || n >= NHP) return;
         float *dst = z + (size_t)m * ZS + n;
         if (ZS != ZW) {                        // padded rows: every column exists
             *reinterpret_cast<float4 *>(dst) = make_float4(v[0] + b.x, v[1] + b.y, v[2] + b.z, v[3] + b.w);
@@ -136,46 +96,59 @@ struct HeadFwdC51 : DenseGather<HIDN> {
 
 // --------------------------- input gradients ------------------------------
 // d(pre_fc) = (dz W_head) * [h > 0]; the contraction length is the padded head width
-template <int HIDN>
-struct HeadDgrad : DenseGatherRt {
-    static constexpr int BM = 64, BN = 64, WAVES_N = 2;
+template <int HIDN, int BM_>
+struct HeadDgrad {
+    static constexpr int BM = BM_, RING = 2;
+    static constexpr bool SHORT_K = true, WIDE = true;
+    const __bf16 *in;    // dz [M][K]
+    int M, K;
     const __bf16 *w;     // [HIDN][K]
     const __bf16 *h;
     __bf16 *out;         // [M][HIDN]
-    __device__ __forceinline__ Row row(int m, int) const { return row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return load_at(r, k); }
-    __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, int) const {
+    __device__ __forceinline__ const __bf16 *act() const { return in; }
+    __device__ __forceinline__ const __bf16 *weights() const { return w; }
+    __device__ __forceinline__ int tiles() const { return HIDN / 16; }
+    __device__ __forceinline__ u32x4 prefetch(int m, int n) const {
+        return *reinterpret_cast<const u32x4 *>(h + (size_t)(m < M ? m : 0) * HIDN + n);
+    }
+    __device__ __forceinline__ void store(int m, int n, f32x4 v, f32x4 v4, u32x4 hw) const {
         if (m >= M) return;
         const size_t at = (size_t)m * HIDN + n;
-        const f32x4 a = unpack_bf16x4(*reinterpret_cast<const u32x2 *>(h + at));
-        *reinterpret_cast<u32x2 *>(out + at) = pack_bf16x4(a[0] > 0.f ? v[0] : 0.f, a[1] > 0.f ? v[1] : 0.f,
-                                                          a[2] > 0.f ? v[2] : 0.f, a[3] > 0.f ? v[3] : 0.f);
+        f32x4 a = unpack_bf16x4(u32x2{hw[0], hw[1]}), b = unpack_bf16x4(u32x2{hw[2], hw[3]});
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            a[e] = a[e] > 0.f ? v[e] : 0.f;
+            b[e] = b[e] > 0.f ? v4[e] : 0.f;
+        }
+        const u32x2 x = pack_bf16x4(a[0], a[1], a[2], a[3]), y = pack_bf16x4(b[0], b[1], b[2], b[3]);
+        *reinterpret_cast<u32x4 *>(out + at) = u32x4{x[0], x[1], y[0], y[1]};
     }
 };
 
-// d(pre3) = (d(pre_fc) W_fc) * [act3 > 0]      [B][FEAT], NHWC index.  BN_ = 64, or 128 for large batches (a third
-// less operand traffic from the L2 per flop; FEAT need not be a multiple of it: N_ROWS).
-template <int FEAT_, int HIDN, int BN_>
-struct FcDgradT : DenseGather<HIDN> {
-    typedef typename DenseGather<HIDN>::Row Row;
-    static constexpr int BM = 128, BN = BN_, WAVES_N = 2, K = HIDN, STAGES = 1, FEAT = FEAT_, N_ROWS = FEAT_;
-    const __bf16 *w;          // [FEAT][512]
-    const uint8_t *maskbits;  // sign bits of act3, bit e&7 of byte e>>3 for element e = m*FEAT + n
+// d(pre of the last convolution) = (d(pre_fc) W_fc) * [act > 0]      [B][FEAT], NHWC index
+template <int FEAT_, int HIDN, int BM_>
+struct FcDgradT {
+    static constexpr int BM = BM_, RING = 2, K = HIDN, FEAT = FEAT_;
+    static constexpr bool SHORT_K = false, WIDE = true;
+    const __bf16 *in;         // [M][HIDN]
+    int M;
+    const __bf16 *w;          // [FEAT][HIDN]
+    const uint8_t *maskbits;  // sign bits of the activations, bit e&7 of byte e>>3 for element e = m*FEAT + n
     __bf16 *out;
-    __device__ __forceinline__ Row row(int m, int) const { return this->row_at(m); }
-    __device__ __forceinline__ u32x4 load(const Row &r, int k) const { return this->load_at(r, k); }
-    __device__ __forceinline__ const __bf16 *weights(int) const { return w; }
-    // the four ReLU-derivative bits of output quad (m, n..n+3), fetched before the k loop
+    __device__ __forceinline__ const __bf16 *act() const { return in; }
+    __device__ __forceinline__ const __bf16 *weights() const { return w; }
+    __device__ __forceinline__ int tiles() const { return FEAT / 16; }
+    // the eight ReLU-derivative bits of outputs (m, n..n+7), fetched before the k loop
     __device__ __forceinline__ uint32_t prefetch(int m, int n) const {
-        const size_t at = (size_t)(m < this->M ? m : 0) * FEAT + (n < FEAT ? n : 0);
-        return (uint32_t)maskbits[at >> 3] >> (at & 7);
+        const size_t at = (size_t)(m < M ? m : 0) * FEAT + (n < FEAT ? n : 0);
+        return maskbits[at >> 3];
     }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, int, uint32_t mb) const {
-        if (m >= this->M || n >= FEAT) return;
+    __device__ __forceinline__ void store(int m, int n, f32x4 v, f32x4 v4, uint32_t mb) const {
+        if (m >= M || n >= FEAT) return;
         const size_t at = (size_t)m * FEAT + n;
-        *reinterpret_cast<u32x2 *>(out + at) =
-            pack_bf16x4(mb & 1 ? v[0] : 0.f, mb & 2 ? v[1] : 0.f, mb & 4 ? v[2] : 0.f, mb & 8 ? v[3] : 0.f);
+        const u32x2 x = pack_bf16x4(mb & 1 ? v[0] : 0.f, mb & 2 ? v[1] : 0.f, mb & 4 ? v[2] : 0.f, mb & 8 ? v[3] : 0.f);
+        const u32x2 y = pack_bf16x4(mb & 16 ? v4[0] : 0.f, mb & 32 ? v4[1] : 0.f, mb & 64 ? v4[2] : 0.f, mb & 128 ? v4[3] : 0.f);
+        *reinterpret_cast<u32x4 *>(out + at) = u32x4{x[0], x[1], y[0], y[1]};
     }
 };
 
@@ -205,13 +178,14 @@ struct LastActsGather {
 };
 // heads: N1 (padded head rows) is a run-time value
 template <int HIDN>
-struct HeadWgrad : DenseGather<HIDN> {
-    typedef typename DenseGather<HIDN>::Row Row;
+struct HeadWgrad {
     static constexpr int BN1 = 64, BK2 = 128, WAVES_X = 4, KP = HIDN;
-    int N1;
+    const __bf16 *in;    // h [M][HIDN]
+    int M, N1;
     const __bf16 *dy;
-    __device__ __forceinline__ Row xrow(long m) const { return this->row_at(m); }
-    __device__ __forceinline__ u32x4 loadx(const Row &r, int k) const { return this->load_at(r, k); }
+    typedef const __bf16 *Row;
+    __device__ __forceinline__ Row xrow(long m) const { return in + (size_t)m * HIDN; }
+    __device__ __forceinline__ u32x4 loadx(Row r, int k) const { return *reinterpret_cast<const u32x4 *>(r + k); }
     __device__ __forceinline__ u32x4 loady(long m, int n) const {
         return *reinterpret_cast<const u32x4 *>(dy + (size_t)m * N1 + n);
     }

@@ -161,7 +161,6 @@ struct PackPlan {
     long w1, w2, w3, wfc, b1, b2, b3, bfc;   // offsets in the flat vector
     MapHeadRow<G::NHID> hr;
     int NHP;
-    int small_head; // the head's matrices are read by the small heads' kernels as register fragments: fragment order
     int blocks;
 };
 
@@ -175,7 +174,6 @@ inline PackPlan<G> make_pack_plan(const Dims &d, void *w_packed) {
     pl.b1 = (long)po.b1; pl.b2 = (long)po.b2; pl.b3 = (long)po.b3; pl.bfc = (long)po.bfc;
     pl.hr = head_rows<G::NHID>(d, po);
     pl.NHP = d.NHP;
-    pl.small_head = d.small ? 1 : 0;
     auto set = [&](int k, long n, size_t out, size_t lo, bool has_lo) {
         pl.seg[k].n = n;
         pl.seg[k].out = b + out;
@@ -259,7 +257,7 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan<G> &pl, const float 
         bf16x8 hi;
 #pragma unroll
         for (int r = 0; r < 8; ++r) hi[r] = (__bf16)s_t[8 * h + r][e];
-        *reinterpret_cast<bf16x8 *>(pl.fc_dgrad + ((size_t)pos * NC + c0 + c) * G::NHID + n0 + 8 * h) = hi;
+        *reinterpret_cast<bf16x8 *>(pl.fc_dgrad + frag_index((long)pos * NC + c0 + c, n0 + 8 * h, G::NHID)) = hi;
     }
 }
 
@@ -302,14 +300,14 @@ __global__ __launch_bounds__(256) void pack_all_kernel(const PackPlan<G> pl, con
     if (k >= PK_B1 && k <= PK_BH) {
         ((float *)out)[i] = v;
     } else {
-        // the convolution weights live in registers as MFMA fragments: packed in fragment order (frag_index)
+        // every matrix is packed in fragment order (frag_index)
         long o = i;
         if (k == PK_W1) o = frag_index(i / KW1, i % KW1, KW1);
         else if (k == PK_W2) o = frag_index(i / G::KW2, i % G::KW2, G::KW2);
         else if (k == PK_W3 || k == PK_W3D) o = frag_index(i / KW3, i % KW3, KW3);
         else if (k == PK_W2D) o = frag_index(i / (4 * G::NC2), i % (4 * G::NC2), 4 * G::NC2);
-        else if (k == PK_WH && pl.small_head) o = frag_index(i / G::NHID, i % G::NHID, G::NHID);
-        else if (k == PK_WHD && pl.small_head) o = frag_index(i / 64, i % 64, 64);
+        else if (k == PK_WH) o = frag_index(i / G::NHID, i % G::NHID, G::NHID);
+        else if (k == PK_WHD) o = frag_index(i / pl.NHP, i % pl.NHP, pl.NHP);
         const __bf16 hi = (__bf16)v;
         ((__bf16 *)out)[o] = hi;
         if (out_lo) ((__bf16 *)out_lo)[o] = (__bf16)(v - (float)hi);

@@ -44,7 +44,7 @@ def test_forward_at_dispatch_edges(gu, geometry, head, sizes):
         gu.tol_check(got, want[:B].reshape(got.shape), "B=%d" % B)
 
 
-@pytest.mark.parametrize("geometry,B", [("84", 129), ("84", 398), ("84", 399), ("paper", 65), ("paper", 180), ("paper", 181),
+@pytest.mark.parametrize("geometry,B", [("84", 129), ("84", 398), ("84", 399), ("84", 641), ("84", 1281), ("paper", 65), ("paper", 180), ("paper", 181),
                                         ("a3c", 21), ("a3c", 128), ("a3c", 129), ("a3c", 361), ("a3c", 362)])
 def test_gradients_at_dispatch_edges(gu, geometry, B):
     A = 7
@@ -56,3 +56,14 @@ def test_gradients_at_dispatch_edges(gu, geometry, B):
     dW, _ = gu.GpuNet(A, "pv", flat, geometry=geometry).train(batch, "a2c")
     got, want = (wl.split_params(v, A, "pv", **shape_of(geometry)) for v in (dW, ref["flat"]))
     gu.check_grads(got, want, "%s B=%d" % (geometry, B))
+
+
+# padded head rows 64 (fewer stages than the dense kernel has slots), 192 and 960 (the last tile half full)
+@pytest.mark.parametrize("A,B", [(1, 33), (3, 129), (18, 70)])
+def test_categorical_gradients_at_tile_edges(gu, A, B):
+    flat, tflat = (wl.he_normal_params(A, "c51", seed, bias_std=0.1) for seed in (2615, 3615))
+    batch = wl.c51_batch(5, B=B)
+    batch["action"] %= A
+    dW, _, ref, _ = gu.train_c51_or_dqn(gu.GpuNet(A, "c51", flat), orc, flat, tflat, batch, "c51", orc.NetSpec(A, "c51"))
+    got, want = (wl.split_params(v, A, "c51") for v in (dW, ref["flat"]))
+    gu.check_grads(got, want, "A=%d B=%d" % (A, B))
