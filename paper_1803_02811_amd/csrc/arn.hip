@@ -228,21 +228,26 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
             launch_fc_small<G, F16, FC_PARTIAL>("fc_fwd", p, B, s);
         }
     } else {
-        typedef typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID>, FcFwdT<G::FEAT, G::NHID>>::type Fc;
-        Fc p;
-        p.in = a3; p.in_lo = a3l; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
-        p.out = h; p.out_lo = hl; p.ksplit = fc_ksplit(G::FEAT, G::NHID, B, F16); p.partial = (float *)(ws + o.fcp);
-        p.to_partial = p.ksplit > 1 || d.small;
-        launch_nt<!F16>("fc_fwd", p, G::NHID, p.ksplit, s);
-        if (p.ksplit > 1 && !d.small) {
+        const int ksplit = fc_ksplit(G::FEAT, G::NHID, B, F16);
+        auto launch = [&](auto bm) {
+            constexpr int BM = decltype(bm)::value;
+            typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID, BM>, FcFwdT<G::FEAT, G::NHID, BM>>::type p;
+            p.in = a3; p.in_lo = a3l; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
+            p.out = h; p.out_lo = hl; p.ksplit = ksplit; p.partial = (float *)(ws + o.fcp);
+            p.to_partial = ksplit > 1 || d.small;
+            launch_nt<!F16>("fc_fwd", p, G::NHID, ksplit, s);
+        };
+        if (fc_tile(G::NHID, B) == 128) launch(std::integral_constant<int, 128>());
+        else launch(std::integral_constant<int, 64>());
+        if (ksplit > 1 && !d.small) {
             ProfScope ps("fc_finish", s);
             const long total = (long)B * G::NHID;
-            hipLaunchKernelGGL(fc_finish_kernel, dim3(cdiv(total / 4, 256)), dim3(256), 0, s, p.partial, p.ksplit,
+            hipLaunchKernelGGL(fc_finish_kernel, dim3(cdiv(total / 4, 256)), dim3(256), 0, s, (const float *)(ws + o.fcp), ksplit,
                                w.bfc, h, hl, G::NHID, total);
         }
         if (d.small && head) {
             ProfScope ps("pv_head", s);
-            head->ks = p.ksplit;
+            head->ks = ksplit;
             head->rpb = infer_rows_per_block(B);
             hipLaunchKernelGGL((pv_head_kernel<false, G::NHID>), dim3(cdiv(B, head->rpb)), dim3(PVH_THREADS), 0, s, *head);
         }

@@ -231,9 +231,8 @@ inline Splits make_splits(const Dims &d, int B) {
 }
 
 // number of k ranges the fc forward GEMM is cut into (fills the chip when B/128 * 4 tiles are too few)
-// f16: the one-product fc layer of the no-gradient forward, whose GEMM is a third of the work: from 128 samples up
-// eight ranges are the better trade (inference at 256 samples 25.4 -> 23.8 us per call, at 512 33.7 -> 31.6; at 64 and
-// below sixteen stay ahead by half a microsecond, and the three-product layer of the gradient step at every size).
+// f16: the one-product fc layer of the no-gradient forward, whose GEMM is a third of the work: at most eight ranges (the
+// kernel also counts on at least eight stages of 32 in a range; the three-product layer on four).
 // Small batches run in fc_small_kernel (one workgroup per 16 or 32 units and 16 or 32 samples, no k ranges in memory).  Its
 // workgroups of one XCD share a band of weights and each XCD reads all activations, so it pays as long as those are few:
 // up to about 2.5 M of them, counting hi and lo parts (one product, 3136 inputs, 256 samples: 10.8 us with the head
@@ -248,9 +247,14 @@ inline FcTile fc_small_tile(int hid, int B) {
     if (n * ((B + 31) / 32) <= 128) return {16, 32};
     return {32, 32};
 }
+// Samples per workgroup tile of that GEMM: 128, or 64 where 128 would need more than eight ranges of the contraction to
+// fill the chip: the partial sums are written and read back once per range (104x80, 512 samples: 64 takes the one-product
+// layer from 13.7 to 10.5 us and the gradient step's layer and heads from 27.1 to 26.8).
+inline int fc_tile(int hid, int B) { return ((B + 127) / 128) * (hid / 128) >= 32 ? 128 : 64; }
 inline int fc_ksplit(int feat, int hid, int B, bool f16) {
     if (fc_small(feat, B, f16)) return 1;
-    const int tiles = ((B + 127) / 128) * (hid / 128);
+    const int bm = fc_tile(hid, B);
+    const int tiles = ((B + bm - 1) / bm) * (hid / 128);
     int ks = 256 / tiles;
     if (ks < 1) ks = 1;
     const int cap = f16 ? 8 : 16;   // the consumer adds the ranges one after the other: more of them costs it more than the GEMM gains

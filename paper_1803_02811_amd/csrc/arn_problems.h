@@ -18,9 +18,9 @@ namespace arn {
 // of the contraction and writes an fp32 partial [z][M][HIDN]; fc_finish_kernel or pv_head_kernel adds the
 // partials in z order and applies bias, ReLU and the hi/lo split.  With
 // ksplit == 1 the epilogue does that directly.
-template <int FEAT_, int HIDN>
+template <int FEAT_, int HIDN, int BM_>
 struct FcFwdT {
-    static constexpr int BM = 128, RING = 2, K = FEAT_;
+    static constexpr int BM = BM_, RING = 2, K = FEAT_;
     static constexpr bool SHORT_K = false, WIDE = false;
     const __bf16 *in, *in_lo;
     int M;
@@ -48,8 +48,8 @@ struct FcFwdT {
 };
 // The same layer with fp16 activations and weights in one product (no-gradient forward): `in` and `w` point at
 // fp16 data of the same layouts; the outputs are the fp32 partial sums or the (hi, lo) bf16 hidden layer as above.
-template <int FEAT_, int HIDN>
-struct FcFwdF16T : FcFwdT<FEAT_, HIDN> {
+template <int FEAT_, int HIDN, int BM_>
+struct FcFwdF16T : FcFwdT<FEAT_, HIDN, BM_> {
     static constexpr bool F16 = true;
     static constexpr int RING = 4;      // one workgroup per CU: bytes on their way hide the latency of memory
 };
