@@ -67,7 +67,7 @@ typedef enum {
     ARN_EINVAL = -1,     /* null or misaligned pointer, B <= 0 or B > 2^20 (1,048,576 samples per call) */
     ARN_ESHAPE = -2,     /* unsupported num_actions / num_atoms / head for this call */
     ARN_EKIND = -3,      /* unknown head_kind / loss_kind / mode */
-    ARN_EWORKSPACE = -4, /* workspace smaller than arn_workspace_bytes() */
+    ARN_EWORKSPACE = -4, /* workspace smaller than the call needs (arn_workspace_bytes() is enough) */
     ARN_EARCH = -5,      /* current device is not gfx950 */
     ARN_EHIP = -6,       /* a HIP runtime call or launch failed */
     ARN_ESTATIC = -7     /* arn_policy_forward_static: the call needs more scratch memory than ARN_STATIC_SCRATCH_BYTES */
@@ -104,7 +104,7 @@ size_t arn_param_count(const arn_config *cfg);
  * input-gradient-layout copies of every weight matrix plus fp32 biases. */
 size_t arn_packed_bytes(const arn_config *cfg);
 
-/* Bytes of scratch device memory that a call with batch size B needs.
+/* Bytes of scratch device memory that calls with batch sizes up to B need.
  * mode = ARN_MODE_FORWARD (arn_policy_forward) or ARN_MODE_TRAIN
  * (arn_train_step_grads).  0 on bad arguments. */
 size_t arn_workspace_bytes(const arn_config *cfg, int B, int mode);

@@ -601,7 +601,7 @@ int arn_policy_forward(const arn_config *cfg, const void *w_packed, const uint8_
     if (int e = check_policy_forward(cfg, w_packed, obs, B, logits, value, probs, greedy, &d)) return e;
     if (!aligned(workspace, 256)) return ARN_EINVAL;
     const Workspace o = make_workspace(d, B, ARN_MODE_FORWARD);
-    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_FORWARD)) return ARN_EWORKSPACE;
+    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
     return policy_forward_launches(cfg, d, o, w_packed, obs, B, logits, value, probs, greedy, (char *)workspace,
                                    (hipStream_t)stream);
@@ -634,7 +634,7 @@ int arn_policy_act(const arn_config *cfg, const void *w_packed, const uint8_t *o
     if (!policy && (!aligned(u2, 16) || !(epsilon >= 0.f && epsilon <= 1.f))) return ARN_EINVAL;
     if (logp && (!policy || !aligned(logp, 16))) return policy ? ARN_EINVAL : ARN_ESHAPE;
     const Workspace o = make_workspace(d, B, ARN_MODE_FORWARD);
-    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_FORWARD)) return ARN_EWORKSPACE;
+    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
@@ -677,7 +677,7 @@ int arn_train_step_grads(const arn_config *cfg, const void *w_packed, const arn_
         if (batch->next_action && !aligned(batch->next_action, 16)) return ARN_EINVAL;
     }
     const Workspace o = make_workspace(d, B, ARN_MODE_TRAIN);
-    if (workspace_bytes < reported_workspace_bytes(d, B, ARN_MODE_TRAIN)) return ARN_EWORKSPACE;
+    if (workspace_bytes < o.total) return ARN_EWORKSPACE;
     if (int e = check_arch()) return e;
 
     hipStream_t s = (hipStream_t)stream;

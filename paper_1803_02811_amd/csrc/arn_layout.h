@@ -206,6 +206,7 @@ inline ConvBwdCost conv_bwd_cost(int geom) {
     return {3.5f, 1.f, 0.f};
 }
 struct ConvBwdSplit { int spw1, spw2, spw3; };   // samples per workgroup
+constexpr int CONV_BWD_MOST1 = 204, CONV_BWD_MOST2 = 85;   // workgroups of the first, of either other range, at most
 inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
     const ConvBwdCost c = conv_bwd_cost(d.geom);
     const int g2 = conv2_wg_g(d), g3 = CONV3_WG_G;
@@ -215,7 +216,8 @@ inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
         s.spw1 = per(c.c1, 1);
         s.spw2 = per(c.c2, g2);
         s.spw3 = d.c3 ? per(c.c3, g3) : 1 << 30;
-        if ((B + s.spw1 - 1) / s.spw1 + (B + s.spw2 - 1) / s.spw2 + (d.c3 ? (B + s.spw3 - 1) / s.spw3 : 0) <= 256) return s;
+        const int n1 = (B + s.spw1 - 1) / s.spw1, n2 = (B + s.spw2 - 1) / s.spw2, n3 = d.c3 ? (B + s.spw3 - 1) / s.spw3 : 0;
+        if (n1 + n2 + n3 <= 256 && n1 <= CONV_BWD_MOST1 && n2 <= CONV_BWD_MOST2 && n3 <= CONV_BWD_MOST2) return s;
     }
 }
 inline Splits make_splits(const Dims &d, int B) {
@@ -294,26 +296,31 @@ inline int loss_blocks(const Dims &d, int B) {
     const int per = d.small ? loss_block(B) : C51_WAVES * c51_loss_spw(B);
     return (B + per - 1) / per;
 }
-inline Workspace make_workspace(const Dims &d, int B, int mode) {
+// `bound`: sizes for which every smaller batch's workspace has room too.
+inline Workspace make_workspace(const Dims &d, int B, int mode, bool bound = false) {
     Workspace w{};
     size_t p = 0;
     auto take = [&](size_t bytes) { size_t at = p; p = align_up(p + bytes, 256); return at; };
     const size_t b = (size_t)B, feat = (size_t)d.feat, hid = (size_t)d.hid;
-    const size_t e1 = b * d.p1 * d.c1, e2 = d.c3 ? b * d.p2 * d.c2 : 0;   // elements of act1 and act2
+    const bool train = mode == ARN_MODE_TRAIN;
+    const size_t e1 = train ? b * d.p1 * d.c1 : 0;                // elements of act1 and act2, which inference keeps on chip
+    const size_t e2 = train && d.c3 ? b * d.p2 * d.c2 : 0;
     w.a1 = take(e1 * 2);
     w.a2 = take(e2 * 2);
-    const size_t b3 = B <= FC_SMALL_MAX ? align_up(b, 32) : b;   // fragment order: whole sample tiles
+    // fragment order: whole sample tiles
+    const size_t b3 = B <= FC_SMALL_MAX ? align_up(b, fc_small_tile(d.hid, B).rows) : b;
     w.a3 = take(b3 * feat * 2);
-    w.h = take(b * hid * 2);
+    w.h = take(train || !d.small ? b * hid * 2 : 0);
     w.a1l = take(d.c3 ? e1 * 2 : 0);                             // two convolutions: act1 goes to conv2 through LDS
     w.a2l = take(e2 * 2);
-    w.a3l = take(b3 * feat * 2);
-    w.hl = take(b * hid * 2);
+    w.a3l = take(train ? b3 * feat * 2 : 0);
+    w.hl = take(train || !d.small ? b * hid * 2 : 0);
     // the fused policy/value head kernel always reads fp32 partials; the categorical path only when k is split
-    const int ks = fc_ksplit(d.feat, d.hid, B, false), ks16 = fc_ksplit(d.feat, d.hid, B, true), ksm = ks > ks16 ? ks : ks16;
-    w.fcp = take((size_t)(ksm > 1 || d.small ? ksm : 0) * b * hid * 4);
-    if (fc_small(d.feat, B, true) && d.small) {
-        w.zp = take(hid / 16 * align_up(b, 32) * 32 * 4);
+    const int ks = std::max(train ? fc_ksplit(d.feat, d.hid, B, false) : 0, fc_ksplit(d.feat, d.hid, B, true));
+    const size_t fcp = (size_t)(ks > 1 || d.small ? ks : 0) * b * hid;   // at most 16 ranges, 256 workgroups of 128 x 128 if several
+    w.fcp = take((bound ? std::max(std::min(16 * b * hid, (size_t)256 * 128 * 128), d.small ? b * hid : 0) : fcp) * 4);
+    if ((bound || fc_small(d.feat, B, true)) && d.small) {
+        w.zp = take(hid / 16 * align_up(std::min(b, (size_t)FC_SMALL_MAX), 32) * 32 * 4);
         w.cnt = take((size_t)FC_SMALL_MAX / 16 * 4);
     }
     // categorical head: atom logits of arn_policy_act (arn_policy_forward writes them to its `logits` argument)
@@ -336,9 +343,16 @@ inline Workspace make_workspace(const Dims &d, int B, int mode) {
         w.dph = take(b * hid * 2);
         w.dp3 = take(b * feat * 2);
         w.dp2 = take(e2 * 2);
-        w.lossp = take((size_t)loss_blocks(d, B) * 4 * 4);
-        w.hbp = take((size_t)loss_blocks(d, B) * (d.small ? 32 : d.NHP) * 4);
-        const Splits s = make_splits(d, B);
+        size_t lb = (size_t)loss_blocks(d, B);
+        Splits s = make_splits(d, B);
+        if (bound) {
+            for (int end : {512, 2048, 4095}) lb = std::max(lb, (size_t)loss_blocks(d, std::min(B, end)));   // fewer, longer blocks beyond
+            s.c1 = std::min(B, CONV_BWD_MOST1);
+            s.c2 = std::min(B, CONV_BWD_MOST2);
+            s.c3 = d.c3 ? std::min(B, CONV_BWD_MOST2) : 0;
+        }
+        w.lossp = take(lb * 4 * 4);
+        w.hbp = take(lb * (d.small ? 32 : d.NHP) * 4);
         w.pw1 = take((size_t)s.c1 * ((size_t)d.c1 * KW1 + d.c1) * 4);
         w.pw2 = take((size_t)s.c2 * ((size_t)d.c2 * d.kw2 + d.c2) * 4);
         w.pw3 = take((size_t)s.c3 * ((size_t)C3 * KW3 + C3) * 4);
@@ -349,8 +363,12 @@ inline Workspace make_workspace(const Dims &d, int B, int mode) {
     return w;
 }
 
-// Sizes reported to callers.  The 2-convolution network reports those of its embedding in the 104x80 three-convolution
-// network (plus that network's flat vector), which are part of its documented interface and larger than what it needs.
+// Sizes reported to callers.  A workspace made for B samples serves every smaller batch too, so what is reported does not
+// decrease with B, although what a call needs does now and then (fewer ranges of the fc contraction, fewer partials).
+// Calls ask for what they need (make_workspace).
+// Inference reports the size that holds every layer's activations: it decides what arn_policy_forward_static accepts.
+// The 2-convolution network reports at least the sizes of its embedding in the 104x80 three-convolution network (plus that
+// network's flat vector), which are part of the documented interface.
 inline Dims embedding_dims(Dims d) {
     d.geom = ARN_GEOM_PAPER;
     set_geometry<GeoPaper>(d);
@@ -361,11 +379,22 @@ inline size_t reported_packed_bytes(const Dims &d) {
     const Dims e = embedding_dims(d);
     return std::max(packed_offsets(d).total, packed_offsets(e).total + align_up(param_offsets(e).total * 4, 256));
 }
+// act1 .. h as (hi, lo) pairs, the fc layer's partial sums in up to 16 ranges, the categorical head's logits
+inline size_t all_activations_bytes(const Dims &d, int B) {
+    size_t p = 0;
+    const size_t b = (size_t)B;
+    for (size_t n : {b * d.p1 * d.c1, b * d.p2 * d.c2, b * d.feat, b * d.hid}) p += 2 * align_up(n * 2, 256);
+    p += align_up(std::max(std::min(16 * b, (size_t)8192), d.small ? b : 0) * d.hid * 4, 256);
+    return p + align_up(d.small ? 0 : b * d.NHP * 4, 256);
+}
 inline size_t reported_workspace_bytes(const Dims &d, int B, int mode) {
-    if (d.geom != ARN_GEOM_A3C) return make_workspace(d, B, mode).total;
+    auto bytes = [&](const Dims &x) {
+        const size_t need = make_workspace(x, B, mode, true).total;
+        return mode == ARN_MODE_TRAIN ? need : std::max(need, all_activations_bytes(x, B));
+    };
+    if (d.geom != ARN_GEOM_A3C) return bytes(d);
     const Dims e = embedding_dims(d);
-    return std::max(make_workspace(d, B, mode).total,
-                    make_workspace(e, B, mode).total + (mode == ARN_MODE_TRAIN ? align_up(param_offsets(e).total * 4, 256) : 0));
+    return std::max(bytes(d), bytes(e) + (mode == ARN_MODE_TRAIN ? align_up(param_offsets(e).total * 4, 256) : 0));
 }
 
 }  // namespace arn

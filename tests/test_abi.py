@@ -84,6 +84,25 @@ def test_sizes_and_bad_configs(lib):
     assert arn.workspace_bytes(cfg, 2048, arn.ARN_MODE_TRAIN) == arn.workspace_bytes(cfg, 2048, arn.ARN_MODE_TRAIN)
 
 
+@pytest.mark.parametrize("geometry", [arn.ARN_GEOM_84, arn.ARN_GEOM_PAPER, arn.ARN_GEOM_A3C])
+@pytest.mark.parametrize("head", [arn.ARN_HEAD_PV, arn.ARN_HEAD_C51, arn.ARN_HEAD_DUEL])
+@pytest.mark.parametrize("mode", [arn.ARN_MODE_FORWARD, arn.ARN_MODE_TRAIN])
+def test_a_workspace_serves_every_smaller_batch(lib, geometry, head, mode):
+    """The reported size does not decrease with the batch: one workspace, made for the largest, is enough for all."""
+    cfg = arn.Config(18, head, geometry=geometry)
+    sizes = [arn.workspace_bytes(cfg, B, mode) for B in [*range(1, 4300), *range(8100, 8300), *range(16380, 16390), 1 << 20]]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+def test_static_scratch_takes_the_groups_it_always_took(lib):
+    """32 MiB hold up to 222 observations of 104x80 frames and 281 of 84x84 ones with the small heads."""
+    for geometry, most in [(arn.ARN_GEOM_84, 281), (arn.ARN_GEOM_PAPER, 222), (arn.ARN_GEOM_A3C, 222)]:
+        for head in (arn.ARN_HEAD_PV, arn.ARN_HEAD_Q, arn.ARN_HEAD_DUEL):
+            cfg = arn.Config(18, head, geometry=geometry)
+            assert arn.workspace_bytes(cfg, most, arn.ARN_MODE_FORWARD) <= arn.STATIC_SCRATCH_BYTES
+            assert arn.workspace_bytes(cfg, most + 1, arn.ARN_MODE_FORWARD) > arn.STATIC_SCRATCH_BYTES
+
+
 def test_argument_errors_are_reported_on_the_host(lib):
     """Null / misaligned pointers, bad kinds and short workspaces return error codes without any launch."""
     cfg = arn.Config(18, arn.ARN_HEAD_PV)
