@@ -430,7 +430,7 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
         auto launch = [&](auto bm) {
             typedef FcDgradT<G::FEAT, G::NHID, decltype(bm)::value> Dg;
             Dg dg;
-            typedef Wgrad<LastActsGather<G::FEAT>, 128, 64, 2, G::NHID, G::FEAT> FcW;
+            typedef FcWgrad<G::FEAT, G::NHID> FcW;
             typedef HeadWgrad<G::NHID> HeadW;
             dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
             DenseBackwardArgs<Dg, FcW, HeadW> p;

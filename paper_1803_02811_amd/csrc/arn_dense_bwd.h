@@ -33,10 +33,10 @@ struct DenseBackwardArgs {
 
 template <class Dgrad, class Wgrad, class HeadW>
 __global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const DenseBackwardArgs<Dgrad, Wgrad, HeadW> a) {
-    constexpr int L1 = gemm_nt_lds_bytes<Dgrad>(), L2 = gemm_tn_lds_bytes<Wgrad>(), L3 = gemm_tn_lds_bytes<HeadW>();
-    constexpr int L12 = L1 > L2 ? L1 : L2;
+    // the weight gradients take as many stages as the input gradient's LDS holds
+    constexpr int L1 = gemm_nt_lds_bytes<Dgrad>(), R2 = L1 / gemm_tn_stage_bytes<Wgrad>(), R3 = L1 / gemm_tn_stage_bytes<HeadW>();
     static_assert(NT_THREADS == DENSE_THREADS, "one block size for all ranges");
-    __shared__ u32x4 lds[(L12 > L3 ? L12 : L3) / 16];
+    __shared__ u32x4 lds[L1 / 16];
     int b = blockIdx.x;
     if (b < a.dg_blocks) {
         gemm_nt_body<Dgrad>(lds, a.dg, b % a.dg_x, b / a.dg_x, 0, a.dg_x, 1, 1);
@@ -45,14 +45,14 @@ __global__ __launch_bounds__(DENSE_THREADS) void dense_backward_kernel(const Den
     b -= a.dg_blocks;
     if (b < a.wg_blocks) {
         constexpr int X = Wgrad::KP / Wgrad::BK2, Y = Wgrad::N1 / Wgrad::BN1;
-        gemm_tn_body<Wgrad>(lds, a.wg, a.wg_part, a.wg_rows, b % X, b / X % Y, b / (X * Y));
+        gemm_tn_body<Wgrad, R2>(lds, a.wg, a.wg_part, a.wg_rows, b % X, b / X % Y, b / (X * Y));
         return;
     }
     b -= a.wg_blocks;
     if (b < a.hw_blocks) {
         constexpr int X = HeadW::KP / HeadW::BK2;
         const int Y = a.hw.N1 / HeadW::BN1;
-        gemm_tn_body<HeadW>(lds, a.hw, a.hw_part, a.hw_rows, b % X, b / X % Y, b / (X * Y));
+        gemm_tn_body<HeadW, R3>(lds, a.hw, a.hw_part, a.hw_rows, b % X, b / X % Y, b / (X * Y));
         return;
     }
     loss_finalize(a.loss.partial, a.loss.blocks, a.loss.B, a.loss.value_coef, a.loss.entropy_coef, a.loss.loss);

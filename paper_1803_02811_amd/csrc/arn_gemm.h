@@ -144,19 +144,6 @@ __device__ __forceinline__ u32x4 zero_u4() { return u32x4{0u, 0u, 0u, 0u}; }
 // of the next sample issued just before -- and every iteration would wait for its own prefetch.
 __device__ __forceinline__ void wait_global_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// v if keep else 0, through a mask the optimiser cannot see through: a gather
-// written as `ok ? *p : 0` is compiled to a branch around the load with a wait
-// right behind it, which serialises the loads of one k-tile.  With the mask the
-// (always in-bounds, clamped) loads are issued back to back.  The mask is applied where
-// the registers are written to LDS, not where they are loaded: applied at the load it sits
-// in the same basic block as the prefetch, and the wavefront waits for the next tile's
-// loads before it starts the MFMAs of the current one.
-__device__ __forceinline__ u32x4 keep_or_zero(u32x4 v, bool keep) {
-    uint32_t mask = keep ? 0xffffffffu : 0u;
-    asm volatile("" : "+v"(mask));
-    return u32x4{v.x & mask, v.y & mask, v.z & mask, v.w & mask};
-}
-
 // Copies 16 bytes per lane from base + voff (base wavefront-uniform) to LDS byte offset lds_off + 16 * lane (lds_off
 // wavefront-uniform), without passing through registers.  It counts as a vector memory operation (wait_global_loads, vmcnt);
 // the compiler does not know of it, so the caller waits before the data is read and before the kernel ends.
@@ -440,86 +427,92 @@ void gemm_nt_kernel(const P p) {
 }
 
 // ---------------------------------------------------------------------------
-// Transposing LDS fragment read.
-//
-// `tile` holds 64 rows (contraction index m) of `row_u4` u32x4 each, columns
-// contiguous.  Returns, for MFMA lane l, the eight values
-//   tile[mbase + 8*(l/32) + e][col0 + l%32],  e = 0..7
-// i.e. an A- or B-operand fragment whose k index is the tile's row index.
-// ds_read_b64_tr_b16 works on groups of 16 lanes: lane 4q+e of a group receives
-// element e of the four 8-byte rows addressed by lanes q, q+4, q+8, q+12.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bf16x8 tr_fragment(const u32x4 *tile, int row_u4, int mbase, int col0, int lane) {
-    const int o = lane & 15, G = lane >> 4;
-    const int row = mbase + 8 * (G >> 1) + (o >> 2);
-    const int col = col0 + 16 * (G & 1) + 4 * (o & 3);
-    const char *addr = reinterpret_cast<const char *>(tile) + (size_t)row * row_u4 * 16 + col * 2;
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr));
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr + (size_t)4 * row_u4 * 16));
-    s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-// ---------------------------------------------------------------------------
 // part[split][n][k] = sum_{m in split} dY[m][n] * act(m,k)       (fp32)
 // part[split][N1*KP + n] = sum_{m in split} dY[m][n]             (bias gradient)
 //
 // Problem P supplies
-//   BN1, BK2         output tile (dY channels x act columns), multiples of 32
+//   BN1, BK2         output tile (dY channels x act columns), multiples of 64
 //   WAVES_X          wavefronts along act columns (1, 2 or 4)
 //   N1, KP           full output shape (rows, columns; static or data members)
-//   XRow xrow(m), u32x4 loadx(xrow, k)    gather of act(m, k..k+7)
-//   u32x4 loady(m, n)                     eight bf16 of dY[m][n..n+7]
-//   int M                                  number of contraction rows
-// Grid: x = column tiles, y = row tiles, z = batch split.  Each split covers
-// `rows_per_split` (a multiple of 64) consecutive m; partials are summed by
-// reduce_partials_kernel in split order, which fixes the rounding order.
+//   dy               dY, row-major bf16 [M][N1]
+//   xbase(m), xoff(r, k)    address of act row m (a multiple of 32), byte offset of act(m + r, k .. k+7) from it, r < 32
+//   int M            number of contraction rows
+// Each split covers `rows_per_split` (a multiple of 64) consecutive m; partials are summed by reduce_all_kernel in split
+// order, which fixes the rounding order.
+//
+// A stage is 32 rows.  Both operands are copied from memory straight to LDS, RING - 1 stages ahead of their use, and read
+// back as fragments by transposing reads; one barrier per stage.  A transposing read takes 64 contiguous bytes of each of
+// four consecutive rows, which is conflict-free when the four are 64 bytes apart modulo 256: rows are not padded (a copy
+// fills 1 KB), so row r's 64-byte blocks are stored permuted, and the copies apply that to their source address.
+//
+// What bounds it: LDS.  A 64 x 32 wavefront tile reads 3 KB per 64 MFMA cycles and four wavefronts share 128 B per cycle; with
+// operands through registers, one 64-row tile ahead, the staging writes came on top and every tile had two barriers.  Steps
+// before / after, us: ppo of 4096 samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
 // ---------------------------------------------------------------------------
-// This is the work of workgroup (bx, by, split) of 256 threads, in the caller's LDS buffer of gemm_tn_lds_bytes<P>().
-constexpr int TN_PAD = 4;   // padding of a staged row in u32x4, see below
+constexpr int TN_ROWS = 32;
 template <class P>
-constexpr int gemm_tn_lds_bytes() { return 64 * (P::BN1 / 8 + TN_PAD + P::BK2 / 8 + TN_PAD) * 16; }
+constexpr int gemm_tn_stage_bytes() { return TN_ROWS * (P::BN1 + P::BK2) * 2; }
+// position of the 16-byte words of row r (of ROWB bytes): word c is stored at c ^ tn_swizzle(r).  Unchanged by r + 4.
+template <int ROWB>
+__device__ __forceinline__ int tn_swizzle(int r) { return ROWB == 128 ? (r & 2) << 1 : (r & 3) << 2; }
 
-template <class P>
+// Transposing LDS fragment read.
+//
+// `tile` holds rows (contraction index m) of ROWB bytes, their words permuted by tn_swizzle.  Returns, for MFMA lane l, the
+// eight values
+//   tile[mbase + 8*(l/32) + e][col0 + l%32],  e = 0..7
+// i.e. an A- or B-operand fragment whose k index is the tile's row index.
+// ds_read_b64_tr_b16 works on groups of 16 lanes: lane 4q+e of a group receives
+// element e of the four 8-byte rows addressed by lanes q, q+4, q+8, q+12.
+template <int ROWB>
+__device__ __forceinline__ bf16x8 tr_fragment(const char *tile, int mbase, int col0, int lane) {
+    const int o = lane & 15, G = lane >> 4;
+    const int row = 8 * (G >> 1) + (o >> 2);
+    const int col = col0 + 16 * (G & 1) + 4 * (o & 3);
+    const char *addr = tile + mbase * ROWB + row * ROWB + ((col * 2) ^ (tn_swizzle<ROWB>(row) * 16));
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
+    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr));
+    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(addr + 4 * ROWB));
+    s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// The work of workgroup (bx, by, split) of 256 threads, in the caller's LDS buffer of RING * gemm_tn_stage_bytes<P>().
+template <class P, int RING>
 __device__ __forceinline__ void gemm_tn_body(u32x4 *lds, const P &p, float *__restrict__ part, int rows_per_split, int bx, int by,
                                              int split) {
     constexpr int BN1 = P::BN1, BK2 = P::BK2, WX = P::WAVES_X, WY = 4 / WX;
     constexpr int TY = BN1 / (32 * WY), TX = BK2 / (32 * WX);
-    constexpr int YC = BN1 / 8, XC = BK2 / 8;          // 16-byte chunks per staged row
-    // Padding of a staged row: 64 bytes, which puts consecutive rows 64 bytes apart modulo 256 (rows are multiples of
-    // 128 bytes).  A transposing read takes 64 contiguous bytes of each of four consecutive rows: with 16 bytes of
-    // padding 54 % of the LDS-active cycles were bank conflicts, with 32 bytes 33 %, with 64 none (measured).
-    constexpr int YROW = YC + TN_PAD, XROW = XC + TN_PAD;        // padded LDS row, in u32x4
-    static_assert(YC % 8 == 0 && XC % 8 == 0, "rows of whole 128 bytes");
-    constexpr int Y_CH = 64 * YC / 256, X_CH = 64 * XC / 256;
-    static_assert(TY >= 1 && TX >= 1 && Y_CH >= 1 && X_CH >= 1, "tile shape");
-    constexpr int BIAS_SCRATCH = (256 / YC) * BN1 * 4;   // bytes: one partial bias sum per thread and column
-    constexpr bool SCRATCH_IN_Y = BIAS_SCRATCH <= 64 * YROW * 16;
-    static_assert(256 % YC == 0 && (SCRATCH_IN_Y || BIAS_SCRATCH <= 64 * XROW * 16), "bias-gradient scratch");
+    constexpr int YB = BN1 * 2, XB = BK2 * 2, Y_BYTES = TN_ROWS * YB, STAGE = gemm_tn_stage_bytes<P>();
+    constexpr int YC = YB / 16, XC = XB / 16;                    // 16-byte words per row
+    constexpr int Y_COPIES = Y_BYTES / 4096, X_COPIES = TN_ROWS * XB / 4096, COPIES = Y_COPIES + X_COPIES;   // per wavefront
+    static_assert(RING >= 3 && RING <= 5 && YB % 128 == 0 && XB % 128 == 0, "slots; rows of whole 128 bytes");
+    static_assert(TY >= 1 && TX >= 1 && Y_COPIES >= 1 && X_COPIES >= 1, "tile shape");
+    static_assert(256 % YC == 0 && (256 / YC) * BN1 * 4 <= RING * STAGE, "bias-gradient scratch");
 
-    u32x4 *const sY = lds, *const sX = lds + 64 * YROW;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wx = wave % WX, wy = wave / WX;
     const int x0 = bx * BK2, y0 = by * BN1;
-    const long m_begin = (long)split * rows_per_split;
-    long m_end = m_begin + rows_per_split;
-    if (m_end > p.M) m_end = p.M;
+    const int m_begin = split * rows_per_split, m_end = min(m_begin + rows_per_split, p.M);
+    const int stages = m_begin < m_end ? (m_end - m_begin + TN_ROWS - 1) / TN_ROWS : 0;
+    const uint32_t lds0 = lds_offset(lds);
+    char *const lds_bytes = reinterpret_cast<char *>(lds);
 
-    u32x4 ry[Y_CH], rx[X_CH];
-    auto gload = [&](long mt) __attribute__((always_inline)) {
+    // copies of the stage of rows mt .. mt+31 into slot `slot`; rows past the end repeat the last one
+    auto copy_stage = [&](int mt, int slot) __attribute__((always_inline)) {
+        const int last = m_end - 1 - mt;
+        const uint32_t to = lds0 + slot * STAGE;
+        const char *y = reinterpret_cast<const char *>(p.dy + (size_t)mt * p.N1 + y0);
+        const char *x = p.xbase(mt);
 #pragma unroll
-        for (int i = 0; i < Y_CH; ++i) {
-            const int c = tid + 256 * i, r = c / YC, cc = c % YC;
-            const long m = mt + r;
-            ry[i] = p.loady(m < m_end ? m : m_begin, y0 + cc * 8);   // clamped; zeroed when staged
+        for (int i = 0; i < Y_COPIES; ++i) {
+            const int at = wave * Y_COPIES + i, w = at * 64 + lane, r = w / YC, c = (w % YC) ^ tn_swizzle<YB>(r);
+            copy_to_lds(y, (uint32_t)(min(r, last) * p.N1 * 2 + c * 16), to + at * 1024);
         }
 #pragma unroll
-        for (int i = 0; i < X_CH; ++i) {
-            const int c = tid + 256 * i, r = c / XC, cc = c % XC;
-            const long m = mt + r;
-            rx[i] = p.loadx(p.xrow(m < m_end ? m : m_begin), x0 + cc * 8);
+        for (int i = 0; i < X_COPIES; ++i) {
+            const int at = wave * X_COPIES + i, w = at * 64 + lane, r = w / XC, c = (w % XC) ^ tn_swizzle<XB>(r);
+            copy_to_lds(x, p.xoff(min(r, last), x0 + c * 8), to + Y_BYTES + at * 1024);
         }
     };
 
@@ -530,45 +523,55 @@ __device__ __forceinline__ void gemm_tn_body(u32x4 *lds, const P &p, float *__re
         for (int b = 0; b < TX; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    // bias gradient (column sums of dY), kept by the workgroups of the first tile column: a thread always
-    // stages the same eight dY columns (256 is a multiple of YC), so it adds what it stages, in fp32
+    // bias gradient (column sums of dY), kept by the workgroups of the first tile column: a thread takes the same eight
+    // dY columns of every stage (256 is a multiple of YC) and adds them in fp32
     float bs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const bool keeps_bias = bx == 0;
 
-    if (m_begin < m_end) gload(m_begin);
-    for (long mt = m_begin; mt < m_end; mt += 64) {
+#pragma unroll
+    for (int s = 0; s < RING - 1; ++s)
+        if (s < stages) copy_stage(m_begin + s * TN_ROWS, s);
+    int slot = 0;
+    for (int s = 0; s < stages; ++s) {
+        // stage s has arrived when only the copies of the stages issued after it are outstanding
+        const int after = min(stages - 1 - s, RING - 2);
+        if (after >= 3) wait_vmem<(RING > 4 ? 3 : 0) * COPIES>();
+        else if (after == 2) wait_vmem<(RING > 3 ? 2 : 0) * COPIES>();
+        else if (after == 1) wait_vmem<COPIES>();
+        else wait_vmem<0>();
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < Y_CH; ++i) {
-            const int c = tid + 256 * i;
-            const u32x4 v = keep_or_zero(ry[i], mt + c / YC < m_end);   // rows past the end of the range: zero
-            sY[(c / YC) * YROW + c % YC] = v;
-            if (keeps_bias) {
-                const bf16x8 f = as_bf16x8(v);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) bs[e] += (float)f[e];
-            }
+        const int mt = m_begin + s * TN_ROWS;
+        // everyone has read the stage before: its slot takes the next copies
+        if (s + RING - 1 < stages) copy_stage(mt + (RING - 1) * TN_ROWS, slot == 0 ? RING - 1 : slot - 1);
+        char *const sY = lds_bytes + slot * STAGE, *const sX = sY + Y_BYTES;
+        if (mt + TN_ROWS > m_end) {                              // the last stage: rows past the end are zero
+            for (int w = (m_end - mt) * YC + tid; w < TN_ROWS * YC; w += 256) reinterpret_cast<u32x4 *>(sY)[w] = zero_u4();
+            for (int w = (m_end - mt) * XC + tid; w < TN_ROWS * XC; w += 256) reinterpret_cast<u32x4 *>(sX)[w] = zero_u4();
+            __syncthreads();
         }
 #pragma unroll
-        for (int i = 0; i < X_CH; ++i) {
-            const int c = tid + 256 * i;
-            sX[(c / XC) * XROW + c % XC] = keep_or_zero(rx[i], mt + c / XC < m_end);
-        }
-        __syncthreads();
-        if (mt + 64 < m_end) gload(mt + 64);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
+        for (int kk = 0; kk < TN_ROWS / 16; ++kk) {
             bf16x8 fy[TY], fx[TX];
 #pragma unroll
-            for (int a = 0; a < TY; ++a) fy[a] = tr_fragment(sY, YROW, kk * 16, (wy * TY + a) * 32, lane);
+            for (int a = 0; a < TY; ++a) fy[a] = tr_fragment<YB>(sY, kk * 16, (wy * TY + a) * 32, lane);
 #pragma unroll
-            for (int b = 0; b < TX; ++b) fx[b] = tr_fragment(sX, XROW, kk * 16, (wx * TX + b) * 32, lane);
+            for (int b = 0; b < TX; ++b) fx[b] = tr_fragment<XB>(sX, kk * 16, (wx * TX + b) * 32, lane);
 #pragma unroll
             for (int a = 0; a < TY; ++a)
 #pragma unroll
                 for (int b = 0; b < TX; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[a], fx[b], acc[a][b], 0, 0, 0);
         }
+        if (keeps_bias) {
+#pragma unroll
+            for (int i = 0; i < TN_ROWS * YC / 256; ++i) {
+                const int w = tid + 256 * i, r = w / YC;
+                const bf16x8 f = as_bf16x8(reinterpret_cast<const u32x4 *>(sY)[w ^ tn_swizzle<YB>(r)]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) bs[e] += (float)f[e];
+            }
+        }
+        slot = slot == RING - 1 ? 0 : slot + 1;
     }
 
     float *out = part + (size_t)split * ((size_t)p.N1 * p.KP + p.N1);
@@ -587,7 +590,7 @@ __device__ __forceinline__ void gemm_tn_body(u32x4 *lds, const P &p, float *__re
     if (keeps_bias) {
         // the 256/YC threads that share a column add their sums in thread order
         __syncthreads();
-        float *scr = reinterpret_cast<float *>(SCRATCH_IN_Y ? sY : sX);
+        float *scr = reinterpret_cast<float *>(lds);
 #pragma unroll
         for (int e = 0; e < 8; ++e) scr[(tid / YC) * BN1 + (tid % YC) * 8 + e] = bs[e];
         __syncthreads();

@@ -154,41 +154,28 @@ struct FcDgradT {
 
 // --------------------------- weight gradients -----------------------------
 // part[n][k] = sum_m dY[m][n] act(m,k); dY is a dense [M][N1] bf16 matrix.
-template <class Gather, int BN1_, int BK2_, int WAVES_X_, int N1_, int KP_>
-struct Wgrad : Gather {
-    static constexpr int BN1 = BN1_, BK2 = BK2_, WAVES_X = WAVES_X_, N1 = N1_, KP = KP_;
-    const __bf16 *dy;
-    __device__ __forceinline__ typename Gather::Row xrow(long m) const { return this->row_at(m); }
-    __device__ __forceinline__ u32x4 loadx(const typename Gather::Row &r, int k) const { return this->load_at(r, k); }
-    __device__ __forceinline__ u32x4 loady(long m, int n) const {
-        return *reinterpret_cast<const u32x4 *>(dy + (size_t)m * N1 + n);
-    }
-};
-// the fc layer's input, in rows or in fragment order (LastActs)
-template <int K_>
-struct LastActsGather {
-    const __bf16 *in;
+// fc layer: its input in rows or in fragment order (LastActs)
+template <int FEAT, int HIDN>
+struct FcWgrad {
+    static constexpr int BN1 = 128, BK2 = 64, WAVES_X = 2, N1 = HIDN, KP = FEAT;
+    const __bf16 *in, *dy;
     int M;
     bool frag;
-    typedef const __bf16 *Row;
-    __device__ __forceinline__ Row row_at(long m) const { return in + (frag ? (size_t)(m >> 4) * (K_ * 16) + (m & 15) * 8 : (size_t)m * K_); }
-    __device__ __forceinline__ u32x4 load_at(Row r, int k) const {   // m < M, k: multiple of 8
-        return *reinterpret_cast<const u32x4 *>(r + (frag ? (k >> 5) * FRAG_STEP + ((k & 31) >> 3) * 128 : k));
+    // m: multiple of 32, so that both orders hold rows m .. in one piece from here on
+    __device__ __forceinline__ const char *xbase(int m) const { return reinterpret_cast<const char *>(in + (size_t)m * FEAT); }
+    __device__ __forceinline__ uint32_t xoff(int r, int k) const {   // k: multiple of 8
+        return frag ? (uint32_t)((r >> 4) * (FEAT * 32) + (r & 15) * 16 + (k >> 5) * (FRAG_STEP * 2) + ((k & 31) >> 3) * 256)
+                    : (uint32_t)(r * (FEAT * 2) + k * 2);
     }
 };
 // heads: N1 (padded head rows) is a run-time value
 template <int HIDN>
 struct HeadWgrad {
     static constexpr int BN1 = 64, BK2 = 128, WAVES_X = 4, KP = HIDN;
-    const __bf16 *in;    // h [M][HIDN]
+    const __bf16 *in, *dy;    // h [M][HIDN]
     int M, N1;
-    const __bf16 *dy;
-    typedef const __bf16 *Row;
-    __device__ __forceinline__ Row xrow(long m) const { return in + (size_t)m * HIDN; }
-    __device__ __forceinline__ u32x4 loadx(Row r, int k) const { return *reinterpret_cast<const u32x4 *>(r + k); }
-    __device__ __forceinline__ u32x4 loady(long m, int n) const {
-        return *reinterpret_cast<const u32x4 *>(dy + (size_t)m * N1 + n);
-    }
+    __device__ __forceinline__ const char *xbase(int m) const { return reinterpret_cast<const char *>(in + (size_t)m * HIDN); }
+    __device__ __forceinline__ uint32_t xoff(int r, int k) const { return (uint32_t)(r * (HIDN * 2) + k * 2); }
 };
 
 }  // namespace arn

@@ -4,12 +4,12 @@
 // dW[co][k'] = sum over samples and output positions m of dY[m][co] * x(m,k').
 // The contraction index m is the slow index of both operands in memory, so both
 // MFMA fragments are taken with the transposing LDS read.  Unlike the generic
-// gemm_tn_kernel no im2col tile is built: a sample's input (converted to bf16
+// gemm_tn_body no im2col tile is built: a sample's input (converted to bf16
 // once) and its dY rows are copied to LDS with contiguous 16-byte loads, and the
 // transposing reads address the overlapping windows inside that image directly.
 // Each workgroup owns a fixed, contiguous range of samples and accumulates in
 // registers; partial results go to part[workgroup][...] and are summed in
-// workgroup order by conv_reduce_kernel, so dW is bit-reproducible.
+// workgroup order by reduce_all_kernel, so dW is bit-reproducible.
 #pragma once
 #include <type_traits>
 
