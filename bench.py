@@ -858,7 +858,7 @@ def paper_geometry_report(args, arn, wl, np, torch, net="nature"):
     (appendix "Atari Frame Processing"): 104x80 frames, 25x19 -> 12x9 -> 12x9 feature maps, fc 6912 -> 512."""
     dev, A, B, k = "cuda:0", 18, args.batch or 2048, 3
     frame, fc_in = wl.PAPER_FRAME, wl.FC_INPUTS[wl.PAPER_FRAME]
-    if net == "a3c":   # 2-convolution network: its own algorithmic flops, whatever the embedding executes
+    if net == "a3c":   # 2-convolution network: its own algorithmic flops
         macs = {"conv1": 25 * 19 * 256 * 16, "conv2": 12 * 9 * 256 * 32, "fc": wl.A3C_FC_INPUTS * 256, "head": (A + 1) * 256}
     else:
         macs = {"conv1": 25 * 19 * 256 * 32, "conv2": 12 * 9 * 512 * 64, "conv3": 12 * 9 * 576 * 64, "fc": fc_in * 512,
