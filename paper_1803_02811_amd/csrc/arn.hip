@@ -511,7 +511,21 @@ int check_update(size_t n, const arn_config *cfg, const void *w_packed, bool *re
     return ARN_OK;
 }
 inline bool unit_interval(float b) { return b >= 0.f && b < 1.f; }
-inline unsigned update_blocks(size_t n) { return (unsigned)((n + 1023) / 1024); }
+
+// One launch: the rule alone, or the rule and every packed copy of the new parameters.
+template <int RULE>
+void launch_update(const char *name, const UpdateArgs &p, bool repack, const Dims &d, void *w_packed, hipStream_t s) {
+    ProfScope ps(name, s);
+    if (!repack) {
+        hipLaunchKernelGGL(update_kernel<RULE>, dim3((unsigned)((p.n + 1023) / 1024)), dim3(256), 0, s, p);
+        return;
+    }
+    with_geometry(d, [&](auto g) {
+        typedef decltype(g) G;
+        const PackPlan<G> pl = make_pack_plan<G>(d, w_packed);
+        hipLaunchKernelGGL((update_pack_kernel<RULE, G>), dim3(update_pack_blocks(pl)), dim3(256), 0, s, pl, p);
+    });
+}
 
 }  // namespace
 
@@ -772,11 +786,7 @@ int arn_rmsprop_update(size_t n, float *theta, const float *g, float *accu, floa
     hipStream_t s = (hipStream_t)stream;
     UpdateArgs p = {};
     p.theta = theta; p.g = g; p.v = accu; p.n = (long)n; p.a = lr; p.beta2 = rho; p.eps = eps;
-    {
-        ProfScope ps("rmsprop", s);
-        hipLaunchKernelGGL(update_kernel<RULE_RMSPROP>, dim3(update_blocks(n)), dim3(256), 0, s, p);
-    }
-    if (repack) launch_pack_all(d, theta, w_packed, s);
+    launch_update<RULE_RMSPROP>("rmsprop", p, repack, d, w_packed, s);
     return launched();
 }
 
@@ -800,11 +810,7 @@ int arn_adam_update(size_t n, float *theta, const float *g, float *m, float *v, 
     UpdateArgs p = {};
     p.theta = theta; p.g = g; p.m = m; p.v = v; p.n = (long)n;
     p.a = adam_scale(t, r, beta1, beta2); p.beta1 = beta1; p.beta2 = beta2; p.eps = eps;
-    {
-        ProfScope ps("adam", s);
-        hipLaunchKernelGGL(update_kernel<RULE_ADAM>, dim3(update_blocks(n)), dim3(256), 0, s, p);
-    }
-    if (repack) launch_pack_all(d, theta, w_packed, s);
+    launch_update<RULE_ADAM>("adam", p, repack, d, w_packed, s);
     return launched();
 }
 
@@ -823,11 +829,7 @@ int arn_async_adam_local_step(size_t n, float *theta, const float *g, float *m, 
     UpdateArgs p = {};
     p.theta = theta; p.g = g; p.m = m; p.v = v; p.a_g = a_g; p.a_g2 = a_g2; p.a_s = a_s; p.n = (long)n;
     p.a = adam_scale(t, r, beta1, beta2); p.beta1 = beta1; p.beta2 = beta2; p.eps = eps;
-    {
-        ProfScope ps("adam_local", s);
-        hipLaunchKernelGGL(update_kernel<RULE_ADAM_LOCAL>, dim3(update_blocks(n)), dim3(256), 0, s, p);
-    }
-    if (repack) launch_pack_all(d, theta, w_packed, s);
+    launch_update<RULE_ADAM_LOCAL>("adam_local", p, repack, d, w_packed, s);
     return launched();
 }
 
@@ -849,11 +851,7 @@ int arn_async_adam_merge(size_t n, float *theta_c, float *m_c, float *v_c, float
     p.a_g = a_g; p.a_g2 = a_g2; p.a_s = a_s; p.n = (long)n; p.beta1 = beta1; p.beta2 = beta2;
     p.beta1_n = (float)pow((double)beta1, (double)n_local);
     p.beta2_n = (float)pow((double)beta2, (double)n_local);
-    {
-        ProfScope ps("adam_merge", s);
-        hipLaunchKernelGGL(merge_kernel, dim3(update_blocks(n)), dim3(256), 0, s, p);
-    }
-    if (repack) launch_pack_all(d, theta, w_packed, s);
+    launch_update<RULE_MERGE>("adam_merge", p, repack, d, w_packed, s);
     return launched();
 }
 

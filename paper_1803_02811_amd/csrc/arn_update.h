@@ -32,95 +32,86 @@ struct UpdateArgs {
     float beta1_n, beta2_n;        // RULE_MERGE: beta^n
 };
 
-// One element of a rule.  State goes in and out through references so that the vector and the tail path
-// share the arithmetic.
+// One element of a rule.  State goes in and out through references.  Fused products are written out, so that every kernel
+// that applies a rule rounds alike (the compiler chooses per context which product of a sum to fuse).
 template <int RULE>
 struct Elem {
     static __device__ __forceinline__ void apply(const UpdateArgs &p, float &th, float &m, float &v, float g,
                                                   float &ag, float &ag2, float &as) {
         if constexpr (RULE == RULE_RMSPROP) {
-            v = p.beta2 * v + (1.f - p.beta2) * g * g;
+            v = fmaf(p.beta2, v, (1.f - p.beta2) * g * g);
             th = th - p.a * g / sqrtf(v + p.eps);
+        } else if constexpr (RULE == RULE_MERGE) {
+            // merge of one learner's accumulated steps into the central values (third block of equations of the appendix)
+            th = th - as;
+            m = fmaf(p.beta1_n, m, (1.f - p.beta1) * ag);
+            v = fmaf(p.beta2_n, v, (1.f - p.beta2) * ag2);
+            ag = ag2 = as = 0.f;
         } else {
-            m = p.beta1 * m + (1.f - p.beta1) * g;
-            v = p.beta2 * v + (1.f - p.beta2) * g * g;
+            m = fmaf(p.beta1, m, (1.f - p.beta1) * g);
+            v = fmaf(p.beta2, v, (1.f - p.beta2) * g * g);
             const float s = p.a * m / (sqrtf(v) + p.eps);
             th = th - s;
             if constexpr (RULE == RULE_ADAM_LOCAL) {
-                ag = p.beta1 * ag + g;
-                ag2 = p.beta2 * ag2 + g * g;
+                ag = fmaf(p.beta1, ag, g);
+                ag2 = fmaf(p.beta2, ag2, g * g);
                 as = as + s;
             }
         }
     }
 };
 
+// The state of a rule at one parameter (V = float) or at four consecutive ones (V = a vector of four).  A merge reads the
+// central values and writes them to the local copies too.
+__device__ __forceinline__ float lane_of(float v, int) { return v; }
+__device__ __forceinline__ void set_lane(float &v, int, float x) { v = x; }
+template <class V> __device__ __forceinline__ float lane_of(const V &v, int e) { return v[e]; }
+template <class V> __device__ __forceinline__ void set_lane(V &v, int e, float x) { v[e] = x; }
+template <int RULE, class V>
+struct RuleState {
+    static constexpr bool MOMENT = RULE != RULE_RMSPROP, ACCU = RULE == RULE_ADAM_LOCAL || RULE == RULE_MERGE;
+    static constexpr bool CENTRAL = RULE == RULE_MERGE;
+    V th, m, v, g, ag, ag2, as;
+    static __device__ __forceinline__ V get(const float *a, long i) { return *(const V *)(a + i); }
+    static __device__ __forceinline__ void put(float *a, long i, const V &x) { *(V *)(a + i) = x; }
+    __device__ __forceinline__ void load(const UpdateArgs &p, long i) {
+        th = get(CENTRAL ? p.theta_c : p.theta, i);
+        v = get(CENTRAL ? p.v_c : p.v, i);
+        m = g = ag = ag2 = as = V{};
+        if constexpr (!CENTRAL) g = get(p.g, i);
+        if constexpr (MOMENT) m = get(CENTRAL ? p.m_c : p.m, i);
+        if constexpr (ACCU) { ag = get(p.a_g, i); ag2 = get(p.a_g2, i); as = get(p.a_s, i); }
+    }
+    __device__ __forceinline__ void step_and_store(const UpdateArgs &p, long i) {
+#pragma unroll
+        for (int e = 0; e < (int)(sizeof(V) / 4); ++e) {
+            float t = lane_of(th, e), mm = lane_of(m, e), vv = lane_of(v, e);
+            float x = lane_of(ag, e), y = lane_of(ag2, e), z = lane_of(as, e);
+            Elem<RULE>::apply(p, t, mm, vv, lane_of(g, e), x, y, z);
+            set_lane(th, e, t); set_lane(m, e, mm); set_lane(v, e, vv);
+            set_lane(ag, e, x); set_lane(ag2, e, y); set_lane(as, e, z);
+        }
+        if constexpr (CENTRAL) { put(p.theta_c, i, th); put(p.m_c, i, m); put(p.v_c, i, v); }
+        put(p.theta, i, th);
+        put(p.v, i, v);
+        if constexpr (MOMENT) put(p.m, i, m);
+        if constexpr (ACCU) { put(p.a_g, i, ag); put(p.a_g2, i, ag2); put(p.a_s, i, as); }
+    }
+};
+
 template <int RULE>
 __global__ __launch_bounds__(256) void update_kernel(UpdateArgs p) {
-    const long q = (long)blockIdx.x * 256 + threadIdx.x;   // group of four
-    const long i0 = q * 4;
-    if (i0 >= p.n) return;
+    const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;   // four parameters
     if (i0 + 4 <= p.n) {
-        f32x4u th = *(const f32x4u *)(p.theta + i0), g = *(const f32x4u *)(p.g + i0);
-        f32x4u v = *(const f32x4u *)(p.v + i0), m = 0.f, ag = 0.f, ag2 = 0.f, as = 0.f;
-        if constexpr (RULE != RULE_RMSPROP) m = *(const f32x4u *)(p.m + i0);
-        if constexpr (RULE == RULE_ADAM_LOCAL) {
-            ag = *(const f32x4u *)(p.a_g + i0);
-            ag2 = *(const f32x4u *)(p.a_g2 + i0);
-            as = *(const f32x4u *)(p.a_s + i0);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float t = th[e], mm = m[e], vv = v[e], x = ag[e], y = ag2[e], z = as[e];
-            Elem<RULE>::apply(p, t, mm, vv, g[e], x, y, z);
-            th[e] = t; m[e] = mm; v[e] = vv; ag[e] = x; ag2[e] = y; as[e] = z;
-        }
-        *(f32x4u *)(p.theta + i0) = th;
-        *(f32x4u *)(p.v + i0) = v;
-        if constexpr (RULE != RULE_RMSPROP) *(f32x4u *)(p.m + i0) = m;
-        if constexpr (RULE == RULE_ADAM_LOCAL) {
-            *(f32x4u *)(p.a_g + i0) = ag;
-            *(f32x4u *)(p.a_g2 + i0) = ag2;
-            *(f32x4u *)(p.a_s + i0) = as;
-        }
-    } else {
-        for (long i = i0; i < p.n; ++i) {
-            float t = p.theta[i], vv = p.v[i], mm = 0.f, x = 0.f, y = 0.f, z = 0.f;
-            if constexpr (RULE != RULE_RMSPROP) mm = p.m[i];
-            if constexpr (RULE == RULE_ADAM_LOCAL) { x = p.a_g[i]; y = p.a_g2[i]; z = p.a_s[i]; }
-            Elem<RULE>::apply(p, t, mm, vv, p.g[i], x, y, z);
-            p.theta[i] = t; p.v[i] = vv;
-            if constexpr (RULE != RULE_RMSPROP) p.m[i] = mm;
-            if constexpr (RULE == RULE_ADAM_LOCAL) { p.a_g[i] = x; p.a_g2[i] = y; p.a_s[i] = z; }
-        }
+        RuleState<RULE, f32x4u> x;
+        x.load(p, i0);
+        x.step_and_store(p, i0);
+        return;
     }
-}
-
-// Merge of one learner's accumulated steps into the central values; the local copies take the new
-// central values and the accumulators are cleared (third block of equations of the appendix).
-__global__ __launch_bounds__(256) void merge_kernel(UpdateArgs p) {
-    const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i0 >= p.n) return;
-    const float c1 = 1.f - p.beta1, c2 = 1.f - p.beta2;
-    if (i0 + 4 <= p.n) {
-        const f32x4u th = *(const f32x4u *)(p.theta_c + i0) - *(const f32x4u *)(p.a_s + i0);
-        const f32x4u m = p.beta1_n * *(const f32x4u *)(p.m_c + i0) + c1 * *(const f32x4u *)(p.a_g + i0);
-        const f32x4u v = p.beta2_n * *(const f32x4u *)(p.v_c + i0) + c2 * *(const f32x4u *)(p.a_g2 + i0);
-        const f32x4u zero = 0.f;
-        *(f32x4u *)(p.theta_c + i0) = th; *(f32x4u *)(p.theta + i0) = th;
-        *(f32x4u *)(p.m_c + i0) = m; *(f32x4u *)(p.m + i0) = m;
-        *(f32x4u *)(p.v_c + i0) = v; *(f32x4u *)(p.v + i0) = v;
-        *(f32x4u *)(p.a_g + i0) = zero; *(f32x4u *)(p.a_g2 + i0) = zero; *(f32x4u *)(p.a_s + i0) = zero;
-    } else {
-        for (long i = i0; i < p.n; ++i) {
-            const float th = p.theta_c[i] - p.a_s[i];
-            const float m = p.beta1_n * p.m_c[i] + c1 * p.a_g[i];
-            const float v = p.beta2_n * p.v_c[i] + c2 * p.a_g2[i];
-            p.theta_c[i] = th; p.theta[i] = th;
-            p.m_c[i] = m; p.m[i] = m;
-            p.v_c[i] = v; p.v[i] = v;
-            p.a_g[i] = 0.f; p.a_g2[i] = 0.f; p.a_s[i] = 0.f;
-        }
+    for (long i = i0; i < p.n; ++i) {
+        RuleState<RULE, float> x;
+        x.load(p, i);
+        x.step_and_store(p, i);
     }
 }
 
@@ -152,6 +143,7 @@ constexpr int PACK_FC_MAX_P3 = 108;   // 12 x 9 positions after conv3 on 104 x 8
 constexpr int PACK_FC_LDS_ROW = PACK_FC_CH * PACK_FC_MAX_P3 + 8;
 static_assert(P3 <= PACK_FC_MAX_P3 && GeoPaper::P3 <= PACK_FC_MAX_P3, "fc tile buffer");
 static_assert(PACK_FC_CH == 8 && PACK_FC_ROWS % 8 == 0, "fc tile shape");
+typedef float PackTile[PACK_FC_ROWS][PACK_FC_LDS_ROW];
 template <class G>
 struct PackPlan {
     PackSeg seg[PK_COUNT];
@@ -210,27 +202,35 @@ inline PackPlan<G> make_pack_plan(const Dims &d, void *w_packed) {
 // One fc tile: hidden units n0 .. n0 + PACK_FC_ROWS - 1, channels c0 .. c0 + PACK_FC_CH - 1.
 // Flat order Wfc[n][c * P + pos]; forward layout [n][pos * NC + c]; input-gradient layout [pos * NC + c][n].
 template <class G>
-__device__ __forceinline__ void pack_fc_tile(const PackPlan<G> &pl, const float *__restrict__ w, int tile,
-                                             float (&s_t)[PACK_FC_ROWS][PACK_FC_LDS_ROW]) {
-    constexpr int p3 = G::PL, NC = G::NCL, feat = G::FEAT, run = PACK_FC_CH * p3;
-    static_assert(G::NHID % PACK_FC_ROWS == 0 && NC % PACK_FC_CH == 0 && p3 <= PACK_FC_MAX_P3, "fc tile shape");
-    constexpr int NL = (PACK_FC_ROWS * run + 255) / 256;
-    const int n0 = (tile / (NC / PACK_FC_CH)) * PACK_FC_ROWS, c0 = (tile % (NC / PACK_FC_CH)) * PACK_FC_CH;
+struct PackFcTile {
+    static constexpr int RUN = PACK_FC_CH * G::PL, CT = G::NCL / PACK_FC_CH;   // floats per hidden unit; tiles per hidden unit
+    static_assert(G::NHID % PACK_FC_ROWS == 0 && G::NCL % PACK_FC_CH == 0 && G::PL <= PACK_FC_MAX_P3, "fc tile shape");
+    int n0, c0;
+    __device__ __forceinline__ explicit PackFcTile(int tile) : n0(tile / CT * PACK_FC_ROWS), c0(tile % CT * PACK_FC_CH) {}
+    // offset in the matrix of float e of row r
+    __device__ __forceinline__ long at(int r, int e) const { return (long)(n0 + r) * G::FEAT + (long)c0 * G::PL + e; }
+};
+template <class G>
+__device__ __forceinline__ void pack_fc_read(const PackPlan<G> &pl, const float *__restrict__ w, PackFcTile<G> f, PackTile &s_t) {
+    constexpr int run = PackFcTile<G>::RUN, NL = (PACK_FC_ROWS * run + 255) / 256;
     const int tid = threadIdx.x;
     float v_in[NL];   // all loads of the tile in flight before the first is used
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
         int i = tid + 256 * j;
         i = i < PACK_FC_ROWS * run ? i : PACK_FC_ROWS * run - 1;
-        const int r = i / run, e = i - r * run;
-        v_in[j] = w[pl.wfc + (long)(n0 + r) * feat + (long)c0 * p3 + e];
+        v_in[j] = w[pl.wfc + f.at(i / run, i % run)];
     }
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
         const int i = tid + 256 * j;
         if (i < PACK_FC_ROWS * run) s_t[i / run][i % run] = v_in[j];
     }
-    __syncthreads();
+}
+template <class G>
+__device__ __forceinline__ void pack_fc_write(const PackPlan<G> &pl, PackFcTile<G> f, const PackTile &s_t) {
+    constexpr int p3 = G::PL, NC = G::NCL, feat = G::FEAT, run = PackFcTile<G>::RUN;
+    const int n0 = f.n0, c0 = f.c0, tid = threadIdx.x;
     // forward layout: one 16-byte word = channels c0 .. c0+7 of (row r, position pos)
     // (fragment order, frag_index: the eight rows' words are neighbours)
     for (int i = tid; i < PACK_FC_ROWS * p3; i += 256) {
@@ -264,9 +264,11 @@ __device__ __forceinline__ void pack_fc_tile(const PackPlan<G> &pl, const float 
 template <class G>
 __global__ __launch_bounds__(256) void pack_all_kernel(const PackPlan<G> pl, const float *__restrict__ w) {
     if ((int)blockIdx.x >= pl.fc_first_block) {
-        __shared__ float s_t[PACK_FC_ROWS][PACK_FC_LDS_ROW];
-        const int tile = (int)blockIdx.x - pl.fc_first_block;
-        pack_fc_tile<G>(pl, w, tile, s_t);
+        __shared__ PackTile s_t;
+        const PackFcTile<G> f((int)blockIdx.x - pl.fc_first_block);
+        pack_fc_read<G>(pl, w, f, s_t);
+        __syncthreads();
+        pack_fc_write<G>(pl, f, s_t);
         return;
     }
     int k = 0;
@@ -313,6 +315,142 @@ __global__ __launch_bounds__(256) void pack_all_kernel(const PackPlan<G> pl, con
         if (out_lo) ((__bf16 *)out_lo)[o] = (__bf16)(v - (float)hi);
         if (out_f16) ((_Float16 *)out_f16)[o] = to_f16_finite(v);
     }
+}
+
+// ------------------------- a rule and every packed layout in one launch -------------------------
+// An update with a re-pack: whoever updates a parameter also writes its packed copies, so the new values are not read back
+// and there is one launch instead of two (a boundary costs about 4 us here, the read of theta 2).  Three ranges of
+// workgroups: fc tiles as above; eight head rows each (through LDS: the forward layouts want eight neighbouring inputs in a
+// 16-byte word, the input-gradient layout eight neighbouring rows); the convolutions and the fc bias, one parameter a thread.
+// Bound by HBM: 28 bytes of state a parameter with Adam and 8 bytes of packed copies.  Adam on the categorical network (2.2 M
+// parameters): 14.5 us, 4.5 TB/s of state, against 23.2 for rule and re-pack as two launches.
+constexpr int PACK_HEAD_ROWS = PACK_FC_ROWS;
+typedef float f32x4p __attribute__((ext_vector_type(4), aligned(4)));   // the value row starts at any parameter
+template <class G>
+inline int update_pack_blocks(const PackPlan<G> &pl) {
+    return G::NHID / PACK_FC_ROWS * PackFcTile<G>::CT + pl.NHP / PACK_HEAD_ROWS + (int)((pl.wfc + G::NHID + 255) / 256);
+}
+
+// The packed copies of parameter i of the convolutions and the fc bias, the inverse of the Map* structs.
+template <class G>
+__device__ __forceinline__ void scatter_packed(const PackPlan<G> &pl, long i, float v) {
+    auto matrix = [&](int seg, long at) {
+        const __bf16 hi = (__bf16)v;
+        ((__bf16 *)pl.seg[seg].out)[at] = hi;
+        if (pl.seg[seg].out_lo) ((__bf16 *)pl.seg[seg].out_lo)[at] = (__bf16)(v - (float)hi);
+        if (pl.seg[seg].out_f16) ((_Float16 *)pl.seg[seg].out_f16)[at] = to_f16_finite(v);
+    };
+    if (i >= pl.bfc) { ((float *)pl.seg[PK_BFC].out)[i - pl.bfc] = v; return; }
+    if constexpr (G::HAS3) {
+        if (i >= pl.b3) { ((float *)pl.seg[PK_B3].out)[i - pl.b3] = v; return; }
+        if (i >= pl.w3) {
+            const int e = (int)(i - pl.w3), co = e / KW3, ci = e % KW3 / (K3 * K3), ky = e % (K3 * K3) / K3, kx = e % K3;
+            matrix(PK_W3, frag_index(co, (ky * K3 + kx) * C2 + ci, KW3));
+            matrix(PK_W3D, frag_index(ci, ((K3 - 1 - ky) * K3 + K3 - 1 - kx) * 64 + co, KW3));
+            return;
+        }
+    }
+    if (i >= pl.b2) { ((float *)pl.seg[PK_B2].out)[i - pl.b2] = v; return; }
+    if (i >= pl.w2) {
+        const int e = (int)(i - pl.w2), co = e / G::KW2, ci = e % G::KW2 / (K2 * K2), ky = e % (K2 * K2) / K2, kx = e % K2;
+        const int z = (ky & 1) * 2 + (kx & 1), tap = (1 - (ky >> 1)) * 2 + 1 - (kx >> 1);
+        matrix(PK_W2, frag_index(co, (ky * K2 + kx) * G::NC1 + ci, G::KW2));
+        matrix(PK_W2D, frag_index(z * G::NC1 + ci, tap * G::NC2 + co, 4 * G::NC2));
+        return;
+    }
+    if (i >= pl.b1) { ((float *)pl.seg[PK_B1].out)[i - pl.b1] = v; return; }
+    matrix(PK_W1, frag_index(i / KW1, i % KW1, KW1));
+}
+
+template <int RULE, class G>
+__global__ __launch_bounds__(256) void update_pack_kernel(const PackPlan<G> pl, const UpdateArgs p) {
+    __shared__ alignas(16) PackTile s_t;
+    constexpr int AHEAD = RuleState<RULE, float>::ACCU ? 2 : 4;   // groups whose loads are in flight: 16 or 12 to 14 registers each
+    const int tid = threadIdx.x;
+    int b = blockIdx.x;
+    constexpr int FC_TILES = G::NHID / PACK_FC_ROWS * PackFcTile<G>::CT;
+    if (b < FC_TILES) {
+        const PackFcTile<G> f(b);
+        constexpr int R4 = PackFcTile<G>::RUN / 4, N4 = PACK_FC_ROWS * R4;   // groups of four parameters
+        static_assert(PackFcTile<G>::RUN % 4 == 0 && G::FEAT % 4 == 0 && PACK_FC_LDS_ROW % 4 == 0, "16-byte groups");
+#pragma unroll
+        for (int j0 = 0; j0 * 256 < N4; j0 += AHEAD) {
+            RuleState<RULE, f32x4u> x[AHEAD];
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) {
+                const int q = tid + 256 * (j0 + j);
+                if (q < N4) x[j].load(p, pl.wfc + f.at(q / R4, 4 * (q % R4)));
+            }
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) {
+                const int q = tid + 256 * (j0 + j);
+                if (q >= N4) continue;
+                x[j].step_and_store(p, pl.wfc + f.at(q / R4, 4 * (q % R4)));
+                *(f32x4u *)&s_t[q / R4][4 * (q % R4)] = x[j].th;
+            }
+        }
+        __syncthreads();
+        pack_fc_write<G>(pl, f, s_t);
+        return;
+    }
+    b -= FC_TILES;
+    if (b < pl.NHP / PACK_HEAD_ROWS) {
+        constexpr int R4 = G::NHID / 4, N4 = PACK_HEAD_ROWS * R4;
+        static_assert(N4 % 256 == 0 && G::NHID <= PACK_FC_LDS_ROW, "head tile shape");
+        const int r0 = b * PACK_HEAD_ROWS;
+#pragma unroll
+        for (int j = 0; j < N4 / 256; ++j) {
+            const int q = tid + 256 * j, r = q / R4, e = 4 * (q % R4);
+            const long row = pl.hr.wrow(r0 + r);
+            f32x4u th = 0.f;     // rows past the last are zeros in the packed matrix
+            if (row >= 0) {
+                RuleState<RULE, f32x4p> x;
+                x.load(p, row + e);
+                x.step_and_store(p, row + e);
+                th = x.th;
+            }
+            *(f32x4u *)&s_t[r][e] = th;
+        }
+        if (tid < PACK_HEAD_ROWS) {
+            const long at = pl.hr.brow(r0 + tid);
+            RuleState<RULE, float> x;
+            x.th = 0.f;
+            if (at >= 0) {
+                x.load(p, at);
+                x.step_and_store(p, at);
+            }
+            ((float *)pl.seg[PK_BH].out)[r0 + tid] = x.th;
+        }
+        __syncthreads();
+        for (int i = tid; i < PACK_HEAD_ROWS * (G::NHID / 8); i += 256) {
+            const int r = i % PACK_HEAD_ROWS, k = i / PACK_HEAD_ROWS * 8;
+            bf16x8 hi, lo;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float v = s_t[r][k + c];
+                hi[c] = (__bf16)v;
+                lo[c] = (__bf16)(v - (float)hi[c]);
+            }
+            const long at = frag_index(r0 + r, k, G::NHID);
+            *reinterpret_cast<bf16x8 *>((__bf16 *)pl.seg[PK_WH].out + at) = hi;
+            *reinterpret_cast<bf16x8 *>((__bf16 *)pl.seg[PK_WH].out_lo + at) = lo;
+        }
+        for (int k = tid; k < G::NHID; k += 256) {
+            bf16x8 hi;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) hi[r] = (__bf16)s_t[r][k];
+            *reinterpret_cast<bf16x8 *>((__bf16 *)pl.seg[PK_WHD].out + frag_index(k, r0, pl.NHP)) = hi;
+        }
+        return;
+    }
+    b -= pl.NHP / PACK_HEAD_ROWS;
+    long i = (long)b * 256 + tid;
+    if (i >= pl.wfc + G::NHID) return;
+    if (i >= pl.wfc) i += pl.bfc - pl.wfc;
+    RuleState<RULE, float> x;
+    x.load(p, i);
+    x.step_and_store(p, i);
+    scatter_packed<G>(pl, i, x.th);
 }
 
 }  // namespace arn

@@ -158,6 +158,45 @@ def test_update_with_repack_matches_separate_prepare(head):
         assert torch.equal(packed, want), rule
 
 
+@pytest.mark.parametrize("rule", ["rmsprop", "adam", "adam_local", "adam_merge"])
+@pytest.mark.parametrize("geometry,head,actions", [("84", "duel", 5), ("84", "q", 3), ("84", "c51", 1), ("paper", "pv", 18),
+                                                   ("paper", "c51", 7), ("a3c", "pv", 4), ("a3c", "q", 18), ("a3c", "c51", 18)])
+def test_update_with_repack_is_the_update_and_the_repack(geometry, head, actions, rule):
+    """Every parameter is updated once and has all its packed copies: state, bit for bit, as the rule alone leaves it, and
+    the blob as arn_weights_prepare makes it, what is no copy of a parameter (gaps) untouched."""
+    cfg = arn.Config(num_actions=actions, head_kind=arn.HEAD_KINDS[head], num_atoms=51, geometry=arn.GEOMETRIES[geometry])
+    n = arn.param_count(cfg)
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    names = ["theta", "m", "v"] + (["a_g", "a_g2", "a_s"] if rule.startswith("adam_") else [])
+    if rule == "rmsprop":
+        names = ["theta", "accu"]
+    if rule == "adam_merge":
+        names = ["theta_c", "m_c", "v_c"] + names
+    start = {k: torch.rand(n, generator=gen, device=DEV) for k in names}
+    g = torch.randn(n, generator=gen, device=DEV)
+
+    def step(s, **pack):
+        if rule == "rmsprop":
+            arn.rmsprop_update(s["theta"], g, s["accu"], lr=1e-3, rho=0.99, eps=1e-6, **pack)
+        elif rule == "adam":
+            arn.adam_update(s["theta"], g, s["m"], s["v"], t=3, r=1e-3, beta1=0.9, beta2=0.999, eps=1e-5, **pack)
+        elif rule == "adam_local":
+            arn.async_adam_local_step(*[s["theta"], g, s["m"], s["v"], s["a_g"], s["a_g2"], s["a_s"]], t=3, r=1e-3, beta1=0.9,
+                                      beta2=0.999, eps=1e-5, **pack)
+        else:
+            arn.async_adam_merge(*[s[k] for k in names], n_local=3, beta1=0.9, beta2=0.999, **pack)
+
+    alone, both = ({k: x.clone() for k, x in start.items()} for _ in range(2))
+    blobs = [torch.full((arn.packed_bytes(cfg),), 0xA5, dtype=torch.uint8, device=DEV) for _ in range(2)]
+    step(alone)
+    arn.weights_prepare(cfg, alone["theta"], blobs[0])
+    step(both, cfg=cfg, w_packed=blobs[1])
+    torch.cuda.synchronize()
+    for k in names:
+        assert torch.equal(alone[k], both[k]), k
+    assert torch.equal(*blobs)
+
+
 def test_one_learner_iteration_gradient_update_gradient():
     """Steps 1-3 of the synchronous procedure on one GPU: gradient, Adam update with repack, gradient again,
     against the same chain in the oracle."""
