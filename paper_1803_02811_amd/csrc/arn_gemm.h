@@ -147,9 +147,14 @@ __device__ __forceinline__ void wait_global_loads() { __builtin_amdgcn_s_waitcnt
 // Copies 16 bytes per lane from base + voff (base wavefront-uniform) to LDS byte offset lds_off + 16 * lane (lds_off
 // wavefront-uniform), without passing through registers.  It counts as a vector memory operation (wait_global_loads, vmcnt);
 // the compiler does not know of it, so the caller waits before the data is read and before the kernel ends.
+// m0 holds the LDS offset and is lost: a value the compiler has put there is set again before its next use.  (The warning is
+// that the compiler does not save a reserved register around the statement, which nothing here asks of it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_to_lds(const void *base, uint32_t voff, uint32_t lds_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ uint32_t lds_offset(const void *p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
 }

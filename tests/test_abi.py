@@ -229,3 +229,18 @@ def test_static_scratch_entry_point_rejects_on_the_host(lib):
         too_big *= 2
     assert fn(c, fake, fake, too_big, fake, fake, None, None, None) == -7
     assert b"static" in lib.arn_status_string(-7)
+
+
+def test_inline_assembly_declares_the_registers_it_writes():
+    """A fixed register named as the first operand of an instruction in an asm statement is written there, so the statement
+    lists it as clobbered: the compiler may otherwise keep a value of its own in it across the statement."""
+    csrc = os.path.join(ROOT, "paper_1803_02811_amd", "csrc")
+    statements = 0
+    for f in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, f)).read()
+        for m in re.finditer(r'asm volatile\(("(?:[^"\\]|\\.)*")(.*?)\);', text, re.S):
+            statements += 1
+            written = {r for r in re.findall(r'(?:"|\\n|\\t)\s*[a-z]\w*\s+(m0|vcc|exec|scc|[sv]\d+)\s*,', m.group(1))}
+            clobbered = set(re.findall(r'"(\w+)"', m.group(2).rsplit(":", 1)[1]))
+            assert written <= clobbered, (f, sorted(written - clobbered))
+    assert statements
