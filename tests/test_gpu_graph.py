@@ -1,7 +1,6 @@
 """HIP-graph capture of the inference and gradient calls: every replay must equal the eager result.
 
-The library launches only kernels and (in the gradient step) event record / wait pairs between the caller's
-stream and its own side stream, all of which can be captured; it issues no memset and allocates nothing.
+The library launches only kernels, all of them on the caller's stream; it issues no memset and allocates nothing.
 Replays are interleaved with eager work and synchronisations, and each is compared bit for bit."""
 import numpy as np
 import pytest
@@ -55,8 +54,7 @@ def test_policy_forward_graph_replays_equal_eager():
 
 
 def test_train_step_graph_replays_equal_eager():
-    """The gradient step forks to and joins from the library's side stream inside the call; captured, the side
-    stream's work becomes part of the graph."""
+    """The gradient step as a graph: every launch of the call is on the caller's stream, so all of them are captured."""
     A, B = 18, 64
     net = GpuNet(A, "pv", wl.he_normal_params(A, "pv", seed=2901, bias_std=0.05))
     batches = [wl.actor_critic_batch(3, B=B), wl.actor_critic_batch(4, B=B)]

@@ -339,9 +339,9 @@ def test_saturated_frames_and_large_batch_tail(gu):
     gu.tol_check(out["value"], ref["value"], "value")
 
 
-def test_single_stream_mode_gives_the_same_bits(gu, tmp_path):
-    """ARN_SINGLE_STREAM=1 keeps every kernel on the caller's stream; the fixed summation order makes the
-    gradient bit-identical to the two-stream run.  The switch is read once per process, hence the child."""
+def test_another_process_gives_the_same_bits(gu, tmp_path):
+    """The fixed summation order makes the gradient a function of the inputs alone: another process, with a stream of its own
+    and a workspace full of not-a-numbers, gives the same bits."""
     import os
     import subprocess
     import sys
@@ -353,12 +353,16 @@ def test_single_stream_mode_gives_the_same_bits(gu, tmp_path):
     code = (
         "import sys, numpy as np\n"
         f"sys.path.insert(0, {os.path.dirname(os.path.dirname(os.path.abspath(__file__)))!r})\n"
+        "import torch\n"
         "import workloads as wl\n"
         "from tests import gpu_util as gu\n"
-        f"flat = wl.he_normal_params({A}, 'pv', 2003)\n"
-        f"dW, loss = gu.GpuNet({A}, 'pv', flat).train(wl.actor_critic_batch(3, B={B}), 'a2c')\n"
+        f"net = gu.GpuNet({A}, 'pv', wl.he_normal_params({A}, 'pv', 2003))\n"
+        f"batch = net.device_batch(wl.actor_critic_batch(3, B={B}))\n"
+        f"net.workspace({B}, 1).fill_(255)\n"
+        "torch.cuda.synchronize()\n"
+        "with torch.cuda.stream(torch.cuda.Stream()):\n"
+        "    dW, loss = net.train(None, 'a2c', dev_batch=batch)\n"
         f"np.save({str(out)!r}, np.concatenate([dW, loss]))\n")
-    env = dict(os.environ, ARN_SINGLE_STREAM="1")
-    subprocess.run([sys.executable, "-c", code], check=True, env=env, timeout=110)
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=110)
     other = np.load(out)
     assert np.array_equal(other[:-4], dW) and np.array_equal(other[-4:], loss)

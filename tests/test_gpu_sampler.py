@@ -98,8 +98,8 @@ def test_alternating_groups_match_the_oracle_and_the_single_group():
 
 
 def test_two_gradient_steps_back_to_back_on_two_streams():
-    """Two arn_train_step_grads calls issued one after the other from this thread on two caller streams (the
-    library's side stream and events are shared between them): each gives the bits of the same call made alone."""
+    """Two arn_train_step_grads calls issued one after the other from this thread on two caller streams, where they may
+    overlap: each gives the bits of the same call made alone."""
     import torch
     import paper_1803_02811_amd as arn
     from tests import gpu_util as gu
@@ -119,6 +119,6 @@ def test_two_gradient_steps_back_to_back_on_two_streams():
         for i in range(2):
             arn.train_step_grads(net.cfg, net.packed, dev[i], "a2c", dW[i], loss[i], workspace=ws[i], stream=streams[i])
         for i in range(2):
-            streams[i].synchronize()        # each caller stream alone orders the whole call, side-stream work included
+            streams[i].synchronize()        # a call's launches are all on its caller's stream
             assert np.array_equal(dW[i].cpu().numpy(), alone[i][0]), (rep, i)
             assert np.array_equal(loss[i].cpu().numpy(), alone[i][1]), (rep, i)

@@ -67,3 +67,42 @@ def test_categorical_gradients_at_tile_edges(gu, A, B):
     dW, _, ref, _ = gu.train_c51_or_dqn(gu.GpuNet(A, "c51", flat), orc, flat, tflat, batch, "c51", orc.NetSpec(A, "c51"))
     got, want = (wl.split_params(v, A, "c51") for v in (dW, ref["flat"]))
     gu.check_grads(got, want, "A=%d B=%d" % (A, B))
+
+
+# Batches whose passes without gradient run in fc_small_kernel (activations in fragment order) while the forward pass of the
+# same step, in the same workspace, runs in the tiled GEMM (activations in rows, several k ranges): both ends of that window.
+@pytest.mark.parametrize("geometry,head,B", [("84", "duel", 399), ("84", "q", 512), ("84", "c51", 450),
+                                             ("paper", "duel", 181), ("paper", "q", 361), ("paper", "c51", 300),
+                                             ("a3c", "duel", 362), ("a3c", "c51", 512)])
+def test_bootstrapped_gradients_where_both_dense_paths_meet(gu, geometry, head, B):
+    A = 7
+    frame, kw = NETS[geometry]
+    kind, double_q = ("c51", 0) if head == "c51" else ("dqn", int(head == "duel"))
+    flat, tflat = (wl.he_normal_params(A, head, seed, bias_std=0.1, **shape_of(geometry)) for seed in (2617, 3617))
+    batch = wl.c51_batch(5, B=B, frame=frame)
+    batch["action"] %= A
+    net = gu.GpuNet(A, head, flat, geometry=geometry, double_q=double_q)
+    net.workspace(B, 1).fill_(255)                 # whatever the workspace holds (here: not-a-numbers)
+    hyper = orc.Hyper(double_q=True) if double_q else None
+    dW, _, ref, _ = gu.train_c51_or_dqn(net, orc, flat, tflat, batch, kind, orc.NetSpec(A, head, **kw), hyper=hyper)
+    got, want = (wl.split_params(v, A, head, **shape_of(geometry)) for v in (dW, ref["flat"]))
+    gu.check_grads(got, want, "%s %s B=%d" % (geometry, head, B))
+
+
+# sizes on each side of the edges between bands and whole samples and between the tiles of fc_small_kernel, up to its largest
+@pytest.mark.parametrize("geometry,head,sizes", [
+    ("84", "pv", (1, 17, 36, 37, 64, 65, 128, 129, 256, 257, 512)),
+    ("84", "c51", (1, 17, 37, 129, 300, 512)),
+    ("paper", "duel", (1, 17, 21, 22, 64, 65, 129, 257, 361)),
+    ("a3c", "pv", (1, 17, 21, 22, 128, 129, 257, 512))])
+def test_outputs_do_not_depend_on_the_batch(gu, geometry, head, sizes):
+    """A sample's outputs have the same bits in every batch that fc_small_kernel serves, whatever the workspace holds."""
+    A = 7
+    flat = wl.he_normal_params(A, head, 2602, bias_std=0.1, **shape_of(geometry))
+    obs = wl.rect_frames(max(sizes), 1602, frame=NETS[geometry][0])
+    net = gu.GpuNet(A, head, flat, geometry=geometry)
+    whole = net.forward(obs)
+    for B in sizes:
+        net.workspace(B, 0).fill_(255)
+        for name, got in net.forward(obs[:B]).items():
+            assert np.array_equal(got, whole[name][:B]), (name, B)
