@@ -136,14 +136,31 @@ def roofline_of(avg_us, B, kernel_flops, kernel_bytes, bytes_per_launch, tag):
 def measured_traffic(kernel, tag):
     """HBM bytes per launch of `kernel` from the committed counter summary of this workload (written by
     `bench.py --summarise-counters`): FETCH_SIZE + WRITE_SIZE, each scaled by what the same counter reads for a
-    plain copy of known size; None if no summary covers the workload or the kernel."""
+    plain copy of known size; None if no summary covers the workload or the kernel, or if the kernels have changed since."""
     path = os.path.join(ROOT, "profiles", "%s_traffic.json" % tag)
     try:
         with open(path) as f:
             prof = json.load(f)
     except (OSError, ValueError):
         return None
+    if prof.get("kernel_sources") != kernel_sources_digest():
+        return None
     return prof.get("hbm_bytes_per_launch", {}).get(kernel)
+
+
+def kernel_sources_digest():
+    """Identifies the kernels that a stored counter summary was taken on: a hash of their sources without comments and
+    white space."""
+    import hashlib
+    import re
+    digest = hashlib.sha256()
+    csrc = os.path.join(ROOT, "paper_1803_02811_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        if name.endswith((".h", ".hip")):
+            with open(os.path.join(csrc, name)) as f:
+                text = re.sub(r"/\*.*?\*/|//[^\n]*", "", f.read(), flags=re.S)
+            digest.update((name + "\0" + "".join(text.split()) + "\0").encode())
+    return digest.hexdigest()[:16]
 
 
 def head_macs(A, head):
@@ -155,14 +172,15 @@ def flop_models(A, head):
     hm = head_macs(A, head)
     flops = dict(KERNEL_FLOPS)
     flops.update({"head_fwd": 2 * hm, "head_wgrad": 2 * hm, "head_dgrad": 2 * hm, "dense_bwd": 4 * MACS["fc"] + 2 * hm,
-                  "conv_infer": 2 * (MACS["conv1"] + MACS["conv2"] + MACS["conv3"])})
+                  "conv_infer": 2 * (MACS["conv1"] + MACS["conv2"] + MACS["conv3"]), "fc_head": 2 * MACS["fc"] + 2 * hm})
     z = 4 * (A * 51 if head == "c51" else A + 1)
     kb = dict(KERNEL_BYTES)
     kb.update({"head_fwd": ACT["h"] + z, "head_wgrad": ACT["h"] + z // 2, "head_dgrad": z // 2 + 2 * ACT["h"],
+               "fc_head": ACT["a3"] + z,                       # act3 in, head outputs out
                "conv_infer": ACT["obs"] + ACT["a3"]})          # frames in, act3 (fp16) out: nothing else leaves the chip
     per_launch = dict(KERNEL_BYTES_PER_LAUNCH)
     per_launch.update({"head_fwd": 2 * hm, "head_dgrad": 2 * hm, "head_wgrad": 4 * hm,
-                       "conv_infer": 2 * 8192 + 2 * 32768 + 2 * 36864})
+                       "conv_infer": 2 * 8192 + 2 * 32768 + 2 * 36864, "fc_head": 2 * MACS["fc"] + 4 * hm})
     return flops, kb, per_launch
 
 
@@ -387,7 +405,7 @@ def workload_report(args, arn, wl, np, torch):
         out["hbm_frac_cold"] = round((bytes_alg * B + bytes_launch) / (float(np.median(cold)) * 1e-3) / 1e9 / PEAK_HBM_GBS, 4)
         del junk
         # the same call captured once into a HIP graph and replayed (what a sampler loop that cannot afford the
-        # launch gaps of three kernels does; arn_policy_forward_static exists for callers under capture)
+        # launch gaps of the call does; arn_policy_forward_static exists for callers under capture)
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g):
             step()
@@ -438,13 +456,31 @@ def workload_report(args, arn, wl, np, torch):
 # ---------------------------------------------------------------------------
 # rocprofv3 counter CSVs -> committed summaries (no GPU needed)
 # ---------------------------------------------------------------------------
+def _instance(kernel, *args):
+    """Pattern of a kernel with these leading template arguments (integers or truth values), in the demangled form and in the
+    mangled one that rocprofv3 leaves where its demangler does not know a type."""
+    dem = ", ".join("(?:%s)" % a if isinstance(a, str) else str(a).lower() for a in args)
+    man = "".join("L[ib](?:%s)E" % a if isinstance(a, str) else "L%s%dE" % ("b" if isinstance(a, bool) else "i", a) for a in args)
+    return r"%s(?:<%s\b|I%s)" % (kernel, dem, man)
+
+
+ANY = r"\d+|true|false"
 KERNEL_NAME_PATTERNS = [   # first match wins: mangled or demangled rocprofv3 kernel name -> instrumented launch name
-    (r"conv123_fwd_kernel", "conv123_fwd"), (r"conv23_fwd_fused", "conv23_fwd"), (r"infer_conv_(pipelined_)?kernel", "conv_infer"),
-    (r"conv_backward_kernel", "conv_bwd"), (r"dense_backward_kernel", "dense_bwd"), (r"reduce_all_kernel", "reduce"), (r"conv1_fwd_resident", "conv1_fwd"), (r"ResConv2Fwd", "conv2_fwd"),
-    (r"ResConv3Fwd", "conv3_fwd"), (r"ResConv3Dgrad", "conv3_dgrad"), (r"FcFwd", "fc_fwd"), (r"FcDgrad", "fc_dgrad"),
-    (r"pv_head_kernel<true>|pv_head_kernelILb1", "pv_head"), (r"pv_head_kernel<false>|pv_head_kernelILb0", "pv_head_infer"),
-    (r"HeadFwdC51", "head_fwd"), (r"HeadDgrad", "head_dgrad"), (r"fc_finish", "fc_finish"), (r"c51_dist", "c51_dist"),
-    (r"c51_loss", "loss"), (r"pack_all", "pack_all"), (r"__amd_rocclr_copyBuffer", "copy"),
+    # kernels with one launch name; they come first because their template arguments name the layers of other launches
+    (r"conv123_fwd_kernel", "conv123_fwd"), (r"conv23_fwd_fused_kernel", "conv23_fwd"), (r"conv12_fwd_kernel", "conv12_fwd"),
+    (r"conv1_fwd_resident_kernel", "conv1_fwd"), (r"infer_conv_(pipelined_|band_)?kernel", "conv_infer"),
+    (r"conv_backward_kernel", "conv_bwd"), (r"dense_backward_kernel", "dense_bwd"), (r"reduce_all_kernel", "reduce"),
+    # one kernel, several layers
+    (r"resident_conv_kernel.*ResConv2Fwd", "conv2_fwd"), (r"resident_conv_kernel.*ResConv3Fwd", "conv3_fwd"),
+    (r"resident_conv_kernel.*ResConv3Dgrad", "conv3_dgrad"),
+    (r"gemm_nt_kernel.*FcFwd", "fc_fwd"), (r"gemm_nt_kernel.*HeadFwdC51", "head_fwd"), (r"gemm_nt_kernel.*HeadDgrad", "head_dgrad"),
+    (_instance("fc_small_kernel", ANY, ANY, ANY, ANY, ANY, 2), "fc_head"), (r"fc_small_kernel", "fc_fwd"),
+    (_instance("pv_head_kernel", True), "pv_head"), (_instance("pv_head_kernel", False), "pv_head_infer"),
+    (r"fc_finish_kernel", "fc_finish"), (r"c51_dist_kernel", "c51_dist"), (r"c51_loss_kernel", "loss"),
+    (_instance("update_(?:pack_)?kernel", 0), "rmsprop"), (_instance("update_(?:pack_)?kernel", 1), "adam"),
+    (_instance("update_(?:pack_)?kernel", 2), "adam_local"), (_instance("update_(?:pack_)?kernel", 3), "adam_merge"),
+    (r"epsilon_greedy_kernel", "epsilon_greedy"),
+    (r"pack_all_kernel", "pack_all"), (r"__amd_rocclr_copyBuffer", "copy"),
 ]
 
 
@@ -527,8 +563,7 @@ def summarise_counters(root, tag, sq):
         a = _counter_means(_find_csv(root, "sq_a", "pmc"))
         b = _counter_means(_find_csv(root, "sq_b", "pmc"))
         md = ["# %s: shader-core counters per kernel" % tag, "",
-              "Commands (one MI355X, repository root; one pass of eight SQ counters each; weight gradients kept on the "
-              "caller's stream so that dispatches do not overlap):", "",
+              "Commands (one MI355X, repository root; one pass of eight SQ counters each):", "",
               "    rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
               "    rocprofv3 --pmc SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_LDS SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INST_LEVEL_LDS -d DIR/sq_b -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
               "    python3 bench.py --summarise-counters DIR --sq --tag %s" % tag, "",
@@ -569,7 +604,7 @@ def summarise_counters(root, tag, sq):
         rows.append((n, f_kib, w_kib, (f_kib * fs + w_kib * ws) * 1024))
     rows.sort(key=lambda r: -r[3])
     md = ["# %s: HBM traffic per kernel launch" % tag, "",
-          "Commands (one MI355X, repository root; weight gradients kept on the caller's stream so that dispatches do not overlap):", "",
+          "Commands (one MI355X, repository root):", "",
           "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o bench --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
           "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o copy --output-format csv -- python3 bench.py --calibrate-copy 256",
           "    (the same two with WRITE_SIZE)",
@@ -582,7 +617,7 @@ def summarise_counters(root, tag, sq):
     with open(os.path.join(prof, "%s_traffic.md" % tag), "w") as f:
         f.write("\n".join(md) + "\n")
     with open(os.path.join(prof, "%s_traffic.json" % tag), "w") as f:
-        json.dump({"workload": tag, "fetch_scale": round(fs, 4), "write_scale": round(ws, 4),
+        json.dump({"workload": tag, "kernel_sources": kernel_sources_digest(), "fetch_scale": round(fs, 4), "write_scale": round(ws, 4),
                    "hbm_bytes_per_launch": {n: int(b) for n, _, _, b in rows}}, f, indent=1)
     print("wrote profiles/%s_traffic.json and .md" % tag)
 
