@@ -236,7 +236,7 @@ def main():
     ap.add_argument("--summarise-stats", metavar="DIR",
                     help="no GPU needed: turn rocprofv3 --kernel-trace --stats output under DIR (bench_kernel_stats.csv and "
                          "log.txt with the bench line) into profiles/<tag>_kernel_stats.md; --cmd gives the command to quote")
-    ap.add_argument("--cmd", default="", help="--summarise-stats: the profiled command, quoted in the summary")
+    ap.add_argument("--cmd", default="", help="--summarise-stats, --summarise-counters: the profiled command, quoted in the summary")
     ap.add_argument("--tag", default="", help="workload tag of --summarise-counters output (default: from --workload)")
     ap.add_argument("--sq", action="store_true", help="--summarise-counters: shader-core counters instead of traffic")
     ap.add_argument("--cpu-samples", type=int, default=0, help="oracle sample size (0 = auto, ~10-30 s)")
@@ -252,7 +252,7 @@ def main():
     if args.summarise_counters:
         import workloads as wl
         tag = args.tag or wl.WORKLOADS[args.workload]["name"]
-        summarise_counters(args.summarise_counters, tag, args.sq)
+        summarise_counters(args.summarise_counters, tag, args.sq, args.cmd)
         return
 
     import numpy as np
@@ -554,18 +554,19 @@ def _find_csv(root, sub, prefix):
     return g[0]
 
 
-def summarise_counters(root, tag, sq):
+def summarise_counters(root, tag, sq, cmd):
     """DIR layout (what the commands quoted in the written .md produce):
          DIR/FETCH_SIZE/{bench,copy}_counter_collection.csv, DIR/WRITE_SIZE/{bench,copy}_counter_collection.csv
        or, with --sq, DIR/sq_a and DIR/sq_b with pmc_counter_collection.csv."""
+    cmd = cmd or "python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline"
     prof = os.path.join(ROOT, "profiles")
     if sq:
         a = _counter_means(_find_csv(root, "sq_a", "pmc"))
         b = _counter_means(_find_csv(root, "sq_b", "pmc"))
         md = ["# %s: shader-core counters per kernel" % tag, "",
               "Commands (one MI355X, repository root; one pass of eight SQ counters each):", "",
-              "    rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
-              "    rocprofv3 --pmc SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_LDS SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INST_LEVEL_LDS -d DIR/sq_b -o pmc --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
+              "    rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- " + cmd,
+              "    rocprofv3 --pmc SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_WAIT_INST_LDS SQ_ACTIVE_INST_ANY SQ_INSTS_LDS SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INST_LEVEL_LDS -d DIR/sq_b -o pmc --output-format csv -- " + cmd,
               "    python3 bench.py --summarise-counters DIR --sq --tag %s" % tag, "",
               "Per-dispatch averages. SQ_BUSY_CYCLES sums the 32 shader engines, SQ_VALU_MFMA_BUSY_CYCLES the 1024 SIMDs, "
               "SQ_LDS_IDX_ACTIVE the 256 CUs; shares of the wavefronts' resident cycles (SQ_WAVE_CYCLES): waiting at an "
@@ -605,7 +606,7 @@ def summarise_counters(root, tag, sq):
     rows.sort(key=lambda r: -r[3])
     md = ["# %s: HBM traffic per kernel launch" % tag, "",
           "Commands (one MI355X, repository root):", "",
-          "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o bench --output-format csv -- python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline",
+          "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o bench --output-format csv -- " + cmd,
           "    rocprofv3 --pmc FETCH_SIZE -d DIR/FETCH_SIZE -o copy --output-format csv -- python3 bench.py --calibrate-copy 256",
           "    (the same two with WRITE_SIZE)",
           "    python3 bench.py --summarise-counters DIR --tag %s" % tag, "",

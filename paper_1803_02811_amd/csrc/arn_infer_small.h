@@ -3,10 +3,10 @@
 //
 //   infer_conv_band_kernel   one sample's last feature map is cut into bands of rows; a workgroup computes one band and
 //                            recomputes the rows of the earlier layers that the band's windows reach into
-//   fc_small_kernel          one workgroup per 16 hidden units and 16*MT samples, no k ranges in memory: the wavefronts
-//                            of the workgroup share the contraction and add up through LDS.  With MODE_HEAD it also
-//                            multiplies its 16 units into the head; the last workgroup of a sample tile to finish adds
-//                            the 32 contributions in order and writes the outputs
+//   fc_small_kernel          one workgroup per 16*NT hidden units and 16*MT samples (fc_small_tile), no k ranges in memory: the
+//                            wavefronts of the workgroup share the contraction and add up through LDS.  With FC_HEAD it
+//                            also multiplies its units into the head, 16 at a time; the last workgroup of a sample tile to
+//                            finish adds the HIDN/16 contributions in order and writes the outputs
 // Sums are formed in the same order for every batch size these kernels serve, so a sample's outputs do not depend on
 // the batch it is in.
 #pragma once

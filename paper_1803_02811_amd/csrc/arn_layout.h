@@ -206,7 +206,9 @@ inline ConvBwdCost conv_bwd_cost(int geom) {
     return {3.5f, 1.f, 0.f};
 }
 struct ConvBwdSplit { int spw1, spw2, spw3; };   // samples per workgroup
-constexpr int CONV_BWD_MOST1 = 204, CONV_BWD_MOST2 = 85;   // workgroups of the first, of either other range, at most
+// Workgroups of the first, of either other range, at most: the largest counts that the rule below comes to for any batch (204
+// samples on the 2-convolution network; 337 samples).  The reported workspace sizes rely on them.
+constexpr int CONV_BWD_MOST1 = 204, CONV_BWD_MOST2 = 85;
 inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
     const ConvBwdCost c = conv_bwd_cost(d.geom);
     const int g2 = conv2_wg_g(d), g3 = CONV3_WG_G;
@@ -282,7 +284,7 @@ struct Workspace {
     size_t a1l, a2l, a3l, hl;           // their low parts (written and read by the forward pass only)
     size_t fcp;                         // fp32 [ksplit][B][512] partial sums of the fc forward GEMM
     size_t zp, cnt;                     // fc_small_kernel: contributions to the head outputs [HID/16][padded B][32], counters
-    size_t z, zv;                       // categorical head: fp32 atom logits, rows padded to NHP floats
+    size_t z;                           // categorical head: fp32 atom logits, rows padded to NHP floats
     size_t ztgt, m;                     // C51: target-net atom logits, projected target
     size_t qt, astar;                   // DQN: target-net Q(s',.) fp32 [B][A]; Double-DQN: online greedy action on s' int32 [B]
     size_t m1, m2, m3;                  // ReLU sign bits of act1, act2 and the last convolution's activations (bit e&7 of byte e>>3, NHWC element e), written by the forward
@@ -327,7 +329,6 @@ inline Workspace make_workspace(const Dims &d, int B, int mode, bool bound = fal
     if (mode == ARN_MODE_FORWARD) w.z = take(d.small ? 0 : b * (size_t)d.NHP * 4);
     if (mode == ARN_MODE_TRAIN) {
         w.z = take(d.small ? 0 : b * (size_t)d.NHP * 4);
-        w.zv = 0;
         if (d.qhead) {
             w.qt = take(b * (size_t)d.A * 4);
             w.astar = take(b * 4);

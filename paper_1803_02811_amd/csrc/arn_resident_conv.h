@@ -92,18 +92,10 @@ struct ResWaves<C, decltype((void)C::WAVES)> {
     static constexpr int value = C::WAVES;
 };
 
-// LDS bytes of resident_conv_body<C>: the image buffers, then the mask buffers
+// Grid: x = sample ranges, y = workgroups that share a range.
 template <class C>
-constexpr int resident_conv_mask_bytes() { return (C::G * (C::MASK_ELEMS / 8) + 15) / 16 * 16; }
-template <class C>
-constexpr int resident_conv_lds_bytes() {
-    return C::NBUF * (C::G * C::IMG * (C::SPLIT ? 2 : 1) + resident_conv_mask_bytes<C>());
-}
-
-// The work of workgroup (block_x, block_y) of a grid with grid_y workgroups per sample range, in the caller's LDS buffer.
-template <class C>
-__device__ __forceinline__ void resident_conv_body(u32x4 *lds, const typename C::Args &a, int block_x, int block_y, int grid_y,
-                                                   int B, int spw) {
+__global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 2 : 1) void resident_conv_kernel(
+    const typename C::Args a, int B, int spw) {
     constexpr int RESC_THREADS = 64 * ResWaves<C>::value;
     constexpr int WPARTS = ResWaves<C>::value / 4;       // wavefronts that share a channel group
     constexpr int CI = C::CI, PS = CI * 2 + 32, NCH = CI / 8;   // pixel stride = 32 mod 64 bytes: conflict-free 16-position x 4-chunk reads (measured)
@@ -120,7 +112,7 @@ __device__ __forceinline__ void resident_conv_body(u32x4 *lds, const typename C:
     typedef typename std::conditional<MW == 8, u32x2, uint32_t>::type MWord;
     constexpr int NMQ = C::G * MSB / MW;                 // mask words per iteration
     constexpr int NML = (NMQ + RESC_THREADS - 1) / RESC_THREADS;
-    constexpr int MBUF = resident_conv_mask_bytes<C>();
+    constexpr int MBUF = (NMQ * MW + 15) / 16 * 16;
     static_assert(C::MASK_ELEMS % 8 == 0 && MSB % MW == 0, "mask bytes per sample in whole words");
     static_assert(KS % 2 == 0, "k-steps split into two halves");
     constexpr int NBUF = C::NBUF;
@@ -128,18 +120,19 @@ __device__ __forceinline__ void resident_conv_body(u32x4 *lds, const typename C:
     static_assert(C::PSB == PS && IMG % 16 == 0, "pixel stride / image alignment");
     static_assert(layout_is_uniform<C>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
 
+    __shared__ u32x4 lds[NBUF * (BUF + MBUF) / 16];      // the image buffers, then the mask buffers
     MWord *const lds_mask8 = reinterpret_cast<MWord *>(lds + NBUF * BUF / 16);
     uint8_t *const lds_mask = reinterpret_cast<uint8_t *>(lds_mask8);
     char *const lds_b = reinterpret_cast<char *>(lds);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3;
     const int li = lane & 15, lg = lane >> 4;
-    const int s_begin = block_x * spw;
+    const int s_begin = blockIdx.x * spw;
     const int s_end = s_begin + spw < B ? s_begin + spw : B;
     if (s_begin >= s_end) return;
-    // small batches: grid_y workgroups share a sample group, each taking every grid_y-th position tile
+    // small batches: gridDim.y workgroups share a sample group, each taking every gridDim.y-th position tile
     // (and the wavefronts that share a channel group split those again)
-    const int t_first = block_y * WPARTS + (tid >> 8), t_step = grid_y * WPARTS;
+    const int t_first = blockIdx.y * WPARTS + (tid >> 8), t_step = gridDim.y * WPARTS;
 
     // weights of this wavefront's channels, all k, as A-operand fragments (loaded below, after the
     // first image loads have been issued, so that staging does not wait for them)
@@ -303,13 +296,6 @@ __device__ __forceinline__ void resident_conv_body(u32x4 *lds, const typename C:
         if constexpr (NBUF == 1) __syncthreads();    // everyone is done reading before the next group is staged
         if constexpr (NBUF == 2) buf ^= 1;
     }
-}
-
-template <class C>
-__global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 2 : 1) void resident_conv_kernel(
-    const typename C::Args a, int B, int spw) {
-    __shared__ u32x4 lds[resident_conv_lds_bytes<C>() / 16];
-    resident_conv_body<C>(lds, a, blockIdx.x, blockIdx.y, gridDim.y, B, spw);
 }
 
 // ---------------------------------------------------------------------------
