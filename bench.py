@@ -499,11 +499,12 @@ def summarise_stats(root, tag, cmd):
         return re.sub(r"^_ZN3arn\d+", "", n)[:100]
     md = ["# %s: kernel trace" % tag, "", "Command (on one MI355X, from the repository root):", "", "    " + cmd, "",
           "    python3 bench.py --summarise-stats DIR --tag %s --cmd '...'" % tag, "",
-          "Per-kernel summary from rocprofv3's `*_kernel_stats.csv` (durations in microseconds).", "",
+          "Per-kernel summary from rocprofv3's `*_kernel_stats.csv` (durations in microseconds), without torch's kernels, which make "
+          "the inputs and evict the caches.", "",
           "| kernel | calls | avg us | min us | max us | % of GPU time |", "|---|---|---|---|---|---|"]
     with open(src[0]) as f:
         for r in csv.DictReader(f):
-            if float(r["Percentage"]) >= 0.05:
+            if float(r["Percentage"]) >= 0.05 and "at::native" not in r["Name"]:
                 md.append("| `%s` | %s | %.2f | %.2f | %.2f | %.2f |" % (
                     short(r["Name"]), r["Calls"], float(r["AverageNs"]) / 1e3, float(r["MinNs"]) / 1e3,
                     float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
@@ -530,8 +531,9 @@ def _short_kernel_name(k):
     return None
 
 
-def _counter_means(path):
-    """{short kernel name: {counter: mean value per dispatch}} of one rocprofv3 *_counter_collection.csv."""
+def _counter_means(path, split_fp16=False):
+    """{short kernel name: {counter: mean value per dispatch}} of one rocprofv3 *_counter_collection.csv.  split_fp16: the fc
+    layer of the no-gradient forward under a name of its own (both are launched as fc_fwd)."""
     import collections
     import csv
     acc = collections.defaultdict(lambda: collections.defaultdict(float))
@@ -541,6 +543,8 @@ def _counter_means(path):
             n = _short_kernel_name(r["Kernel_Name"])
             if n is None:
                 continue
+            if split_fp16 and n == "fc_fwd" and "F16" in r["Kernel_Name"]:
+                n = "fc_fwd (fp16)"
             acc[n][r["Counter_Name"]] += float(r["Counter_Value"])
             cnt[n][r["Counter_Name"]] += 1
     return {n: {c: acc[n][c] / cnt[n][c] for c in acc[n]} for n in acc}
@@ -561,8 +565,8 @@ def summarise_counters(root, tag, sq, cmd):
     cmd = cmd or "python3 bench.py <workload flags> --steps 3 --warmup 1 --no-cpu-baseline"
     prof = os.path.join(ROOT, "profiles")
     if sq:
-        a = _counter_means(_find_csv(root, "sq_a", "pmc"))
-        b = _counter_means(_find_csv(root, "sq_b", "pmc"))
+        a = _counter_means(_find_csv(root, "sq_a", "pmc"), split_fp16=True)
+        b = _counter_means(_find_csv(root, "sq_b", "pmc"), split_fp16=True)
         md = ["# %s: shader-core counters per kernel" % tag, "",
               "Commands (one MI355X, repository root; one pass of eight SQ counters each):", "",
               "    rocprofv3 --pmc SQ_BUSY_CYCLES SQ_WAVE_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE -d DIR/sq_a -o pmc --output-format csv -- " + cmd,
