@@ -192,10 +192,11 @@ __device__ __forceinline__ void wait_vmem() {
 // wavefront's fragments of stage s+1 are read from LDS between its MFMAs on stage s.  The order of the words in LDS makes
 // the fragment reads conflict-free under the bank rule of arn_resident_conv.h; the copies apply it to their source address.
 //
-// What bounds it: with three products the matrix cores (82% of their cycles in the loop; the chip's power limit then sets
-// the clock, 1.65 - 2.0 GHz, which is also why the MFMAs are 16x16x32: 32x32x16 ran the same loop in fewer cycles at a lower
-// clock, 58 against 55 us); with one product LDS bandwidth (a 64 x 64 wavefront tile reads 8 KB per 256 MFMA cycles and
-// four wavefronts share 128 B per cycle).  Measured before (operands through registers, one stage ahead) and after, us:
+// What bounds it: with three products the matrix cores come nearest (busy 60% of a launch's cycles at 8192 samples, 48% at
+// 2048; LDS 20 and 16%; the chip's power limit sets the clock, 1.7 - 1.9 GHz here, which is also why the MFMAs are 16x16x32:
+// 32x32x16 ran the same loop in fewer cycles at a lower clock, 58 against 55 us); with one product nothing is near its rate
+// (matrix cores 38%, LDS 19% at 8192 samples) and wavefronts wait, for the copies at the start of a range and at every
+// stage's barrier (35% of their cycles at a wait).  Measured before (operands through registers, one stage ahead) and after, us:
 // fc forward of 8192 samples, three products 87 -> 65; of 2048 samples 26.7 -> 22.6; one product, 8192 samples 41 -> 35;
 // categorical head of 8192 samples and 960 rows 35 -> 32, its input gradient 19.4 -> 15.5.
 // ---------------------------------------------------------------------------
@@ -450,9 +451,10 @@ void gemm_nt_kernel(const P p) {
 // four consecutive rows, which is conflict-free when the four are 64 bytes apart modulo 256: rows are not padded (a copy
 // fills 1 KB), so row r's 64-byte blocks are stored permuted, and the copies apply that to their source address.
 //
-// What bounds it: LDS.  A 64 x 32 wavefront tile reads 3 KB per 64 MFMA cycles and four wavefronts share 128 B per cycle; with
-// operands through registers, one 64-row tile ahead, the staging writes came on top and every tile had two barriers.  Steps
-// before / after, us: ppo of 4096 samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
+// What bounds it: latency.  In the launch it is a part of (dense_backward_kernel, 2048 and 8192 samples) the matrix cores are
+// busy 22 and 25% of the cycles, LDS 14 and 16%, a hundredth of that bank conflicts; wavefronts spend 37 and 34% at a wait, 32
+// and 34% waiting to issue.  With operands through registers, one 64-row tile ahead, the staging writes came on top and every
+// tile had two barriers.  Steps before / after, us: ppo of 4096 samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
 // ---------------------------------------------------------------------------
 constexpr int TN_ROWS = 32;
 template <class P>

@@ -42,7 +42,8 @@ __device__ __forceinline__ bf16x8 tr_pair(const char *lds_base, int off_a, int o
 //   RS  image row stride:   WP * PS plus a gap chosen so that the step from the last window of an output row to
 //                           the first of the next is STRIDE * PS modulo 256 as well
 // when that fits the 160 KB; otherwise (the padded 12x9 layer with four samples) the compact layout with
-// 16 bytes of padding per pixel and row, which is conflict-free within 16 lanes only.
+// 16 bytes of padding per pixel and row, which is conflict-free within 16 lanes only.  Bank conflicts as shares of the
+// LDS-active cycles, writes included: conv2 14% (84x84) and 12% (104x80), conv3 4% and, in the compact layout, 41%.
 constexpr int CW_THREADS = 512;   // eight wavefronts, two per SIMD: one hides the other's LDS latency
 
 constexpr int wgrad_stride_for(int data_bytes, int step) {   // smallest s >= data_bytes, multiple of 16, with step*s = 64 or 192 mod 256
