@@ -181,7 +181,9 @@ __device__ __forceinline__ void wait_vmem() {
 //   prefetch(m, n)                   what the epilogue of an output reads (bias, sign of an activation), loaded before the
 //                                    k loop: a load in the epilogue would be waited for once per output
 //   store(m, n, v, z, prefetched)    epilogue for channels n..n+3 of position m
-//   store(m, n, v, v4, prefetched)   WIDE: for channels n..n+7
+//   prefetch(m, n)                   WIDE: the same for channels n..n+7 and n+32..n+39, what a lane has of a position, in
+//                                    PREFETCH_LOADS loads
+//   store(m, n, half, v, v4, prefetched)   WIDE: for channels n..n+7, the prefetched first (half 0) or second eight
 // Grid: x = position tiles, y = channel tiles, z = range of the contraction (problems with a member ksplit).
 //
 // SPLIT = true is the three-product bf16 scheme of the gradient step's forward: each operand is a pair (hi, lo) of bf16 with
@@ -313,11 +315,18 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
     constexpr int QUADS = P::WIDE ? 2 : 1;
     const auto m_of = [&](int b) { return m0 + (wm * MB + b) * 16 + li; };
     const auto n_of = [&](int a) { return n0 + (wn * 4 + a) * 16 + 4 * QUADS * lg; };
-    decltype(p.prefetch(0, 0)) pre[4 / QUADS][MB];
+    decltype(p.prefetch(0, 0)) pre[P::WIDE ? 1 : 4][MB];
+    auto prefetch_all = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < 4; a += QUADS)
+        for (int a = 0; a < (P::WIDE ? 1 : 4); ++a)
 #pragma unroll
-        for (int b = 0; b < MB; ++b) pre[a / QUADS][b] = p.prefetch(m_of(b), n_of(a));
+            for (int b = 0; b < MB; ++b) pre[a][b] = p.prefetch(m_of(b), n_of(a));
+    };
+    // What WIDE problems read per position comes from memory, not from the L2, and loads return in order: ahead of the first
+    // copies it would hold up the first stage.  It is asked for when the last copies have been.  (fc input gradient alone, with one
+    // word instead of eight single bytes per lane: 16.0 -> 14.7 us at 2048 samples, 49.9 -> 46.0 at 8192.)
+    constexpr int LATE = MB * P::PREFETCH_LOADS;
+    if constexpr (!P::WIDE) prefetch_all();
 #pragma unroll
     for (int s = 0; s < 2 * RING; s += 2)
         if (s < NS) {
@@ -373,17 +382,19 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
         }
     };
     auto store_all = [&]() __attribute__((always_inline)) {
+        // a position's channels one after the other: they share cache lines
 #pragma unroll
-        for (int a = 0; a < 4; a += QUADS)
+        for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int b = 0; b < MB; ++b) {
-                if constexpr (P::WIDE) p.store(m_of(b), n_of(a), acc[a][b], acc[a + 1][b], pre[a / 2][b]);
+            for (int a = 0; a < 4; a += QUADS) {
+                if constexpr (P::WIDE) p.store(m_of(b), n_of(a), a / 2, acc[a][b], acc[a + 1][b], pre[0][b]);
                 else p.store(m_of(b), n_of(a), acc[a][b], z, pre[a][b]);
             }
     };
     Frags fa, fb;
     if constexpr (P::SHORT_K) {
         if (NS < 2 * RING) {                                     // fewer stages than slots: everything is in LDS at once
+            if constexpr (P::WIDE) prefetch_all();
             wait_vmem<0>();
             __syncthreads();
             for (int s = 0; s < NS; ++s) {
@@ -405,10 +416,11 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
         stage(Count<(RING - 1) * PAIR_COPIES>(), Count<W_COPIES>(), Count<0>(), s, fa, fb);
         stage(Count<(RING - 2) * PAIR_COPIES + 2 * W_COPIES>(), Count<W_COPIES>(), Count<A_COPIES>(), s + 1, fb, fa);
     }
+    if constexpr (P::WIDE) prefetch_all();
     auto last_pair = [&](auto left) __attribute__((always_inline)) {    // `left` pairs follow this one
         constexpr int N = decltype(left)::value;
-        stage(Count<N * PAIR_COPIES>(), Count<0>(), Count<0>(), s, fa, fb);
-        stage(Count<(N - 1) * PAIR_COPIES + W_COPIES>(), Count<0>(), Count<0>(), s + 1, fb, fa);
+        stage(Count<N * PAIR_COPIES + LATE>(), Count<0>(), Count<0>(), s, fa, fb);
+        stage(Count<(N - 1) * PAIR_COPIES + W_COPIES + LATE>(), Count<0>(), Count<0>(), s + 1, fb, fa);
         s += 2;
     };
     if constexpr (RING > 2) {
@@ -416,7 +428,7 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
         last_pair(Count<2>());
     }
     last_pair(Count<1>());
-    stage(Count<0>(), Count<0>(), Count<0>(), s, fa, fb);
+    stage(Count<LATE>(), Count<0>(), Count<0>(), s, fa, fb);
 #pragma unroll
     for (int q = 0; q < MFMAS; ++q) multiply_one(q, fb);
     store_all();

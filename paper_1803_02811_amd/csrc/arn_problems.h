@@ -22,6 +22,7 @@ template <int FEAT_, int HIDN, int BM_>
 struct FcFwdT {
     static constexpr int BM = BM_, RING = 2, K = FEAT_;
     static constexpr bool SHORT_K = false, WIDE = false;
+    static constexpr int PREFETCH_LOADS = 0;
     const __bf16 *in, *in_lo;
     int M;
     int ksplit;
@@ -61,6 +62,7 @@ template <int HIDN, int BM_>
 struct HeadFwdC51 {
     static constexpr int BM = BM_, RING = 2, K = HIDN;
     static constexpr bool SHORT_K = false, WIDE = false;
+    static constexpr int PREFETCH_LOADS = 0;
     const __bf16 *in, *in_lo;
     int M;
     const __bf16 *w, *w_lo;
@@ -108,11 +110,15 @@ struct HeadDgrad {
     __device__ __forceinline__ const __bf16 *act() const { return in; }
     __device__ __forceinline__ const __bf16 *weights() const { return w; }
     __device__ __forceinline__ int tiles() const { return HIDN / 16; }
-    __device__ __forceinline__ u32x4 prefetch(int m, int n) const {
-        return *reinterpret_cast<const u32x4 *>(h + (size_t)(m < M ? m : 0) * HIDN + n);
+    static constexpr int PREFETCH_LOADS = 2;
+    struct Hidden { u32x4 w[2]; };
+    __device__ __forceinline__ Hidden prefetch(int m, int n) const {
+        const u32x4 *at = reinterpret_cast<const u32x4 *>(h + (size_t)(m < M ? m : 0) * HIDN + n);
+        return Hidden{{at[0], at[4]}};
     }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, f32x4 v4, u32x4 hw) const {
+    __device__ __forceinline__ void store(int m, int n, int half, f32x4 v, f32x4 v4, const Hidden &hidden) const {
         if (m >= M) return;
+        const u32x4 hw = hidden.w[half];
         const size_t at = (size_t)m * HIDN + n;
         f32x4 a = unpack_bf16x4(u32x2{hw[0], hw[1]}), b = unpack_bf16x4(u32x2{hw[2], hw[3]});
 #pragma unroll
@@ -138,13 +144,17 @@ struct FcDgradT {
     __device__ __forceinline__ const __bf16 *act() const { return in; }
     __device__ __forceinline__ const __bf16 *weights() const { return w; }
     __device__ __forceinline__ int tiles() const { return FEAT / 16; }
-    // the eight ReLU-derivative bits of outputs (m, n..n+7), fetched before the k loop
-    __device__ __forceinline__ uint32_t prefetch(int m, int n) const {
-        const size_t at = (size_t)(m < M ? m : 0) * FEAT + (n < FEAT ? n : 0);
-        return maskbits[at >> 3];
+    static constexpr int PREFETCH_LOADS = 1;
+    // the ReLU-derivative bits of the 64 outputs (m, n / 64 * 64 ..) as one word (a wavefront's channels of a position), fetched
+    // before the epilogue; FEAT is a multiple of 64, so that it holds them all or none
+    __device__ __forceinline__ u32x2 prefetch(int m, int n) const {
+        static_assert(FEAT % 64 == 0, "whole words");
+        const size_t at = (size_t)(m < M ? m : 0) * FEAT + (n < FEAT ? n & ~63 : 0);
+        return *reinterpret_cast<const u32x2 *>(maskbits + (at >> 3));
     }
-    __device__ __forceinline__ void store(int m, int n, f32x4 v, f32x4 v4, uint32_t mb) const {
+    __device__ __forceinline__ void store(int m, int n, int half, f32x4 v, f32x4 v4, u32x2 bits) const {
         if (m >= M || n >= FEAT) return;
+        const uint32_t mb = bits[half] >> (n & 31);
         const size_t at = (size_t)m * FEAT + n;
         const u32x2 x = pack_bf16x4(mb & 1 ? v[0] : 0.f, mb & 2 ? v[1] : 0.f, mb & 4 ? v[2] : 0.f, mb & 8 ? v[3] : 0.f);
         const u32x2 y = pack_bf16x4(mb & 16 ? v4[0] : 0.f, mb & 32 ? v4[1] : 0.f, mb & 64 ? v4[2] : 0.f, mb & 128 ? v4[3] : 0.f);
