@@ -181,13 +181,12 @@ void with_geometry(const Dims &d, F f) {
     else f(Geo84());
 }
 
-// Calls f with the positions per workgroup tile of a dense contraction over M rows and N columns: 128 where that makes at
-// least 256 workgroups, fewer (more workgroups) below.
+// Calls f with the positions per workgroup tile of a dense contraction over M rows and N columns (dense_tile).
 template <class F>
 void with_tile(long M, int N, F f) {
-    const long nt = cdiv(N, NT_BN);
-    if (cdiv(M, 128) * nt >= 256) f(std::integral_constant<int, 128>());
-    else if (cdiv(M, 64) * nt >= 256) f(std::integral_constant<int, 64>());
+    const int tile = dense_tile(M, N);
+    if (tile == 128) f(std::integral_constant<int, 128>());
+    else if (tile == 64) f(std::integral_constant<int, 64>());
     else f(std::integral_constant<int, 32>());
 }
 
@@ -427,10 +426,10 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
     float *part1 = (float *)(ws + o.pw1), *part2 = (float *)(ws + o.pw2), *part3 = (float *)(ws + o.pw3);
     float *partfc = (float *)(ws + o.pwfc);
     {
-        auto launch = [&](auto bm) {
+        auto launch = [&](auto bm, auto units) {
             typedef FcDgradT<G::FEAT, G::NHID, decltype(bm)::value> Dg;
             Dg dg;
-            typedef FcWgrad<G::FEAT, G::NHID> FcW;
+            typedef FcWgrad<G::FEAT, G::NHID, decltype(units)::value> FcW;
             typedef HeadWgrad<G::NHID> HeadW;
             dg.in = dph; dg.M = B; dg.w = w.wfcd; dg.maskbits = (const uint8_t *)(ws + o.m3); dg.out = dp3;
             DenseBackwardArgs<Dg, FcW, HeadW> p;
@@ -447,7 +446,12 @@ void backward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, c
             hipLaunchKernelGGL((dense_backward_kernel<Dg, FcW, HeadW>), dim3(p.dg_blocks + p.wg_blocks + p.hw_blocks + 1),
                                dim3(DENSE_THREADS), 0, s, p);
         };
-        with_tile(B, G::FEAT, launch);
+        with_tile(B, G::FEAT, [&](auto bm) {
+            if constexpr (decltype(bm)::value == 128 && G::NHID > 256) {
+                if (fc_wgrad_units(G::FEAT, G::NHID, B) == 256) return launch(bm, Count<256>());
+            }
+            launch(bm, Count<128>());
+        });
     }
     if constexpr (G::HAS3) {
         typename Cfg::Dgrad3::Args p;

@@ -463,8 +463,10 @@ void gemm_nt_kernel(const P p) {
 // four consecutive rows, which is conflict-free when the four are 64 bytes apart modulo 256: rows are not padded (a copy
 // fills 1 KB), so row r's 64-byte blocks are stored permuted, and the copies apply that to their source address.
 //
-// What bounds it: latency.  In the launch it is a part of (dense_backward_kernel, 2048 and 8192 samples) the matrix cores are
-// busy 22 and 25% of the cycles, LDS 14 and 16%, a hundredth of that bank conflicts; wavefronts spend 37 and 34% at a wait, 32
+// What bounds it: with 64 x 64 outputs per wavefront (FcWgrad of large batches; 64 x 32 before: 20.8 -> 18.3 us alone at 2048 samples,
+// 63.8 -> 48.6 at 8192) the transposing reads, four 8-byte reads of a wavefront per 32x32x16 MFMA and 128 bytes per clock from a CU's
+// LDS; with 64 x 32, six, and latency: in the launch it is a part of (dense_backward_kernel, 2048 and 8192 samples) the matrix cores were
+// busy 22 and 25% of the cycles, LDS 14 and 16%, a hundredth of that bank conflicts; wavefronts spent 37 and 34% at a wait, 32
 // and 34% waiting to issue.  With operands through registers, one 64-row tile ahead, the staging writes came on top and every
 // tile had two barriers.  Steps before / after, us: ppo of 4096 samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
 // ---------------------------------------------------------------------------

@@ -222,6 +222,21 @@ inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
         if (n1 + n2 + n3 <= 256 && n1 <= CONV_BWD_MOST1 && n2 <= CONV_BWD_MOST2 && n3 <= CONV_BWD_MOST2) return s;
     }
 }
+// Positions per workgroup tile of a dense contraction over M rows and N columns: 128 where that makes at least 256 workgroups,
+// fewer (more workgroups) below.
+inline int dense_tile(long M, int N) {
+    const long nt = (N + 127) / 128;
+    return (M + 127) / 128 * nt >= 256 ? 128 : (M + 63) / 64 * nt >= 256 ? 64 : 32;
+}
+// Hidden units per workgroup tile of the fc layer's weight gradient: 256 (64 x 64 outputs per wavefront, a third fewer LDS
+// reads per product than 64 x 32, and half the act3 traffic) for batches that have at least 500 tiles of 128 x 128 in the input
+// gradient (84x84: 2433 samples, 104x80: 1153); below, the launch is a few rounds of workgroups or less, and twice as many half as
+// long ones are as fast or faster.  Launch and sums of the partials in us, 128 / 256 units, 84x84: 333 samples 20.7 / 23.2, 2048:
+// 41.1 / 40.0, 4096: 70.4 / 64.1, 8192: 129.2 / 121.3; 104x80, 512 samples: 31.5 / 34.0.  Whole A2C step, 84x84, 1930 samples: 231.2 /
+// 231.9, 3000: 330.6 / 327.0; 104x80, 900: 204.7 / 205.6, 2048: 363.7 / 356.7.
+inline int fc_wgrad_units(int feat, int hid, int B) {
+    return hid > 256 && (long)((B + 127) / 128) * ((feat + 127) / 128) >= 500 ? 256 : 128;
+}
 inline Splits make_splits(const Dims &d, int B) {
     Splits s;
     const ConvBwdSplit cs = conv_bwd_split(d, B);
@@ -229,7 +244,7 @@ inline Splits make_splits(const Dims &d, int B) {
     s.c2 = (B + cs.spw2 - 1) / cs.spw2;
     s.c3 = d.c3 ? (B + cs.spw3 - 1) / cs.spw3 : 0;
     // the dense layers' weight-gradient GEMMs are cut along the batch so that about 400 to 500 workgroups exist
-    s.fc = pick_split(B, (d.feat / 64) * (d.hid / 128), d.geom == ARN_GEOM_84 ? 392 : 512);
+    s.fc = pick_split(B, (d.feat / 64) * (d.hid / fc_wgrad_units(d.feat, d.hid, B)), d.geom == ARN_GEOM_84 ? 392 : 512);
     s.hd = pick_split(B, (d.hid / 128) * (d.NHP / 64), 256);
     return s;
 }

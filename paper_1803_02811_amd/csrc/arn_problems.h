@@ -165,9 +165,9 @@ struct FcDgradT {
 // --------------------------- weight gradients -----------------------------
 // part[n][k] = sum_m dY[m][n] act(m,k); dY is a dense [M][N1] bf16 matrix.
 // fc layer: its input in rows or in fragment order (LastActs)
-template <int FEAT, int HIDN>
+template <int FEAT, int HIDN, int UNITS>   // UNITS: fc_wgrad_units
 struct FcWgrad {
-    static constexpr int BN1 = 128, BK2 = 64, WAVES_X = 2, N1 = HIDN, KP = FEAT;
+    static constexpr int BN1 = UNITS, BK2 = 64, WAVES_X = UNITS == 256 ? 1 : 2, N1 = HIDN, KP = FEAT;
     const __bf16 *in, *dy;
     int M;
     bool frag;

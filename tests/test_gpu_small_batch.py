@@ -58,6 +58,13 @@ def test_gradients_at_dispatch_edges(gu, geometry, B):
     gu.check_grads(got, want, "%s B=%d" % (geometry, B))
 
 
+@pytest.mark.parametrize("geometry,B", [("84", 1280), ("84", 2432), ("84", 2463), ("paper", 1153)])
+def test_gradients_at_fc_weight_tile_edges(gu, geometry, B):
+    """Both sides of the batch from which the fc weight gradient takes 256 hidden units a tile (84x84: 2433, 104x80: 1153) and of the one from which the input gradient takes 128 positions (1281), with
+    a ragged last stage of 32 rows."""
+    test_gradients_at_dispatch_edges(gu, geometry, B)
+
+
 # padded head rows 64 (fewer stages than the dense kernel has slots), 192 and 960 (the last tile half full)
 @pytest.mark.parametrize("A,B", [(1, 33), (3, 129), (18, 70)])
 def test_categorical_gradients_at_tile_edges(gu, A, B):
