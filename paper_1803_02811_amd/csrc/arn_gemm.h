@@ -70,6 +70,31 @@ __device__ __forceinline__ uint32_t sign_bits16(float a, float b, float c, float
     return a32[0] | a32[1];
 }
 
+// relu(v) as the bf16 pair (hi, lo), four channels
+__device__ __forceinline__ void relu_split(f32x4 v, u32x2 &hi, u32x2 &lo) {
+    const float r0 = fmaxf(v[0], 0.f), r1 = fmaxf(v[1], 0.f), r2 = fmaxf(v[2], 0.f), r3 = fmaxf(v[3], 0.f);
+    hi = pack_bf16x4(r0, r1, r2, r3);
+    lo = pack_bf16x4(r0 - __uint_as_float(hi.x << 16), r1 - __uint_as_float(hi.x & 0xffff0000u), r2 - __uint_as_float(hi.y << 16),
+                     r3 - __uint_as_float(hi.y & 0xffff0000u));
+}
+// which of eight bf16 are positive, bit i for value i
+__device__ __forceinline__ uint32_t positive_bits(u32x4 v) {
+    typedef short s16x2 __attribute__((ext_vector_type(2)));
+    uint32_t z = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const s16x2 w = __builtin_bit_cast(s16x2, (uint32_t)v[i]), zero = {0, 0}, one = {1, 1};
+        z |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_max(w, zero), one)) << (2 * i);
+    }
+    return (z | z >> 15) & 0xff;     // even values' bits in the lower half, odd ones' in the upper
+}
+// The value, as the compiler sees it a new one each time: what is computed from it is computed where it is used, not kept in
+// registers across a loop.
+__device__ __forceinline__ int recomputed(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 __device__ __forceinline__ f32x4 unpack_bf16x4(u32x2 u) {
     bf16x4 v = __builtin_bit_cast(bf16x4, u);
     f32x4 r = {(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
