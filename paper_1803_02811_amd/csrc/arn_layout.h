@@ -199,9 +199,12 @@ inline int resident_groups(int B, int target_wgs) {
 // together; every workgroup has a prologue of about 3 us and writes a full fp32 partial, so one round of longer workgroups
 // also means less of both.  (256 workgroups for the first range and 256 for the others, in two rounds, took 61 + 14.5 us
 // with the sums at 2048 samples and 84x84 frames, this 56.5 + 11; 104x80 frames: 122 against 75 us.)
+// 84x84: alone, each with its share, the three ranges took 185, 196 and 145 us of a launch of 217 at 8192 samples with costs of
+// 3.2 : 1.5 : 1.25; with 3.2 : 1.7 : 1.05 the launch takes 200 us (4096 samples: 119 -> 110, 2048: level, the counts are too small to
+// follow).  For the other networks no ratio tried near theirs was faster.
 struct ConvBwdCost { float c1, c2, c3; };   // conv2 input gradient with conv1 weight gradient, conv2's, conv3's weight gradient
 inline ConvBwdCost conv_bwd_cost(int geom) {
-    if (geom == ARN_GEOM_84) return {3.2f, 1.5f, 1.25f};
+    if (geom == ARN_GEOM_84) return {3.2f, 1.7f, 1.05f};
     if (geom == ARN_GEOM_PAPER) return {3.f, 1.5f, 1.5f};
     return {3.5f, 1.f, 0.f};
 }
