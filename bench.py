@@ -467,7 +467,7 @@ def _instance(kernel, *args):
 ANY = r"\d+|true|false"
 KERNEL_NAME_PATTERNS = [   # first match wins: mangled or demangled rocprofv3 kernel name -> instrumented launch name
     # kernels with one launch name; they come first because their template arguments name the layers of other launches
-    (r"conv123_fwd_kernel", "conv123_fwd"), (r"conv23_fwd_fused_kernel", "conv23_fwd"), (r"conv12_fwd_kernel", "conv12_fwd"),
+    (r"conv123_(fwd|chain)_kernel", "conv123_fwd"), (r"conv23_fwd_fused_kernel", "conv23_fwd"), (r"conv12_fwd_kernel", "conv12_fwd"),
     (r"conv1_fwd_resident_kernel", "conv1_fwd"), (r"infer_conv_(pipelined_|band_)?kernel", "conv_infer"),
     (r"conv_backward_kernel", "conv_bwd"), (r"dense_backward_kernel", "dense_bwd"), (r"reduce_all_kernel", "reduce"),
     # one kernel, several layers

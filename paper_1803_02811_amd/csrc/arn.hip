@@ -271,6 +271,8 @@ struct ConvConfigs {
     typedef ResConv3DgradGeo<G> Dgrad3;
     typedef ResConv2DgradGeo<G> Dgrad2;
     static int conv1_parts(int) { return 1; }
+    // from 65 samples on (below, several workgroups share a sample of conv2 and conv3): the three convolutions in one launch
+    static bool chain(int B) { return B >= 65; }
     // conv2 -> conv3 through LDS needs both layers' images in one CU's LDS: not with the bordered images of this geometry
     static bool fused_conv23(int) { return false; }
     static void launch_conv23(const Conv23Args &, int, int, hipStream_t) {}
@@ -289,6 +291,7 @@ struct ConvConfigs<Geo84> {
     typedef ResConv3Fwd Fwd3;
     typedef ResConv3Dgrad Dgrad3;
     typedef ResConv2Dgrad Dgrad2;
+    static bool chain(int) { return false; }
     // few samples: three workgroups share one (one workgroup fits per CU)
     static int conv1_parts(int B) { return 3 * B <= 256 ? 3 : 1; }
     // one workgroup per sample range and no tile splitting: measured equal to the two kernels at B = 64, faster above
@@ -324,7 +327,23 @@ void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, ch
         hipLaunchKernelGGL((conv12_fwd_kernel<G, typename Cfg::Fwd2>), dim3(cdiv(B, spw) * bp.bands), dim3(C12_THREADS), 0, s, p, B,
                            spw, bp.rows, bp.bands);
     } else {
+        typename Cfg::Fwd2::Args p2;
+        p2.in = a1; p2.in_lo = a1l; p2.w = w.w2; p2.w_lo = w.w2l; p2.mask = nullptr; p2.bias = w.b2; p2.out = a2; p2.out_lo = a2l;
+        p2.mask_out = m2;
+        typename Cfg::Fwd3::Args p3;
+        p3.in = a2; p3.in_lo = a2l; p3.w = w.w3; p3.w_lo = w.w3l; p3.mask = nullptr; p3.bias = w.b3; p3.out = a3; p3.out_lo = a3l;
+        p3.mask_out = m3; p3.frag = fc_small(G::FEAT, B, false);
         const bool chained = Cfg::fused_conv23(B) && Cfg::conv1_parts(B) == 1;
+        if (Cfg::chain(B)) {
+            if constexpr (G::PAD2 > 0) {
+                ProfScope ps("conv123_fwd", s);
+                const int spw = resident_spw(B, 256);
+                hipLaunchKernelGGL((conv123_chain_kernel<G, typename Cfg::Fwd2, EightWaves<typename Cfg::Fwd3>>), dim3(cdiv(B, spw)),
+                                   dim3(RES_THREADS), 0, s, obs, w.w1, w.w1l, w.b1, m1, p2, p3, B, spw);
+            }
+            fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);
+            return;
+        }
         if (!chained) {
             ProfScope ps("conv1_fwd", s);
             const int spw = resident_spw(B, 256);
@@ -344,18 +363,8 @@ void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, ch
             if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, m1, p, B, spw, s);
             else Cfg::launch_conv23(p, B, spw, s);
         } else {
-            {
-                typename Cfg::Fwd2::Args p;
-                p.in = a1; p.in_lo = a1l; p.w = w.w2; p.w_lo = w.w2l; p.mask = nullptr; p.bias = w.b2; p.out = a2; p.out_lo = a2l;
-                p.mask_out = m2;
-                launch_resident<typename Cfg::Fwd2>("conv2_fwd", p, B, s);
-            }
-            {
-                typename Cfg::Fwd3::Args p;
-                p.in = a2; p.in_lo = a2l; p.w = w.w3; p.w_lo = w.w3l; p.mask = nullptr; p.bias = w.b3; p.out = a3; p.out_lo = a3l;
-                p.mask_out = m3; p.frag = fc_small(G::FEAT, B, false);
-                launch_resident<typename Cfg::Fwd3>("conv3_fwd", p, B, s);
-            }
+            launch_resident<typename Cfg::Fwd2>("conv2_fwd", p2, B, s);
+            launch_resident<typename Cfg::Fwd3>("conv3_fwd", p3, B, s);
         }
     }
     fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);

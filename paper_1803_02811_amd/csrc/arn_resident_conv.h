@@ -92,10 +92,16 @@ struct ResWaves<C, decltype((void)C::WAVES)> {
     static constexpr int value = C::WAVES;
 };
 
-// Grid: x = sample ranges, y = workgroups that share a range.
+// LDS bytes of resident_conv_body<C>: the image buffers, then the mask buffers (sixteen-byte words)
 template <class C>
-__global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 2 : 1) void resident_conv_kernel(
-    const typename C::Args a, int B, int spw) {
+constexpr int resident_conv_lds_bytes() {
+    constexpr int MSB = C::MASK_ELEMS / 8, MW = MSB % 8 == 0 ? 8 : 4;
+    return C::NBUF * (C::G * C::IMG * (C::SPLIT ? 2 : 1) + (C::G * MSB / MW * MW + 15) / 16 * 16);
+}
+
+// The work of one of `parts` workgroups that share sample range `block`, in the caller's LDS buffer.
+template <class C>
+__device__ __forceinline__ void resident_conv_body(u32x4 *lds, const typename C::Args &a, int block, int part, int parts, int B, int spw) {
     constexpr int RESC_THREADS = 64 * ResWaves<C>::value;
     constexpr int WPARTS = ResWaves<C>::value / 4;       // wavefronts that share a channel group
     constexpr int CI = C::CI, PS = CI * 2 + 32, NCH = CI / 8;   // pixel stride = 32 mod 64 bytes: conflict-free 16-position x 4-chunk reads (measured)
@@ -120,19 +126,19 @@ __global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 
     static_assert(C::PSB == PS && IMG % 16 == 0, "pixel stride / image alignment");
     static_assert(layout_is_uniform<C>(), "fragment rows must advance by one pixel stride modulo 256 bytes");
 
-    __shared__ u32x4 lds[NBUF * (BUF + MBUF) / 16];      // the image buffers, then the mask buffers
+    static_assert(resident_conv_lds_bytes<C>() == NBUF * (BUF + MBUF), "LDS buffer");
     MWord *const lds_mask8 = reinterpret_cast<MWord *>(lds + NBUF * BUF / 16);
     uint8_t *const lds_mask = reinterpret_cast<uint8_t *>(lds_mask8);
     char *const lds_b = reinterpret_cast<char *>(lds);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3;
     const int li = lane & 15, lg = lane >> 4;
-    const int s_begin = blockIdx.x * spw;
+    const int s_begin = block * spw;
     const int s_end = s_begin + spw < B ? s_begin + spw : B;
     if (s_begin >= s_end) return;
-    // small batches: gridDim.y workgroups share a sample group, each taking every gridDim.y-th position tile
+    // small batches: `parts` workgroups share a sample group, each taking every parts-th position tile
     // (and the wavefronts that share a channel group split those again)
-    const int t_first = blockIdx.y * WPARTS + (tid >> 8), t_step = gridDim.y * WPARTS;
+    const int t_first = part * WPARTS + (tid >> 8), t_step = parts * WPARTS;
 
     // weights of this wavefront's channels, all k, as A-operand fragments (loaded below, after the
     // first image loads have been issued, so that staging does not wait for them)
@@ -296,6 +302,14 @@ __global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 
         if constexpr (NBUF == 1) __syncthreads();    // everyone is done reading before the next group is staged
         if constexpr (NBUF == 2) buf ^= 1;
     }
+}
+
+// Grid: x = sample ranges, y = workgroups that share a range.
+template <class C>
+__global__ __launch_bounds__(64 * ResWaves<C>::value, ResWaves<C>::value == 4 ? 2 : 1) void resident_conv_kernel(
+    const typename C::Args a, int B, int spw) {
+    __shared__ u32x4 lds[resident_conv_lds_bytes<C>() / 16];
+    resident_conv_body<C>(lds, a, blockIdx.x, blockIdx.y, gridDim.y, B, spw);
 }
 
 // ---------------------------------------------------------------------------
@@ -760,5 +774,33 @@ struct ResConv2DgradGeo {
         return (unsigned)y < (unsigned)Geo::H1 && (unsigned)x < (unsigned)Geo::W1 ? y * Geo::W1 + x : -1;
     }
 };
+
+// The three forward convolutions of a workgroup's sample range one after the other, in one launch, where the layers' images do not
+// fit side by side (104x80): a workgroup waits for its own act1 and act2, which it reads back, instead of for the whole grid
+// three times, and two launch boundaries and the first and last workgroups of three grids are gone.  Eight wavefronts in every
+// layer; the same products in the same order as in the layers' own kernels.  A2C step on 104x80 frames, three launches / this one,
+// us: 66 samples 87.6 / 82.3, 255: 105.8 / 99.4, 512: 138.9 / 131.6, 2048: 359.2 / 339.4, 4000: 632.5 / 608.3.
+template <class C>
+struct EightWaves : C {
+    static constexpr int WAVES = 8;
+};
+template <class Geo, class F2, class F3>
+__global__ __launch_bounds__(RES_THREADS) void conv123_chain_kernel(const uint8_t *__restrict__ obs, const __bf16 *__restrict__ w1,
+                                                                    const __bf16 *__restrict__ w1_lo, const float *__restrict__ b1,
+                                                                    uint8_t *__restrict__ m1, const typename F2::Args a2,
+                                                                    const typename F3::Args a3, int B, int spw) {
+    static_assert(ResWaves<F2>::value == 8 && ResWaves<F3>::value == 8 && RES_THREADS == 512, "one block size for all bodies");
+    constexpr int L1 = conv1_fwd_lds_bytes<Geo>(), L2 = resident_conv_lds_bytes<F2>(), L3 = resident_conv_lds_bytes<F3>();
+    constexpr int L12 = L1 > L2 ? L1 : L2;
+    __shared__ u32x4 lds[(L12 > L3 ? L12 : L3) / 16];
+    const int block = sample_block(blockIdx.x, gridDim.x, spw, a3.frag);
+    conv1_fwd_resident_body<Geo, true>(lds, block, 0, 1, obs, w1, w1_lo, b1, const_cast<__bf16 *>(a2.in), const_cast<__bf16 *>(a2.in_lo),
+                                       m1, B, spw);
+    // the barriers order this workgroup's stores before its own loads (a workgroup's wavefronts share the CU's vector cache)
+    __syncthreads();
+    resident_conv_body<F2>(lds, a2, block, 0, 1, B, spw);
+    __syncthreads();
+    resident_conv_body<F3>(lds, a3, block, 0, 1, B, spw);
+}
 
 }  // namespace arn

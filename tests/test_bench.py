@@ -13,6 +13,7 @@ GEO84 = "arn::Geometry<84, 84, 0, 0, 32, 64, true, 512>"
 NAMES = {
     "conv123_fwd_kernel": [("_ZN3arn18conv123_fwd_kernelINS_8GeometryILi84ELi84ELi0ELi0ELi32ELi64ELb1ELi512EEENS_11ResConv2FwdENS_11ResConv3FwdEEEvPKh",
                             "conv123_fwd")],
+    "conv123_chain_kernel": [("_ZN3arn20conv123_chain_kernelINS_8GeometryILi104ELi80ELi1ELi1ELi32ELi64ELb1ELi512EEENS_14ResConv2FwdGeoIS2_EE", "conv123_fwd")],
     "conv23_fwd_fused_kernel": [("void arn::conv23_fwd_fused_kernel<arn::ResConv2Fwd, arn::ResConv3Fwd>(arn::Conv23Args, int, int)", "conv23_fwd")],
     "conv12_fwd_kernel": [("void arn::conv12_fwd_kernel<G, arn::ResConv2FwdGeo<G> >(arn::Conv12Args, int, int, int, int)", "conv12_fwd")],
     "conv1_fwd_resident_kernel": [("void arn::conv1_fwd_resident_kernel<%s >(unsigned char const*)" % GEO84, "conv1_fwd")],

@@ -65,6 +65,12 @@ def test_gradients_at_fc_weight_tile_edges(gu, geometry, B):
     test_gradients_at_dispatch_edges(gu, geometry, B)
 
 
+@pytest.mark.parametrize("B", [64, 257])
+def test_gradients_at_chained_convolution_edges(gu, B):
+    """104x80: the last batch with a launch per convolution (from 65 on they are one), and two samples a workgroup with one left over."""
+    test_gradients_at_dispatch_edges(gu, "paper", B)
+
+
 # padded head rows 64 (fewer stages than the dense kernel has slots), 192 and 960 (the last tile half full)
 @pytest.mark.parametrize("A,B", [(1, 33), (3, 129), (18, 70)])
 def test_categorical_gradients_at_tile_edges(gu, A, B):
