@@ -406,15 +406,21 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    // WIDE: a position's channels one after the other, they share cache lines.  fp32 rows: channel group by channel group; in the
+    // order of WIDE the fc layer's partials of 512 samples of 104x80 took 8.6 instead of 8.2 us (one product), the head kernel that
+    // reads them 9.3 instead of 9.1, and the A2C gradient at 2048 samples of 84x84 241.5 instead of 239.5.
     auto store_all = [&]() __attribute__((always_inline)) {
-        // a position's channels one after the other: they share cache lines
+        if constexpr (P::WIDE) {
 #pragma unroll
-        for (int b = 0; b < MB; ++b)
+            for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int a = 0; a < 4; a += QUADS) {
-                if constexpr (P::WIDE) p.store(m_of(b), n_of(a), a / 2, acc[a][b], acc[a + 1][b], pre[0][b]);
-                else p.store(m_of(b), n_of(a), acc[a][b], z, pre[a][b]);
-            }
+                for (int a = 0; a < 4; a += 2) p.store(m_of(b), n_of(a), a / 2, acc[a][b], acc[a + 1][b], pre[0][b]);
+        } else {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < MB; ++b) p.store(m_of(b), n_of(a), acc[a][b], z, pre[a][b]);
+        }
     };
     Frags fa, fb;
     if constexpr (P::SHORT_K) {
