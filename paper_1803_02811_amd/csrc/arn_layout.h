@@ -199,30 +199,34 @@ inline int resident_groups(int B, int target_wgs) {
 // together; every workgroup has a prologue of about 3 us and writes a full fp32 partial, so one round of longer workgroups
 // also means less of both.  (256 workgroups for the first range and 256 for the others, in two rounds, took 61 + 14.5 us
 // with the sums at 2048 samples and 84x84 frames, this 56.5 + 11; 104x80 frames: 122 against 75 us.)
-// 84x84: alone, each with its share, the three ranges took 185, 196 and 145 us of a launch of 217 at 8192 samples with costs of
-// 3.2 : 1.5 : 1.25; with 3.2 : 1.7 : 1.05 the launch takes 200 us (4096 samples: 119 -> 110, 2048: level, the counts are too small to
-// follow).  For the other networks no ratio tried near theirs was faster.
-struct ConvBwdCost { float c1, c2, c3; };   // conv2 input gradient with conv1 weight gradient, conv2's, conv3's weight gradient
-inline ConvBwdCost conv_bwd_cost(int geom) {
-    if (geom == ARN_GEOM_84) return {3.2f, 1.7f, 1.05f};
-    if (geom == ARN_GEOM_PAPER) return {3.f, 1.5f, 1.5f};
-    return {3.5f, 1.f, 0.f};
+// A range's time is first + cost per sample: on 84x84 frames the first range's workgroups take about 2 us longer before and after
+// their samples than the others', and conv2's weight gradient, which reads the most bytes in a given time, costs more per sample in
+// batches whose activations the 256 MB Infinity Cache does not hold (about 110 KB a sample: from 2400 samples on).  Launch and
+// sums of the partials in us, with 3.2 : 1.5 : 1.25 and no first time / 3.2 : 1.7 : 1.05 and none / these, 150 samples: 20.1 / 23.2 /
+// 20.1, 333: 28.2 / 27.0 / 26.2, 560: 30.2 / 32.8 / 30.2, 1000: 40.0 / 42.7 / 40.0, 1500: 51.0 / 52.5 / 51.2, 2048: 64.9 / 65.6 / 64.7, 2500:
+// 82.4 / 81.1 / 79.0, 4096: 123.5 / 115.8 / 115.8.  Of 47 batches from 100 to 8192 none is more than 1.4% above the better of the other two.
+// For the other networks no ratio tried near theirs was faster.
+struct ConvBwdCost { float first, c1, c2, c3; };   // c1: conv2 input gradient with conv1 weight gradient, c2, c3: conv2's, conv3's weight gradient
+inline ConvBwdCost conv_bwd_cost(int geom, int B) {
+    if (geom == ARN_GEOM_84) return {2.f, 3.2f, B <= 2400 ? 1.5f : 1.7f, 1.05f};
+    if (geom == ARN_GEOM_PAPER) return {0.f, 3.f, 1.5f, 1.5f};
+    return {0.f, 3.5f, 1.f, 0.f};
 }
 struct ConvBwdSplit { int spw1, spw2, spw3; };   // samples per workgroup
 // Workgroups of the first, of either other range, at most: the largest counts that the rule below comes to for any batch (204
-// samples on the 2-convolution network; 337 samples).  The reported workspace sizes rely on them.
+// samples on the 2-convolution network; 337 samples on 104x80).  The reported workspace sizes rely on them.
 constexpr int CONV_BWD_MOST1 = 204, CONV_BWD_MOST2 = 85;
-inline ConvBwdSplit conv_bwd_split(const Dims &d, int B) {
-    const ConvBwdCost c = conv_bwd_cost(d.geom);
+inline ConvBwdSplit conv_bwd_split(const Dims &d, int B, int most1 = CONV_BWD_MOST1, int most2 = CONV_BWD_MOST2) {
+    const ConvBwdCost c = conv_bwd_cost(d.geom, B);
     const int g2 = conv2_wg_g(d), g3 = CONV3_WG_G;
     ConvBwdSplit s;
     for (double t = (double)B * (c.c1 + c.c2 + c.c3) / 256;; t *= 1.01) {
-        auto per = [&](double cost, int g) { const int n = (int)(t / (cost * g)); return (n < 1 ? 1 : n) * g; };
-        s.spw1 = per(c.c1, 1);
-        s.spw2 = per(c.c2, g2);
-        s.spw3 = d.c3 ? per(c.c3, g3) : 1 << 30;
+        auto per = [&](double first, double cost, int g) { const int n = (int)((t - first) / (cost * g)); return (n < 1 ? 1 : n) * g; };
+        s.spw1 = per(c.first, c.c1, 1);
+        s.spw2 = per(0, c.c2, g2);
+        s.spw3 = d.c3 ? per(0, c.c3, g3) : 1 << 30;
         const int n1 = (B + s.spw1 - 1) / s.spw1, n2 = (B + s.spw2 - 1) / s.spw2, n3 = d.c3 ? (B + s.spw3 - 1) / s.spw3 : 0;
-        if (n1 + n2 + n3 <= 256 && n1 <= CONV_BWD_MOST1 && n2 <= CONV_BWD_MOST2 && n3 <= CONV_BWD_MOST2) return s;
+        if (n1 + n2 + n3 <= 256 && n1 <= most1 && n2 <= most2 && n3 <= most2) return s;
     }
 }
 // Positions per workgroup tile of a dense contraction over M rows and N columns: 128 where that makes at least 256 workgroups,
