@@ -271,7 +271,9 @@ struct ConvConfigs {
     typedef ResConv3DgradGeo<G> Dgrad3;
     typedef ResConv2DgradGeo<G> Dgrad2;
     static int conv1_parts(int) { return 1; }
-    // from 65 samples on (below, several workgroups share a sample of conv2 and conv3): the three convolutions in one launch
+    // the three convolutions one after the other in one launch (conv123_chain_kernel), from 65 samples on: below, several
+    // workgroups share a sample of conv2 and conv3
+    static constexpr bool CHAINS = true;
     static bool chain(int B) { return B >= 65; }
     // conv2 -> conv3 through LDS needs both layers' images in one CU's LDS: not with the bordered images of this geometry
     static bool fused_conv23(int) { return false; }
@@ -291,7 +293,7 @@ struct ConvConfigs<Geo84> {
     typedef ResConv3Fwd Fwd3;
     typedef ResConv3Dgrad Dgrad3;
     typedef ResConv2Dgrad Dgrad2;
-    static bool chain(int) { return false; }
+    static constexpr bool CHAINS = false;
     // few samples: three workgroups share one (one workgroup fits per CU)
     static int conv1_parts(int B) { return 3 * B <= 256 ? 3 : 1; }
     // one workgroup per sample range and no tile splitting: measured equal to the two kernels at B = 64, faster above
@@ -333,38 +335,40 @@ void forward_trunk(const Dims &d, const Packed &w, const uint8_t *obs, int B, ch
         typename Cfg::Fwd3::Args p3;
         p3.in = a2; p3.in_lo = a2l; p3.w = w.w3; p3.w_lo = w.w3l; p3.mask = nullptr; p3.bias = w.b3; p3.out = a3; p3.out_lo = a3l;
         p3.mask_out = m3; p3.frag = fc_small(G::FEAT, B, false);
-        const bool chained = Cfg::fused_conv23(B) && Cfg::conv1_parts(B) == 1;
-        if (Cfg::chain(B)) {
-            if constexpr (G::PAD2 > 0) {
-                ProfScope ps("conv123_fwd", s);
-                const int spw = resident_spw(B, 256);
-                hipLaunchKernelGGL((conv123_chain_kernel<G, typename Cfg::Fwd2, EightWaves<typename Cfg::Fwd3>>), dim3(cdiv(B, spw)),
-                                   dim3(RES_THREADS), 0, s, obs, w.w1, w.w1l, w.b1, m1, p2, p3, B, spw);
+        const int spw = resident_spw(B, 256);
+        auto chain_launch = [&]() {     // whether it launched them
+            if constexpr (Cfg::CHAINS) {
+                if (Cfg::chain(B)) {
+                    ProfScope ps("conv123_fwd", s);
+                    hipLaunchKernelGGL((conv123_chain_kernel<G, typename Cfg::Fwd2, EightWaves<typename Cfg::Fwd3>>), dim3(cdiv(B, spw)),
+                                       dim3(RES_THREADS), 0, s, obs, w.w1, w.w1l, w.b1, m1, p2, p3, B, spw);
+                    return true;
+                }
             }
-            fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);
-            return;
-        }
-        if (!chained) {
-            ProfScope ps("conv1_fwd", s);
-            const int spw = resident_spw(B, 256);
-            hipLaunchKernelGGL(conv1_fwd_resident_kernel<G>, dim3(cdiv(B, spw), Cfg::conv1_parts(B)), dim3(RES_THREADS), 0, s,
-                               obs, w.w1, w.w1l, w.b1, a1, a1l, m1, B, spw);
-        }
-        if (Cfg::fused_conv23(B)) {
-            // conv2 and conv3 in one kernel: act2 passes through LDS; with one workgroup per sample range in conv1 too,
-            // conv1 runs in the same launch, ahead of them in every workgroup
-            ProfScope ps(chained ? "conv123_fwd" : "conv23_fwd", s);
-            Conv23Args p;
-            p.a1 = a1; p.a1_lo = a1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.w3 = w.w3; p.w3_lo = w.w3l; p.b2 = w.b2; p.b3 = w.b3;
-            p.a2 = a2; p.a3 = a3; p.a3_lo = a3l;
-            p.m2 = m2; p.m3 = m3;
-            p.frag = fc_small(G::FEAT, B, false);
-            const int spw = resident_spw(B, 256);
-            if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, m1, p, B, spw, s);
-            else Cfg::launch_conv23(p, B, spw, s);
-        } else {
-            launch_resident<typename Cfg::Fwd2>("conv2_fwd", p2, B, s);
-            launch_resident<typename Cfg::Fwd3>("conv3_fwd", p3, B, s);
+            return false;
+        };
+        if (!chain_launch()) {
+            const bool chained = Cfg::fused_conv23(B) && Cfg::conv1_parts(B) == 1;
+            if (!chained) {
+                ProfScope ps("conv1_fwd", s);
+                hipLaunchKernelGGL(conv1_fwd_resident_kernel<G>, dim3(cdiv(B, spw), Cfg::conv1_parts(B)), dim3(RES_THREADS), 0, s,
+                                   obs, w.w1, w.w1l, w.b1, a1, a1l, m1, B, spw);
+            }
+            if (Cfg::fused_conv23(B)) {
+                // conv2 and conv3 in one kernel: act2 passes through LDS; with one workgroup per sample range in conv1 too,
+                // conv1 runs in the same launch, ahead of them in every workgroup
+                ProfScope ps(chained ? "conv123_fwd" : "conv23_fwd", s);
+                Conv23Args p;
+                p.a1 = a1; p.a1_lo = a1l; p.w2 = w.w2; p.w2_lo = w.w2l; p.w3 = w.w3; p.w3_lo = w.w3l; p.b2 = w.b2; p.b3 = w.b3;
+                p.a2 = a2; p.a3 = a3; p.a3_lo = a3l;
+                p.m2 = m2; p.m3 = m3;
+                p.frag = fc_small(G::FEAT, B, false);
+                if (chained) Cfg::launch_conv123(obs, w.w1, w.w1l, w.b1, m1, p, B, spw, s);
+                else Cfg::launch_conv23(p, B, spw, s);
+            } else {
+                launch_resident<typename Cfg::Fwd2>("conv2_fwd", p2, B, s);
+                launch_resident<typename Cfg::Fwd3>("conv3_fwd", p3, B, s);
+            }
         }
     }
     fc_and_head_launches<G, false>(d, w, B, ws, o, z_out, zstride, nullptr, s);
