@@ -5,11 +5,11 @@
 // conv2's weights (16 output channels each, hi and lo parts) and compute act2 of sample s+1 from the staged act1
 // image; their epilogue (bias, ReLU, hi/lo split) writes the 16 x 16 tile straight into conv3's LDS image, one of
 // two buffers.  Four "consumers" hold conv3's weights and compute act3 of sample s from the other buffer.  act2's
-// low part never exists in HBM, its high part and sign bits are written only when the backward pass will need
-// them, by the consumers (333 samples: a learner's iteration 115.6 -> 114.5 us; 2048 samples: 240.4 -> 239.4), and conv3 has no
-// staging phase.  The two roles sit in two branches that execute the same barriers, so
-// registers are allocated for one role only (conv2's 128 + conv3's 144 weight registers would not fit one
-// wavefront).  All three products of the split-bf16 forward are kept.
+// low part never exists in HBM, its high part and sign bits, which the backward pass needs, are written by the
+// consumers (333 samples: a learner's iteration 115.6 -> 114.5 us; 2048 samples: level), and conv3 has no staging
+// phase.  The two roles sit in two branches that execute the same barriers, so registers are allocated for one role
+// only (conv2's 128 + conv3's 144 weight registers would not fit one wavefront).  All three products of the split-bf16
+// forward are kept.
 #pragma once
 #include "arn_resident_conv.h"
 
@@ -21,9 +21,9 @@ struct Conv23Args {
     const __bf16 *a1, *a1_lo;        // act1 [B][P1][32], hi and lo
     const __bf16 *w2, *w2_lo, *w3, *w3_lo;
     const float *b2, *b3;
-    __bf16 *a2;                      // act2 hi [B][P2][64] for the backward pass, or null
+    __bf16 *a2;                      // act2 hi [B][P2][64] for the backward pass
     __bf16 *a3, *a3_lo;              // act3 [B][P3][64], hi and lo
-    uint8_t *m2, *m3;                // sign bits of act2 / act3 for the backward pass, or null
+    uint8_t *m2, *m3;                // sign bits of act2 / act3 for the backward pass
     bool frag;                       // act3 in fragment order (LastActs)
 };
 
@@ -33,8 +33,8 @@ constexpr int conv23_fwd_lds_bytes() { return 2 * P2::IMG + 4 * P3::IMG; }
 
 // The work of workgroup `block` (of C23_THREADS threads) in the caller's LDS buffer.
 // P2, P3: the LDS image descriptions of conv2 forward (one sample per iteration) and conv3 forward.
-// FULL: act2, act3's lo part and all sign bits are written unconditionally (see conv1_fwd_resident_body).
-template <class P2, class P3, bool FULL = false>
+// Everything that the backward pass needs is written: no output pointer is null (see FULL of conv1_fwd_resident_body).
+template <class P2, class P3>
 __device__ __forceinline__ void conv23_fwd_fused_body(u32x4 *lds, int block, const Conv23Args &a, int B, int spw) {
     // conv2 (producers)
     constexpr int CI2 = P2::CI, NCH2 = CI2 / 8, IMG2 = P2::IMG, KS2 = P2::K / 32;
@@ -232,7 +232,7 @@ __device__ __forceinline__ void conv23_fwd_fused_body(u32x4 *lds, int block, con
             // act2's high part and sign bits for the backward pass, from the image, eight channels a lane: the producers, who
             // are on the critical path, have neither the stores nor the bits to form (a lone wavefront issues a vector instruction
             // every 6 to 8 clocks)
-            if (FULL || a.a2) {
+            {
                 constexpr int CH = CI3 / 8, N = R2 * CH, T = C23_THREADS / 2;
                 char *const out = reinterpret_cast<char *>(a.a2 + (size_t)s * (R2 * CI3));
                 uint8_t *const bits_out = a.m2 + (size_t)s * N;
@@ -260,11 +260,9 @@ __device__ __forceinline__ void conv23_fwd_fused_body(u32x4 *lds, int block, con
                 const int pos = t * 16 + li;
                 const bool valid = pos < R3;
                 const size_t at = ((size_t)s * R3 + pos) * P3::CO + n0;
-                if (valid) store_bf16x4_split(a.a3, a.a3_lo, LastActs<P3::CO, R3>::at(a.frag, s, pos, n0), r0, r1, r2, r3, std::integral_constant<bool, FULL>());
-                if (FULL || a.m3) {
-                    const uint32_t bits = sign_bits16(r0, r1, r2, r3, lg);     // all lanes take part
-                    if (lg == 0 && valid) *reinterpret_cast<uint16_t *>(a.m3 + (at >> 3)) = (uint16_t)bits;
-                }
+                if (valid) store_bf16x4_split(a.a3, a.a3_lo, LastActs<P3::CO, R3>::at(a.frag, s, pos, n0), r0, r1, r2, r3, std::true_type());
+                const uint32_t bits = sign_bits16(r0, r1, r2, r3, lg);     // all lanes take part
+                if (lg == 0 && valid) *reinterpret_cast<uint16_t *>(a.m3 + (at >> 3)) = (uint16_t)bits;
             }
             cur ^= 1;
         }
@@ -296,7 +294,7 @@ __global__ __launch_bounds__(C23_THREADS) void conv123_fwd_kernel(const uint8_t 
     // vector cache).  A device-wide fence here is ruinous: it writes back and invalidates the whole L2 of the XCD,
     // once per workgroup (measured: 186 instead of 97 us).
     __syncthreads();
-    conv23_fwd_fused_body<P2, P3, true>(lds, block, a, B, spw);
+    conv23_fwd_fused_body<P2, P3>(lds, block, a, B, spw);
 }
 
 }  // namespace arn
