@@ -206,8 +206,10 @@ __device__ __forceinline__ void wait_vmem() {
 //   prefetch(m, n)                   what the epilogue of an output reads (bias, sign of an activation), loaded before the
 //                                    k loop: a load in the epilogue would be waited for once per output
 //   store(m, n, v, z, prefetched)    epilogue for channels n..n+3 of position m
-//   prefetch(m, n)                   WIDE: the same for channels n..n+7 and n+32..n+39, what a lane has of a position, in
-//                                    PREFETCH_LOADS loads
+//   prefetch(m, n)                   WIDE: the same for channels n..n+7 and n+32..n+39, what a lane has of a position
+//   PREFETCH_LOADS                   WIDE: vector memory loads that prefetch() compiles to.  Never more than there are: the waits
+//                                    for the last copies leave that many operations outstanding, so one too many and fragments
+//                                    are read before they have arrived.  Checked to be the fewest that its result can take
 //   store(m, n, half, v, v4, prefetched)   WIDE: for channels n..n+7, the prefetched first (half 0) or second eight
 // Grid: x = position tiles, y = channel tiles, z = range of the contraction (problems with a member ksplit).
 //
@@ -351,6 +353,7 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
     // copies it would hold up the first stage.  It is asked for when the last copies have been.  (fc input gradient alone, with one
     // word instead of eight single bytes per lane: 16.0 -> 14.7 us at 2048 samples, 49.9 -> 46.0 at 8192.)
     constexpr int LATE = MB * P::PREFETCH_LOADS;
+    static_assert(!P::WIDE || P::PREFETCH_LOADS == (sizeof(pre[0][0]) + 15) / 16, "what a load brings at most: 16 bytes");
     if constexpr (!P::WIDE) prefetch_all();
 #pragma unroll
     for (int s = 0; s < 2 * RING; s += 2)
