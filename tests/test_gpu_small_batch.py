@@ -58,10 +58,10 @@ def test_gradients_at_dispatch_edges(gu, geometry, B):
     gu.check_grads(got, want, "%s B=%d" % (geometry, B))
 
 
-@pytest.mark.parametrize("geometry,B", [("84", 1280), ("84", 2432), ("84", 2463), ("paper", 1153)])
+@pytest.mark.parametrize("geometry,B", [("84", 1280), ("84", 2432), ("84", 2433), ("84", 2463), ("paper", 1152), ("paper", 1153)])
 def test_gradients_at_fc_weight_tile_edges(gu, geometry, B):
-    """Both sides of the batch from which the fc weight gradient takes 256 hidden units a tile (84x84: 2433, 104x80: 1153) and of the one from which the input gradient takes 128 positions (1281), with
-    a ragged last stage of 32 rows."""
+    """Both sides of the batch from which the fc weight gradient takes 256 hidden units a tile (84x84: 2433, 104x80: 1153) and of the
+    one from which the input gradient takes 128 positions (84x84: 1281), last stages of 1, 31 and 32 rows."""
     test_gradients_at_dispatch_edges(gu, geometry, B)
 
 
