@@ -351,7 +351,9 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
     };
     // What WIDE problems read per position comes from memory, not from the L2, and loads return in order: ahead of the first
     // copies it would hold up the first stage.  It is asked for when the last copies have been.  (fc input gradient alone, with one
-    // word instead of eight single bytes per lane: 16.0 -> 14.7 us at 2048 samples, 49.9 -> 46.0 at 8192.)
+    // word instead of eight single bytes per lane: 16.0 -> 14.7 us at 2048 samples, 49.9 -> 46.0 at 8192.  Tiles below 128 positions and the
+    // eight stages of the 2-convolution network: ahead of the first copies, right behind them or here, whole steps are within 0.4%, but
+    // right behind them costs 104x80 0.7 to 1% at 200 and 255 samples.)
     constexpr int LATE = MB * P::PREFETCH_LOADS;
     static_assert(!P::WIDE || P::PREFETCH_LOADS == (sizeof(pre[0][0]) + 15) / 16, "what a load brings at most: 16 bytes");
     if constexpr (!P::WIDE) prefetch_all();
@@ -497,12 +499,13 @@ void gemm_nt_kernel(const P p) {
 // four consecutive rows, which is conflict-free when the four are 64 bytes apart modulo 256: rows are not padded (a copy
 // fills 1 KB), so row r's 64-byte blocks are stored permuted, and the copies apply that to their source address.
 //
-// What bounds it: with 64 x 64 outputs per wavefront (FcWgrad of large batches; 64 x 32 before: 20.8 -> 18.3 us alone at 2048 samples,
-// 63.8 -> 48.6 at 8192) the transposing reads, four 8-byte reads of a wavefront per 32x32x16 MFMA and 128 bytes per clock from a CU's
-// LDS; with 64 x 32, six, and latency: in the launch it is a part of (dense_backward_kernel, 2048 and 8192 samples) the matrix cores were
-// busy 22 and 25% of the cycles, LDS 14 and 16%, a hundredth of that bank conflicts; wavefronts spent 37 and 34% at a wait, 32
-// and 34% waiting to issue.  With operands through registers, one 64-row tile ahead, the staging writes came on top and every
-// tile had two barriers.  Steps before / after, us: ppo of 4096 samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
+// What bounds it: latency.  At 8192 samples its MFMAs would take 11 us at 2.4 GHz, and so would its LDS reads at 128 bytes per clock of a
+// CU (two 8-byte reads of a wavefront per 32x32x16 MFMA with 64 x 64 outputs per wavefront, FcWgrad of large batches; three with 64 x 32);
+// alone the range takes 49 (64 x 32: 64; at 2048 samples 18.3 and 20.8).  In the launch it is a part of
+// (dense_backward_kernel, 2048 samples with 64 x 32 and 8192 with 64 x 64) the matrix cores are busy 23 and 29% of the cycles, LDS 15 and
+// 16%, a hundredth of that bank conflicts; wavefronts spend 38 and 34% at a wait, 30 and 37% waiting to issue.  With operands through
+// registers, one 64-row tile ahead, the staging writes came on top and every tile had two barriers.  Steps before / after, us: ppo of 4096
+// samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
 // ---------------------------------------------------------------------------
 constexpr int TN_ROWS = 32;
 template <class P>

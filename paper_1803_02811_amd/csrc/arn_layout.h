@@ -236,11 +236,13 @@ inline int dense_tile(long M, int N) {
     return (M + 127) / 128 * nt >= 256 ? 128 : (M + 63) / 64 * nt >= 256 ? 64 : 32;
 }
 // Hidden units per workgroup tile of the fc layer's weight gradient: 256 (64 x 64 outputs per wavefront, a third fewer LDS
-// reads per product than 64 x 32, and half the act3 traffic) for batches that have at least 500 tiles of 128 x 128 in the input
-// gradient (84x84: 2433 samples, 104x80: 1153); below, the launch is a few rounds of workgroups or less, and twice as many half as
-// long ones are as fast or faster.  Launch and sums of the partials in us, 128 / 256 units, 84x84: 333 samples 20.7 / 23.2, 2048:
-// 41.1 / 40.0, 4096: 70.4 / 64.1, 8192: 129.2 / 121.3; 104x80, 512 samples: 31.5 / 34.0.  Whole A2C step, 84x84, 1930 samples: 231.2 /
-// 231.9, 3000: 330.6 / 327.0; 104x80, 900: 204.7 / 205.6, 2048: 363.7 / 356.7.
+// reads per product than 64 x 32, and half the act3 traffic, for twice the ranges of the batch and so twice the partials) for batches
+// that have at least 500 tiles of 128 x 128 in the input gradient (84x84: 2433 samples, 104x80: 1153); with fewer, the launch is a few
+// rounds of workgroups or less, and what the launch gains the sums of the partials lose.  Launch and sums in us, 128 / 256 units, 84x84:
+// 333 samples 20.7 / 23.2, 2048: 39.8 / 38.5, 4096: 69.4 / 64.2, 8192: 118.4 / 104.5; 104x80, 512 samples: 31.5 / 34.0.  Whole A2C step,
+// 84x84: 1281 samples 178.9 / 180.9, 1800: 228.3 / 230.9, 2048: 237.3 / 237.0, 2304: 268.6 / 267.6, 2432: 284.5 / 280.8, 4096: 419.5 / 414.7, 8192:
+// 777.8 / 768.4; 104x80: 900 samples 198.6 / 204.4, 1100: 245.2 / 247.4, 1153: 247.0 / 247.6, 1408: 280.6 / 281.6, 1600: 312.3 / 310.3, 2048: 350.2 /
+// 347.3.  By 84x84 alone the line would lie at 2049 samples, by 104x80 alone at about 1450, where they are level.
 inline int fc_wgrad_units(int feat, int hid, int B) {
     return hid > 256 && (long)((B + 127) / 128) * ((feat + 127) / 128) >= 500 ? 256 : 128;
 }

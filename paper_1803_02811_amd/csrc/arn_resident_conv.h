@@ -779,7 +779,7 @@ struct ResConv2DgradGeo {
 // fit side by side (104x80): a workgroup waits for its own act1 and act2, which it reads back, instead of for the whole grid
 // three times, and two launch boundaries and the first and last workgroups of three grids are gone.  Eight wavefronts in every
 // layer; the same products in the same order as in the layers' own kernels.  A2C step on 104x80 frames, three launches / this one,
-// us: 66 samples 87.6 / 82.3, 255: 105.8 / 99.4, 512: 138.9 / 131.6, 2048: 359.2 / 339.4, 4000: 632.5 / 608.3.
+// us: 66 samples 88.4 / 82.8, 255: 109.1 / 102.6, 512: 144.5 / 137.9, 2048: 361.9 / 351.0, 4096: 648 / 630.
 template <class C>
 struct EightWaves : C {
     static constexpr int WAVES = 8;
