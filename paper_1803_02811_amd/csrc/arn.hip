@@ -228,16 +228,19 @@ void fc_and_head_launches(const Dims &d, const Packed &w, int B, char *ws, const
         }
     } else {
         const int ksplit = fc_ksplit(G::FEAT, G::NHID, B, F16);
-        auto launch = [&](auto bm) {
+        const bool partial = ksplit > 1 || d.small;
+        auto launch = [&](auto bm, auto to_partial) {
             constexpr int BM = decltype(bm)::value;
-            typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID, BM>, FcFwdT<G::FEAT, G::NHID, BM>>::type p;
+            constexpr bool P = decltype(to_partial)::value;
+            typename std::conditional<F16, FcFwdF16T<G::FEAT, G::NHID, BM, P>, FcFwdT<G::FEAT, G::NHID, BM, P>>::type p;
             p.in = a3; p.in_lo = a3l; p.M = B; p.w = F16 ? (const __bf16 *)w.wfch : w.wfc; p.w_lo = w.wfcl; p.bias = w.bfc;
             p.out = h; p.out_lo = hl; p.ksplit = ksplit; p.partial = (float *)(ws + o.fcp);
-            p.to_partial = ksplit > 1 || d.small;
             launch_nt<!F16>("fc_fwd", p, G::NHID, ksplit, s);
         };
-        if (fc_tile(G::NHID, B) == 128) launch(std::integral_constant<int, 128>());
-        else launch(std::integral_constant<int, 64>());
+        // a tile of 64 is one of at most 64 tiles: its contraction is always cut
+        if (fc_tile(G::NHID, B) != 128) launch(Count<64>(), std::true_type());
+        else if (partial) launch(Count<128>(), std::true_type());
+        else launch(Count<128>(), std::false_type());
         if (ksplit > 1 && !d.small) {
             ProfScope ps("fc_finish", s);
             const long total = (long)B * G::NHID;

@@ -206,6 +206,7 @@ __device__ __forceinline__ void wait_vmem() {
 //   prefetch(m, n)                   what the epilogue of an output reads (bias, sign of an activation), loaded before the
 //                                    k loop: a load in the epilogue would be waited for once per output
 //   store(m, n, v, z, prefetched)    epilogue for channels n..n+3 of position m
+//   STORES_16BIT                     not WIDE: whether that writes 16-bit values or fp32, which decides the order of the stores
 //   prefetch(m, n)                   WIDE: the same for channels n..n+7 and n+32..n+39, what a lane has of a position
 //   PREFETCH_LOADS                   WIDE: vector memory loads that prefetch() compiles to.  Never more than there are: the waits
 //                                    for the last copies leave that many operations outstanding, so one too many and fragments
@@ -411,15 +412,23 @@ __device__ __forceinline__ void gemm_nt_body(u32x4 *lds, const P &p, int bx, int
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // WIDE: a position's channels one after the other, they share cache lines.  fp32 rows: channel group by channel group; in the
-    // order of WIDE the fc layer's partials of 512 samples of 104x80 took 8.6 instead of 8.2 us (one product), the head kernel that
-    // reads them 9.3 instead of 9.1, and the A2C gradient at 2048 samples of 84x84 241.5 instead of 239.5.
+    // 16-bit outputs: a position's channels one after the other, a cache line holds the 64 of a wavefront; the fc layer's hidden units
+    // of 8192 samples, channel group by channel group, cost 1.4 us a launch (65.4 / 64.0, one
+    // product 35.0 / 33.6) and 31 MB of writes instead of 16; the categorical step of 8192 samples took 1052.5 us, now 1046.9.
+    // fp32 rows: channel group by channel group; in the order of 16-bit outputs the fc layer's partials of 512 samples of 104x80 took
+    // 8.6 instead of 8.2 us (one product), the head kernel that reads them 9.3 instead of 9.1, and the A2C gradient at 2048 samples of
+    // 84x84 241.5 instead of 239.5.
     auto store_all = [&]() __attribute__((always_inline)) {
         if constexpr (P::WIDE) {
 #pragma unroll
             for (int b = 0; b < MB; ++b)
 #pragma unroll
                 for (int a = 0; a < 4; a += 2) p.store(m_of(b), n_of(a), a / 2, acc[a][b], acc[a + 1][b], pre[0][b]);
+        } else if constexpr (P::STORES_16BIT) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) p.store(m_of(b), n_of(a), acc[a][b], z, pre[a][b]);
         } else {
 #pragma unroll
             for (int a = 0; a < 4; ++a)

@@ -82,6 +82,28 @@ def test_categorical_gradients_at_tile_edges(gu, A, B):
     gu.check_grads(got, want, "A=%d B=%d" % (A, B))
 
 
+# 84x84: the last batch whose fc contraction is cut in two and the first whose is not: its tiles write the hidden layer themselves
+@pytest.mark.parametrize("B", [4096, 4097])
+def test_categorical_network_where_the_fc_tiles_finish_the_layer(gu, B):
+    """Logits of the first and last samples against the oracle; the gradient against the mean of two shards, whose contraction is
+    cut.  One action, so that no greedy decision stands between them."""
+    A = 1
+    flat, tflat = (wl.he_normal_params(A, "c51", seed, bias_std=0.1) for seed in (2618, 3618))
+    batch = wl.c51_batch(5, B=B)
+    batch["action"] %= A
+    net, spec = gu.GpuNet(A, "c51", flat), orc.NetSpec(A, "c51")
+    rows = np.r_[0:9, B - 9:B]
+    want = orc.forward(orc.unflatten(flat, spec), batch["obs"][rows], spec)["atom_logits"]
+    got = net.forward(batch["obs"])["logits"][rows]
+    gu.tol_check(got, want.reshape(got.shape), "B=%d" % B)
+    target = net.pack(tflat)
+    whole = net.train(batch, "c51", target_packed=target)[0]
+    shards = [slice(0, 2048), slice(2048, B)]
+    mean = sum((s.stop - s.start) / B * net.train({k: v[s] for k, v in batch.items()}, "c51", target_packed=target)[0].astype(np.float64)
+               for s in shards)
+    gu.check_grads(*(wl.split_params(v, A, "c51") for v in (whole, mean)), "B=%d against two shards" % B)
+
+
 # Batches whose passes without gradient run in fc_small_kernel (activations in fragment order) while the forward pass of the
 # same step, in the same workspace, runs in the tiled GEMM (activations in rows, several k ranges): both ends of that window.
 @pytest.mark.parametrize("geometry,head,B", [("84", "duel", 399), ("84", "q", 512), ("84", "c51", 450),
