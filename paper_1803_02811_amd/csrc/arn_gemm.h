@@ -511,8 +511,8 @@ void gemm_nt_kernel(const P p) {
 // What bounds it: latency.  At 8192 samples its MFMAs would take 11 us at 2.4 GHz, and so would its LDS reads at 128 bytes per clock of a
 // CU (two 8-byte reads of a wavefront per 32x32x16 MFMA with 64 x 64 outputs per wavefront, FcWgrad of large batches; three with 64 x 32);
 // alone the range takes 49 (64 x 32: 64; at 2048 samples 18.3 and 20.8).  In the launch it is a part of
-// (dense_backward_kernel, 2048 samples with 64 x 32 and 8192 with 64 x 64) the matrix cores are busy 23 and 29% of the cycles, LDS 15 and
-// 16%, a hundredth of that bank conflicts; wavefronts spend 38 and 34% at a wait, 30 and 37% waiting to issue.  With operands through
+// (dense_backward_kernel, 2048 samples with 64 x 32 and 8192 with 64 x 64) the matrix cores are busy 22 and 28% of the cycles, LDS 14 and
+// 15%, a hundredth of that bank conflicts; wavefronts spend 38 and 34% at a wait, 32 and 37% waiting to issue.  With operands through
 // registers, one 64-row tile ahead, the staging writes came on top and every tile had two barriers.  Steps before / after, us: ppo of 4096
 // samples 440 / 431, c51 of 8192 samples 1128 / 1111, a2c of 2048 samples 247 / 244.
 // ---------------------------------------------------------------------------
